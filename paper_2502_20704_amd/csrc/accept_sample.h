@@ -199,7 +199,8 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
         const long s0 = static_cast<long>(gs) * P.sps;
         const long s1 = (s0 + P.sps < P.nslots) ? s0 + P.sps : P.nslots;
         // thr, rthr: scores the winner is known to reach (see the bounds below)
-        float thr = neg_inf(), rthr = neg_inf();
+        // (from the lowest finite score up: an entry without mass, masked or cut off by the warpers, stays below)
+        float thr = -FLT_MAX, rthr = -FLT_MAX;
         const float thr_b = P.thr ? P.thr[b] : neg_inf();
         // the trip count is the same for every lane: the thresholds are wavefront reductions
         // the next round's slot is requested before this round's is worked on: the loads of the rounds
@@ -214,12 +215,20 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
             unpack<BF16>(raw, z);
             if (P.thr && P.mode == FSD_SAMPLE) {
                 // temperature, then the kept set of top-k / top-p: everything else leaves the draw
+                bool any_kept = false;
 #pragma unroll
                 for (int e = 0; e < VE; ++e) {
                     bad |= !(z[e] < __builtin_inff());
                     const float sv = __fmul_rn(z[e], P.inv_temp);
-                    z[e] = (sv >= thr_b) ? sv : neg_inf();
+                    const bool keep = sv >= thr_b;
+                    z[e] = keep ? sv : neg_inf();
+                    any_kept |= keep;
                 }
+                // A wavefront without a kept entry has nothing to draw: no random numbers are formed for it.
+                // (Top-k keeps a handful of a row's entries: nearly every wavefront leaves here.  Before, such
+                // a wavefront had no score to reach and evaluated all its variates.  C2's shape with
+                // temperature 0.7, top-k 50, top-p 0.9: 35.6 -> 11.4 us for this kernel.)
+                if (!__any(any_kept)) continue;
             }
             if (live) {
             float rres[VE];   // strict SD on a tree: p after the chain's rejections, minus the last draft row
@@ -342,7 +351,7 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
             }
             if (P.mode == FSD_SAMPLE) {
                 thr = fmaxf(thr, wave_max(best.score));
-                if (residual) rthr = wave_max(rbest.score);
+                if (residual) rthr = fmaxf(rthr, wave_max(rbest.score));
             }
         }
     }
