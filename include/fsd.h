@@ -14,8 +14,8 @@
  *     library never allocates, frees or keeps it.  Tensors are dense and
  *     row-major.  Logits are binary32 (FSD_F32) or bfloat16 (FSD_BF16).
  *     Rows that start on 16-byte boundaries (V * element size a multiple of
- *     16 and aligned base pointers) take the 128-bit load path; anything else
- *     is still correct through an element-wise path.
+ *     16 and aligned base pointers) are read fastest; any other alignment of
+ *     whole elements is read with 128-bit loads as well.
  *   - -inf logits are legal (masked vocabulary entries).  A NaN or +inf logit,
  *     or a row that is -inf everywhere, in a row the method reads is reported
  *     per sequence in row_status (FSD_ROW_NONFINITE): that sequence gets

@@ -49,7 +49,7 @@ __device__ __forceinline__ Best wave_best(Best v) {
     return v;
 }
 
-template <bool BF16, bool ALIGNED, int KIND>
+template <bool BF16, int LD, int KIND>
 __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
     constexpr int VE = Slot<BF16>::VE;
     constexpr int ES = BF16 ? 2 : 4;
@@ -205,13 +205,14 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
         // the trip count is the same for every lane: the thresholds are wavefront reductions
         // the next round's slot is requested before this round's is worked on: the loads of the rounds
         // overlap with the arithmetic instead of each being waited for in turn
-        uint4 raw_next = load_slot<BF16, ALIGNED>(trow, (s0 + tid < s1) ? s0 + tid : s1 - 1, P.V);
+        uint4 raw_next = load_slot<BF16, LD>(trow, (s0 + tid < s1) ? s0 + tid : s1 - 1, P.V);
         for (long sb = s0; sb < s1; sb += kWG) {
             const long s = sb + tid;
             const bool live = s < s1;
             float z[VE], zd[VE], lnr[VE];
-            const uint4 raw = raw_next;
-            if (sb + kWG < s1) raw_next = load_slot<BF16, ALIGNED>(trow, (s + kWG < s1) ? s + kWG : s1 - 1, P.V);
+            uint4 raw = raw_next;
+            if (sb + kWG < s1) raw_next = load_slot<BF16, LD>(trow, (s + kWG < s1) ? s + kWG : s1 - 1, P.V);
+            settle_slot<BF16, LD>(raw, live ? s : s1 - 1, P.V);
             unpack<BF16>(raw, z);
             if (P.thr && P.mode == FSD_SAMPLE) {
                 // temperature, then the kept set of top-k / top-p: everything else leaves the draw
@@ -241,7 +242,8 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
                     for (int e = 0; e < VE; ++e) rres[e] = hw_exp2(fmaf(z[e], kLog2e, -lt));
                     for (int m = 0; m < nchain; ++m) {
                         const char* dr = P.draft + (static_cast<size_t>(b) * rows + ch[m]) * static_cast<size_t>(P.V) * ES;
-                        const uint4 rawd = load_slot<BF16, ALIGNED>(dr, s, P.V);
+                        uint4 rawd = load_slot<BF16, LD>(dr, s, P.V);
+                        settle_slot<BF16, LD>(rawd, s, P.V);
                         unpack<BF16>(rawd, zd);
                         const float ldm = ldv[m];
                         if (m + 1 < nchain) {
@@ -256,7 +258,8 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
                     }
                 }
             } else if (residual) {
-                const uint4 rawd = load_slot<BF16, ALIGNED>(drow, s, P.V);
+                uint4 rawd = load_slot<BF16, LD>(drow, s, P.V);
+                settle_slot<BF16, LD>(rawd, s, P.V);
                 unpack<BF16>(rawd, zd);
             }
             // ln of the residual's entries (-inf where it has no mass)

@@ -9,6 +9,8 @@
 #include <float.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "fsd.h"
 
 namespace {
@@ -191,22 +193,35 @@ __device__ __forceinline__ uint4 slot_neg_inf() {
     return make_uint4(w, w, w, w);
 }
 
-// ALIGNED: rows start on 16-byte boundaries and V is a multiple of the slot width.
-// Otherwise elements are fetched one by one and the ragged tail is padded with -inf.
+// How a slot is fetched:
+//   LOAD_ALIGNED  rows start on 16-byte boundaries and V is a multiple of the slot width: one 128-bit load.
+//   LOAD_WIDE     any alignment, V at least a slot's width: one 128-bit load as well (the hardware takes global
+//                 loads at any address).  The last slot of a ragged row is fetched as the VE entries that
+//                 end the row, so nothing behind the row is touched, and settle_slot moves them into place.
+//   LOAD_ELEM     rows shorter than a slot: element by element, the tail padded with -inf.
+// Before LOAD_WIDE every row of such a tensor was fetched element by element: 80 pairs of rows of 128259
+// bfloat16 entries took 56 us in the reduction kernel, now 22; aligned rows (128256) take 19.5.
+enum { LOAD_ELEM = 0, LOAD_ALIGNED = 1, LOAD_WIDE = 2 };
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 
-template <bool BF16, bool ALIGNED, bool STREAM = false>
+// 16 bytes at a 32-bit offset from the row (rows are at most 2 MiB): the row pointer stays scalar
+template <int LD, bool STREAM>
+__device__ __forceinline__ uint4 load_16(const char* row, unsigned off) {
+    using Vec = typename std::conditional<LD == LOAD_ALIGNED, u32x4, u32x4_any>::type;
+    const Vec* at = reinterpret_cast<const Vec*>(row + static_cast<size_t>(off));
+    Vec v;
+    if constexpr (STREAM) v = __builtin_nontemporal_load(at);   // read once by this kernel
+    else v = *at;
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+template <bool BF16, int LD, bool STREAM = false>
 __device__ __forceinline__ uint4 load_slot(const char* row, long slot, long V) {
-    if constexpr (ALIGNED) {
-        // a 32-bit offset from the row (rows are at most 2 MiB): the row pointer stays scalar
-        const char* at = row + static_cast<size_t>(static_cast<unsigned>(slot) * 16u);
-        if constexpr (STREAM) {
-            // read once by this kernel: marked non-temporal
-            const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(at));
-            return make_uint4(v.x, v.y, v.z, v.w);
-        } else {
-            return *reinterpret_cast<const uint4*>(at);
-        }
+    if constexpr (LD == LOAD_ALIGNED) {
+        return load_16<LD, STREAM>(row, static_cast<unsigned>(slot) * 16u);
+    } else if constexpr (LD == LOAD_WIDE) {
+        const unsigned off = static_cast<unsigned>(slot) * 16u, last = static_cast<unsigned>(V) * (BF16 ? 2 : 4) - 16u;
+        return load_16<LD, STREAM>(row, off < last ? off : last);
     } else if constexpr (BF16) {
         const unsigned short* p = reinterpret_cast<const unsigned short*>(row);
         unsigned w[4];
@@ -227,6 +242,26 @@ __device__ __forceinline__ uint4 load_slot(const char* row, long slot, long V) {
             w[d] = (e < V) ? p[e] : 0xFF800000u;
         }
         return make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
+// What load_slot<LOAD_WIDE> fetched for the slot that reaches past the end of its row, moved into place:
+// `fill` (one 32-bit word of entries) takes the places behind the row.  Any other slot is left as it is.
+// Called where the slot is used, not where it is requested: it needs the loaded words.
+template <bool BF16, int LD>
+__device__ __forceinline__ void settle_slot(uint4& w, long slot, long V, unsigned fill = BF16 ? 0xFF80FF80u : 0xFF800000u) {
+    if constexpr (LD == LOAD_WIDE) {
+        constexpr int VE = Slot<BF16>::VE;
+        int missing = static_cast<int>((slot + 1) * VE - V);
+        for (; missing > 0; --missing) {
+            if constexpr (BF16) {
+                w.x = (w.x >> 16) | (w.y << 16);
+                w.y = (w.y >> 16) | (w.z << 16);
+                w.z = (w.z >> 16) | (w.w << 16);
+                w.w = (w.w >> 16) | (fill << 16);
+            } else {
+                w.x = w.y; w.y = w.z; w.z = w.w; w.w = fill;
+            }
+        }
     }
 }
 

@@ -226,12 +226,12 @@ Residency residency_of(Kernel kernel, int threads, Residency (&cache)[16]) {
     return cache[dev];
 }
 
-template <bool BF16, int NV, int MODE, bool ALIGNED, bool TSHARED = false>
+template <bool BF16, int NV, int MODE, int LD, bool TSHARED = false>
 void launch_pair_k(hipStream_t st, const PairParams& P0) {
     // persistent grid: as many whole teams as fit on the device at once (at least one, whose workgroups
     // fit by the limit on the team size), in whole workgroups; the wavefronts left over leave at once
     static Residency cache[16] = {};
-    const Residency res = residency_of(pair_kernel<BF16, NV, MODE, ALIGNED, TSHARED>, kWG, cache);
+    const Residency res = residency_of(pair_kernel<BF16, NV, MODE, LD, TSHARED>, kWG, cache);
     const long waves_per_wg = kWG / 64;
     long nteams = res.total * waves_per_wg / P0.G;
     if (nteams > P0.npairs) nteams = P0.npairs;
@@ -243,33 +243,51 @@ void launch_pair_k(hipStream_t st, const PairParams& P0) {
     if (g_prof_pair) {
         // timed launch: the events take the start and the end of this dispatch itself (what a
         // kernel trace shows), not the time between two markers around it in the stream
-        hipExtLaunchKernelGGL((pair_kernel<BF16, NV, MODE, ALIGNED, TSHARED>), dim3(static_cast<unsigned>(grid)), dim3(kWG), res.pad_lds, st,
+        hipExtLaunchKernelGGL((pair_kernel<BF16, NV, MODE, LD, TSHARED>), dim3(static_cast<unsigned>(grid)), dim3(kWG), res.pad_lds, st,
                               g_prof_pair[0], g_prof_pair[1], 0, P);
     } else {
-        hipLaunchKernelGGL((pair_kernel<BF16, NV, MODE, ALIGNED, TSHARED>), dim3(static_cast<unsigned>(grid)), dim3(kWG), res.pad_lds, st, P);
+        hipLaunchKernelGGL((pair_kernel<BF16, NV, MODE, LD, TSHARED>), dim3(static_cast<unsigned>(grid)), dim3(kWG), res.pad_lds, st, P);
     }
 }
 template <bool BF16, int NV, int MODE>
-void launch_pair_a(bool aligned, hipStream_t st, const PairParams& P) {
-    if (!aligned) {
-        launch_pair_k<BF16, NV, MODE, false>(st, P);   // (rows that are not 16-byte aligned: no tree variant, a tree's target rows are then not kept cached)
+void launch_pair_a(int load, hipStream_t st, const PairParams& P) {
+    // a tree (shared target rows) has variants of its own, for 16-byte aligned rows and for the library's
+    // own shapes
+    constexpr bool kOwn = BF16 ? (NV == 4 || NV == 6) : (NV == 8);
+    const bool shared = P.parent != nullptr;
+    if (load == LOAD_ALIGNED) {
+        if (shared) launch_pair_k<BF16, NV, MODE, LOAD_ALIGNED, true>(st, P);
+        else launch_pair_k<BF16, NV, MODE, LOAD_ALIGNED>(st, P);
     } else {
-        if (P.parent != nullptr) launch_pair_k<BF16, NV, MODE, true, true>(st, P);   // a tree: shared target rows
-        else launch_pair_k<BF16, NV, MODE, true>(st, P);
+        if constexpr (kOwn) {
+            if (shared) { launch_pair_k<BF16, NV, MODE, LOAD_WIDE, true>(st, P); return; }
+        }
+        launch_pair_k<BF16, NV, MODE, LOAD_WIDE>(st, P);
     }
 }
 template <bool BF16, int NV>
-void launch_pair_m(int mode, bool aligned, hipStream_t st, const PairParams& P) {
+void launch_pair_m(int mode, int load, hipStream_t st, const PairParams& P) {
     switch (mode) {
-        case MODE_KL: launch_pair_a<BF16, NV, MODE_KL>(aligned, st, P); break;
-        case MODE_JS: launch_pair_a<BF16, NV, MODE_JS>(aligned, st, P); break;
-        case MODE_TV: launch_pair_a<BF16, NV, MODE_TV>(aligned, st, P); break;
-        case MODE_KLP: launch_pair_a<BF16, NV, MODE_KLP>(aligned, st, P); break;
-        case MODE_JSE: launch_pair_a<BF16, NV, MODE_JS>(aligned, st, P); break;   // (its own shape is launched by launch_pair)
-        default: launch_pair_a<BF16, NV, MODE_LSE>(aligned, st, P); break;
+        case MODE_KL: launch_pair_a<BF16, NV, MODE_KL>(load, st, P); break;
+        case MODE_JS: launch_pair_a<BF16, NV, MODE_JS>(load, st, P); break;
+        case MODE_TV: launch_pair_a<BF16, NV, MODE_TV>(load, st, P); break;
+        case MODE_KLP: launch_pair_a<BF16, NV, MODE_KLP>(load, st, P); break;
+        case MODE_JSE: launch_pair_a<BF16, NV, MODE_JS>(load, st, P); break;   // (its own shape is launched by launch_pair)
+        default: launch_pair_a<BF16, NV, MODE_LSE>(load, st, P); break;
     }
 }
-void launch_pair(int dtype, int NV, int mode, bool aligned, hipStream_t st, const PairParams& P) {
+// rows shorter than a slot: one shape
+template <bool BF16>
+void launch_pair_elem(int mode, hipStream_t st, const PairParams& P) {
+    switch (mode) {
+        case MODE_KL: launch_pair_k<BF16, 2, MODE_KL, LOAD_ELEM>(st, P); break;
+        case MODE_JS: launch_pair_k<BF16, 2, MODE_JS, LOAD_ELEM>(st, P); break;
+        case MODE_TV: launch_pair_k<BF16, 2, MODE_TV, LOAD_ELEM>(st, P); break;
+        case MODE_KLP: launch_pair_k<BF16, 2, MODE_KLP, LOAD_ELEM>(st, P); break;
+        default: launch_pair_k<BF16, 2, MODE_LSE, LOAD_ELEM>(st, P); break;
+    }
+}
+void launch_pair(int dtype, int NV, int mode, int load, hipStream_t st, const PairParams& P) {
     const bool prof = g_prof_on && g_prof_n < kMaxProf;
     if (prof) {
         if (!g_prof_made) {
@@ -278,19 +296,22 @@ void launch_pair(int dtype, int NV, int mode, bool aligned, hipStream_t st, cons
         }
         g_prof_pair = &g_prof_ev[2 * g_prof_n];
     }
-    if (dtype == FSD_BF16) {
-        if (NV == 2) launch_pair_m<true, 2>(mode, aligned, st, P);
+    if (load == LOAD_ELEM) {
+        if (dtype == FSD_BF16) launch_pair_elem<true>(mode, st, P);
+        else launch_pair_elem<false>(mode, st, P);
+    } else if (dtype == FSD_BF16) {
+        if (NV == 2) launch_pair_m<true, 2>(mode, load, st, P);
         else if (NV == 6) {   // the library's own shape of the two-phase kernels
-            if (mode == MODE_JSE) launch_pair_a<true, 6, MODE_JSE>(aligned, st, P);
-            else if (mode == MODE_TV) launch_pair_a<true, 6, MODE_TV>(aligned, st, P);
-            else launch_pair_a<true, 6, MODE_JS>(aligned, st, P);
+            if (mode == MODE_JSE) launch_pair_a<true, 6, MODE_JSE>(load, st, P);
+            else if (mode == MODE_TV) launch_pair_a<true, 6, MODE_TV>(load, st, P);
+            else launch_pair_a<true, 6, MODE_JS>(load, st, P);
         }
-        else if (NV == 5) launch_pair_m<true, 5>(mode, aligned, st, P);
-        else launch_pair_m<true, 4>(mode, aligned, st, P);
+        else if (NV == 5) launch_pair_m<true, 5>(mode, load, st, P);
+        else launch_pair_m<true, 4>(mode, load, st, P);
     } else {
-        if (NV == 2) launch_pair_m<false, 2>(mode, aligned, st, P);
-        else if (NV == 4) launch_pair_m<false, 4>(mode, aligned, st, P);
-        else launch_pair_m<false, 8>(mode, aligned, st, P);
+        if (NV == 2) launch_pair_m<false, 2>(mode, load, st, P);
+        else if (NV == 4) launch_pair_m<false, 4>(mode, load, st, P);
+        else launch_pair_m<false, 8>(mode, load, st, P);
     }
     if (prof) {
         g_prof_pair = nullptr;
@@ -298,23 +319,25 @@ void launch_pair(int dtype, int NV, int mode, bool aligned, hipStream_t st, cons
     }
 }
 
-template <bool BF16, bool ALIGNED>
+template <bool BF16, int LD>
 void launch_sample_k(int kind, dim3 grid, size_t lds, hipStream_t st, const SampleParams& P) {
     switch (kind) {
-        case KIND_CHAIN: hipLaunchKernelGGL((accept_sample<BF16, ALIGNED, KIND_CHAIN>), grid, dim3(kWG), lds, st, P); break;
-        case KIND_TREE: hipLaunchKernelGGL((accept_sample<BF16, ALIGNED, KIND_TREE>), grid, dim3(kWG), lds, st, P); break;
-        case KIND_RFSD: hipLaunchKernelGGL((accept_sample<BF16, ALIGNED, KIND_RFSD>), grid, dim3(kWG), lds, st, P); break;
-        case KIND_TREESD: hipLaunchKernelGGL((accept_sample<BF16, ALIGNED, KIND_TREESD>), grid, dim3(kWG), lds, st, P); break;
-        default: hipLaunchKernelGGL((accept_sample<BF16, ALIGNED, KIND_SD>), grid, dim3(kWG), lds, st, P); break;
+        case KIND_CHAIN: hipLaunchKernelGGL((accept_sample<BF16, LD, KIND_CHAIN>), grid, dim3(kWG), lds, st, P); break;
+        case KIND_TREE: hipLaunchKernelGGL((accept_sample<BF16, LD, KIND_TREE>), grid, dim3(kWG), lds, st, P); break;
+        case KIND_RFSD: hipLaunchKernelGGL((accept_sample<BF16, LD, KIND_RFSD>), grid, dim3(kWG), lds, st, P); break;
+        case KIND_TREESD: hipLaunchKernelGGL((accept_sample<BF16, LD, KIND_TREESD>), grid, dim3(kWG), lds, st, P); break;
+        default: hipLaunchKernelGGL((accept_sample<BF16, LD, KIND_SD>), grid, dim3(kWG), lds, st, P); break;
     }
 }
-void launch_sample(int dtype, bool aligned, int kind, dim3 grid, size_t lds, hipStream_t st, const SampleParams& P) {
+void launch_sample(int dtype, int load, int kind, dim3 grid, size_t lds, hipStream_t st, const SampleParams& P) {
     if (dtype == FSD_BF16) {
-        if (aligned) launch_sample_k<true, true>(kind, grid, lds, st, P);
-        else launch_sample_k<true, false>(kind, grid, lds, st, P);
+        if (load == LOAD_ALIGNED) launch_sample_k<true, LOAD_ALIGNED>(kind, grid, lds, st, P);
+        else if (load == LOAD_WIDE) launch_sample_k<true, LOAD_WIDE>(kind, grid, lds, st, P);
+        else launch_sample_k<true, LOAD_ELEM>(kind, grid, lds, st, P);
     } else {
-        if (aligned) launch_sample_k<false, true>(kind, grid, lds, st, P);
-        else launch_sample_k<false, false>(kind, grid, lds, st, P);
+        if (load == LOAD_ALIGNED) launch_sample_k<false, LOAD_ALIGNED>(kind, grid, lds, st, P);
+        else if (load == LOAD_WIDE) launch_sample_k<false, LOAD_WIDE>(kind, grid, lds, st, P);
+        else launch_sample_k<false, LOAD_ELEM>(kind, grid, lds, st, P);
     }
 }
 
@@ -336,9 +359,10 @@ void launch_walk(Kernel kernel, int B, long nslots, size_t lds, hipStream_t st, 
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(gsw), static_cast<unsigned>(B)), dim3(kWalkWG), lds, st, P);
 }
 
-bool is_aligned(const void* a, const void* b, long V, int VE) {
-    return (V % VE == 0) && (reinterpret_cast<uintptr_t>(a) % 16 == 0) &&
-           (b == nullptr || reinterpret_cast<uintptr_t>(b) % 16 == 0);
+// how the kernels fetch a slot of these rows (see load_slot)
+int load_of(const void* a, const void* b, long V, int VE) {
+    if (V < VE) return LOAD_ELEM;
+    return (V % VE == 0 && reinterpret_cast<uintptr_t>(a) % 16 == 0 && reinterpret_cast<uintptr_t>(b) % 16 == 0) ? LOAD_ALIGNED : LOAD_WIDE;
 }
 
 // Device address of the static scratch array on the current device (nullptr if the runtime will not
@@ -386,7 +410,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     }
 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const bool aligned = is_aligned(target, draft, V, p.VE);
+    const int load = load_of(target, draft, V, p.VE);
     const int R = B * rows;
 
     // which reduction kernel, and its shape
@@ -394,8 +418,16 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     if (k1mode == MODE_KL && dtype == FSD_F32) k1mode = MODE_KLP;
     // bfloat16 JS: the entropy form (reducible FSD, whose finisher also forms the candidates' log-ratios,
     // and the shapes of the tuning hook stay with the pointwise form)
-    if (k1mode == MODE_JS && dtype == FSD_BF16 && kind != KIND_RFSD && !g_exact_js && !g_shape_nv) k1mode = MODE_JSE;
-    if (dtype == FSD_BF16 && !g_shape_nv && (k1mode == MODE_JS || k1mode == MODE_TV || k1mode == MODE_JSE)) {
+    if (load == LOAD_ELEM) {
+        // a row shorter than a slot: one lane of one wavefront, in the smallest shape (the only one with
+        // element-wise loads)
+        p.NV = 2;
+        p.G = 1;
+        p.spm = static_cast<int>(p.nslots);
+    } else if (k1mode == MODE_JS && dtype == FSD_BF16 && kind != KIND_RFSD && !g_exact_js && !g_shape_nv) {
+        k1mode = MODE_JSE;
+    }
+    if (load != LOAD_ELEM && dtype == FSD_BF16 && !g_shape_nv && (k1mode == MODE_JS || k1mode == MODE_TV || k1mode == MODE_JSE)) {
         // The bfloat16 two-phase kernels are bound by instruction issue, a third of it per step and not
         // per entry: they hold 6 slots of each row per lane (96 logits a step), which fits two wavefronts
         // per SIMD (256 registers) because 5 of the 12 chunks of each set of kept exponentials live in
@@ -454,7 +486,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     pp.want_ratio = (kind == KIND_RFSD) ? 1 : 0;
     pp.js_floor = g_js_floor;
     pp.ws = ws;
-    launch_pair(dtype, p.NV, k1mode, aligned, st, pp);
+    launch_pair(dtype, p.NV, k1mode, load, st, pp);
 
     SampleParams sp;
     sp.target = static_cast<const char*>(target);
@@ -496,14 +528,18 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         wp.top_p = top_p;
         wp.thr = ws.thr;
         wp.ws = ws;
-        const bool keep = dtype == FSD_BF16 && aligned && p.nslots <= static_cast<long>(kWarpKeep) * kWarpWG;
+        const bool keep = dtype == FSD_BF16 && load != LOAD_ELEM && p.nslots <= static_cast<long>(kWarpKeep) * kWarpWG;
+        const auto warp = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(B), dim3(kWarpWG), 0, st, wp); };
         if (dtype == FSD_BF16) {
-            if (keep) hipLaunchKernelGGL((warp_select<true, true, true>), dim3(B), dim3(kWarpWG), 0, st, wp);
-            else if (aligned) hipLaunchKernelGGL((warp_select<true, true, false>), dim3(B), dim3(kWarpWG), 0, st, wp);
-            else hipLaunchKernelGGL((warp_select<true, false, false>), dim3(B), dim3(kWarpWG), 0, st, wp);
+            if (keep && load == LOAD_ALIGNED) warp(warp_select<true, LOAD_ALIGNED, true>);
+            else if (keep) warp(warp_select<true, LOAD_WIDE, true>);
+            else if (load == LOAD_ALIGNED) warp(warp_select<true, LOAD_ALIGNED, false>);
+            else if (load == LOAD_WIDE) warp(warp_select<true, LOAD_WIDE, false>);
+            else warp(warp_select<true, LOAD_ELEM, false>);
         } else {
-            if (aligned) hipLaunchKernelGGL((warp_select<false, true, false>), dim3(B), dim3(kWarpWG), 0, st, wp);
-            else hipLaunchKernelGGL((warp_select<false, false, false>), dim3(B), dim3(kWarpWG), 0, st, wp);
+            if (load == LOAD_ALIGNED) warp(warp_select<false, LOAD_ALIGNED, false>);
+            else if (load == LOAD_WIDE) warp(warp_select<false, LOAD_WIDE, false>);
+            else warp(warp_select<false, LOAD_ELEM, false>);
         }
         sp.thr = ws.thr;
         sp.inv_temp = wp.inv_temp;
@@ -526,17 +562,20 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         wk.ws = ws;
         wk.spin_limit = g_spin_limit;
         const size_t wlds = static_cast<size_t>(rows) * 24 + 16;
+        const auto walk = [&](auto kernel) { launch_walk(kernel, B, p.nslots, wlds, st, wk); };
         if (dtype == FSD_BF16) {
-            if (aligned) launch_walk(tree_sd_walk<true, true>, B, p.nslots, wlds, st, wk);
-            else launch_walk(tree_sd_walk<true, false>, B, p.nslots, wlds, st, wk);
+            if (load == LOAD_ALIGNED) walk(tree_sd_walk<true, LOAD_ALIGNED>);
+            else if (load == LOAD_WIDE) walk(tree_sd_walk<true, LOAD_WIDE>);
+            else walk(tree_sd_walk<true, LOAD_ELEM>);
         } else {
-            if (aligned) launch_walk(tree_sd_walk<false, true>, B, p.nslots, wlds, st, wk);
-            else launch_walk(tree_sd_walk<false, false>, B, p.nslots, wlds, st, wk);
+            if (load == LOAD_ALIGNED) walk(tree_sd_walk<false, LOAD_ALIGNED>);
+            else if (load == LOAD_WIDE) walk(tree_sd_walk<false, LOAD_WIDE>);
+            else walk(tree_sd_walk<false, LOAD_ELEM>);
         }
     }
     const size_t lds = (kind == KIND_TREE) ? static_cast<size_t>(rows) * 16
                      : (kind == KIND_TREESD) ? static_cast<size_t>(rows) * 12 : 0;
-    launch_sample(dtype, aligned, kind, dim3(p.GS, B), lds, st, sp);
+    launch_sample(dtype, load, kind, dim3(p.GS, B), lds, st, sp);
 
     return (hipGetLastError() == hipSuccess) ? FSD_OK : FSD_ERR_LAUNCH;
 }

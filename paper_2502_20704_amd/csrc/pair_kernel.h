@@ -259,7 +259,7 @@ __device__ __noinline__ SumMore sum_f64_more_rounds(const unsigned long long* p2
 // The pointwise form of App. C.2 over this wavefront's slice of one pair, from the rows' log2-sum-exp2:
 // p = 2^(a log2e - L_t), q likewise, sum of p log2(2p/s) + q log2(2q/s).  Not pipelined: used for the
 // few pairs whose entropy-form result is below the floor.
-template <int NV, bool ALIGNED>
+template <int NV, int LD>
 __device__ __noinline__ float js_pointwise_slice(const char* tptr, const char* dptr, long V, int sl0, int sl_end,
                                                  int sl_last, float Lt, float Ld) {
     float acc = 0.0f;
@@ -268,8 +268,10 @@ __device__ __noinline__ float js_pointwise_slice(const char* tptr, const char* d
         const int sk = sl0 + 64 * k;
         const bool own = sk < sl_end;
         const long sl = own ? sk : sl_last;
-        uint4 ra = load_slot<true, ALIGNED, false>(tptr, sl, V);
-        uint4 rb = load_slot<true, ALIGNED, false>(dptr, sl, V);
+        uint4 ra = load_slot<true, LD, false>(tptr, sl, V);
+        uint4 rb = load_slot<true, LD, false>(dptr, sl, V);
+        settle_slot<true, LD>(ra, sl, V);
+        settle_slot<true, LD>(rb, sl, V);
         if (!own) { ra = slot_neg_inf<true>(); rb = slot_neg_inf<true>(); }
         float a[8], c[8];
         unpack<true>(ra, a);
@@ -365,7 +367,7 @@ __device__ __noinline__ bool team_arrived(const unsigned long long* slots, int G
     return true;
 }
 
-template <bool BF16, int NV, int MODE, bool ALIGNED, bool TSHARED = false>
+template <bool BF16, int NV, int MODE, int LD, bool TSHARED = false>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(pair_kernel_waves(BF16, NV, MODE))))
 void pair_kernel(PairParams P) {
     constexpr int VE = Slot<BF16>::VE;
@@ -503,6 +505,9 @@ void pair_kernel(PairParams P) {
     const int sl0 = static_cast<int>(s0) + lane;
     const int sl_last = (s1 > s0) ? static_cast<int>(s1) - 1 : 0;
     const int sl_end = static_cast<int>(s1);
+    // byte offset of the last 16 bytes of the slice (at the end of a ragged row: the 16 that end the row)
+    [[maybe_unused]] const unsigned off_last = (LD == LOAD_WIDE && s1 > s0 && s1 * VE > P.V) ? static_cast<unsigned>(P.V) * ES - 16u
+                                                                            : static_cast<unsigned>(sl_last) * 16u;
     const bool fill_needed = s0 + NV * 64 > s1;   // wavefront-uniform: some lane lacks a slot
     // target rows of the pair in work, of the one before it and of the one requested last (entropy-form JS on
     // a tree: a pair whose target row is its predecessor's takes over that row's exponentials and sums)
@@ -529,13 +534,33 @@ void pair_kernel(PairParams P) {
         if constexpr (RECOMPUTE_SLOTS) asm volatile("" : "+v"(first));
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
-            const int sk = first + 64 * k;
-            const long sl = wanted ? (sk < sl_end ? sk : sl_last) : 0;   // not wanted: one cached slot for all lanes
-            ra[k] = load_slot<BF16, ALIGNED, !TSHARED>(tptr, sl, P.V);
-            rb[k] = load_slot<BF16, ALIGNED, true>(dptr, sl, P.V);
+            if constexpr (LD == LOAD_WIDE) {
+                // (one minimum keeps a lane inside the slice and inside the row; not wanted: one cached slot)
+                const unsigned off = static_cast<unsigned>(first) * 16u + 1024u * k, limit = wanted ? off_last : 0u;
+                ra[k] = load_16<LD, !TSHARED>(tptr, off < limit ? off : limit);
+                rb[k] = load_16<LD, true>(dptr, off < limit ? off : limit);
+            } else {
+                const int sk = first + 64 * k;
+                const long sl = wanted ? (sk < sl_end ? sk : sl_last) : 0;   // not wanted: one cached slot for all lanes
+                ra[k] = load_slot<BF16, LD, !TSHARED>(tptr, sl, P.V);
+                rb[k] = load_slot<BF16, LD, true>(dptr, sl, P.V);
+            }
         }
     };
     auto fill_unowned = [&](uint4 (&ra)[NV], uint4 (&rb)[NV]) __attribute__((always_inline)) {
+        if constexpr (LD == LOAD_WIDE) {
+            // the slot that reaches past the end of the row belongs to one lane of the team's last member
+            if (s1 > s0 && s1 * VE > P.V) {
+                asm volatile("");   // stays a branch
+#pragma unroll
+                for (int k = 0; k < NV; ++k) {
+                    if (sl0 + 64 * k == sl_end - 1) {
+                        settle_slot<BF16, LD>(ra[k], sl_end - 1, P.V, JSE ? kJsFill : slot_neg_inf<BF16>().x);
+                        settle_slot<BF16, LD>(rb[k], sl_end - 1, P.V, JSE ? kJsFill : slot_neg_inf<BF16>().x);
+                    }
+                }
+            }
+        }
         if (fill_needed) {
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
@@ -1358,7 +1383,7 @@ void pair_kernel(PairParams P) {
                 const unsigned hi = __builtin_amdgcn_readlane(static_cast<unsigned>(sw >> 32), i);
                 const char *tptr, *dptr;
                 row_ptrs(rp, tptr, dptr);
-                const float part = js_pointwise_slice<NV, ALIGNED>(tptr, dptr, P.V, sl0, sl_end, sl_last, __uint_as_float(lo),
+                const float part = js_pointwise_slice<NV, LD>(tptr, dptr, P.V, sl0, sl_end, sl_last, __uint_as_float(lo),
                                                                    __uint_as_float(hi));
                 // the partial replaces this member's sums of exponentials, which nobody reads any more once the
                 // pair's state word is out (a sum is never -1)

@@ -46,7 +46,7 @@ struct WalkParams {
 
 constexpr int kWalkWG = 1024;
 
-template <bool BF16, bool ALIGNED>
+template <bool BF16, int LD>
 __global__ __launch_bounds__(kWalkWG) void tree_sd_walk(WalkParams P) {
     constexpr int VE = Slot<BF16>::VE;
     constexpr int ES = BF16 ? 2 : 4;
@@ -170,11 +170,12 @@ __global__ __launch_bounds__(kWalkWG) void tree_sd_walk(WalkParams P) {
                     const long sl = base + static_cast<long>(c) * kWalkWG + tid;
                     in[c] = sl < sl_hi;
                     slc[c] = in[c] ? sl : P.nslots - 1;
-                    raw[c] = load_slot<BF16, ALIGNED>(trow, slc[c], P.V);
+                    raw[c] = load_slot<BF16, LD>(trow, slc[c], P.V);
                 }
 #pragma unroll
                 for (int c = 0; c < CH; ++c) {
                     float z[VE];
+                    settle_slot<BF16, LD>(raw[c], slc[c], P.V);
                     unpack<BF16>(raw[c], z);
 #pragma unroll
                     for (int e = 0; e < VE; ++e) pv[c][e] = in[c] ? prob(z[e], lt2) : 0.0f;
@@ -183,12 +184,13 @@ __global__ __launch_bounds__(kWalkWG) void tree_sd_walk(WalkParams P) {
                     const size_t pc = static_cast<size_t>(b) * N + chain[m];
                     const char* cr = P.draft + pc * rowb;
 #pragma unroll
-                    for (int c = 0; c < CH; ++c) raw[c] = load_slot<BF16, ALIGNED>(cr, slc[c], P.V);
+                    for (int c = 0; c < CH; ++c) raw[c] = load_slot<BF16, LD>(cr, slc[c], P.V);
                     const double ldm = lse_of[2 * chain[m] + 1];
                     const float izm = s_invz[m];
 #pragma unroll
                     for (int c = 0; c < CH; ++c) {
                         float zd[VE];
+                        settle_slot<BF16, LD>(raw[c], slc[c], P.V);
                         unpack<BF16>(raw[c], zd);
 #pragma unroll
                         for (int e = 0; e < VE; ++e)
@@ -196,10 +198,11 @@ __global__ __launch_bounds__(kWalkWG) void tree_sd_walk(WalkParams P) {
                     }
                 }
 #pragma unroll
-                for (int c = 0; c < CH; ++c) raw[c] = load_slot<BF16, ALIGNED>(drow, slc[c], P.V);
+                for (int c = 0; c < CH; ++c) raw[c] = load_slot<BF16, LD>(drow, slc[c], P.V);
 #pragma unroll
                 for (int c = 0; c < CH; ++c) {
                     float zd[VE];
+                    settle_slot<BF16, LD>(raw[c], slc[c], P.V);
                     unpack<BF16>(raw[c], zd);
                     float part = 0.0f;
 #pragma unroll

@@ -51,7 +51,7 @@ constexpr int kWarpFastK = 512;   // largest top-k of the short way
 constexpr int kWarpBins = 2048;   // bins of the value histogram (16 KB of LDS)
 constexpr float kWarpRange = 28.0f;   // what lies further below the maximum weighs less than 2^-40: one bin
 
-template <bool BF16, bool ALIGNED, bool KEEP>
+template <bool BF16, int LD, bool KEEP>
 __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     constexpr int VE = Slot<BF16>::VE;
     constexpr int ES = BF16 ? 2 : 4;
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
 #pragma unroll
         for (int c = 0; c < kWarpKeep; ++c) {
             const long sl = static_cast<long>(c) * kWarpWG + tid;
-            kept[c] = load_slot<BF16, ALIGNED>(row, sl < P.nslots ? sl : P.nslots - 1, P.V);
+            kept[c] = load_slot<BF16, LD>(row, sl < P.nslots ? sl : P.nslots - 1, P.V);
         }
     }
     // one pass over the row: f(scaled logit, key) for every entry
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         unpack<BF16>(raw, z);
 #pragma unroll
         for (int e = 0; e < VE; ++e) {
-            if (ALIGNED || sl * VE + e < P.V) {   // aligned rows have no ragged last slot
+            if (LD == LOAD_ALIGNED || sl * VE + e < P.V) {   // aligned rows have no ragged last slot
                 const float sv = __fmul_rn(z[e], P.inv_temp);
                 f(sv, ordered_key(sv));
             }
@@ -160,7 +160,10 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
                 // otherwise be hoisted out of the passes and kept as well, far beyond the register file
                 uint4 r = kept[c];
                 asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w));
-                if (sl < P.nslots) for_slot(r, sl, f);
+                if (sl < P.nslots) {
+                    settle_slot<BF16, LD>(r, sl, P.V);
+                    for_slot(r, sl, f);
+                }
             }
         } else {
             constexpr int CH = 4;
@@ -169,12 +172,15 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
 #pragma unroll
                 for (int c = 0; c < CH; ++c) {
                     const long sl = base + static_cast<long>(c) * kWarpWG + tid;
-                    raw[c] = load_slot<BF16, ALIGNED>(row, sl < P.nslots ? sl : P.nslots - 1, P.V);
+                    raw[c] = load_slot<BF16, LD>(row, sl < P.nslots ? sl : P.nslots - 1, P.V);
                 }
 #pragma unroll
                 for (int c = 0; c < CH; ++c) {
                     const long sl = base + static_cast<long>(c) * kWarpWG + tid;
-                    if (sl < P.nslots) for_slot(raw[c], sl, f);
+                    if (sl < P.nslots) {
+                        settle_slot<BF16, LD>(raw[c], sl, P.V);
+                        for_slot(raw[c], sl, f);
+                    }
                 }
             }
         }

@@ -6,7 +6,8 @@ import pytest
 import paper_2502_20704_amd as fsd
 from paper_2502_20704_amd import synth
 from tests import parity_util as pu
-from tests.test_gpu_parity import check_warped, run_warped
+from tests.test_gpu_parity import (_random_tree_inputs, check_rfsd, check_sd, check_sd_tree, check_warped, run_chain,
+                                   run_rfsd, run_sd_tree, run_tree, run_warped)
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +49,55 @@ def test_selection_by_value(torch_cuda, oracle, V, dtype):
         active = 0 < kw.get("top_k", 0) < V or kw.get("top_p", 1.0) < 1.0
         check_warped(g, o, 0.1, pu.rel_tol(dtype), f"selection by value V={V} {dtype} {kw}", cut_active=active,
                      envelope=pu.Envelope(dtype))
+
+
+# entries a team member holds: 3072 (bfloat16 JS, TV), 2048 (the other kernels); a slot: 8 or 4
+@pytest.mark.parametrize("V", [3, 7, 8, 9, 15, 2047, 2049, 3071, 3073, 6151])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_ragged_rows(torch_cuda, oracle, V, dtype):
+    """Rows that are not 16-byte aligned, through every entry point: rows shorter than a slot, rows whose last slot
+    is all that the team's last member has, and rows one entry short of or past a member's share.  The last row of
+    each tensor ends its allocation's used part, so its last slot is the one that must not reach behind."""
+    inp = synth.chain_inputs(3, 4, V, dtype, "gauss2", 1.0, seed=V)
+    tol, env = pu.rel_tol(dtype), pu.Envelope(dtype)
+    for div in (fsd.DIV_JS, fsd.DIV_TV, fsd.DIV_KL):
+        for mode in (fsd.SAMPLE, fsd.GREEDY):
+            print("ragged", V, dtype, div, mode, flush=True)
+            g = run_chain(torch_cuda, inp, 0.1, div, mode, seed=5, offset=2)
+            o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], 0.1, div, mode, seed=5, offset=2)
+            pu.check_chain(g, o, 0.1, tol, f"ragged V={V} {dtype} div={div}", envelope=env)
+    g = run_rfsd(torch_cuda, inp, 0.1, fsd.DIV_JS, seed=5, offset=2)
+    o = oracle.rfsd_verify_chain(inp["target"], inp["draft"], inp["cand"], 0.1, fsd.DIV_JS, seed=5, offset=2)
+    check_rfsd(g, o, 0.1, tol, f"ragged rFSD V={V} {dtype}", envelope=env)
+    d = pu.to_dev(inp, ("target", "draft", "cand"))
+    out = fsd.sd_verify_chain(d["target"], d["draft"], d["cand"], seed=5, offset=2)
+    torch_cuda.cuda.synchronize()
+    o = oracle.sd_verify_chain(inp["target"], inp["draft"], inp["cand"], seed=5, offset=2)
+    check_sd(pu.host(out, pu.SD_KEYS), o, f"ragged SD V={V} {dtype}")
+    tin = _random_tree_inputs(np.random.default_rng(V), 3, 9, V, dtype)
+    g = run_tree(torch_cuda, tin, 0.1, fsd.DIV_JS, 9, seed=5, offset=2)
+    o = oracle.verify_tree(tin["target"], tin["draft"], tin["node_tokens"], tin["parent"], 9, 0.1, fsd.DIV_JS, seed=5, offset=2)
+    pu.check_tree(g, o, 0.1, tol, f"ragged tree V={V} {dtype}", envelope=env)
+    g = run_sd_tree(torch_cuda, tin, 9, fsd.SAMPLE, seed=5, offset=2)
+    o = oracle.sd_verify_tree(tin["target"], tin["draft"], tin["node_tokens"], tin["parent"], 9, fsd.SAMPLE, seed=5, offset=2)
+    check_sd_tree(g, o, f"ragged SD tree V={V} {dtype}", tin)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_rows_on_odd_addresses(torch_cuda, oracle, dtype):
+    """Tensors whose first row starts one element past a 16-byte boundary (V a multiple of the slot)."""
+    B, K, V = 2, 3, 4096
+    inp = synth.chain_inputs(B, K, V, dtype, "peaked", 1.0, seed=3)
+    d = pu.to_dev(inp, ("target", "draft", "cand"))
+
+    def shifted(t):
+        buf = torch_cuda.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
+        buf[1:] = t.reshape(-1)
+        return buf[1:].view(t.shape)
+
+    for div in (fsd.DIV_JS, fsd.DIV_KL):
+        out = fsd.fsd_verify_chain(shifted(d["target"]), shifted(d["draft"]), d["cand"], 0.1, div, seed=5, offset=2)
+        torch_cuda.cuda.synchronize()
+        o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], 0.1, div, seed=5, offset=2)
+        pu.check_chain(pu.host(out, pu.CHAIN_KEYS), o, 0.1, pu.rel_tol(dtype), f"odd addresses {dtype} div={div}",
+                       envelope=pu.Envelope(dtype))
