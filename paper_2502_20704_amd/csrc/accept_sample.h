@@ -49,13 +49,188 @@ __device__ __forceinline__ Best wave_best(Best v) {
     return v;
 }
 
+// what a draw needs beside the row: cut = the warpers' scale and threshold apply (FSD_SAMPLE only)
+struct DrawArgs {
+    long V;
+    int mode;
+    unsigned seed_lo, seed_hi, off_lo, off_hi;
+    bool cut;
+    float thr_b, inv_temp;
+};
+// strict SD on a tree: the rejected siblings' draft rows that shape the residual (their rows of the sequence's
+// draft tensor, 1 / normalisers and log2-sum-exp2 values, one after the other in LDS)
+struct DrawChain { const char* draft; int rows, n; const int* s; };
+
+// The best score over slots [s0, s1) of the row, dealt to the workgroup's threads: of the row's entries or, with
+// `residual`, of the positive part of p - q.  bad: a NaN or +inf logit was seen.
+//
+// What bounds it: the chain from the row's first load to its last score, and the random numbers (ten rounds of
+// two 64-bit products per four entries).  A lane takes 8 entries a round (16 cost more registers than the
+// loads in flight return: 15.3 instead of 15.9 us for 64 rows of 128256 bfloat16 entries, but 10.6 instead of
+// 8.5 for 16, and 11.4 instead of 10.4 under top-k) and requests the next round's rows, the draft's too, before it
+// works on this one's.  (The residual's draw used to score the row's own entries along with it, for the case that
+// no entry has any positive part; that case is now a second pass of the last workgroup.  With the earlier
+// request of the draft row: strict SD on 64 rows of 128256 bfloat16 entries 24.5 -> 20.4 us.)  256 rows of 151936 binary32 entries: 48.3 us with 4 entries a round, 43.4 with 8.
+template <bool BF16, int LD, bool TREESD>
+__device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char* trow, bool residual, const char* drow,
+                                           float lt, float ld, [[maybe_unused]] const DrawChain& C, long s0, long s1, int tid,
+                                           Best& best, int& bad) {
+    constexpr int VE = Slot<BF16>::VE;
+    [[maybe_unused]] constexpr int ES = BF16 ? 2 : 4;
+    constexpr int NE = 8, NS = NE / VE, STRIDE = kWG;
+    // a score the winner is known to reach (see the bounds below), from the lowest finite one up: an entry
+    // without mass, masked or cut off by the warpers, stays below
+    float thr = -FLT_MAX;
+    // a lane without a slot of its own re-reads the last one; its entries leave the draw
+    auto request = [&](const char* row, long s, uint4 (&raw)[NS]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k) raw[k] = load_slot<BF16, LD>(row, (s + k * STRIDE < s1) ? s + k * STRIDE : s1 - 1, A.V);
+    };
+    auto entries = [&](uint4 (&raw)[NS], long s, float (&z)[NE]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            settle_slot<BF16, LD>(raw[k], (s + k * STRIDE < s1) ? s + k * STRIDE : s1 - 1, A.V);
+            unpack<BF16>(raw[k], z + k * VE);
+        }
+    };
+    uint4 next[NS], nextd[NS];
+    request(trow, s0 + tid, next);
+    const bool pair = !TREESD && residual;
+    if (pair) request(drow, s0 + tid, nextd);
+    // the trip count is the same for every lane: the thresholds are wavefront reductions
+    for (long sb = s0; sb < s1; sb += NS * STRIDE) {
+        const long s = sb + tid;
+        float z[NE];   // what is scored: the logits, or ln of the residual's entries (-inf where it has no mass)
+        uint4 raw[NS], rawd[NS];
+#pragma unroll
+        for (int k = 0; k < NS; ++k) { raw[k] = next[k]; rawd[k] = nextd[k]; }
+        if (sb + NS * STRIDE < s1) {
+            request(trow, s + NS * STRIDE, next);
+            if (pair) request(drow, s + NS * STRIDE, nextd);
+        }
+        entries(raw, s, z);
+        if (A.cut) {
+            // temperature, then the kept set of top-k / top-p: everything else leaves the draw
+            bool any_kept = false;
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                bad |= !(z[e] < __builtin_inff());
+                const float sv = __fmul_rn(z[e], A.inv_temp);
+                const bool keep = sv >= A.thr_b;
+                z[e] = keep ? sv : neg_inf();
+                any_kept |= keep;
+            }
+            // A wavefront without a kept entry has nothing to draw: no random numbers are formed for it.
+            // (Top-k keeps a handful of a row's entries: nearly every wavefront leaves here.  Before, such
+            // a wavefront had no score to reach and evaluated all its variates.  C2's shape with
+            // temperature 0.7, top-k 50, top-p 0.9: 35.6 -> 11.4 us for this kernel.)
+            if (!__any(any_kept)) continue;
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) bad |= !(z[e] < __builtin_inff());
+        if (residual) {
+            float r[NE];
+#pragma unroll
+            for (int e = 0; e < NE; ++e) r[e] = hw_exp2(fmaf(z[e], kLog2e, -lt));
+            if constexpr (TREESD) {
+                // strict SD on a tree: p after the chain's rejections, minus the last draft row
+                const int* ch = C.s;
+                const float* iz = reinterpret_cast<const float*>(C.s + C.rows);
+                const float* ldv = reinterpret_cast<const float*>(C.s + 2 * C.rows);
+                for (int m = 0; m < C.n; ++m) {
+                    float zd[NE];
+                    request(C.draft + static_cast<size_t>(ch[m]) * static_cast<size_t>(A.V) * ES, s, raw);
+                    entries(raw, s, zd);
+                    const float ldm = ldv[m];
+                    if (m + 1 < C.n) {
+                        const float izm = iz[m];
+#pragma unroll
+                        for (int e = 0; e < NE; ++e) r[e] = fmaxf(r[e] - hw_exp2(fmaf(zd[e], kLog2e, -ldm)), 0.0f) * izm;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < NE; ++e) r[e] = r[e] - hw_exp2(fmaf(zd[e], kLog2e, -ldm));
+                    }
+                }
+            } else {
+                float zd[NE];
+                entries(rawd, s, zd);
+#pragma unroll
+                for (int e = 0; e < NE; ++e) r[e] = r[e] - hw_exp2(fmaf(zd[e], kLog2e, -ld));
+            }
+#pragma unroll
+            for (int e = 0; e < NE; ++e) z[e] = (r[e] > 0.0f) ? hw_log2(r[e]) * static_cast<float>(kLn2) : neg_inf();
+        }
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            if (s + k * STRIDE >= s1) {
+#pragma unroll
+                for (int e = 0; e < VE; ++e) z[k * VE + e] = neg_inf();
+            }
+        }
+        auto index_of = [&](int e) __attribute__((always_inline)) { return static_cast<int>((s + (e / VE) * STRIDE) * VE + e % VE); };
+        if (A.mode == FSD_SAMPLE) {
+            // Bounds of a variate from the position c of the leading one of m = (1 - u) 2^24 alone
+            // (c = clz(m) - 8, so 2^-(c+1) <= 1 - u < 2^-c), G = -ln(-ln u) and -ln u between 1 - u and
+            // (1 - u)/u:
+            //     (c - 1) ln2 <= G <= (c + 1) ln2       (c >= 1; G >= -ln(24 ln2) = -2.8116 always)
+            // The largest lower bound of a score in the wavefront is a score the winner must reach, so
+            // an entry whose upper bound stays below it (or below a score already seen) cannot be the
+            // argmax: its variate, two exact-operation logarithms, is never evaluated.  1e-3 covers
+            // the rounding of that routine by a wide margin.
+            float gub[NE];
+            unsigned w[NE];
+            float lo = neg_inf();
+#pragma unroll
+            for (int q = 0; q < NE / 4; ++q) {
+                const U4 r = philox4x32_10(static_cast<unsigned>(index_of(4 * q)) >> 2, static_cast<unsigned>(b), A.off_lo,
+                                           A.off_hi, A.seed_lo, A.seed_hi);
+                w[q * 4 + 0] = r.x; w[q * 4 + 1] = r.y; w[q * 4 + 2] = r.z; w[q * 4 + 3] = r.w;
+            }
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                const unsigned m = 0x00FFFFFFu ^ ((w[e] >> 9) << 1);   // (1 - u) 2^24, odd, >= 1
+                const float c = static_cast<float>(__clz(static_cast<int>(m)) - 8);
+                gub[e] = fmaf(c, 0.693148f, 0.693148f + 1e-3f);
+                const float glb = (c >= 1.0f) ? fmaf(c, 0.693147f, -0.693148f - 1e-3f) : -2.82f;
+                lo = fmaxf(lo, __fadd_rn(z[e], glb));      // (max() drops the NaN of a NaN logit)
+            }
+            thr = fmaxf(thr, wave_max(lo));
+            // The entries that are left, at most a few per wavefront: every lane works through its own,
+            // lowest index first (one pass of the loop serves one entry of every lane that has any).
+            unsigned todo = 0;
+#pragma unroll
+            for (int e = 0; e < NE; ++e) todo |= !(__fadd_rn(z[e], gub[e]) < thr) ? (1u << e) : 0u;
+            while (__any(todo != 0)) {
+                if (todo != 0) {
+                    const int e = __builtin_ctz(todo);
+                    todo &= todo - 1;
+                    float zz = z[0];
+                    unsigned ww = w[0];
+#pragma unroll
+                    for (int i = 1; i < NE; ++i) {
+                        zz = (e == i) ? z[i] : zz;
+                        ww = (e == i) ? w[i] : ww;
+                    }
+                    const float score = __fadd_rn(zz, gumbel(ww));
+                    if (score > best.score) best = Best{score, index_of(e)};
+                }
+            }
+            thr = fmaxf(thr, wave_max(best.score));
+        } else {
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                if (z[e] > best.score) best = Best{z[e], index_of(e)};
+            }
+        }
+    }
+}
+
 template <bool BF16, int LD, int KIND>
 __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
-    constexpr int VE = Slot<BF16>::VE;
     constexpr int ES = BF16 ? 2 : 4;
     extern __shared__ int s_dyn[];   // tree: par[N], anc[N], acc[N], dep[N]
     __shared__ int s_n, s_st, s_key, s_last;
-    __shared__ Best s_best[8];
+    __shared__ Best s_best[4];
     __shared__ int s_bad[4];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -193,228 +368,85 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
             ld = static_cast<float>(P.ws.lse2[2 * (b * rows + n) + 1]);
         }
     }
-    Best best{neg_inf(), 0x7FFFFFFF}, rbest{neg_inf(), 0x7FFFFFFF};
-    int bad = 0;
-    if (!status) {
-        const long s0 = static_cast<long>(gs) * P.sps;
-        const long s1 = (s0 + P.sps < P.nslots) ? s0 + P.sps : P.nslots;
-        // thr, rthr: scores the winner is known to reach (see the bounds below)
-        // (from the lowest finite score up: an entry without mass, masked or cut off by the warpers, stays below)
-        float thr = -FLT_MAX, rthr = -FLT_MAX;
-        const float thr_b = P.thr ? P.thr[b] : neg_inf();
-        // the trip count is the same for every lane: the thresholds are wavefront reductions
-        // the next round's slot is requested before this round's is worked on: the loads of the rounds
-        // overlap with the arithmetic instead of each being waited for in turn
-        uint4 raw_next = load_slot<BF16, LD>(trow, (s0 + tid < s1) ? s0 + tid : s1 - 1, P.V);
-        for (long sb = s0; sb < s1; sb += kWG) {
-            const long s = sb + tid;
-            const bool live = s < s1;
-            float z[VE], zd[VE], lnr[VE];
-            uint4 raw = raw_next;
-            if (sb + kWG < s1) raw_next = load_slot<BF16, LD>(trow, (s + kWG < s1) ? s + kWG : s1 - 1, P.V);
-            settle_slot<BF16, LD>(raw, live ? s : s1 - 1, P.V);
-            unpack<BF16>(raw, z);
-            if (P.thr && P.mode == FSD_SAMPLE) {
-                // temperature, then the kept set of top-k / top-p: everything else leaves the draw
-                bool any_kept = false;
-#pragma unroll
-                for (int e = 0; e < VE; ++e) {
-                    bad |= !(z[e] < __builtin_inff());
-                    const float sv = __fmul_rn(z[e], P.inv_temp);
-                    const bool keep = sv >= thr_b;
-                    z[e] = keep ? sv : neg_inf();
-                    any_kept |= keep;
-                }
-                // A wavefront without a kept entry has nothing to draw: no random numbers are formed for it.
-                // (Top-k keeps a handful of a row's entries: nearly every wavefront leaves here.  Before, such
-                // a wavefront had no score to reach and evaluated all its variates.  C2's shape with
-                // temperature 0.7, top-k 50, top-p 0.9: 35.6 -> 11.4 us for this kernel.)
-                if (!__any(any_kept)) continue;
-            }
-            if (live) {
-            float rres[VE];   // strict SD on a tree: p after the chain's rejections, minus the last draft row
-            if constexpr (KIND == KIND_TREESD) {
-                if (residual) {
-                    const int* ch = s_dyn;
-                    const float* iz = reinterpret_cast<const float*>(s_dyn + rows);
-                    const float* ldv = reinterpret_cast<const float*>(s_dyn + 2 * rows);
-#pragma unroll
-                    for (int e = 0; e < VE; ++e) rres[e] = hw_exp2(fmaf(z[e], kLog2e, -lt));
-                    for (int m = 0; m < nchain; ++m) {
-                        const char* dr = P.draft + (static_cast<size_t>(b) * rows + ch[m]) * static_cast<size_t>(P.V) * ES;
-                        uint4 rawd = load_slot<BF16, LD>(dr, s, P.V);
-                        settle_slot<BF16, LD>(rawd, s, P.V);
-                        unpack<BF16>(rawd, zd);
-                        const float ldm = ldv[m];
-                        if (m + 1 < nchain) {
-                            const float izm = iz[m];
-#pragma unroll
-                            for (int e = 0; e < VE; ++e)
-                                rres[e] = fmaxf(rres[e] - hw_exp2(fmaf(zd[e], kLog2e, -ldm)), 0.0f) * izm;
-                        } else {
-#pragma unroll
-                            for (int e = 0; e < VE; ++e) rres[e] = rres[e] - hw_exp2(fmaf(zd[e], kLog2e, -ldm));
-                        }
-                    }
-                }
-            } else if (residual) {
-                uint4 rawd = load_slot<BF16, LD>(drow, s, P.V);
-                settle_slot<BF16, LD>(rawd, s, P.V);
-                unpack<BF16>(rawd, zd);
-            }
-            // ln of the residual's entries (-inf where it has no mass)
-#pragma unroll
-            for (int e = 0; e < VE; ++e) {
-                bad |= !(z[e] < __builtin_inff());
-                lnr[e] = neg_inf();
-                if (residual) {
-                    float r;
-                    if constexpr (KIND == KIND_TREESD) {
-                        r = rres[e];
-                    } else {
-                        const float p = hw_exp2(fmaf(z[e], kLog2e, -lt));
-                        const float qq = hw_exp2(fmaf(zd[e], kLog2e, -ld));
-                        r = p - qq;
-                    }
-                    if (r > 0.0f) lnr[e] = hw_log2(r) * static_cast<float>(kLn2);
-                }
-            }
-            }
-            if (P.mode == FSD_SAMPLE) {
-                // Bounds of a variate from the position c of the leading one of m = (1 - u) 2^24 alone
-                // (c = clz(m) - 8, so 2^-(c+1) <= 1 - u < 2^-c), G = -ln(-ln u) and -ln u between 1 - u and
-                // (1 - u)/u:
-                //     (c - 1) ln2 <= G <= (c + 1) ln2       (c >= 1; G >= -ln(24 ln2) = -2.8116 always)
-                // The largest lower bound of a score in the wavefront is a score the winner must reach, so
-                // an entry whose upper bound stays below it (or below a score already seen) cannot be the
-                // argmax: its variate, two exact-operation logarithms, is never evaluated.  1e-3 covers
-                // the rounding of that routine by a wide margin.
-                float gub[VE];
-                unsigned w[VE];
-                float lo = neg_inf(), rlo = neg_inf();
-                if (live) {
-#pragma unroll
-                    for (int blk = 0; blk < VE / 4; ++blk) {
-                        const long e0 = s * VE + blk * 4;
-                        const U4 r = philox4x32_10(static_cast<unsigned>(e0 >> 2), static_cast<unsigned>(b), P.off_lo,
-                                                   P.off_hi, P.seed_lo, P.seed_hi);
-                        w[blk * 4 + 0] = r.x; w[blk * 4 + 1] = r.y; w[blk * 4 + 2] = r.z; w[blk * 4 + 3] = r.w;
-                    }
-#pragma unroll
-                    for (int e = 0; e < VE; ++e) {
-                        const unsigned m = 0x00FFFFFFu ^ ((w[e] >> 9) << 1);   // (1 - u) 2^24, odd, >= 1
-                        const float c = static_cast<float>(__clz(static_cast<int>(m)) - 8);
-                        gub[e] = fmaf(c, 0.693148f, 0.693148f + 1e-3f);
-                        const float glb = (c >= 1.0f) ? fmaf(c, 0.693147f, -0.693148f - 1e-3f) : -2.82f;
-                        lo = fmaxf(lo, __fadd_rn(z[e], glb));      // (max() drops the NaN of a NaN logit)
-                        rlo = fmaxf(rlo, __fadd_rn(lnr[e], glb));
-                    }
-                }
-                thr = fmaxf(thr, wave_max(lo));
-                if (residual) rthr = fmaxf(rthr, wave_max(rlo));
-                // The entries that are left, at most a few per wavefront: every lane works through its own,
-                // lowest index first (one pass of the loop serves one entry of every lane that has any).
-                unsigned todo = 0;
-                if (live) {
-#pragma unroll
-                    for (int e = 0; e < VE; ++e) {
-                        const bool may = !(__fadd_rn(z[e], gub[e]) < thr) || (residual && !(__fadd_rn(lnr[e], gub[e]) < rthr));
-                        todo |= may ? (1u << e) : 0u;
-                    }
-                }
-                while (__any(todo != 0)) {
-                    if (todo != 0) {
-                        const int e = __builtin_ctz(todo);
-                        todo &= todo - 1;
-                        float zz = z[0], ll = lnr[0];
-                        unsigned ww = w[0];
-#pragma unroll
-                        for (int i = 1; i < VE; ++i) {
-                            zz = (e == i) ? z[i] : zz;
-                            ll = (e == i) ? lnr[i] : ll;
-                            ww = (e == i) ? w[i] : ww;
-                        }
-                        const int idx = static_cast<int>(s * VE + e);
-                        const float g = gumbel(ww);
-                        const float score = __fadd_rn(zz, g);
-                        if (score > best.score) best = Best{score, idx};
-                        if (ll > neg_inf()) {
-                            const float rs = __fadd_rn(ll, g);
-                            if (rs > rbest.score) rbest = Best{rs, idx};
-                        }
-                    }
-                }
-            } else if (live) {
-#pragma unroll
-                for (int e = 0; e < VE; ++e) {
-                    const int idx = static_cast<int>(s * VE + e);
-                    if (z[e] > best.score) best = Best{z[e], idx};
-                    if (lnr[e] > rbest.score) rbest = Best{lnr[e], idx};
-                }
-            }
-            if (P.mode == FSD_SAMPLE) {
-                thr = fmaxf(thr, wave_max(best.score));
-                if (residual) rthr = fmaxf(rthr, wave_max(rbest.score));
+    long s0 = static_cast<long>(gs) * P.sps;
+    long s1 = (s0 + P.sps < P.nslots) ? s0 + P.sps : P.nslots;
+    bool alone = false;   // the last workgroup once more, over the whole row: see the end of the loop
+    for (;;) {
+        Best best{neg_inf(), 0x7FFFFFFF};
+        int bad = 0;
+        if (!status) {
+            const bool cut = P.thr != nullptr && P.mode == FSD_SAMPLE;
+            const DrawArgs A{P.V, P.mode, P.seed_lo, P.seed_hi, P.off_lo, P.off_hi, cut, cut ? P.thr[b] : neg_inf(), P.inv_temp};
+            const DrawChain C{P.draft + static_cast<size_t>(b) * rows * static_cast<size_t>(P.V) * ES, rows, nchain, s_dyn};
+            draw_share<BF16, LD, KIND == KIND_TREESD>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, best, bad);
+        }
+        best = wave_best(best);
+        bad = __any(bad);
+        if (lane == 0) { s_best[wave] = best; s_bad[wave] = bad; }
+        __syncthreads();
+        if (tid == 0) {
+            Best m = s_best[0];
+            int bd = s_bad[0];
+            for (int k = 1; k < 4; ++k) { m = better(m, s_best[k]); bd |= s_bad[k]; }
+            if (alone) {
+                s_key = m.idx;
+            } else {
+                // The share of this workgroup: two words that say by themselves whether they have arrived.  The
+                // sampler's shares are cleared with the exchange words at the start of the call and a posted
+                // word is never zero (the index goes out plus one, the flag with bit 1 set), so nothing has to
+                // order these stores before the count below: whoever merges looks until the words are there.
+                unsigned long long* slot = P.ws.spart + (static_cast<size_t>(b) * P.GS + gs) * 4;
+                __hip_atomic_store(slot + 0, (static_cast<unsigned long long>(__float_as_uint(m.score)) << 32) | (static_cast<unsigned>(m.idx) + 1u), __ATOMIC_RELAXED, AGENT);
+                __hip_atomic_store(slot + 1, static_cast<unsigned long long>(bd ? 3 : 2), __ATOMIC_RELAXED, AGENT);
+                const unsigned prev = __hip_atomic_fetch_add(P.ws.sdone + static_cast<size_t>(b) * kSdoneStride, 1u, __ATOMIC_RELAXED, AGENT);
+                s_last = (prev == static_cast<unsigned>(P.GS) - 1u) ? 1 : 0;
             }
         }
-    }
-    best = wave_best(best);
-    rbest = wave_best(rbest);
-    bad = __any(bad);
-    if (lane == 0) { s_best[wave] = best; s_best[4 + wave] = rbest; s_bad[wave] = bad; }
-    __syncthreads();
-    if (tid == 0) {
-        Best m = s_best[0], r = s_best[4];
-        int bd = s_bad[0];
-        for (int k = 1; k < 4; ++k) { m = better(m, s_best[k]); r = better(r, s_best[4 + k]); bd |= s_bad[k]; }
-        // The share of this workgroup: three words that say by themselves whether they have arrived.  The
-        // sampler's shares are cleared with the exchange words at the start of the call and a posted
-        // word is never zero (the index goes out plus one, the flag with bit 1 set), so nothing has to
-        // order these stores before the count below: whoever merges looks until the words are there.
-        unsigned long long* slot = P.ws.spart + (static_cast<size_t>(b) * P.GS + gs) * 4;
-        __hip_atomic_store(slot + 0, (static_cast<unsigned long long>(__float_as_uint(m.score)) << 32) | (static_cast<unsigned>(m.idx) + 1u), __ATOMIC_RELAXED, AGENT);
-        __hip_atomic_store(slot + 1, (static_cast<unsigned long long>(__float_as_uint(r.score)) << 32) | (static_cast<unsigned>(r.idx) + 1u), __ATOMIC_RELAXED, AGENT);
-        __hip_atomic_store(slot + 2, static_cast<unsigned long long>(bd ? 3 : 2), __ATOMIC_RELAXED, AGENT);
-        const unsigned prev = __hip_atomic_fetch_add(P.ws.sdone + static_cast<size_t>(b) * kSdoneStride, 1u, __ATOMIC_RELAXED, AGENT);
-        s_last = (prev == static_cast<unsigned>(P.GS) - 1u) ? 1 : 0;
-    }
-    __syncthreads();
-    if (!s_last) return;
+        __syncthreads();
+        if (alone) break;
+        if (!s_last) return;
 
-    // ---- the last workgroup of the sequence merges the shares and writes the outputs
-    if (wave == 0) {   // one share per lane: the loads of all shares are in flight together
-        Best m{neg_inf(), 0x7FFFFFFF}, r{neg_inf(), 0x7FFFFFFF};
-        int bd = 0;
-        bool late = false;
-        for (int k = lane; k < P.GS; k += 64) {
-            const unsigned long long* slot = P.ws.spart + (static_cast<size_t>(b) * P.GS + k) * 4;
-            // every workgroup of the sequence has counted itself, so its words are on their way: normally
-            // they are there at the first look (bounded wait otherwise)
-            unsigned long long w0 = 0, w1 = 0, w2 = 0;
-            for (unsigned polls = 0;; ++polls) {
-                w0 = __hip_atomic_load(slot + 0, __ATOMIC_RELAXED, AGENT);
-                w1 = __hip_atomic_load(slot + 1, __ATOMIC_RELAXED, AGENT);
-                w2 = __hip_atomic_load(slot + 2, __ATOMIC_RELAXED, AGENT);
-                if ((w0 != 0 && w1 != 0 && w2 != 0) || polls >= P.spin_limit) break;
-                __builtin_amdgcn_s_sleep(1);
+        // ---- the last workgroup of the sequence merges the shares and writes the outputs
+        if (wave == 0) {   // one share per lane: the loads of all shares are in flight together
+            Best m{neg_inf(), 0x7FFFFFFF};
+            int bd = 0;
+            bool late = false;
+            for (int k = lane; k < P.GS; k += 64) {
+                const unsigned long long* slot = P.ws.spart + (static_cast<size_t>(b) * P.GS + k) * 4;
+                // every workgroup of the sequence has counted itself, so its words are on their way: normally
+                // they are there at the first look (bounded wait otherwise)
+                unsigned long long w0 = 0, w1 = 0;
+                for (unsigned polls = 0;; ++polls) {
+                    w0 = __hip_atomic_load(slot + 0, __ATOMIC_RELAXED, AGENT);
+                    w1 = __hip_atomic_load(slot + 1, __ATOMIC_RELAXED, AGENT);
+                    if ((w0 != 0 && w1 != 0) || polls >= P.spin_limit) break;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                if (w0 == 0 || w1 == 0) { late = true; continue; }
+                bd |= static_cast<int>(w1 & 1);
+                m = better(m, Best{__uint_as_float(static_cast<unsigned>(w0 >> 32)), static_cast<int>(static_cast<unsigned>(w0) - 1u)});
             }
-            if (w0 == 0 || w1 == 0 || w2 == 0) { late = true; continue; }
-            bd |= static_cast<int>(w2 & 1);
-            m = better(m, Best{__uint_as_float(static_cast<unsigned>(w0 >> 32)), static_cast<int>(static_cast<unsigned>(w0) - 1u)});
-            r = better(r, Best{__uint_as_float(static_cast<unsigned>(w1 >> 32)), static_cast<int>(static_cast<unsigned>(w1) - 1u)});
+            m = wave_best(m);
+            bd = __any(bd);
+            late = __any(late);
+            if (lane == 0) {
+                int st = status;
+                if (late) st |= FSD_ROW_INTERNAL;   // a share never arrived (never expected)
+                if (!st && (bd || (m.idx == 0x7FFFFFFF && !residual))) st |= FSD_ROW_NONFINITE;
+                s_st = st;
+                s_key = m.idx;
+            }
         }
-        m = wave_best(m);
-        r = wave_best(r);
-        bd = __any(bd);
-        late = __any(late);
-        if (lane == 0) {
-            int st = status;
-            if (late) st |= FSD_ROW_INTERNAL;   // a share never arrived (never expected)
-            if (!st && (bd || m.idx == 0x7FFFFFFF)) st |= FSD_ROW_NONFINITE;
-            const int tok = (residual && r.idx != 0x7FFFFFFF) ? r.idx : m.idx;
-            s_st = st;
-            s_key = tok;
-        }
+        __syncthreads();
+        if (!residual || s_st || s_key != 0x7FFFFFFF) break;
+        // No entry has a positive part (p = q to rounding, which a genuine rejection all but excludes): the
+        // token is drawn from the row itself, by this workgroup alone.  (A rejected row is one the reduction
+        // has found usable: it has an entry above -inf.)
+        residual = false;
+        alone = true;
+        s0 = 0;
+        s1 = P.nslots;
+        __syncthreads();   // (s_st and s_key have been read)
     }
     __syncthreads();
     status = s_st;

@@ -101,3 +101,33 @@ def test_rows_on_odd_addresses(torch_cuda, oracle, dtype):
         o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], 0.1, div, seed=5, offset=2)
         pu.check_chain(pu.host(out, pu.CHAIN_KEYS), o, 0.1, pu.rel_tol(dtype), f"odd addresses {dtype} div={div}",
                        envelope=pu.Envelope(dtype))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("mode", [fsd.SAMPLE, fsd.GREEDY])
+def test_residual_without_a_positive_part(torch_cuda, oracle, dtype, mode):
+    """Strict SD rejects a token whose draft probability is a little larger than its target probability, both so
+    small (e^-30) that the other entries' p - q vanish in binary32: no entry of the residual has any mass and the
+    token comes from the target row itself, which is what FSD draws when it rejects (same random stream)."""
+    B, V = 64, 4099
+    rng = np.random.default_rng(7)
+    t = (rng.standard_normal((B, 2, V)) * 2).astype(np.float32)
+    t[:, 0, 11] = -30.0
+    d = t[:, :1].copy()
+    d[:, 0, 11] = -29.0                    # accepted with probability e^-1
+    cand = np.full((B, 1), 11, dtype=np.int32)
+    if dtype == "bf16":
+        t, d = synth.to_bf16_bits(t), synth.to_bf16_bits(d)
+    inp = dict(target=t, draft=d, cand=cand)
+    dv = pu.to_dev(inp, ("target", "draft", "cand"))
+    plain = fsd.fsd_verify_chain(dv["target"], dv["draft"], dv["cand"], -1.0, fsd.DIV_TV, mode, seed=6, offset=3)
+    for call in (lambda: fsd.sd_verify_chain(dv["target"], dv["draft"], dv["cand"], mode, seed=6, offset=3),
+                 lambda: fsd.rfsd_verify_chain(dv["target"], dv["draft"], dv["cand"], -1.0, fsd.DIV_TV, mode, seed=6, offset=3)):
+        out = call()
+        torch_cuda.cuda.synchronize()
+        n, tok = out["accept_len"].cpu().numpy(), out["out_tokens"].cpu().numpy()
+        o = oracle.sd_verify_chain(inp["target"], inp["draft"], inp["cand"], mode, seed=6, offset=3)
+        assert (n == o["accept_len"]).all() and (out["row_status"].cpu().numpy() == 0).all()
+        rejected = n == 0
+        assert 20 <= rejected.sum() <= 60
+        assert (tok[rejected, 0] == plain["out_tokens"].cpu().numpy()[rejected, 0]).all()
