@@ -344,19 +344,31 @@ void launch_sample(int dtype, int load, int kind, dim3 grid, size_t lds, hipStre
 // The workgroups that share a sequence wait for each other, so the whole grid has to be resident:
 // as many per sequence as fit (at most kWalkShare, and no more than there are passes' worth of
 // slots), a single one otherwise.
-template <typename Kernel>
-void launch_walk(Kernel kernel, int B, long nslots, size_t lds, hipStream_t st, const WalkParams& P) {
-    int dev = 0, per_cu = 0, cus = 0;
+template <bool BF16, int LD>
+void launch_walk(int B, long nslots, size_t lds, hipStream_t st, const WalkParams& P) {
+    int dev = 0, cus = 0;
     (void)hipGetDevice(&dev);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kWalkWG, lds) != hipSuccess) per_cu = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
-    (void)hipGetLastError();
-    long gsw = (static_cast<long>(per_cu) * cus) / B;
-    if (gsw > kWalkShare) gsw = kWalkShare;
-    const long by_work = (nslots + kWalkWG - 1) / kWalkWG;
-    if (gsw > by_work) gsw = by_work;
-    if (gsw < 1) gsw = 1;
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(gsw), static_cast<unsigned>(B)), dim3(kWalkWG), lds, st, P);
+    const auto shares = [&](auto kernel) -> long {
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kWalkWG, lds) != hipSuccess) per_cu = 0;
+        (void)hipGetLastError();
+        long gsw = (static_cast<long>(per_cu) * cus) / B;
+        if (gsw > kWalkShare) gsw = kWalkShare;
+        const long by_work = (nslots + kWalkWG - 1) / kWalkWG;
+        if (gsw > by_work) gsw = by_work;
+        return gsw < 1 ? 1 : gsw;
+    };
+    if constexpr (LD != LOAD_ELEM) {
+        // the distribution in force in registers where a workgroup's share of a row allows it
+        const long gsw = shares(tree_sd_walk<BF16, LD, true>);
+        if ((nslots + gsw - 1) / gsw <= static_cast<long>(WalkKeep<BF16>::CH) * kWalkWG) {
+            hipLaunchKernelGGL((tree_sd_walk<BF16, LD, true>), dim3(static_cast<unsigned>(gsw), static_cast<unsigned>(B)), dim3(kWalkWG), lds, st, P);
+            return;
+        }
+    }
+    const long gsw = shares(tree_sd_walk<BF16, LD, false>);
+    hipLaunchKernelGGL((tree_sd_walk<BF16, LD, false>), dim3(static_cast<unsigned>(gsw), static_cast<unsigned>(B)), dim3(kWalkWG), lds, st, P);
 }
 
 // how the kernels fetch a slot of these rows (see load_slot)
@@ -562,15 +574,14 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         wk.ws = ws;
         wk.spin_limit = g_spin_limit;
         const size_t wlds = static_cast<size_t>(rows) * 24 + 16;
-        const auto walk = [&](auto kernel) { launch_walk(kernel, B, p.nslots, wlds, st, wk); };
         if (dtype == FSD_BF16) {
-            if (load == LOAD_ALIGNED) walk(tree_sd_walk<true, LOAD_ALIGNED>);
-            else if (load == LOAD_WIDE) walk(tree_sd_walk<true, LOAD_WIDE>);
-            else walk(tree_sd_walk<true, LOAD_ELEM>);
+            if (load == LOAD_ALIGNED) launch_walk<true, LOAD_ALIGNED>(B, p.nslots, wlds, st, wk);
+            else if (load == LOAD_WIDE) launch_walk<true, LOAD_WIDE>(B, p.nslots, wlds, st, wk);
+            else launch_walk<true, LOAD_ELEM>(B, p.nslots, wlds, st, wk);
         } else {
-            if (load == LOAD_ALIGNED) walk(tree_sd_walk<false, LOAD_ALIGNED>);
-            else if (load == LOAD_WIDE) walk(tree_sd_walk<false, LOAD_WIDE>);
-            else walk(tree_sd_walk<false, LOAD_ELEM>);
+            if (load == LOAD_ALIGNED) launch_walk<false, LOAD_ALIGNED>(B, p.nslots, wlds, st, wk);
+            else if (load == LOAD_WIDE) launch_walk<false, LOAD_WIDE>(B, p.nslots, wlds, st, wk);
+            else launch_walk<false, LOAD_ELEM>(B, p.nslots, wlds, st, wk);
         }
     }
     const size_t lds = (kind == KIND_TREE) ? static_cast<size_t>(rows) * 16

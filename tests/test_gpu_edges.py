@@ -131,3 +131,16 @@ def test_residual_without_a_positive_part(torch_cuda, oracle, dtype, mode):
         rejected = n == 0
         assert 20 <= rejected.sum() <= 60
         assert (tok[rejected, 0] == plain["out_tokens"].cpu().numpy()[rejected, 0]).all()
+
+
+# a wavefront's lanes hold 64 children; a workgroup keeps 3072 slots of a row (8 workgroups a tree)
+@pytest.mark.parametrize("B,N,V,dtype", [(3, 64, 300, "bf16"), (3, 65, 300, "f32"), (2, 130, 77, "bf16"), (2, 5, 150000, "bf16"),
+                                         (2, 5, 200001, "bf16"), (2, 5, 200004, "f32"), (40, 6, 20000, "f32")])
+def test_sd_tree_walk_edges(torch_cuda, oracle, B, N, V, dtype):
+    """Strict SD over star-shaped trees (every rejection is followed by another sibling): more children than a
+    wavefront has lanes, and rows around what the walk keeps in registers."""
+    inp = _random_tree_inputs(np.random.default_rng(N + V), B, N, V, dtype, star=True, noise=(1.5, 3.0))
+    g = run_sd_tree(torch_cuda, inp, 1, fsd.SAMPLE, seed=3, offset=1)
+    o = oracle.sd_verify_tree(inp["target"], inp["draft"], inp["node_tokens"], inp["parent"], 1, fsd.SAMPLE, seed=3, offset=1)
+    r = check_sd_tree(g, o, f"walk edges B={B} N={N} V={V} {dtype}", inp)
+    print(r, "tried", (~np.isnan(o["log_ratio"])).sum(1), flush=True)
