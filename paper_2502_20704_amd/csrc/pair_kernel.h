@@ -376,6 +376,9 @@ void pair_kernel(PairParams P) {
     constexpr bool JSE = (MODE == MODE_JSE);   // bfloat16 only (the host sends binary32 JS to MODE_JS)
     constexpr bool RECOMPUTE_SLOTS = JSE && TSHARED;   // (the tree variant of the entropy form is the one short of registers)
     constexpr bool SHARE = JSE && TSHARED;     // consecutive pairs with one target row share its phase 1 (see step)
+    // strict SD on a tree: such a pair takes over that row's reference exponent and sum (see step), and its target
+    // row is not even requested
+    constexpr bool SHARE_SUM = MODE == MODE_LSE && TSHARED && LD != LOAD_ELEM;
     constexpr int NE = TWO_PHASE ? NV * VE : 1;   // exponentials kept per row and lane
     constexpr int PW = (MODE == MODE_TV || MODE == MODE_KLP) ? 2 : 1;   // divergence words a member posts (two sums each)
     constexpr int FW = TWO_PHASE ? PW : 4;          // words per member the finisher reads
@@ -506,7 +509,7 @@ void pair_kernel(PairParams P) {
     const int sl_last = (s1 > s0) ? static_cast<int>(s1) - 1 : 0;
     const int sl_end = static_cast<int>(s1);
     // byte offset of the last 16 bytes of the slice (at the end of a ragged row: the 16 that end the row)
-    [[maybe_unused]] const unsigned off_last = (LD == LOAD_WIDE && s1 > s0 && s1 * VE > P.V) ? static_cast<unsigned>(P.V) * ES - 16u
+    [[maybe_unused]] const unsigned off_last = ((LD == LOAD_WIDE) && s1 > s0 && s1 * VE > P.V) ? static_cast<unsigned>(P.V) * ES - 16u
                                                                             : static_cast<unsigned>(sl_last) * 16u;
     const bool fill_needed = s0 + NV * 64 > s1;   // wavefront-uniform: some lane lacks a slot
     // target rows of the pair in work, of the one before it and of the one requested last (entropy-form JS on
@@ -522,6 +525,7 @@ void pair_kernel(PairParams P) {
             if (load_j >= P.rows) { load_j -= P.rows; ++load_b; }
         }
         row_ptrs_bj(pair, load_b, load_j, tptr, dptr);
+        [[maybe_unused]] const bool again = tptr == tp_next;   // the row requested last
         tp_next = tptr;
         // A draft row is read once.  So is a target row of a chain (but for the one the token is drawn
         // from); in a tree the children of a node share their parent's target row, which should stay
@@ -532,6 +536,23 @@ void pair_kernel(PairParams P) {
         // being kept: hidden from the hoisting of loop invariants)
         int first = sl0;
         if constexpr (RECOMPUTE_SLOTS) asm volatile("" : "+v"(first));
+        if constexpr (SHARE_SUM) {
+            // the target's requests first: with them the draft's are the last in flight whether or not they are
+            // made, so the wait for the draft row stays exact
+            const unsigned limit = wanted ? off_last : 0u;
+            const auto off_of = [&](int k) __attribute__((always_inline)) {
+                const unsigned off = static_cast<unsigned>(first) * 16u + 1024u * k;
+                return off < limit ? off : limit;
+            };
+            if (!again) {
+#pragma unroll
+                for (int k = 0; k < NV; ++k) ra[k] = load_16<LD, false>(tptr, off_of(k));
+            }
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int k = 0; k < NV; ++k) rb[k] = load_16<LD, true>(dptr, off_of(k));
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             if constexpr (LD == LOAD_WIDE) {
@@ -1015,6 +1036,8 @@ void pair_kernel(PairParams P) {
     // pair is all there is to remember.
     const int sp_delay = (GW - 1 < 16) ? GW - 1 : 16;
     int sp_pair = -1, sp_due = 0;
+    [[maybe_unused]] float last_kt = 0.0f;     // SHARE_SUM: the last step's reference exponent and sum of the target row
+    [[maybe_unused]] double last_sum = 0.0;
 
     // One step: phase 1 of `pair` into (ect, ecd), then phase 2 of the previous pair from (ept, epd).
     // Memory operations return in the order they were issued, so the order of the requests decides
@@ -1062,7 +1085,7 @@ void pair_kernel(PairParams P) {
         // is only made sometimes would make the count of requests in flight inexact).
         tp_prev = tp_cur;
         tp_cur = tp_next;
-        const bool same_target = SHARE && iter > 0 && tp_cur == tp_prev;
+        const bool same_target = (SHARE || SHARE_SUM) && iter > 0 && tp_cur == tp_prev;
         float kt, kd, st = 0.0f, sd = 0.0f, wacc = 0.0f, dmax = JSE ? 0.0f : neg_inf();
         auto phase1 = [&](auto SAME_T) __attribute__((always_inline)) {
             constexpr bool SAME = decltype(SAME_T)::value;
@@ -1104,7 +1127,7 @@ void pair_kernel(PairParams P) {
             }
             PT(0);   // load wait + max pass
             if constexpr (SAME) md = wave_max(md); else wave_max2(mt, md);
-            kt = SAME ? due.kt : ((mt == neg_inf()) ? 0.0f : ceilf(mt * kLog2e));
+            kt = SAME ? (SHARE_SUM ? last_kt : due.kt) : ((mt == neg_inf()) ? 0.0f : ceilf(mt * kLog2e));
             kd = (md == neg_inf()) ? 0.0f : ceilf(md * kLog2e);
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
@@ -1159,7 +1182,7 @@ void pair_kernel(PairParams P) {
                 }
             }
         };
-        if constexpr (SHARE) {
+        if constexpr (SHARE || SHARE_SUM) {
             if (same_target) {
                 asm volatile("");
                 phase1(BoolTag<true>{});
@@ -1214,7 +1237,13 @@ void pair_kernel(PairParams P) {
             }
             mine = (lane == 0) ? w0 : pack2(st, sd);
         } else {
-            const double pst_ = wave_sum(static_cast<double>(st));
+            double pst_;
+            if (SHARE_SUM && same_target) {
+                pst_ = last_sum;
+            } else {
+                pst_ = wave_sum(static_cast<double>(st));
+            }
+            if constexpr (SHARE_SUM) { last_kt = kt; last_sum = pst_; }
             const double psd_ = wave_sum(static_cast<double>(sd));
             double pw_ = 0.0;
             if constexpr (MODE == MODE_KL) {

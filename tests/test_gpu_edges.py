@@ -144,3 +144,21 @@ def test_sd_tree_walk_edges(torch_cuda, oracle, B, N, V, dtype):
     o = oracle.sd_verify_tree(inp["target"], inp["draft"], inp["node_tokens"], inp["parent"], 1, fsd.SAMPLE, seed=3, offset=1)
     r = check_sd_tree(g, o, f"walk edges B={B} N={N} V={V} {dtype}", inp)
     print(r, "tried", (~np.isnan(o["log_ratio"])).sum(1), flush=True)
+
+
+@pytest.mark.parametrize("star", [False, True])
+@pytest.mark.parametrize("V,dtype", [(2048, "bf16"), (4100, "bf16"), (128256, "bf16"), (2050, "f32"), (40004, "f32")])
+def test_sd_tree_siblings_share_sums(torch_cuda, oracle, V, dtype, star):
+    """Strict SD over trees: siblings share their target row's sum instead of forming it again.  A star (one row for
+    all), random trees (runs of siblings of any length, the teams' runs of pairs crossing sequences), and an
+    unusable shared row, which must spoil every pair that refers to it and no other sequence."""
+    B, N = (3, 7) if V > 100000 else (5, 24)
+    inp = _random_tree_inputs(np.random.default_rng(V), B, N, V, dtype, star=star)
+    depth = 1 if star else N
+    g = run_sd_tree(torch_cuda, inp, depth, fsd.SAMPLE, seed=3, offset=1)
+    o = oracle.sd_verify_tree(inp["target"], inp["draft"], inp["node_tokens"], inp["parent"], depth, fsd.SAMPLE, seed=3, offset=1)
+    check_sd_tree(g, o, f"siblings share sums V={V} {dtype} star={star}", inp)
+    inp["target"][1, 0, V // 2] = np.uint16(0x7FC0) if dtype == "bf16" else np.float32(np.nan)
+    g = run_sd_tree(torch_cuda, inp, depth, fsd.SAMPLE, seed=3, offset=1)
+    assert g["row_status"][1] == fsd.ROW_NONFINITE and (np.delete(g["row_status"], 1) == 0).all()
+    assert (g["path_nodes"][1] == -1).all() and (g["out_tokens"][1] == -1).all()
