@@ -371,6 +371,33 @@ void launch_walk(int B, long nslots, size_t lds, hipStream_t st, const WalkParam
     hipLaunchKernelGGL((tree_sd_walk<BF16, LD, false>), dim3(static_cast<unsigned>(gsw), static_cast<unsigned>(B)), dim3(kWalkWG), lds, st, P);
 }
 
+// warp_select with several workgroups per sequence, which wait for each other: false (nothing launched) if fewer
+// than two per sequence are resident, or a share does not fit their registers
+template <bool BF16, int LD>
+bool launch_warp_split(int B, hipStream_t st, const WarpParams& P) {
+    static std::atomic<long> resident[16] = {};
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    if (dev < 0 || dev >= 16) dev = 0;
+    long total = resident[dev].load(std::memory_order_relaxed);
+    if (total == 0) {
+        int per_cu = 0, cus = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, warp_select<BF16, LD, true, true>, kWarpWG, 0) != hipSuccess) per_cu = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
+        (void)hipGetLastError();
+        total = static_cast<long>(per_cu) * cus;
+        if (total < 1) total = 1;
+        resident[dev].store(total, std::memory_order_relaxed);
+    }
+    long W = total / B;
+    if (W > kWarpShare) W = kWarpShare;
+    const long by_work = (P.nslots + kWarpWG - 1) / kWarpWG;
+    if (W > by_work) W = by_work;
+    if (W < 2 || (P.nslots + W - 1) / W > static_cast<long>(kSplitKeep) * kWarpWG) return false;
+    hipLaunchKernelGGL((warp_select<BF16, LD, true, true>), dim3(static_cast<unsigned>(W), static_cast<unsigned>(B)), dim3(kWarpWG), 0, st, P);
+    return true;
+}
+
 // how the kernels fetch a slot of these rows (see load_slot)
 int load_of(const void* a, const void* b, long V, int VE) {
     if (V < VE) return LOAD_ELEM;
@@ -425,6 +452,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     const int load = load_of(target, draft, V, p.VE);
     const int R = B * rows;
 
+    const int plan_G = p.G;   // what the workspace is laid out for
     // which reduction kernel, and its shape
     int k1mode = (kind == KIND_SD || kind == KIND_TREESD) ? MODE_LSE : div;
     if (k1mode == MODE_KL && dtype == FSD_F32) k1mode = MODE_KLP;
@@ -541,8 +569,21 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         wp.thr = ws.thr;
         wp.ws = ws;
         const bool keep = dtype == FSD_BF16 && load != LOAD_ELEM && p.nslots <= static_cast<long>(kWarpKeep) * kWarpWG;
+        wp.area = reinterpret_cast<char*>(ws.part1);
+        wp.seq_bytes = static_cast<size_t>(rows) * plan_G * 64;
+        wp.spin_limit = g_spin_limit;
+        const bool want_k = top_k > 0 && top_k < V, want_p = top_p < 1.0f;
         const auto warp = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(B), dim3(kWarpWG), 0, st, wp); };
-        if (dtype == FSD_BF16) {
+        // several workgroups a sequence, where a setting allows it, the workspace has room for what they leave each
+        // other and all of them are resident
+        const bool split = load != LOAD_ELEM && (want_k ? top_k <= kWarpFastK : want_p) && wp.seq_bytes >= kSplitBytes &&
+                           (dtype == FSD_BF16 ? (load == LOAD_ALIGNED ? launch_warp_split<true, LOAD_ALIGNED>(B, st, wp)
+                                                                      : launch_warp_split<true, LOAD_WIDE>(B, st, wp))
+                                              : (load == LOAD_ALIGNED ? launch_warp_split<false, LOAD_ALIGNED>(B, st, wp)
+                                                                      : launch_warp_split<false, LOAD_WIDE>(B, st, wp)));
+        if (split) {
+            // (launched)
+        } else if (dtype == FSD_BF16) {
             if (keep && load == LOAD_ALIGNED) warp(warp_select<true, LOAD_ALIGNED, true>);
             else if (keep) warp(warp_select<true, LOAD_WIDE, true>);
             else if (load == LOAD_ALIGNED) warp(warp_select<true, LOAD_ALIGNED, false>);

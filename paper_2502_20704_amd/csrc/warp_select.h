@@ -4,20 +4,21 @@
 #define FSD_CSRC_WARP_SELECT_H_
 
 #include "device_common.h"
+#include "pair_kernel.h"
 
 namespace {
 
 // ------------------------------------------------------------------------------------------
 // sampling-method warpers (Sec. 4: the token is drawn with "whatever sampling method the user
 // sets"): temperature, then top-k, then top-p, in that order, on the row the token is drawn from.
-// One workgroup per sequence finds the smallest kept scaled logit s = z inv_temp:
+// One workgroup per sequence, or several (SPLIT), find the smallest kept scaled logit s = z inv_temp:
 //   top-k   the k-th largest s: a select over the order-preserving 32-bit image of s;
 //   top-p   the largest t with sum_{s >= t} e^(s - max) >= top_p sum_{kept} e^(s - max), by the same
 //           select on weights; the weights are 2^40 fixed-point integers, so that the sums do not
 //           depend on the order of the atomic additions (results are the same run to run).
 // Ties at either threshold are kept.  accept_sample then drops every entry below the threshold.
-// What bounds it: one workgroup, hence one compute unit, passes over the row three times (range, sums or
-// per-thread maxima, gathering), and the selects in LDS are chains of barriers.
+// What bounds it: the passes over the row (range, sums or per-thread maxima, gathering) on few compute units, the
+// selects in LDS, which are chains of barriers, and with SPLIT the round trips between the workgroups.
 
 __device__ __forceinline__ unsigned ordered_key(float x) {
     const unsigned u = __float_as_uint(x);
@@ -38,10 +39,23 @@ struct WarpParams {
     int top_k;            // 0 = off
     float top_p;          // 1 = off
     float* thr;           // [B] out
+    // SPLIT: memory of a sequence's workgroups, seq_bytes each (the exchange words of the reduction, which has ended)
+    char* area;
+    size_t seq_bytes;
+    unsigned spin_limit;
     Ws ws;
 };
 
 constexpr int kWarpWG = 1024;
+
+// An interval that holds every value of a bin of the value histogram: a cheap first question for the passes that
+// gather one bin's entries (the bin itself is decided by the same operations as in the histogram).  The slack
+// covers the rounding of those operations (1e-6 of a difference of at most 2048 bins) and of the bounds.
+struct Interval { float lo, hi; };
+__device__ __forceinline__ Interval bin_interval(float top, float scale, int bin) {
+    const float slack = 0.01f / scale + fabsf(top) * 1e-6f, at = static_cast<float>(bin);
+    return Interval{top - (at + 1.0f) / scale - slack, top - at / scale + slack};
+}
 
 // KEEP: the row fits 16 slots per thread (bfloat16 rows up to 131072 entries) and is read once into
 // registers; otherwise every pass streams it again, four loads in flight per thread.
@@ -51,7 +65,24 @@ constexpr int kWarpFastK = 512;   // largest top-k of the short way
 constexpr int kWarpBins = 2048;   // bins of the value histogram (16 KB of LDS)
 constexpr float kWarpRange = 28.0f;   // what lies further below the maximum weighs less than 2^-40: one bin
 
-template <bool BF16, int LD, bool KEEP>
+// SPLIT: gridDim.x workgroups share a sequence, each with at most kSplitKeep slots of the row per thread, for the
+// usual settings (top-k of at most kWarpFastK, or top-p alone).  One workgroup's time is a compute unit
+// reading and passing over a whole row while most of the device is idle, so up to eight share a row and what is left
+// for one of them is the select (rows of 128256 bfloat16 entries: 64 of them under temperature 0.7, top-k 50, top-p 0.9
+// take 23 us with four workgroups each, 30 with one; 8 of them under top-p 0.95 30 us with eight, 49 with one):
+//   top-k   every workgroup leaves the entries at or above the k-th largest of its own threads' maxima (the
+//           row's k largest are among them) and counts itself; whoever counts last selects from all of them.
+//   top-p   the workgroups agree on the row's range (one word each, zero until posted; the wait is bounded, and
+//           all are resident, which the host checks), add their histograms of values in memory and count
+//           themselves; whoever counts last finds the bin of the crossing, gathers it from the row and selects.
+// Words and counts lie in the sequence's counter line, which every call clears.  What is left for others is stored
+// with device-scope stores and performed (s_waitcnt) before the count.
+constexpr int kWarpShare = 8;
+constexpr int kSplitKeep = 5;
+constexpr int kSplitBins = kWarpWG;
+constexpr size_t kSplitBytes = 16384;   // a sequence's lists: 4096 keys; or its histogram
+
+template <bool BF16, int LD, bool KEEP, bool SPLIT = false>
 __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     constexpr int VE = Slot<BF16>::VE;
     constexpr int ES = BF16 ? 2 : 4;
@@ -68,7 +99,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     __shared__ unsigned long long s_need;
     __shared__ float s_max, s_min;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b = blockIdx.x;
+    const int b = SPLIT ? blockIdx.y : blockIdx.x;
 
     // ---- the row the token will be drawn from: the first rejected position, or the row after the last
     // (chain); the row after the deepest node whose ancestors are all accepted, lowest index on ties (tree)
@@ -131,12 +162,18 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     }
     const char* row = P.target + (static_cast<size_t>(b) * (P.rows + 1) + s_n) * static_cast<size_t>(P.V) * ES;
 
-    uint4 kept[KEEP ? kWarpKeep : 1];
+    constexpr int NK = SPLIT ? kSplitKeep : kWarpKeep;
+    // this workgroup's share of the row
+    const long share = SPLIT ? (P.nslots + gridDim.x - 1) / gridDim.x : P.nslots;
+    const long sl_lo = SPLIT ? static_cast<long>(blockIdx.x) * share : 0;
+    const long sl_hi = (sl_lo + share < P.nslots) ? sl_lo + share : P.nslots;
+    bool whole = !SPLIT;   // SPLIT: the last workgroup passes over the whole row
+    uint4 kept[KEEP ? NK : 1];
     if constexpr (KEEP) {
 #pragma unroll
-        for (int c = 0; c < kWarpKeep; ++c) {
-            const long sl = static_cast<long>(c) * kWarpWG + tid;
-            kept[c] = load_slot<BF16, LD>(row, sl < P.nslots ? sl : P.nslots - 1, P.V);
+        for (int c = 0; c < NK; ++c) {
+            const long sl = sl_lo + static_cast<long>(c) * kWarpWG + tid;
+            kept[c] = load_slot<BF16, LD>(row, sl < sl_hi ? sl : P.nslots - 1, P.V);
         }
     }
     // one pass over the row: f(scaled logit, key) for every entry
@@ -153,19 +190,22 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     };
     auto for_each = [&](auto&& f) __attribute__((always_inline)) {
         if constexpr (KEEP) {
+            if (!SPLIT || !whole) {
 #pragma unroll
-            for (int c = 0; c < kWarpKeep; ++c) {
-                const long sl = static_cast<long>(c) * kWarpWG + tid;
-                // the copy is made opaque: what is derived from the kept words (scaled values, keys) would
-                // otherwise be hoisted out of the passes and kept as well, far beyond the register file
-                uint4 r = kept[c];
-                asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w));
-                if (sl < P.nslots) {
-                    settle_slot<BF16, LD>(r, sl, P.V);
-                    for_slot(r, sl, f);
+                for (int c = 0; c < NK; ++c) {
+                    const long sl = sl_lo + static_cast<long>(c) * kWarpWG + tid;
+                    // the copy is made opaque: what is derived from the kept words (scaled values, keys) would
+                    // otherwise be hoisted out of the passes and kept as well, far beyond the register file
+                    uint4 r = kept[c];
+                    asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w));
+                    if (sl < sl_hi) {
+                        settle_slot<BF16, LD>(r, sl, P.V);
+                        for_slot(r, sl, f);
+                    }
                 }
             }
-        } else {
+        }
+        if (!KEEP || (SPLIT && whole)) {
             constexpr int CH = 4;
             for (long base = 0; base < P.nslots; base += static_cast<long>(kWarpWG) * CH) {
                 uint4 raw[CH];
@@ -262,10 +302,11 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     // Radix select from the top over an array of order-preserving keys in LDS, 8 bits a pass: the
     // smallest key whose entries, together with everything above them, weigh at least s_need.
     // wgt(sv, key) gives an entry's weight (0 = not taking part); first_total, called with the
-    // total weight of the first histogram, may set s_need.
-    auto lds_select = [&](const unsigned* keys, int n, auto&& wgt, auto&& first_total) __attribute__((always_inline)) {
+    // total weight of the first histogram, may set s_need.  down_to: the last digit's shift (16: the upper half of
+    // the key, a lower bound of it).
+    auto lds_select = [&](const unsigned* keys, int n, auto&& wgt, auto&& first_total, int down_to = 0) __attribute__((always_inline)) {
         if (tid == 0) { s_prefix = 0u; s_mask = 0u; }
-        for (int shift = 24; shift >= 0; shift -= 8) {
+        for (int shift = 24; shift >= down_to; shift -= 8) {
             if (tid < 256) { s_hist[tid] = 0ull; s_cnt[tid] = 0u; }
             __syncthreads();
             const unsigned prefix = s_prefix, mask = s_mask;
@@ -386,8 +427,9 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         __syncthreads();
         const int chosen = s_bin;
         if (chosen < 0) return false;
+        const Interval near = bin_interval(top, scale, chosen);
         for_each([&](float sv, unsigned key) {
-            if (bin_of(sv) == chosen && wgt(sv, key)) {
+            if (sv >= near.lo && sv <= near.hi && bin_of(sv) == chosen && wgt(sv, key)) {
                 const int at = atomicAdd(&s_nlist, 1);
                 if (at < kWarpList) s_lkey[at] = key;
             }
@@ -407,7 +449,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         return;
     }
     const float tmax = row_range();
-    const float cmax = s_max * kLog2e;
+    float cmax = s_max * kLog2e;
     auto one = [&](float, unsigned) __attribute__((always_inline)) -> unsigned long long { return 1ull; };
     // e^(s - max) in 2^-40 units; entries at -inf or below the top-k cut weigh nothing
     auto weight = [&](float sv, unsigned) __attribute__((always_inline)) -> unsigned long long {
@@ -426,17 +468,179 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     };
     auto first_k = [&](unsigned long long) __attribute__((always_inline)) -> unsigned long long { return static_cast<unsigned long long>(P.top_k); };
 
+    if constexpr (SPLIT) {
+        unsigned* const line = P.ws.sdone + static_cast<size_t>(b) * kSdoneStride;   // word 0 is the sampler's count
+        unsigned* const count = line + 1;
+        char* const area = P.area + static_cast<size_t>(b) * P.seq_bytes;
+        const int g = static_cast<int>(blockIdx.x), W = static_cast<int>(gridDim.x);
+        // everything this workgroup has stored is performed, then it counts itself: true for the last one
+        auto count_self = [&]() __attribute__((always_inline)) -> bool {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (tid == 0) s_bin = (__hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, AGENT) == static_cast<unsigned>(W) - 1u) ? 1 : 0;
+            __syncthreads();
+            const bool last = s_bin != 0;
+            __syncthreads();   // (s_bin is used again)
+            return last;
+        };
+        if (want_k) {
+            // lists of cap keys, each behind its length
+            const int cap = static_cast<int>(kSplitBytes / 4) / W - 1;
+            unsigned* const lists = reinterpret_cast<unsigned*>(area);
+            s_tmax[tid] = ordered_key(tmax);
+            if (tid == 0) { s_need = static_cast<unsigned long long>(P.top_k); s_nlist = 0; }
+            __syncthreads();
+            lds_select(s_tmax, kWarpWG, one, [](unsigned long long) {}, 16);   // (any bound with k entries at or above it)
+            const unsigned low = s_prefix;
+            for_each([&](float, unsigned key) {
+                if (key >= low) {
+                    const int at = atomicAdd(&s_nlist, 1);
+                    if (at < cap) s_lkey[at] = key;
+                }
+            });
+            __syncthreads();
+            const int left = s_nlist;
+            for (int i = tid; i < left && i < cap; i += kWarpWG)
+                __hip_atomic_store(lists + g * (cap + 1) + 1 + i, s_lkey[i], __ATOMIC_RELAXED, AGENT);
+            if (tid == 0) __hip_atomic_store(lists + g * (cap + 1), static_cast<unsigned>(left), __ATOMIC_RELAXED, AGENT);
+            if (!count_self()) return;
+            if (tid == 0) s_nlist = 0;
+            __syncthreads();
+            // (a stretch of threads per list: all lists are read at once; at most kSplitBytes / 4 <= kWarpList keys)
+            const int per = kWarpWG / W, w = tid / per;
+            bool too_long = false;
+            if (w < W) {
+                const int n = static_cast<int>(__hip_atomic_load(lists + w * (cap + 1), __ATOMIC_RELAXED, AGENT));
+                too_long = n > cap;
+                for (int i = tid - w * per; i < n && !too_long; i += per) {
+                    const unsigned key = __hip_atomic_load(lists + w * (cap + 1) + 1 + i, __ATOMIC_RELAXED, AGENT);
+                    s_lkey[atomicAdd(&s_nlist, 1)] = key;
+                }
+            }
+            const bool fits = __syncthreads_or(too_long) == 0;
+            whole = true;
+            if (fits) {
+                const int n = s_nlist;
+                if (tid == 0) s_need = static_cast<unsigned long long>(P.top_k);
+                unsigned top = 0u;
+                for (int i = tid; i < n; i += kWarpWG) top = s_lkey[i] > top ? s_lkey[i] : top;
+                block_range(key_value(top), 0.0f);   // (a thread without a key brings the NaN of key 0, which max() drops)
+                cmax = s_max * kLog2e;
+                lds_select(s_lkey, n, one, [](unsigned long long) {});
+                t_k = key_value(s_prefix);
+                __syncthreads();
+                if (want_p) {
+                    lds_select(s_lkey, n, weight, [&](unsigned long long Z) { s_need = nucleus_need(Z); });
+                    t_p = key_value(s_prefix);
+                }
+                if (tid == 0) P.thr[b] = fmaxf(t_k, t_p);
+                return;
+            }
+            row_range();
+            cmax = s_max * kLog2e;
+        } else {
+            unsigned long long* const bins = reinterpret_cast<unsigned long long*>(area);
+            unsigned long long* const words = reinterpret_cast<unsigned long long*>(line + 2);
+            // this workgroup's part of the histogram is cleared before its word is posted
+            for (int i = g * kSplitBins / W + tid; i < (g + 1) * kSplitBins / W; i += kWarpWG)
+                __hip_atomic_store(bins + i, 0ull, __ATOMIC_RELAXED, AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            s_bins[tid] = 0ull;
+            __syncthreads();
+            if (tid == 0) post64(words + g, pack2(s_max, -s_min));
+            if (wave == 0) {
+                unsigned long long v = 1ull;
+                for (unsigned polls = 0;; ++polls) {
+                    v = read64(words + (lane < W ? lane : 0));
+                    if (!__any(v == 0ull) || polls >= P.spin_limit) break;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                const bool missing = __any(v == 0ull) != 0;
+                float m = lo_f(v), neg = hi_f(v);
+                wave_max2(m, neg);
+                if (lane == 0) { s_max = m; s_min = -neg; s_bin = missing ? 1 : 0; }
+            }
+            __syncthreads();
+            if (s_bin != 0) {   // a workgroup of this sequence never posted: the call reports it
+                if (tid == 0) { flag_failure(P.ws); P.thr[b] = neg_inf(); }
+                return;
+            }
+            cmax = s_max * kLog2e;
+            const float top = s_max;
+            const float scale = static_cast<float>(kSplitBins - 2) / fmaxf(fminf(top - s_min, kWarpRange), 1e-30f);
+            auto bin_of = [&](float sv) __attribute__((always_inline)) -> int {
+                return static_cast<int>(fminf(fmaxf((top - sv) * scale, 0.0f), static_cast<float>(kSplitBins - 1)));
+            };
+            unsigned long long tail = 0ull;   // (the last bin: see bin_select)
+            for_each([&](float sv, unsigned key) {
+                const unsigned long long w = weight(sv, key);
+                const int bin = bin_of(sv);
+                if (bin == kSplitBins - 1) tail += w;
+                else if (w) atomicAdd(&s_bins[bin], w);
+            });
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) tail += __shfl_xor(tail, o);
+            if (lane == 0 && tail) atomicAdd(&s_bins[kSplitBins - 1], tail);
+            __syncthreads();
+            const unsigned long long mine = s_bins[tid];
+            if (mine) (void)__hip_atomic_fetch_add(bins + tid, mine, __ATOMIC_RELAXED, AGENT);
+            if (!count_self()) return;
+            whole = true;
+            // running sums from the top, one bin per thread
+            const unsigned long long h = read64(bins + tid);
+            unsigned long long v = h;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned long long x = __shfl_up(v, o);
+                if (lane >= o) v += x;
+            }
+            if (lane == 63) s_wsum[wave] = v;
+            if (tid == 0) { s_nlist = 0; s_bin = -1; }
+            __syncthreads();
+            unsigned long long above = v - h, total = 0ull;
+            for (int w = 0; w < kWarpWG / 64; ++w) {
+                if (w < wave) above += s_wsum[w];
+                total += s_wsum[w];
+            }
+            const unsigned long long need = nucleus_need(total);
+            if (tid < kSplitBins - 1 && above < need && above + h >= need) { s_bin = tid; s_need = need - above; }
+            __syncthreads();
+            const int chosen = s_bin;
+            if (chosen >= 0) {
+                const Interval near = bin_interval(top, scale, chosen);
+                for_each([&](float sv, unsigned key) {
+                    if (sv >= near.lo && sv <= near.hi && bin_of(sv) == chosen && weight(sv, key)) {
+                        const int at = atomicAdd(&s_nlist, 1);
+                        if (at < kWarpList) s_lkey[at] = key;
+                    }
+                });
+                __syncthreads();
+                const int nl = s_nlist;
+                if (nl <= kWarpList) {
+                    lds_select(s_lkey, nl, weight, [](unsigned long long) {});
+                    t_p = key_value(s_prefix);
+                    done_p = true;
+                }
+            }
+            if (done_p) {
+                if (tid == 0) P.thr[b] = t_p;
+                return;
+            }
+            __syncthreads();
+        }
+    }
+
     // ---- the short way of a small top-k.  Every thread has noted the largest entry it saw; the k-th
     // largest of these 1024 maxima, L, has at least k entries of the row at or above it, so the k-th
     // largest entry is one of the entries >= L, and there are few of those (the entries are dealt to the
     // threads without regard to their values): they are gathered in one more pass and everything else
     // happens in LDS.  If the list overflows (many equal entries), the selects over the row take over.
-    if (want_k && P.top_k <= kWarpFastK) {
+    if (!SPLIT && want_k && P.top_k <= kWarpFastK) {
         s_tmax[tid] = ordered_key(tmax);
         if (tid == 0) { s_need = static_cast<unsigned long long>(P.top_k); s_nlist = 0; }
         __syncthreads();
-        lds_select(s_tmax, kWarpWG, one, [](unsigned long long) {});
-        const unsigned low = s_prefix;   // key of L
+        lds_select(s_tmax, kWarpWG, one, [](unsigned long long) {}, 16);   // (any bound with k entries at or above it)
+        const unsigned low = s_prefix;   // at most the key of L
         for_each([&](float, unsigned key) {
             if (key >= low) {
                 const int at = atomicAdd(&s_nlist, 1);

@@ -162,3 +162,35 @@ def test_sd_tree_siblings_share_sums(torch_cuda, oracle, V, dtype, star):
     g = run_sd_tree(torch_cuda, inp, depth, fsd.SAMPLE, seed=3, offset=1)
     assert g["row_status"][1] == fsd.ROW_NONFINITE and (np.delete(g["row_status"], 1) == 0).all()
     assert (g["path_nodes"][1] == -1).all() and (g["out_tokens"][1] == -1).all()
+
+
+# a split selection: rows of at least 1025 slots (two workgroups), at most 5120 slots a workgroup, room for its lists
+@pytest.mark.parametrize("B,K,V,dtype", [(2, 5, 8200, "bf16"), (3, 5, 40000, "bf16"), (2, 9, 131073, "bf16"), (2, 5, 327688, "bf16"),
+                                         (3, 5, 16004, "f32"), (2, 9, 163840, "f32"), (2, 9, 163844, "f32"), (300, 2, 9001, "bf16")])
+def test_selection_by_several_workgroups(torch_cuda, oracle, B, K, V, dtype):
+    """The warpers' cut where several workgroups share a row: the smallest and largest shares, more sequences than
+    fit with two each, lists that overflow (equal entries, masked rows), and a graph's worth of repeats on one
+    workspace (the counters and words of the last call must not matter)."""
+    rng = np.random.default_rng(V + B)
+    t = (rng.standard_normal((B, K + 1, V), dtype=np.float32) * np.float32(3))
+    t[0] = np.float32(0.5)                                             # all equal: every list overflows
+    t[1, :, rng.permutation(V)[: V - 700]] = -np.inf                   # fewer entries than threads
+    d = (t[:, :K] + rng.standard_normal((B, K, V), dtype=np.float32) * np.float32(0.3))
+    cand = rng.integers(0, V, (B, K)).astype(np.int32)
+    inp = dict(target=t, draft=d, cand=cand)
+    if dtype == "bf16":
+        inp = dict(target=synth.to_bf16_bits(t), draft=synth.to_bf16_bits(d), cand=cand)
+    dev = pu.to_dev(inp, ("target", "draft", "cand"))
+    code = fsd.BF16 if dtype == "bf16" else fsd.F32
+    ws = torch_cuda.empty(fsd.fsd_workspace_bytes(B, K, V, code) + 256, dtype=torch_cuda.uint8, device="cuda")
+    ws.random_(0, 256)
+    for kw in (dict(top_k=40, top_p=0.9), dict(top_k=512), dict(top_p=0.8), dict(temperature=0.5, top_p=0.99)):
+        print("split selection", B, K, V, dtype, kw, flush=True)
+        o = oracle.verify_chain_warped(inp["target"], inp["draft"], inp["cand"], 0.1, fsd.DIV_TV, fsd.SAMPLE, 9, 4, **kw)
+        for rep in range(2):
+            out = fsd.fsd_verify_chain_warped(dev["target"], dev["draft"], dev["cand"], 0.1, fsd.DIV_TV, fsd.SAMPLE, 9, 4,
+                                              workspace=ws, **kw)
+            torch_cuda.cuda.synchronize()
+            g = pu.host(out, pu.CHAIN_KEYS)
+            g["threshold"] = fsd.debug_warp_thresholds(out, B, K, V, code).cpu().numpy()
+            check_warped(g, o, 0.1, pu.rel_tol(dtype), f"split selection B={B} V={V} {dtype} {kw}", envelope=pu.Envelope(dtype))
