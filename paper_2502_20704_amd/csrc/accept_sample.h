@@ -182,6 +182,11 @@ __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char*
             float lo = neg_inf();
 #pragma unroll
             for (int q = 0; q < NE / 4; ++q) {
+                // (a slot the round has no thread for, the second half of a short binary32 share: no numbers)
+                if (q * 4 / VE > 0 && sb + (q * 4 / VE) * STRIDE >= s1) {
+                    w[q * 4 + 0] = w[q * 4 + 1] = w[q * 4 + 2] = w[q * 4 + 3] = 0u;
+                    continue;
+                }
                 const U4 r = philox4x32_10(static_cast<unsigned>(index_of(4 * q)) >> 2, static_cast<unsigned>(b), A.off_lo,
                                            A.off_hi, A.seed_lo, A.seed_hi);
                 w[q * 4 + 0] = r.x; w[q * 4 + 1] = r.y; w[q * 4 + 2] = r.z; w[q * 4 + 3] = r.w;
