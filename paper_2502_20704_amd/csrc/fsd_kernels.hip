@@ -479,6 +479,19 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         // slots has lanes without one (those lanes cost it selections the others do not pay for)
         if (k1mode == MODE_JSE) p.spm = 64 * p.NV;
     }
+    if (dtype == FSD_F32 && load != LOAD_ELEM && !g_shape_nv) {
+        // A call whose pairs all fit the device at once is one step per wavefront, and its time the chain of that
+        // step: half the slots per lane (twice the members, who post at most twice what the workspace is laid
+        // out for) shorten it.  One sequence of 4 positions, V=32000: 15.5 -> 14.1 us a call; 8 positions, V=128256:
+        // 15.9 -> 15.5; 4 sequences of 5, V=64000, KL: 17.5 -> 16.8.  The line is drawn at the most wavefronts it was
+        // measured to help with (1280; at 2384, more than one step, 21.9 -> 22.6).
+        const long G4 = team_size(p.nslots, 4);
+        if (G4 <= kMaxTeam && static_cast<long>(R) * G4 * 32 <= 5 * max_resident_wavefronts()) {
+            p.NV = 4;
+            p.G = static_cast<int>(G4);
+            p.spm = static_cast<int>((p.nslots + G4 - 1) / G4);
+        }
+    }
     // exchange words a member posts in this mode: only those are laid out and cleared
     const bool two_phase = (k1mode == MODE_JS || k1mode == MODE_TV || k1mode == MODE_KLP || k1mode == MODE_JSE);
     const int n1 = two_phase ? 2 : 4;

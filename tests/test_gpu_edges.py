@@ -194,3 +194,20 @@ def test_selection_by_several_workgroups(torch_cuda, oracle, B, K, V, dtype):
             g = pu.host(out, pu.CHAIN_KEYS)
             g["threshold"] = fsd.debug_warp_thresholds(out, B, K, V, code).cpu().numpy()
             check_warped(g, o, 0.1, pu.rel_tol(dtype), f"split selection B={B} V={V} {dtype} {kw}", envelope=pu.Envelope(dtype))
+
+
+# 5 wavefronts a compute unit (1280 on 256 of them) with 1024 entries of a binary32 row each
+@pytest.mark.parametrize("B,K,V", [(1, 4, 32000), (10, 4, 32000), (11, 4, 32000), (1, 8, 128256), (1, 1, 262144), (1, 1, 262145), (40, 8, 4096)])
+@pytest.mark.parametrize("div", [fsd.DIV_JS, fsd.DIV_TV, fsd.DIV_KL])
+def test_small_binary32_calls(torch_cuda, oracle, B, K, V, div):
+    """Both sides of the line where a binary32 call takes half the slots per lane, and the largest team (256)."""
+    inp = synth.chain_inputs(B, K, V, "f32", "gauss2", 0.5, seed=V % 97)
+    g = run_chain(torch_cuda, inp, 0.1, div, seed=5, offset=2)
+    o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], 0.1, div, seed=5, offset=2)
+    pu.check_chain(g, o, 0.1, 1e-5, f"small binary32 B={B} K={K} V={V} div={div}", envelope=pu.Envelope("f32"))
+    if div == fsd.DIV_JS:
+        d = pu.to_dev(inp, ("target", "draft", "cand"))
+        out = fsd.sd_verify_chain(d["target"], d["draft"], d["cand"], seed=5, offset=2)
+        torch_cuda.cuda.synchronize()
+        o = oracle.sd_verify_chain(inp["target"], inp["draft"], inp["cand"], seed=5, offset=2)
+        check_sd(pu.host(out, pu.SD_KEYS), o, f"small binary32 SD B={B} K={K} V={V}")
