@@ -211,3 +211,50 @@ def test_small_binary32_calls(torch_cuda, oracle, B, K, V, div):
         torch_cuda.cuda.synchronize()
         o = oracle.sd_verify_chain(inp["target"], inp["draft"], inp["cand"], seed=5, offset=2)
         check_sd(pu.host(out, pu.SD_KEYS), o, f"small binary32 SD B={B} K={K} V={V}")
+
+
+def test_routes_under_capture(torch_cuda):
+    """Calls with a split selection, over a tree with the walk, on ragged rows and on a small binary32 batch, recorded
+    into a graph: three replays, with the program's own eager calls in between, each equal to the eager result."""
+    torch = torch_cuda
+    c = pu.to_dev(synth.chain_inputs(4, 6, 40004, "bf16", "peaked", (0.25, 2.0), seed=12), ("target", "draft", "cand"))
+    r = pu.to_dev(synth.chain_inputs(3, 4, 40005, "bf16", "peaked", 1.0, seed=13), ("target", "draft", "cand"))
+    f = pu.to_dev(synth.chain_inputs(2, 4, 32000, "f32", "gauss2", 0.5, seed=14), ("target", "draft", "cand"))
+    t = pu.to_dev(_random_tree_inputs(np.random.default_rng(5), 3, 9, 9000, "bf16"), ("target", "draft", "node_tokens", "parent"))
+    calls = [
+        lambda **k: fsd.fsd_verify_chain_warped(c["target"], c["draft"], c["cand"], 0.1, seed=4, offset=9, temperature=0.7,
+                                                top_k=50, top_p=0.9, **k),
+        lambda **k: fsd.fsd_verify_chain_warped(c["target"], c["draft"], c["cand"], 0.1, seed=4, offset=9, top_p=0.9, **k),
+        lambda **k: fsd.fsd_verify_chain(r["target"], r["draft"], r["cand"], 0.1, seed=4, offset=9, **k),
+        lambda **k: fsd.fsd_verify_chain(f["target"], f["draft"], f["cand"], 0.1, seed=4, offset=9, **k),
+        lambda **k: fsd.sd_verify_tree(t["target"], t["draft"], t["node_tokens"], t["parent"], 9, seed=4, offset=9, **k),
+    ]
+    eager = [call() for call in calls]
+    torch.cuda.synchronize()
+    want = [pu.host(e, [k for k in e if k != "_workspace"]) for e in eager]
+    keep = [dict(out={k: torch.empty_like(v) for k, v in e.items() if k != "_workspace"},
+                 workspace=torch.empty_like(e["_workspace"]).random_(0, 256)) for e in eager]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        for call, k in zip(calls, keep):
+            call(**k)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for call, k in zip(calls, keep):
+            call(**k)
+    for rep in range(3):
+        for k in keep:
+            for name, v in k["out"].items():
+                if name != "_workspace":
+                    v.fill_(-7)
+        for call in calls:
+            call()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for w, k in zip(want, keep):
+            for name, v in w.items():
+                assert np.array_equal(k["out"][name].cpu().numpy(), v, equal_nan=True), (rep, name)
