@@ -128,7 +128,9 @@ __global__ __launch_bounds__(kWalkWG) void tree_sd_walk(WalkParams P) {
     auto prob = [&](float z, double lse2) __attribute__((always_inline)) -> float {
         const double x = fma(static_cast<double>(z), kLog2eD, -lse2);
         const float xh = static_cast<float>(x);
-        const float xl = static_cast<float>(x - static_cast<double>(xh));
+        // (a masked entry, -inf or far below the row: xh is -inf and the difference no number; both bounds hold
+        // for any entry that has a probability, and max() drops the NaN)
+        const float xl = fminf(fmaxf(static_cast<float>(x - static_cast<double>(xh)), -1.0f), 1.0f);
         return hw_exp2(xh) * fmaf(xl, static_cast<float>(kLn2), 1.0f);
     };
     // (the value of a row's entry in float64, for the tests against single tokens)

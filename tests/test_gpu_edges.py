@@ -146,6 +146,36 @@ def test_sd_tree_walk_edges(torch_cuda, oracle, B, N, V, dtype):
     print(r, "tried", (~np.isnan(o["log_ratio"])).sum(1), flush=True)
 
 
+# (a workgroup's share of the last two rows is more than the walk keeps of a row)
+@pytest.mark.parametrize("V,dtype", [(4100, "bf16"), (4100, "f32"), (4101, "bf16"), (200001, "bf16"), (200004, "f32")])
+@pytest.mark.parametrize("where", ["draft", "target", "both"])
+@pytest.mark.parametrize("value", [-np.inf, -3.3e38])
+def test_sd_tree_masked_rows(torch_cuda, oracle, V, dtype, where, value):
+    """Strict SD over trees whose rows are cut to a few entries, by -inf or by a finite value far below the others:
+    a masked entry has probability 0, so where the draft alone is cut the target's mass there stays in the
+    distribution after a rejection.  Stars, in which every rejection but the last is followed by a sibling."""
+    rng = np.random.default_rng(V)
+    B, N = (2, 5) if V > 100000 else (8, 8)
+    t = (rng.standard_normal((B, N + 1, V), dtype=np.float32) * np.float32(2))
+    d = t[:, :1] + rng.standard_normal((B, N, V), dtype=np.float32) * np.float32(2.5)
+    if where != "draft":
+        t[:, :, rng.permutation(V)[: V // 2]] = value
+    if where != "target":
+        low = np.partition(d, V - V // 8, axis=2)[:, :, V - V // 8, None]
+        d[d < low] = value
+    q = np.exp(d.astype(np.float64) - d.max(axis=2, keepdims=True))
+    toks = np.array([[rng.choice(V, p=q[b, j] / q[b, j].sum()) for j in range(N)] for b in range(B)], dtype=np.int32)
+    if dtype == "bf16":
+        t, d = synth.to_bf16_bits(t), synth.to_bf16_bits(d)
+    inp = dict(target=t, draft=d, node_tokens=toks, parent=np.full((B, N), -1, dtype=np.int32))
+    g = run_sd_tree(torch_cuda, inp, 1, fsd.SAMPLE, seed=3, offset=1)
+    o = oracle.sd_verify_tree(inp["target"], inp["draft"], inp["node_tokens"], inp["parent"], 1, fsd.SAMPLE, seed=3, offset=1)
+    tried = (~np.isnan(o["log_ratio"])).sum(1)
+    print("masked rows", V, dtype, where, value, "tried", tried, flush=True)
+    assert tried.max() >= 3
+    check_sd_tree(g, o, f"masked rows V={V} {dtype} {where} {value}", inp)
+
+
 @pytest.mark.parametrize("star", [False, True])
 @pytest.mark.parametrize("V,dtype", [(2048, "bf16"), (4100, "bf16"), (128256, "bf16"), (2050, "f32"), (40004, "f32")])
 def test_sd_tree_siblings_share_sums(torch_cuda, oracle, V, dtype, star):
