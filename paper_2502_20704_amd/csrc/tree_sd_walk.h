@@ -45,8 +45,12 @@ struct WalkParams {
 };
 
 constexpr int kWalkWG = 1024;
-// Slots of a row a thread keeps of the distribution in force (KEEP): 24 entries
-template <bool BF16> struct WalkKeep { static constexpr int CH = BF16 ? 3 : 6; };
+// Slots of a row a thread keeps of the distribution in force (KEEP): 24 bfloat16 entries, 16 binary32 ones.  A
+// 1024-thread workgroup has 128 registers, which the kept entries share with a draft row in flight (twice the
+// registers an entry for binary32) and the positive parts formed from both: with 24 binary32 entries 77 registers were
+// spilled and the walk took twice as long as one that reads everything again (one tree of 24 nodes,
+// V=128256: 46 us against 23); with 16 there are 8 (bfloat16: 16 of 24 entries, 20 on unaligned rows).
+template <bool BF16> struct WalkKeep { static constexpr int CH = BF16 ? 3 : 4; };
 
 // What bounds the walk is its chain of dependent steps (a context's tries, and a pass after every rejection
 // but the last), each of which costs round trips to memory.  So nothing is read or formed twice and
@@ -56,10 +60,11 @@ template <bool BF16> struct WalkKeep { static constexpr int CH = BF16 ? 3 : 6; }
 //     force is brought up to date after every rejection, instead of being formed along the whole chain at its
 //     try.  (In float64: done by all sixteen wavefronts alike it would take each step a microsecond or two of
 //     every SIMD.)  The decision goes to the others through LDS;
-//   - with KEEP (a workgroup's share of a row is at most 24 entries a thread) the distribution in force stays in
-//     registers from pass to pass, so a pass reads one draft row instead of the target row and all rejected ones,
-//     and that row is requested before the try whose rejection needs it.
-// 32 trees of 60 nodes, V=128256 bfloat16: 72-83 -> 50-54 us.
+//   - with KEEP (a workgroup's share of a row is at most WalkKeep's slots a thread) the distribution in force stays
+//     with the thread from pass to pass, so a pass reads one draft row instead of the target row and all rejected
+//     ones, and that row is requested before the try whose rejection needs it.
+// 32 trees of 60 nodes, V=128256 bfloat16: 72-83 -> 50-54 us.  Whole calls on trees of 24 nodes, binary32, before
+// any of this -> now: V=32000, 1 tree 46.1 -> 34.6; V=128256, 4 trees 76.8 -> 57.0, 32 trees 194.7 -> 167.8.
 template <bool BF16, int LD, bool KEEP>
 __global__ __launch_bounds__(kWalkWG) void tree_sd_walk(WalkParams P) {
     constexpr int VE = Slot<BF16>::VE;

@@ -133,9 +133,11 @@ def test_residual_without_a_positive_part(torch_cuda, oracle, dtype, mode):
         assert (tok[rejected, 0] == plain["out_tokens"].cpu().numpy()[rejected, 0]).all()
 
 
-# a wavefront's lanes hold 64 children; a workgroup keeps 3072 slots of a row (8 workgroups a tree)
+# a wavefront's lanes hold 64 children; a workgroup keeps 3072 slots of a bfloat16 row, 4096 of a binary32 one (8
+# workgroups a tree; 256 compute units hold 5 a tree for 44 trees)
 @pytest.mark.parametrize("B,N,V,dtype", [(3, 64, 300, "bf16"), (3, 65, 300, "f32"), (2, 130, 77, "bf16"), (2, 5, 150000, "bf16"),
-                                         (2, 5, 200001, "bf16"), (2, 5, 200004, "f32"), (40, 6, 20000, "f32")])
+                                         (2, 5, 200001, "bf16"), (2, 5, 200004, "f32"), (40, 6, 20000, "f32"),
+                                         (2, 5, 131072, "f32"), (2, 5, 131073, "f32"), (2, 5, 131076, "f32"), (44, 3, 128256, "bf16")])
 def test_sd_tree_walk_edges(torch_cuda, oracle, B, N, V, dtype):
     """Strict SD over star-shaped trees (every rejection is followed by another sibling): more children than a
     wavefront has lanes, and rows around what the walk keeps in registers."""
