@@ -344,6 +344,10 @@ int fsd_debug_set_shape(int wavefronts, int slots_per_thread);
  * the number of its workgroups the device can hold at once, which caps it. */
 void fsd_debug_last_launch(int* grid, int* resident);
 
+/* Test hook: workgroups a sequence of the last warped call's selection of kept
+ * logits (1: one works alone). */
+int fsd_debug_last_selection(void);
+
 /* Test hook: byte offset, inside a workspace of fsd_workspace_bytes(B,
  * rows_per_seq, V, dtype), of the B binary32 values fsd_verify_chain_warped
  * leaves there: per sequence the smallest scaled logit its warpers kept on the

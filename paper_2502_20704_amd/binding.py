@@ -85,6 +85,8 @@ def library() -> ctypes.CDLL:
         L.fsd_debug_set_js_floor.restype = f32
         L.fsd_debug_set_exact_js.argtypes = [i32]
         L.fsd_debug_set_exact_js.restype = i32
+        L.fsd_debug_last_selection.argtypes = []
+        L.fsd_debug_last_selection.restype = i32
         L.fsd_debug_set_self_clear.argtypes = [i32]
         L.fsd_debug_set_self_clear.restype = i32
         L.fsd_debug_set_spin_limit.argtypes = [c.c_uint]
@@ -432,6 +434,11 @@ def debug_warp_thresholds(out, B: int, rows: int, V: int, dtype_code: int):
     ws = out["_workspace"]
     base = (-ws.data_ptr()) % 256          # the binding hands the library a 256-byte aligned start
     return ws[base + off: base + off + 4 * B].view(torch.float32).clone()
+
+
+def debug_last_selection() -> int:
+    """workgroups a sequence of the last warped call's selection (test hook)"""
+    return int(library().fsd_debug_last_selection())
 
 
 def debug_set_js_floor(floor_nats: float) -> float:

@@ -23,6 +23,7 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 #include <float.h>
+#include <limits.h>
 #include <math.h>
 
 #include <atomic>
@@ -371,8 +372,23 @@ void launch_walk(int B, long nslots, size_t lds, hipStream_t st, const WalkParam
     hipLaunchKernelGGL((tree_sd_walk<BF16, LD, false>), dim3(static_cast<unsigned>(gsw), static_cast<unsigned>(B)), dim3(kWalkWG), lds, st, P);
 }
 
-// warp_select with several workgroups per sequence, which wait for each other: false (nothing launched) if fewer
-// than two per sequence are resident, or a share does not fit their registers
+int g_last_selection = 0;   // workgroups a sequence of the last warped call's selection (see fsd_debug_last_selection)
+
+// Keys a workgroup's list has to hold under top-k.  A share's entries are dealt to T threads (1024, or as many as have
+// any); the k-th largest of their maxima has about T ln(T / (T - k)) entries at or above it, with the variance of
+// the number of draws that reach k of T places.  Four of its standard deviations are added, and a
+// sixteenth for the bound's missing lower half (entries that agree with it in the upper 16 bits).
+long list_keys(long k, long T) {
+    if (k >= T) return LONG_MAX;
+    const double x = -log1p(-static_cast<double>(k) / static_cast<double>(T)), n = static_cast<double>(T) * x;
+    return static_cast<long>(n * 1.0625 + 4.0 * sqrt(static_cast<double>(T) * (expm1(x) - x))) + 1;
+}
+
+// warp_select with several workgroups per sequence: false (nothing launched) if fewer than two per sequence are
+// resident (under top-p alone they wait for each other), if a share does not fit their registers, or if it takes
+// fewer workgroups than that for their lists to hold a large top-k.  (A list that overflows
+// costs the last workgroup the whole row again: 8 rows of 128256 bfloat16 entries, top-k 512: 69 us a call with
+// eight workgroups a row, 55 with one, 49 with four.)
 template <bool BF16, int LD>
 bool launch_warp_split(int B, hipStream_t st, const WarpParams& P) {
     static std::atomic<long> resident[16] = {};
@@ -393,7 +409,15 @@ bool launch_warp_split(int B, hipStream_t st, const WarpParams& P) {
     if (W > kWarpShare) W = kWarpShare;
     const long by_work = (P.nslots + kWarpWG - 1) / kWarpWG;
     if (W > by_work) W = by_work;
+    if (P.top_k > 0 && P.top_k < P.V) {
+        const auto fits = [&](long w) {
+            const long share = (P.nslots + w - 1) / w;
+            return list_keys(P.top_k, share < kWarpWG ? share : kWarpWG) <= static_cast<long>(kSplitBytes / 4) / w - 1;
+        };
+        while (W >= 2 && !fits(W)) --W;
+    }
     if (W < 2 || (P.nslots + W - 1) / W > static_cast<long>(kSplitKeep) * kWarpWG) return false;
+    g_last_selection = static_cast<int>(W);
     hipLaunchKernelGGL((warp_select<BF16, LD, true, true>), dim3(static_cast<unsigned>(W), static_cast<unsigned>(B)), dim3(kWarpWG), 0, st, P);
     return true;
 }
@@ -586,7 +610,10 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         wp.seq_bytes = static_cast<size_t>(rows) * plan_G * 64;
         wp.spin_limit = g_spin_limit;
         const bool want_k = top_k > 0 && top_k < V, want_p = top_p < 1.0f;
-        const auto warp = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(B), dim3(kWarpWG), 0, st, wp); };
+        const auto warp = [&](auto kernel) {
+            g_last_selection = 1;
+            hipLaunchKernelGGL(kernel, dim3(B), dim3(kWarpWG), 0, st, wp);
+        };
         // several workgroups a sequence, where a setting allows it, the workspace has room for what they leave each
         // other and all of them are resident
         const bool split = load != LOAD_ELEM && (want_k ? top_k <= kWarpFastK : want_p) && wp.seq_bytes >= kSplitBytes &&
@@ -828,6 +855,8 @@ void fsd_debug_last_launch(int* grid, int* resident) {
     if (grid) *grid = g_last_grid;
     if (resident) *resident = g_last_total;
 }
+
+int fsd_debug_last_selection(void) { return g_last_selection; }
 
 float fsd_debug_set_js_floor(float floor_nats) {
     const float prev = g_js_floor;

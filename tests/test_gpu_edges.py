@@ -228,6 +228,55 @@ def test_selection_by_several_workgroups(torch_cuda, oracle, B, K, V, dtype):
             check_warped(g, o, 0.1, pu.rel_tol(dtype), f"split selection B={B} V={V} {dtype} {kw}", envelope=pu.Envelope(dtype))
 
 
+def _longest_list(row, W, k, inv_temp, VE):
+    """The longest list a workgroup of a split top-k leaves: its entries at or above the k-th largest of its 1024
+    threads' maxima, of which the upper half of the 32-bit key counts."""
+    sv = row.astype(np.float32) * np.float32(inv_temp)
+    u = sv.view(np.uint32)
+    key = np.where(u >> 31, ~u, u | np.uint32(0x80000000)).astype(np.uint32)
+    nslots = -(-len(row) // VE)
+    key = np.concatenate([key, np.zeros(nslots * VE - len(row), np.uint32)]).reshape(nslots, VE)
+    share = -(-nslots // W)
+    longest = 0
+    for lo in range(0, nslots, share):
+        mine = key[lo: lo + share]
+        maxima = np.zeros(1024, np.uint32)
+        np.maximum.at(maxima, np.arange(len(mine)) % 1024, mine.max(axis=1))
+        bound = np.sort(maxima)[::-1][k - 1] & np.uint32(0xFFFF0000)
+        longest = max(longest, int((mine >= bound).sum()))
+    return longest
+
+
+# (4096 keys for all lists of a sequence, each behind its length)
+@pytest.mark.parametrize("V,dtype,k,W", [(131073, "bf16", 300, 8), (131073, "bf16", 512, 4), (131073, "bf16", 400, 6),
+                                         (65540, "f32", 512, 4), (65540, "f32", 460, 5), (163840, "f32", 512, 1)])
+@pytest.mark.parametrize("temperature", [1.0, 0.3])
+def test_split_selection_lists_hold_a_large_top_k(torch_cuda, oracle, V, dtype, k, W, temperature):
+    """Under a large top-k as few workgroups share a row as their lists need to be long enough, a single one where
+    that leaves them more than they can keep of it."""
+    rng = np.random.default_rng(V + k)
+    B, K, VE = 2, 9, 8 if dtype == "bf16" else 4
+    t = (rng.standard_normal((B, K + 1, V), dtype=np.float32) * np.float32(3))
+    d = (t[:, :K] + rng.standard_normal((B, K, V), dtype=np.float32) * np.float32(0.3))
+    cand = rng.integers(0, V, (B, K)).astype(np.int32)
+    rows = t[:, 0]
+    inp = dict(target=t, draft=d, cand=cand)
+    if dtype == "bf16":
+        inp = dict(target=synth.to_bf16_bits(t), draft=synth.to_bf16_bits(d), cand=cand)
+        rows = (inp["target"][:, 0].astype(np.uint32) << 16).view(np.float32)
+    kw = dict(temperature=temperature, top_k=k)
+    print("large top-k", V, dtype, kw, flush=True)
+    g = run_warped(torch_cuda, inp, -1.0, fsd.DIV_TV, fsd.SAMPLE, 9, 4, **kw)   # (row 0 is drawn from)
+    used = fsd.debug_last_selection()
+    if used > 1:
+        longest = max(_longest_list(r, used, k, np.float32(1.0 / temperature), VE) for r in rows)
+        print("workgroups", used, "longest list", longest, "room", 4096 // used - 1, flush=True)
+        assert longest <= 4096 // used - 1
+    assert used == W
+    o = oracle.verify_chain_warped(inp["target"], inp["draft"], inp["cand"], -1.0, fsd.DIV_TV, fsd.SAMPLE, 9, 4, **kw)
+    check_warped(g, o, -1.0, pu.rel_tol(dtype), f"large top-k V={V} {dtype} {kw}", envelope=pu.Envelope(dtype))
+
+
 # 5 wavefronts a compute unit (1280 on 256 of them) with 1024 entries of a binary32 row each
 @pytest.mark.parametrize("B,K,V", [(1, 4, 32000), (10, 4, 32000), (11, 4, 32000), (1, 8, 128256), (1, 1, 262144), (1, 1, 262145), (40, 8, 4096)])
 @pytest.mark.parametrize("div", [fsd.DIV_JS, fsd.DIV_TV, fsd.DIV_KL])
