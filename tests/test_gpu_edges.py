@@ -277,6 +277,22 @@ def test_split_selection_lists_hold_a_large_top_k(torch_cuda, oracle, V, dtype, 
     check_warped(g, o, -1.0, pu.rel_tol(dtype), f"large top-k V={V} {dtype} {kw}", envelope=pu.Envelope(dtype))
 
 
+# 128 sequences: 8 workgroups a row; a share's last round has slots for one lane, one wavefront, one lane more, ...
+@pytest.mark.parametrize("share", [255, 256, 257, 319, 320, 321, 511, 512, 513, 577])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_shares_of_a_draw(torch_cuda, oracle, share, dtype):
+    """The draw where a share's last round is all, part or none of a wavefront's, with the last share a slot shorter."""
+    B, V = 128, (8 * share - 1) * (8 if dtype == "bf16" else 4)
+    inp = synth.chain_inputs(B, 1, V, dtype, "gauss2", 1.0, seed=share)
+    for kw in (dict(mode=fsd.SAMPLE), dict(mode=fsd.GREEDY)):
+        g = run_chain(torch_cuda, inp, -1.0, fsd.DIV_TV, kw["mode"], seed=5, offset=2)
+        o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], -1.0, fsd.DIV_TV, kw["mode"], seed=5, offset=2)
+        pu.check_chain(g, o, -1.0, pu.rel_tol(dtype), f"share {share} {dtype} {kw}", envelope=pu.Envelope(dtype))
+    g = run_warped(torch_cuda, inp, -1.0, fsd.DIV_TV, fsd.SAMPLE, 5, 2, temperature=0.7)
+    o = oracle.verify_chain_warped(inp["target"], inp["draft"], inp["cand"], -1.0, fsd.DIV_TV, fsd.SAMPLE, 5, 2, temperature=0.7)
+    check_warped(g, o, -1.0, pu.rel_tol(dtype), f"share {share} {dtype} warped", cut_active=False, envelope=pu.Envelope(dtype))
+
+
 # 5 wavefronts a compute unit (1280 on 256 of them) with 1024 entries of a binary32 row each
 @pytest.mark.parametrize("B,K,V", [(1, 4, 32000), (10, 4, 32000), (11, 4, 32000), (1, 8, 128256), (1, 1, 262144), (1, 1, 262145), (40, 8, 4096)])
 @pytest.mark.parametrize("div", [fsd.DIV_JS, fsd.DIV_TV, fsd.DIV_KL])
