@@ -71,13 +71,13 @@ struct DrawChain { const char* draft; int rows, n; const int* s; };
 // works on this one's.  (The residual's draw used to score the row's own entries along with it, for the case that
 // no entry has any positive part; that case is now a second pass of the last workgroup.  With the earlier
 // request of the draft row: strict SD on 64 rows of 128256 bfloat16 entries 24.5 -> 20.4 us.)  256 rows of 151936 binary32 entries: 48.3 us with 4 entries a round, 43.4 with 8.
-template <bool BF16, int LD, bool TREESD>
+template <bool BF16, int LD, bool TREESD, int NE>
 __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char* trow, bool residual, const char* drow,
                                            float lt, float ld, [[maybe_unused]] const DrawChain& C, long s0, long s1, int tid,
                                            Best& best, int& bad) {
     constexpr int VE = Slot<BF16>::VE;
     [[maybe_unused]] constexpr int ES = BF16 ? 2 : 4;
-    constexpr int NE = 8, NS = NE / VE, STRIDE = kWG;
+    constexpr int NS = NE / VE, STRIDE = kWG;
     // a score the winner is known to reach (see the bounds below), from the lowest finite one up: an entry
     // without mass, masked or cut off by the warpers, stays below
     float thr = -FLT_MAX;
@@ -185,7 +185,7 @@ __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char*
             float lo = neg_inf();
 #pragma unroll
             for (int q = 0; q < NE / 4; ++q) {
-                // (a round whose second slots this wavefront does not have, in binary32: no numbers)
+                // (a last round whose second slots this wavefront does not have, in binary32: no numbers)
                 if (q * 4 / VE > 0 && sb + before + (q * 4 / VE) * STRIDE >= s1) {
                     w[q * 4 + 0] = w[q * 4 + 1] = w[q * 4 + 2] = w[q * 4 + 3] = 0u;
                     continue;
@@ -386,7 +386,13 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
             const bool cut = P.thr != nullptr && P.mode == FSD_SAMPLE;
             const DrawArgs A{P.V, P.mode, P.seed_lo, P.seed_hi, P.off_lo, P.off_hi, cut, cut ? P.thr[b] : neg_inf(), P.inv_temp};
             const DrawChain C{P.draft + static_cast<size_t>(b) * rows * static_cast<size_t>(P.V) * ES, rows, nchain, s_dyn};
-            draw_share<BF16, LD, KIND == KIND_TREESD>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, best, bad);
+            // binary32: a share of one slot a lane takes 4 entries a round, any longer one 8 (a second slot that no
+            // lane has still costs its instructions; whole calls on 16 sequences of 2, V=64000: 18.5 us with 8 entries,
+            // 17.9 with 4; on 40 of 2, V=50048, shares of two slots a lane: 23.5 and 24.1)
+            if (!BF16 && s1 - s0 <= kWG)
+                draw_share<BF16, LD, KIND == KIND_TREESD, 4 + 4 * BF16>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, best, bad);
+            else
+                draw_share<BF16, LD, KIND == KIND_TREESD, 8>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, best, bad);
         }
         best = wave_best(best);
         bad = __any(bad);
