@@ -605,7 +605,10 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         wp.top_p = top_p;
         wp.thr = ws.thr;
         wp.ws = ws;
-        const bool keep = dtype == FSD_BF16 && load != LOAD_ELEM && p.nslots <= static_cast<long>(kWarpKeep) * kWarpWG;
+        // one workgroup a row keeps an aligned bfloat16 row in registers.  (Unaligned rows are streamed: with the
+        // moves of their last slot the kept form spills 107 registers.  Calls on 4 sequences under top-k 50, kept and streamed:
+        // V=8197 58.1 and 34.7 us, V=32001 59.1 and 38.9, V=128259 66.6 and 53.6.)
+        const bool keep = dtype == FSD_BF16 && load == LOAD_ALIGNED && p.nslots <= static_cast<long>(kWarpKeep) * kWarpWG;
         wp.area = reinterpret_cast<char*>(ws.part1);
         wp.seq_bytes = static_cast<size_t>(rows) * plan_G * 64;
         wp.spin_limit = g_spin_limit;
@@ -624,8 +627,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         if (split) {
             // (launched)
         } else if (dtype == FSD_BF16) {
-            if (keep && load == LOAD_ALIGNED) warp(warp_select<true, LOAD_ALIGNED, true>);
-            else if (keep) warp(warp_select<true, LOAD_WIDE, true>);
+            if (keep) warp(warp_select<true, LOAD_ALIGNED, true>);
             else if (load == LOAD_ALIGNED) warp(warp_select<true, LOAD_ALIGNED, false>);
             else if (load == LOAD_WIDE) warp(warp_select<true, LOAD_WIDE, false>);
             else warp(warp_select<true, LOAD_ELEM, false>);
