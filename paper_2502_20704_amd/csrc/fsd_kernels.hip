@@ -384,13 +384,26 @@ long list_keys(long k, long T) {
     return static_cast<long>(n * 1.0625 + 4.0 * sqrt(static_cast<double>(T) * (expm1(x) - x))) + 1;
 }
 
-// warp_select with several workgroups per sequence: false (nothing launched) if fewer than two per sequence are
-// resident (under top-p alone they wait for each other), if a share does not fit their registers, or if it takes
-// fewer workgroups than that for their lists to hold a large top-k.  (A list that overflows
-// costs the last workgroup the whole row again: 8 rows of 128256 bfloat16 entries, top-k 512: 69 us a call with
-// eight workgroups a row, 55 with one, 49 with four.)
+// Rows of fewer entries are left to one workgroup, whose selection the extra stores, the count and the second reading
+// then outweigh.  Whole calls on 8 sequences, one workgroup a row and several (us):
+//   top-k 50, top-p 0.9   bfloat16   V=16000 44.5 and 45.2, 24000 39.5 and 39.3; V=20001 42.5 and 43.5, 24001 43.4 and 42.8
+//                         binary32   V=32000 43.6 and 43.8, 40000 48.3 and 47.5; V=16001 48.4 and 49.8, 20001 43.5 and 43.3
+//   top-p 0.95            bfloat16   V=8200 40.3 and 39.7;                       V=12001 42.8 and 43.4, 16001 47.8 and 47.4
+//                         binary32   V=16000 44.4 and 44.9, 20000 51.7 and 50.9; V=12001 44.6 and 44.6, 16001 (1 sequence) 33.4 and 32.4
+// (Binary32 rows are streamed by the one workgroup, unaligned ones of either type with moves for their last slot.)
+constexpr long split_least(bool bf16, bool aligned, bool top_k) {
+    return top_k ? (bf16 ? 24000 : aligned ? 40000 : 20000) : (!aligned ? 16000 : bf16 ? 0 : 20000);
+}
+
+// warp_select with several workgroups per sequence: false (nothing launched) if the row is short, if fewer than two
+// per sequence are resident (under top-p alone they wait for each other), if a share does not fit their registers, or
+// if it takes fewer workgroups than that for their lists to hold a large top-k.  (A list that overflows costs the last
+// workgroup the whole row again: 8 rows of 128256 bfloat16 entries, top-k 512: 69 us a call with eight workgroups a
+// row, 55 with one, 49 with four.)
 template <bool BF16, int LD>
 bool launch_warp_split(int B, hipStream_t st, const WarpParams& P) {
+    const bool want_k = P.top_k > 0 && P.top_k < P.V;
+    if (P.V < split_least(BF16, LD == LOAD_ALIGNED, want_k)) return false;
     static std::atomic<long> resident[16] = {};
     int dev = 0;
     (void)hipGetDevice(&dev);
@@ -409,7 +422,7 @@ bool launch_warp_split(int B, hipStream_t st, const WarpParams& P) {
     if (W > kWarpShare) W = kWarpShare;
     const long by_work = (P.nslots + kWarpWG - 1) / kWarpWG;
     if (W > by_work) W = by_work;
-    if (P.top_k > 0 && P.top_k < P.V) {
+    if (want_k) {
         const auto fits = [&](long w) {
             const long share = (P.nslots + w - 1) / w;
             return list_keys(P.top_k, share < kWarpWG ? share : kWarpWG) <= static_cast<long>(kSplitBytes / 4) / w - 1;

@@ -196,13 +196,24 @@ def test_sd_tree_siblings_share_sums(torch_cuda, oracle, V, dtype, star):
     assert (g["path_nodes"][1] == -1).all() and (g["out_tokens"][1] == -1).all()
 
 
-# a split selection: rows of at least 1025 slots (two workgroups), at most 5120 slots a workgroup, room for its lists
-@pytest.mark.parametrize("B,K,V,dtype", [(2, 5, 8200, "bf16"), (3, 5, 40000, "bf16"), (2, 9, 131073, "bf16"), (2, 5, 327688, "bf16"),
-                                         (3, 5, 16004, "f32"), (2, 9, 163840, "f32"), (2, 9, 163844, "f32"), (300, 2, 9001, "bf16")])
-def test_selection_by_several_workgroups(torch_cuda, oracle, B, K, V, dtype):
-    """The warpers' cut where several workgroups share a row: the smallest and largest shares, more sequences than
-    fit with two each, lists that overflow (equal entries, masked rows), and a graph's worth of repeats on one
-    workspace (the counters and words of the last call must not matter)."""
+# W: workgroups a row where the setting allows them, under top-k and under top-p alone.  A split selection takes rows of
+# a length that depends on the setting, the type and the alignment, 16 KB of exchange words a sequence (K times the
+# row's wavefronts: 256), at most a workgroup per 1024 slots and per unit of 256 / B, and at most 5120 slots a workgroup.
+@pytest.mark.parametrize("B,K,V,dtype,W", [
+    (2, 5, 8200, "bf16", (1, 1)), (3, 5, 40000, "bf16", (1, 1)), (3, 5, 16004, "f32", (1, 1)), (300, 2, 9001, "bf16", (1, 1)),
+    (2, 25, 20000, "bf16", (1, 1)),                                                   # (all of these: too little room)
+    (2, 64, 8192, "bf16", (1, 1)), (2, 64, 8200, "bf16", (1, 2)), (2, 32, 15999, "bf16", (1, 1)), (2, 32, 16001, "bf16", (1, 2)),
+    (2, 26, 23992, "bf16", (1, 3)), (2, 22, 24000, "bf16", (3, 3)), (2, 22, 23999, "bf16", (1, 3)), (2, 22, 24001, "bf16", (3, 3)),
+    (2, 16, 32000, "bf16", (4, 4)), (2, 13, 40003, "bf16", (5, 5)), (2, 11, 48000, "bf16", (6, 6)), (2, 10, 57000, "bf16", (7, 7)),
+    (2, 9, 131073, "bf16", (8, 8)), (2, 5, 327680, "bf16", (8, 8)), (2, 5, 327688, "bf16", (1, 1)),
+    (2, 32, 15999, "f32", (1, 1)), (2, 32, 16001, "f32", (1, 4)), (2, 26, 19996, "f32", (1, 1)), (2, 26, 20000, "f32", (1, 5)),
+    (2, 26, 19999, "f32", (1, 5)), (2, 26, 20001, "f32", (5, 5)), (2, 13, 39996, "f32", (1, 8)), (2, 13, 40000, "f32", (8, 8)),
+    (2, 9, 163840, "f32", (8, 8)), (2, 9, 163844, "f32", (1, 1)),
+    (88, 22, 24000, "bf16", (2, 2)), (129, 22, 24000, "bf16", (1, 1))])
+def test_selection_by_several_workgroups(torch_cuda, oracle, B, K, V, dtype, W):
+    """The warpers' cut where several workgroups share a row: both sides of every line of the rule that splits a
+    row, every number of workgroups, unaligned rows, lists that overflow (equal entries, masked rows), and a graph's
+    worth of repeats on one workspace (the counters and words of the last call must not matter)."""
     rng = np.random.default_rng(V + B)
     t = (rng.standard_normal((B, K + 1, V), dtype=np.float32) * np.float32(3))
     t[0] = np.float32(0.5)                                             # all equal: every list overflows
@@ -216,12 +227,14 @@ def test_selection_by_several_workgroups(torch_cuda, oracle, B, K, V, dtype):
     code = fsd.BF16 if dtype == "bf16" else fsd.F32
     ws = torch_cuda.empty(fsd.fsd_workspace_bytes(B, K, V, code) + 256, dtype=torch_cuda.uint8, device="cuda")
     ws.random_(0, 256)
-    for kw in (dict(top_k=40, top_p=0.9), dict(top_k=512), dict(top_p=0.8), dict(temperature=0.5, top_p=0.99)):
+    for kw in (dict(top_k=40, top_p=0.9), dict(top_p=0.8), dict(top_k=512), dict(temperature=0.5, top_p=0.99))[:2 if B > 80 else 4]:
         print("split selection", B, K, V, dtype, kw, flush=True)
         o = oracle.verify_chain_warped(inp["target"], inp["draft"], inp["cand"], 0.1, fsd.DIV_TV, fsd.SAMPLE, 9, 4, **kw)
         for rep in range(2):
             out = fsd.fsd_verify_chain_warped(dev["target"], dev["draft"], dev["cand"], 0.1, fsd.DIV_TV, fsd.SAMPLE, 9, 4,
                                               workspace=ws, **kw)
+            used, want = fsd.debug_last_selection(), W[0 if "top_k" in kw else 1]
+            assert used == want or (kw.get("top_k") == 512 and used < want), (used, want, kw)   # (its lists may want fewer)
             torch_cuda.cuda.synchronize()
             g = pu.host(out, pu.CHAIN_KEYS)
             g["threshold"] = fsd.debug_warp_thresholds(out, B, K, V, code).cpu().numpy()
