@@ -96,8 +96,9 @@ bool make_plan(int B, int rows, long V, int dtype, Plan& p) {
     p.off_state = o; o = align_up(o + R * 8, 256);
     p.off_wz = o; o = align_up(o + R * kWalkShare * 8, 256);
     p.off_spart = o; o = align_up(o + static_cast<size_t>(B) * p.GS * 32, 256);
-    // the two exchange arrays, sized for the mode that posts most (4 words per member in each); a call
-    // lays them out densely for its own mode (see carve) and clears only that much
+    // the two exchange arrays: 8 words of 8 bytes for every member of the plan's team, twice what the mode that posts
+    // most (4 words a member) needs of it, so that a shape may have twice the members (small binary32 calls do).  A call
+    // lays them out densely for its own mode and shape (see carve) and clears only that much
     p.off_part1 = o; o = align_up(o + R * p.G * 32, 256) + align_up(R * p.G * 32, 256);
     p.zero_bytes = o;
     p.off_div = o; o = align_up(o + R * 4, 256);
@@ -136,8 +137,8 @@ unsigned long long next_nonce() {
     return n;
 }
 
-// G, n1, n2: wavefronts per pair and exchange words per member of this call's reduction kernel (never
-// more than the plan allowed for); zero_bytes: how much of the workspace's head the call has to clear
+// G, n1, n2: wavefronts per pair and exchange words per member of this call's reduction kernel (G (n1 + n2) is at most
+// 8 times the plan's G: the caller checks); zero_bytes: how much of the workspace's head the call has to clear
 Ws carve(void* workspace, const Plan& p, int B, int rows, int G, int n1, int n2, size_t& zero_bytes) {
     char* base = static_cast<char*>(workspace);
     const size_t R = static_cast<size_t>(B) * rows;
@@ -535,6 +536,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     const int n2 = (k1mode == MODE_TV || k1mode == MODE_KLP) ? 2 : two_phase ? 1 : 0;
     size_t zero_bytes = 0;
     const Ws ws = carve(workspace, p, B, rows, p.G, n1, n2, zero_bytes);
+    if (zero_bytes > p.zero_bytes) return FSD_ERR_WORKSPACE;   // the exchange words would run into what follows them (no shape here does)
 
     // The calls have no clearing kernel: the reduction clears what it and the kernels after it need (see
     // clear_own_words in pair_kernel.h; C2: -3 us a call, C4: -2 us), unless there are more than 4 MB to
