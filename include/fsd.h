@@ -30,7 +30,10 @@
  *     anything is launched and leave all outputs untouched.
  *   - The vocabulary-reduction kernel is persistent: the wavefronts that share a
  *     row pair wait for each other's partial results, so its grid is sized to
- *     what an otherwise idle device holds at once.  If other work occupies the
+ *     what an otherwise idle device holds at once.  So do the workgroups that
+ *     share a sequence in two kernels after it: the walk of strict SD over a
+ *     tree, and the selection of a warped call under top_p without top_k
+ *     where it splits a long row.  If other work occupies the
  *     GPU while a call runs (another stream, another process), some of its
  *     workgroups may start late; every wait is bounded (see
  *     fsd_debug_set_spin_limit), and a wait that expires ends the call with
@@ -309,10 +312,15 @@ int fsd_calibrate_threshold(const float* divergences, int B, int K, float target
 int fsd_profile_enable(int on);
 int fsd_profile_collect(float* mean_ms, float* min_ms);
 
-/* Test hook: number of polls a wavefront spends waiting for the words of the
- * other wavefronts that share its row pair before it gives up and the call
+/* Test hook: number of polls a wavefront spends waiting for the words of those
+ * it shares a row pair or a sequence with before it gives up and the call
  * flags FSD_ROW_INTERNAL (default 1<<22).  Returns the previous value. */
 unsigned fsd_debug_set_spin_limit(unsigned polls);
+
+/* Test hook: a smaller number of polls for one of these waits alone, that of the
+ * workgroups which share a row in a warped call's selection under top_p
+ * (default: no smaller one).  Returns the previous value. */
+unsigned fsd_debug_set_selection_spin_limit(unsigned polls);
 
 /* Test hooks of the bfloat16 Jensen-Shannon reduction.  It evaluates App. C.2 in
  * entropy form (one logarithm per entry), whose absolute error (about 1e-7

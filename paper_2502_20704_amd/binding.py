@@ -85,6 +85,8 @@ def library() -> ctypes.CDLL:
         L.fsd_debug_set_js_floor.restype = f32
         L.fsd_debug_set_exact_js.argtypes = [i32]
         L.fsd_debug_set_exact_js.restype = i32
+        L.fsd_debug_set_selection_spin_limit.argtypes = [c.c_uint]
+        L.fsd_debug_set_selection_spin_limit.restype = c.c_uint
         L.fsd_debug_last_selection.argtypes = []
         L.fsd_debug_last_selection.restype = i32
         L.fsd_debug_set_self_clear.argtypes = [i32]
@@ -421,6 +423,11 @@ def profile_collect():
 
 def debug_set_spin_limit(polls: int) -> int:
     return int(library().fsd_debug_set_spin_limit(polls))
+
+
+def debug_set_selection_spin_limit(polls: int) -> int:
+    """polls of the wait in a warped call's selection under top-p alone (test hook); returns the previous value"""
+    return int(library().fsd_debug_set_selection_spin_limit(polls))
 
 
 def debug_warp_thresholds(out, B: int, rows: int, V: int, dtype_code: int):

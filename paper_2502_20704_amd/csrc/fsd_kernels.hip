@@ -165,6 +165,7 @@ Ws carve(void* workspace, const Plan& p, int B, int rows, int G, int n1, int n2,
 }
 
 unsigned g_spin_limit = 1u << 22;
+unsigned g_selection_spin_limit = UINT_MAX;   // test hook: a smaller limit for the selection's wait alone
 // The entropy form of JS (bfloat16 logits) carries an absolute error of a few 1e-7 whatever the
 // result: below this floor (nats) a pair is evaluated again in the pointwise form, so that what the
 // caller sees is within 2e-3 relative everywhere (with a margin of five to ten).
@@ -626,7 +627,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         const bool keep = dtype == FSD_BF16 && load == LOAD_ALIGNED && p.nslots <= static_cast<long>(kWarpKeep) * kWarpWG;
         wp.area = reinterpret_cast<char*>(ws.part1);
         wp.seq_bytes = static_cast<size_t>(rows) * plan_G * 64;
-        wp.spin_limit = g_spin_limit;
+        wp.spin_limit = g_spin_limit < g_selection_spin_limit ? g_spin_limit : g_selection_spin_limit;
         const bool want_k = top_k > 0 && top_k < V, want_p = top_p < 1.0f;
         const auto warp = [&](auto kernel) {
             g_last_selection = 1;
@@ -896,6 +897,12 @@ int fsd_debug_set_self_clear(int on) {
 unsigned fsd_debug_set_spin_limit(unsigned polls) {
     const unsigned prev = g_spin_limit;
     g_spin_limit = polls;
+    return prev;
+}
+
+unsigned fsd_debug_set_selection_spin_limit(unsigned polls) {
+    const unsigned prev = g_selection_spin_limit;
+    g_selection_spin_limit = polls;
     return prev;
 }
 

@@ -241,6 +241,44 @@ def test_selection_by_several_workgroups(torch_cuda, oracle, B, K, V, dtype, W):
             check_warped(g, o, 0.1, pu.rel_tol(dtype), f"split selection B={B} V={V} {dtype} {kw}", envelope=pu.Envelope(dtype))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_selection_wait_expires_cleanly(torch_cuda, oracle, dtype):
+    """The workgroups that share a row under top-p wait for each other's range with a poll budget.  With one of zero
+    the kernel ends and the call flags every sequence, unless all words were there at the first look; the
+    next call on the same workspace is right."""
+    B, K, V = 4, 13, 40003
+    inp = synth.chain_inputs(B, K, V, dtype, "peaked", 1.0, seed=21)
+    dev = pu.to_dev(inp, ("target", "draft", "cand"))
+    code = fsd.BF16 if dtype == "bf16" else fsd.F32
+    ws = torch_cuda.empty(fsd.fsd_workspace_bytes(B, K, V, code) + 256, dtype=torch_cuda.uint8, device="cuda")
+    o = oracle.verify_chain_warped(inp["target"], inp["draft"], inp["cand"], 0.1, fsd.DIV_TV, fsd.SAMPLE, 9, 4, top_p=0.9)
+
+    def call():
+        out = fsd.fsd_verify_chain_warped(dev["target"], dev["draft"], dev["cand"], 0.1, fsd.DIV_TV, fsd.SAMPLE, 9, 4,
+                                          workspace=ws, top_p=0.9)
+        assert fsd.debug_last_selection() > 1
+        torch_cuda.cuda.synchronize()
+        g = pu.host(out, pu.CHAIN_KEYS)
+        g["threshold"] = fsd.debug_warp_thresholds(out, B, K, V, code).cpu().numpy()
+        return g
+
+    for rep in range(3):
+        prev = fsd.debug_set_selection_spin_limit(0)
+        try:
+            g = call()
+        finally:
+            fsd.debug_set_selection_spin_limit(prev)
+        flagged = (g["row_status"] & fsd.ROW_INTERNAL) != 0
+        print("selection wait", dtype, "flagged", flagged, flush=True)
+        assert flagged.all() or not flagged.any()
+        if flagged.all():
+            assert (g["accept_len"] == 0).all() and (g["out_tokens"] == -1).all()
+        else:
+            check_warped(g, o, 0.1, pu.rel_tol(dtype), f"zero poll budget, nothing expired {dtype}", envelope=pu.Envelope(dtype))
+        g = call()
+        check_warped(g, o, 0.1, pu.rel_tol(dtype), f"after restoring the poll budget {dtype}", envelope=pu.Envelope(dtype))
+
+
 def _longest_list(row, W, k, inv_temp, VE):
     """The longest list a workgroup of a split top-k leaves: its entries at or above the k-th largest of its 1024
     threads' maxima, of which the upper half of the 32-bit key counts."""
