@@ -104,6 +104,52 @@ def test_rows_on_odd_addresses(torch_cuda, oracle, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_every_call_on_odd_addresses(torch_cuda, oracle, dtype):
+    """The entry points beside the plain chain call, on tensors whose first row starts one element past a 16-byte
+    boundary (V a multiple of the slot)."""
+    def shifted(d, *names):
+        out = dict(d)
+        for name in names:
+            buf = torch_cuda.empty(d[name].numel() + 1, dtype=d[name].dtype, device="cuda")
+            buf[1:] = d[name].reshape(-1)
+            out[name] = buf[1:].view(d[name].shape)
+        return out
+
+    V, tol, env = 4096, pu.rel_tol(dtype), pu.Envelope(dtype)
+    inp = synth.chain_inputs(3, 4, V, dtype, "gauss2", 1.0, seed=8)
+    d = shifted(pu.to_dev(inp, ("target", "draft", "cand")), "target", "draft")
+    print("odd addresses", dtype, "sd", flush=True)
+    out = fsd.sd_verify_chain(d["target"], d["draft"], d["cand"], seed=5, offset=2)
+    torch_cuda.cuda.synchronize()
+    check_sd(pu.host(out, pu.SD_KEYS), oracle.sd_verify_chain(inp["target"], inp["draft"], inp["cand"], seed=5, offset=2),
+             f"odd addresses SD {dtype}")
+    print("odd addresses", dtype, "rfsd", flush=True)
+    out = fsd.rfsd_verify_chain(d["target"], d["draft"], d["cand"], 0.1, fsd.DIV_JS, seed=5, offset=2)
+    torch_cuda.cuda.synchronize()
+    check_rfsd(pu.host(out, pu.RFSD_KEYS), oracle.rfsd_verify_chain(inp["target"], inp["draft"], inp["cand"], 0.1, fsd.DIV_JS, seed=5, offset=2),
+               0.1, tol, f"odd addresses rFSD {dtype}", envelope=env)
+    for kw in (dict(top_k=40, top_p=0.9), dict(top_p=0.8)):
+        print("odd addresses", dtype, kw, flush=True)
+        out = fsd.fsd_verify_chain_warped(d["target"], d["draft"], d["cand"], 0.1, fsd.DIV_TV, fsd.SAMPLE, 5, 2, **kw)
+        torch_cuda.cuda.synchronize()
+        g = pu.host(out, pu.CHAIN_KEYS)
+        g["threshold"] = fsd.debug_warp_thresholds(out, 3, 4, V, fsd.BF16 if dtype == "bf16" else fsd.F32).cpu().numpy()
+        o = oracle.verify_chain_warped(inp["target"], inp["draft"], inp["cand"], 0.1, fsd.DIV_TV, fsd.SAMPLE, 5, 2, **kw)
+        check_warped(g, o, 0.1, tol, f"odd addresses warped {dtype} {kw}", envelope=env)
+    tin = _random_tree_inputs(np.random.default_rng(8), 3, 9, V, dtype)
+    t = shifted(pu.to_dev(tin, ("target", "draft", "node_tokens", "parent")), "target", "draft")
+    print("odd addresses", dtype, "trees", flush=True)
+    out = fsd.fsd_verify_tree(t["target"], t["draft"], t["node_tokens"], t["parent"], 9, 0.1, fsd.DIV_JS, seed=5, offset=2)
+    torch_cuda.cuda.synchronize()
+    o = oracle.verify_tree(tin["target"], tin["draft"], tin["node_tokens"], tin["parent"], 9, 0.1, fsd.DIV_JS, seed=5, offset=2)
+    pu.check_tree(pu.host(out, pu.TREE_KEYS), o, 0.1, tol, f"odd addresses tree {dtype}", envelope=env)
+    out = fsd.sd_verify_tree(t["target"], t["draft"], t["node_tokens"], t["parent"], 9, fsd.SAMPLE, seed=5, offset=2)
+    torch_cuda.cuda.synchronize()
+    o = oracle.sd_verify_tree(tin["target"], tin["draft"], tin["node_tokens"], tin["parent"], 9, fsd.SAMPLE, seed=5, offset=2)
+    check_sd_tree(pu.host(out, pu.TREESD_KEYS), o, f"odd addresses SD tree {dtype}", tin)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("mode", [fsd.SAMPLE, fsd.GREEDY])
 def test_residual_without_a_positive_part(torch_cuda, oracle, dtype, mode):
     """Strict SD rejects a token whose draft probability is a little larger than its target probability, both so
@@ -241,6 +287,34 @@ def test_selection_by_several_workgroups(torch_cuda, oracle, B, K, V, dtype, W):
             check_warped(g, o, 0.1, pu.rel_tol(dtype), f"split selection B={B} V={V} {dtype} {kw}", envelope=pu.Envelope(dtype))
 
 
+@pytest.mark.parametrize("V,dtype", [(40000, "bf16"), (40003, "bf16"), (40000, "f32"), (40003, "f32")])
+def test_split_selection_over_a_tree(torch_cuda, oracle, V, dtype):
+    """Every workgroup that shares a row finds the row for itself, over a tree by its deepest accepted path."""
+    B, N = 4, 14
+    inp = _random_tree_inputs(np.random.default_rng(V), B, N, V, dtype)
+    d = pu.to_dev(inp, ("target", "draft", "node_tokens", "parent"))
+    code = fsd.BF16 if dtype == "bf16" else fsd.F32
+    for kw in (dict(temperature=0.7, top_k=50, top_p=0.9), dict(top_p=0.8)):
+        what = f"split selection over a tree V={V} {dtype} {kw}"
+        print(what, flush=True)
+        out = fsd.fsd_verify_tree_warped(d["target"], d["draft"], d["node_tokens"], d["parent"], N, 0.12, fsd.DIV_JS, fsd.SAMPLE, 5, 2, **kw)
+        assert fsd.debug_last_selection() > 1, what
+        torch_cuda.cuda.synchronize()
+        g = pu.host(out, pu.TREE_KEYS)
+        thr = fsd.debug_warp_thresholds(out, B, N, V, code).cpu().numpy()
+        o = oracle.verify_tree_warped(inp["target"], inp["draft"], inp["node_tokens"], inp["parent"], N, 0.12, fsd.DIV_JS, fsd.SAMPLE, 5, 2, **kw)
+        assert (g["row_status"] == 0).all() and (o["row_status"] == 0).all(), what
+        near = pu.near_threshold(o["divs"], 0.12)
+        for b in range(B):
+            if not (g["path_nodes"][b] == o["path_nodes"][b]).all():
+                assert near[b].any(), what
+                continue
+            if o["slack"][b] >= 1e-5:
+                assert thr[b] == o["threshold"][b], f"{what}: cut[{b}] gpu {thr[b]} oracle {o['threshold'][b]}"
+            if not (g["out_tokens"][b] == o["out_tokens"][b]).all():
+                assert o["slack"][b] < 1e-5 or o["gap"][b] < 1e-6, f"{what}: tokens[{b}]"
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_selection_wait_expires_cleanly(torch_cuda, oracle, dtype):
     """The workgroups that share a row under top-p wait for each other's range with a poll budget.  With one of zero
@@ -365,7 +439,7 @@ def test_routes_under_capture(torch_cuda):
     """Calls with a split selection, over a tree with the walk, on ragged rows and on a small binary32 batch, recorded
     into a graph: three replays, with the program's own eager calls in between, each equal to the eager result."""
     torch = torch_cuda
-    c = pu.to_dev(synth.chain_inputs(4, 6, 40004, "bf16", "peaked", (0.25, 2.0), seed=12), ("target", "draft", "cand"))
+    c = pu.to_dev(synth.chain_inputs(4, 13, 40004, "bf16", "peaked", (0.25, 2.0), seed=12), ("target", "draft", "cand"))
     r = pu.to_dev(synth.chain_inputs(3, 4, 40005, "bf16", "peaked", 1.0, seed=13), ("target", "draft", "cand"))
     f = pu.to_dev(synth.chain_inputs(2, 4, 32000, "f32", "gauss2", 0.5, seed=14), ("target", "draft", "cand"))
     t = pu.to_dev(_random_tree_inputs(np.random.default_rng(5), 3, 9, 9000, "bf16"), ("target", "draft", "node_tokens", "parent"))
@@ -377,7 +451,10 @@ def test_routes_under_capture(torch_cuda):
         lambda **k: fsd.fsd_verify_chain(f["target"], f["draft"], f["cand"], 0.1, seed=4, offset=9, **k),
         lambda **k: fsd.sd_verify_tree(t["target"], t["draft"], t["node_tokens"], t["parent"], 9, seed=4, offset=9, **k),
     ]
-    eager = [call() for call in calls]
+    eager = []
+    for i, call in enumerate(calls):
+        eager.append(call())
+        assert i > 1 or fsd.debug_last_selection() > 1
     torch.cuda.synchronize()
     want = [pu.host(e, [k for k in e if k != "_workspace"]) for e in eager]
     keep = [dict(out={k: torch.empty_like(v) for k, v in e.items() if k != "_workspace"},
