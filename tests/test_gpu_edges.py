@@ -316,6 +316,30 @@ def test_split_selection_over_a_tree(torch_cuda, oracle, V, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [40000, 40003, 300])
+def test_selection_on_an_unusable_row(torch_cuda, dtype, V):
+    """The row after the last candidate, which the reduction does not read: NaN, +inf or no entry above -inf is found
+    by the draw and reported for that sequence alone, whichever way its cut was looked for."""
+    B, K = 6, 13
+    inp = synth.chain_inputs(B, K, V, dtype, "peaked", 1.0, seed=31)
+    put = (lambda x: synth.to_bf16_bits(np.full(1, x, np.float32))[0]) if dtype == "bf16" else np.float32
+    inp["target"][1, K, V // 2] = put(np.nan)
+    inp["target"][2, K, V - 1] = put(np.inf)
+    inp["target"][3, K] = put(-np.inf)
+    inp["target"][4, K, 1:] = put(-np.inf)                             # one entry: the token
+    d = pu.to_dev(inp, ("target", "draft", "cand"))
+    for kw in (dict(top_k=40, top_p=0.9), dict(top_k=40), dict(top_p=0.9), dict(top_k=V - 2)):
+        print("unusable row", V, dtype, kw, flush=True)
+        out = fsd.fsd_verify_chain_warped(d["target"], d["draft"], d["cand"], float("inf"), fsd.DIV_TV, fsd.SAMPLE, 9, 4, **kw)
+        assert V < 40000 or kw.get("top_k", 0) > 512 or fsd.debug_last_selection() > 1
+        torch_cuda.cuda.synchronize()
+        g = pu.host(out, pu.CHAIN_KEYS)
+        assert list(g["row_status"]) == [0] + 3 * [fsd.ROW_NONFINITE] + [0, 0], kw
+        assert (g["accept_len"] == np.array([K, 0, 0, 0, K, K])).all() and (g["out_tokens"][1:4] == -1).all()
+        assert g["out_tokens"][4, K] == 0 and (g["out_tokens"][[0, 5], K] >= 0).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_selection_wait_expires_cleanly(torch_cuda, oracle, dtype):
     """The workgroups that share a row under top-p wait for each other's range with a poll budget.  With one of zero
     the kernel ends and the call flags every sequence, unless all words were there at the first look; the
