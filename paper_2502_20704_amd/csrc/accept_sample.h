@@ -65,12 +65,12 @@ struct DrawChain { const char* draft; int rows, n; const int* s; };
 // `residual`, of the positive part of p - q.  bad: a NaN or +inf logit was seen.
 //
 // What bounds it: the chain from the row's first load to its last score, and the random numbers (ten rounds of
-// two 64-bit products per four entries).  A lane takes 8 entries a round (16 cost more registers than the
-// loads in flight return: 15.3 instead of 15.9 us for 64 rows of 128256 bfloat16 entries, but 10.6 instead of
-// 8.5 for 16, and 11.4 instead of 10.4 under top-k) and requests the next round's rows, the draft's too, before it
-// works on this one's.  (The residual's draw used to score the row's own entries along with it, for the case that
-// no entry has any positive part; that case is now a second pass of the last workgroup.  With the earlier
-// request of the draft row: strict SD on 64 rows of 128256 bfloat16 entries 24.5 -> 20.4 us.)  256 rows of 151936 binary32 entries: 48.3 us with 4 entries a round, 43.4 with 8.
+// two 64-bit products per four entries).  A lane takes NE = 8 entries a round (16 cost more registers than the loads
+// in flight return: 64 rows of 128256 bfloat16 entries 14.8 us with either, 16 rows 8.2 with 8 and 9.4 with 16, 64 rows
+// under top-k 10.6 and 12.2; 256 rows of 151936 binary32 entries 48.7 with 4 and 45.3 with 8) and requests the next
+// round's rows, the draft's too, before it works on this one's.  (The residual's draw used to score the row's own
+// entries along with it, for the case that no entry has any positive part; that case is now a second pass of the last
+// workgroup.  With the earlier request of the draft row: strict SD on 64 rows of 128256 bfloat16 entries 23.1 -> 20.0 us.)
 template <bool BF16, int LD, bool TREESD, int NE>
 __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char* trow, bool residual, const char* drow,
                                            float lt, float ld, [[maybe_unused]] const DrawChain& C, long s0, long s1, int tid,
@@ -126,7 +126,7 @@ __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char*
             // A wavefront without a kept entry has nothing to draw: no random numbers are formed for it.
             // (Top-k keeps a handful of a row's entries: nearly every wavefront leaves here.  Before, such
             // a wavefront had no score to reach and evaluated all its variates.  C2's shape with
-            // temperature 0.7, top-k 50, top-p 0.9: 35.6 -> 11.4 us for this kernel.)
+            // temperature 0.7, top-k 50, top-p 0.9: 33.0 -> 10.6 us for this kernel.)
             if (!__any(any_kept)) continue;
         }
 #pragma unroll

@@ -415,7 +415,9 @@ void pair_kernel(PairParams P) {
     // chunks there: that is what lets them hold 6 slots per lane (96 logits a step) in 256 registers,
     // and with two workgroups of 80 KB it takes all of a compute unit's LDS.  (TV at 5 slots per lane,
     // a shape of the tuning hook, keeps one.)
-    constexpr int NL = (JSE || (BF16 && NV == 6 && TWO_PHASE)) ? 5 : (BF16 && NV == 5 && MODE == MODE_TV) ? 1 : 0;   // (the least that leaves no register spilled, per variant)
+    // (The least that leaves no register spilled on aligned rows.  Unaligned rows need a few registers more, for the
+    // slot at the end of the row: JS spills 6, TV 5, the entropy form on trees 3.)
+    constexpr int NL = (JSE || (BF16 && NV == 6 && TWO_PHASE)) ? 5 : (BF16 && NV == 5 && MODE == MODE_TV) ? 1 : 0;
     __shared__ float4 lds_keep[NL ? NB * NL * 2 * kWG : 1];
     auto put4 = [&](auto S, int c, const float (&t4)[4], const float (&d4)[4]) __attribute__((always_inline)) {
         constexpr int s_ = decltype(S)::value;

@@ -14,12 +14,11 @@ namespace {
 // The tree analogue of strict SD's acceptance (Sec. 3, eq. 1-3, applied child by child as in the
 // tree-verification methods Sec. 2 cites).  At the current context with target distribution p the
 // children are tried in index order: child j is accepted iff min(1, p(x_j)/q_j(x_j)) > y_j; after a
-// rejection p becomes the normalised positive part of p - q_j.  One workgroup per sequence walks
-// the tree.  The first child of a context is tested against the log-ratio the reduction kernel has
-// stored; a later child needs p after the rejections so far, evaluated at its token through the
-// chain of rejected draft rows, and every rejection that is followed by another sibling costs one
-// pass over the vocabulary for its normaliser.  The token itself is drawn by accept_sample from
-// what this kernel leaves in the workspace.
+// rejection p becomes the normalised positive part of p - q_j.  The first child of a context is tested
+// against the log-ratio the reduction kernel has stored; a later child needs p after the rejections
+// so far at its token, which is kept for every child and brought up to date with each rejection, and
+// every rejection that is followed by another sibling costs one pass over the vocabulary for its
+// normaliser.  The token itself is drawn by accept_sample from what this kernel leaves in the workspace.
 //
 // gridDim.x workgroups share a sequence (all of them resident at once, which the host checks):
 // every one walks the same tree and takes the same decisions, a pass is split between them, and
@@ -49,7 +48,7 @@ constexpr int kWalkWG = 1024;
 // 1024-thread workgroup has 128 registers, which the kept entries share with a draft row in flight (twice the
 // registers an entry for binary32) and the positive parts formed from both: with 24 binary32 entries 77 registers were
 // spilled and the walk took twice as long as one that reads everything again (one tree of 24 nodes,
-// V=128256: 46 us against 23); with 16 there are 8 (bfloat16: 16 of 24 entries, 20 on unaligned rows).
+// V=128256: 46 us against 23); with 16 it is 8, 10 on unaligned rows (bfloat16, 24 entries: 16 and 20).
 template <bool BF16> struct WalkKeep { static constexpr int CH = BF16 ? 3 : 4; };
 
 // What bounds the walk is its chain of dependent steps (a context's tries, and a pass after every rejection
@@ -62,7 +61,8 @@ template <bool BF16> struct WalkKeep { static constexpr int CH = BF16 ? 3 : 4; }
 //     every SIMD.)  The decision goes to the others through LDS;
 //   - with KEEP (a workgroup's share of a row is at most WalkKeep's slots a thread) the distribution in force stays
 //     with the thread from pass to pass, so a pass reads one draft row instead of the target row and all rejected
-//     ones, and that row is requested before the try whose rejection needs it.
+//     ones, and that row is requested before the try whose rejection needs it.  (Where the share is longer, which
+//     more trees bring about as well, a pass reads the rejected rows again: V=128256 from 43 trees on, binary32 from 33.)
 // 32 trees of 60 nodes, V=128256 bfloat16: 72-83 -> 50-54 us.  Whole calls on trees of 24 nodes, binary32, before
 // any of this -> now: V=32000, 1 tree 46.1 -> 34.6; V=128256, 4 trees 76.8 -> 57.0, 32 trees 194.7 -> 167.8.
 template <bool BF16, int LD, bool KEEP>
