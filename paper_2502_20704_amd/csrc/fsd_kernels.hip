@@ -375,7 +375,7 @@ void launch_walk(int B, long nslots, size_t lds, hipStream_t st, const WalkParam
     hipLaunchKernelGGL((tree_sd_walk<BF16, LD, false>), dim3(static_cast<unsigned>(gsw), static_cast<unsigned>(B)), dim3(kWalkWG), lds, st, P);
 }
 
-int g_last_selection = 0;   // workgroups a sequence of the last warped call's selection (see fsd_debug_last_selection)
+std::atomic<int> g_last_selection{0};   // workgroups a sequence of the last warped call's selection (see fsd_debug_last_selection)
 
 // Keys a workgroup's list has to hold under top-k.  A share's entries are dealt to T threads (1024, or as many as have
 // any); the k-th largest of their maxima has about T ln(T / (T - k)) entries at or above it, with the variance of
@@ -433,7 +433,7 @@ bool launch_warp_split(int B, hipStream_t st, const WarpParams& P) {
         while (W >= 2 && !fits(W)) --W;
     }
     if (W < 2 || (P.nslots + W - 1) / W > static_cast<long>(kSplitKeep) * kWarpWG) return false;
-    g_last_selection = static_cast<int>(W);
+    g_last_selection.store(static_cast<int>(W), std::memory_order_relaxed);
     hipLaunchKernelGGL((warp_select<BF16, LD, true, true>), dim3(static_cast<unsigned>(W), static_cast<unsigned>(B)), dim3(kWarpWG), 0, st, P);
     return true;
 }
@@ -631,7 +631,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         wp.spin_limit = g_spin_limit < g_selection_spin_limit ? g_spin_limit : g_selection_spin_limit;
         const bool want_k = top_k > 0 && top_k < V, want_p = top_p < 1.0f;
         const auto warp = [&](auto kernel) {
-            g_last_selection = 1;
+            g_last_selection.store(1, std::memory_order_relaxed);
             hipLaunchKernelGGL(kernel, dim3(B), dim3(kWarpWG), 0, st, wp);
         };
         // several workgroups a sequence, where a setting allows it, the workspace has room for what they leave each
@@ -875,7 +875,7 @@ void fsd_debug_last_launch(int* grid, int* resident) {
     if (resident) *resident = g_last_total;
 }
 
-int fsd_debug_last_selection(void) { return g_last_selection; }
+int fsd_debug_last_selection(void) { return g_last_selection.load(std::memory_order_relaxed); }
 
 float fsd_debug_set_js_floor(float floor_nats) {
     const float prev = g_js_floor;

@@ -58,7 +58,8 @@ __device__ __forceinline__ Interval bin_interval(float top, float scale, int bin
 }
 
 // KEEP: the row fits 16 slots per thread (aligned bfloat16 rows up to 131072 entries), or a share of it
-// kSplitKeep (SPLIT), and is read once into registers; otherwise every pass streams it again, four loads in flight per thread.
+// kSplitKeep (SPLIT), and is read once into registers; otherwise every pass streams it again, four loads in
+// flight per thread.
 constexpr int kWarpKeep = 16;
 constexpr int kWarpList = 8192;   // entries the select can finish from LDS
 constexpr int kWarpFastK = 512;   // largest top-k of the short way
