@@ -61,12 +61,29 @@ struct DrawArgs {
 // draft tensor, 1 / normalisers and log2-sum-exp2 values, one after the other in LDS)
 struct DrawChain { const char* draft; int rows, n; const int* s; };
 
+// The score a workgroup has seen so far, shared by its wavefronts through LDS as an order-preserving integer: the
+// winner of the sequence reaches it.  (Read without any ordering: whatever value is seen is a score of this row.)
+__device__ __forceinline__ unsigned score_key(float x) {
+    const unsigned u = __float_as_uint(x);
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+__device__ __forceinline__ float score_of_key(unsigned k) {
+    return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
+}
+__device__ __forceinline__ float max3_nan(float a, float b, float c) {   // the maximum, or NaN if any of the three is
+    float r;
+    asm("v_maximum3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 // The best score over slots [s0, s1) of the row, dealt to the workgroup's threads: of the row's entries or, with
-// `residual`, of the positive part of p - q.  bad: a NaN or +inf logit was seen.
+// `residual`, of the positive part of p - q.  bad: a NaN or +inf logit was seen.  s_thr: the workgroup's shared score.
 //
-// What bounds it: the chain from the row's first load to its last score, and the random numbers (ten rounds of
-// two 64-bit products per four entries).  A lane takes NE = 8 entries a round (16 cost more registers than the loads
-// in flight return: 64 rows of 128256 bfloat16 entries 14.8 us with either, 16 rows 8.2 with 8 and 9.4 with 16, 64 rows
+// What bounds it: vector-ALU issue, most of it the random numbers (ten rounds of two 64-bit products per four entries);
+// in small calls the chain from the row's first load to its last score.  Beside the random numbers an entry costs a
+// bound of its score, one logarithm; only a wavefront with an entry that can still win does more.
+// A lane takes NE = 8 entries a round (16 cost more registers than the loads
+// in flight return: 64 rows of 128256 bfloat16 entries, before the bounds below: 14.8 us with either, 16 rows 8.2 with 8 and 9.4 with 16, 64 rows
 // under top-k 10.6 and 12.2; 256 rows of 151936 binary32 entries 48.7 with 4 and 45.3 with 8) and requests the next
 // round's rows, the draft's too, before it works on this one's.  (The residual's draw used to score the row's own
 // entries along with it, for the case that no entry has any positive part; that case is now a second pass of the last
@@ -74,7 +91,7 @@ struct DrawChain { const char* draft; int rows, n; const int* s; };
 template <bool BF16, int LD, bool TREESD, int NE>
 __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char* trow, bool residual, const char* drow,
                                            float lt, float ld, [[maybe_unused]] const DrawChain& C, long s0, long s1, int tid,
-                                           Best& best, int& bad) {
+                                           unsigned* s_thr, Best& best, int& bad) {
     constexpr int VE = Slot<BF16>::VE;
     [[maybe_unused]] constexpr int ES = BF16 ? 2 : 4;
     constexpr int NS = NE / VE, STRIDE = kWG;
@@ -93,6 +110,49 @@ __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char*
             unpack<BF16>(raw[k], z + k * VE);
         }
     };
+    // ln of the residual's entries (-inf where it has no mass) from the row's logits
+    auto residual_of = [&](float (&z)[NE], [[maybe_unused]] uint4 (&rawd)[NS], long s) __attribute__((always_inline)) {
+        float r[NE];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) r[e] = hw_exp2(fmaf(z[e], kLog2e, -lt));
+        if constexpr (TREESD) {
+            // strict SD on a tree: p after the chain's rejections, minus the last draft row
+            const int* ch = C.s;
+            const float* iz = reinterpret_cast<const float*>(C.s + C.rows);
+            const float* ldv = reinterpret_cast<const float*>(C.s + 2 * C.rows);
+            for (int m = 0; m < C.n; ++m) {
+                uint4 raw[NS];
+                float zd[NE];
+                request(C.draft + static_cast<size_t>(ch[m]) * static_cast<size_t>(A.V) * ES, s, raw);
+                entries(raw, s, zd);
+                const float ldm = ldv[m];
+                if (m + 1 < C.n) {
+                    const float izm = iz[m];
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) r[e] = fmaxf(r[e] - hw_exp2(fmaf(zd[e], kLog2e, -ldm)), 0.0f) * izm;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) r[e] = r[e] - hw_exp2(fmaf(zd[e], kLog2e, -ldm));
+                }
+            }
+        } else {
+            float zd[NE];
+            entries(rawd, s, zd);
+#pragma unroll
+            for (int e = 0; e < NE; ++e) r[e] = r[e] - hw_exp2(fmaf(zd[e], kLog2e, -ld));
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) z[e] = (r[e] > 0.0f) ? hw_log2(r[e]) * static_cast<float>(kLn2) : neg_inf();
+    };
+    // What a residual's score is bounded with before it is formed: its entry is at most p times the chain's factors, and
+    // ln p is the exponential's own argument.  The constant covers the rounding of the exponential and the logarithm.
+    float over = 2e-3f;
+    if constexpr (TREESD) {
+        if (residual) {
+            const float* iz = reinterpret_cast<const float*>(C.s + C.rows);
+            for (int m = 0; m + 1 < C.n; ++m) over = fmaf(hw_log2(iz[m]), static_cast<float>(kLn2), over);
+        }
+    }
     uint4 next[NS], nextd[NS];
     request(trow, s0 + tid, next);
     const bool pair = !TREESD && residual;
@@ -103,7 +163,7 @@ __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char*
     const long before = static_cast<long>(__builtin_amdgcn_readfirstlane(tid >> 6)) * 64;   // this wavefront's first slot of a round
     for (long sb = s0; sb + before < s1; sb += NS * STRIDE) {
         const long s = sb + tid;
-        float z[NE];   // what is scored: the logits, or ln of the residual's entries (-inf where it has no mass)
+        float z[NE];   // what is scored: the logits, or ln of the residual's entries
         uint4 raw[NS], rawd[NS];
 #pragma unroll
         for (int k = 0; k < NS; ++k) { raw[k] = next[k]; rawd[k] = nextd[k]; }
@@ -129,60 +189,31 @@ __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char*
             // temperature 0.7, top-k 50, top-p 0.9: 33.0 -> 10.6 us for this kernel.)
             if (!__any(any_kept)) continue;
         }
+        if (sb + before + 63 + (NS - 1) * STRIDE >= s1) {   // some lane lacks a slot
+            asm volatile("");   // stays a branch
 #pragma unroll
-        for (int e = 0; e < NE; ++e) bad |= !(z[e] < __builtin_inff());
-        if (residual) {
-            float r[NE];
+            for (int k = 0; k < NS; ++k) {
+                if (s + k * STRIDE >= s1) {
 #pragma unroll
-            for (int e = 0; e < NE; ++e) r[e] = hw_exp2(fmaf(z[e], kLog2e, -lt));
-            if constexpr (TREESD) {
-                // strict SD on a tree: p after the chain's rejections, minus the last draft row
-                const int* ch = C.s;
-                const float* iz = reinterpret_cast<const float*>(C.s + C.rows);
-                const float* ldv = reinterpret_cast<const float*>(C.s + 2 * C.rows);
-                for (int m = 0; m < C.n; ++m) {
-                    float zd[NE];
-                    request(C.draft + static_cast<size_t>(ch[m]) * static_cast<size_t>(A.V) * ES, s, raw);
-                    entries(raw, s, zd);
-                    const float ldm = ldv[m];
-                    if (m + 1 < C.n) {
-                        const float izm = iz[m];
-#pragma unroll
-                        for (int e = 0; e < NE; ++e) r[e] = fmaxf(r[e] - hw_exp2(fmaf(zd[e], kLog2e, -ldm)), 0.0f) * izm;
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < NE; ++e) r[e] = r[e] - hw_exp2(fmaf(zd[e], kLog2e, -ldm));
-                    }
+                    for (int e = 0; e < VE; ++e) z[k * VE + e] = neg_inf();
                 }
-            } else {
-                float zd[NE];
-                entries(rawd, s, zd);
-#pragma unroll
-                for (int e = 0; e < NE; ++e) r[e] = r[e] - hw_exp2(fmaf(zd[e], kLog2e, -ld));
-            }
-#pragma unroll
-            for (int e = 0; e < NE; ++e) z[e] = (r[e] > 0.0f) ? hw_log2(r[e]) * static_cast<float>(kLn2) : neg_inf();
-        }
-#pragma unroll
-        for (int k = 0; k < NS; ++k) {
-            if (s + k * STRIDE >= s1) {
-#pragma unroll
-                for (int e = 0; e < VE; ++e) z[k * VE + e] = neg_inf();
             }
         }
         auto index_of = [&](int e) __attribute__((always_inline)) { return static_cast<int>((s + (e / VE) * STRIDE) * VE + e % VE); };
         if (A.mode == FSD_SAMPLE) {
-            // Bounds of a variate from the position c of the leading one of m = (1 - u) 2^24 alone
-            // (c = clz(m) - 8, so 2^-(c+1) <= 1 - u < 2^-c), G = -ln(-ln u) and -ln u between 1 - u and
-            // (1 - u)/u:
-            //     (c - 1) ln2 <= G <= (c + 1) ln2       (c >= 1; G >= -ln(24 ln2) = -2.8116 always)
-            // The largest lower bound of a score in the wavefront is a score the winner must reach, so
-            // an entry whose upper bound stays below it (or below a score already seen) cannot be the
-            // argmax: its variate, two exact-operation logarithms, is never evaluated.  1e-3 covers
-            // the rounding of that routine by a wide margin.
-            float gub[NE];
+            // Bounds of a variate G = -ln(-ln u) from x = 1 - u, which is exact in binary32: -ln u lies above x, so
+            //     G <= -ln x,    and    G >= -ln x - 2.82 x
+            // (-ln x - G is convex in x, 0 at 0 and at most 2.8116 at the largest x).  1e-3 covers the rounding of
+            // the hardware logarithm and of the variate's own routine by a wide margin.  An entry whose upper bound
+            // stays below a score the winner must reach cannot be the argmax: its variate, two exact-operation
+            // logarithms, is never evaluated.  The largest lower bound of a score in the wavefront is such a score, and so
+            // is the best one any wavefront of the workgroup has seen.  (The bounds used to be a binade wide, from the
+            // position of the leading one of x: nearly every round then had entries to evaluate, which cost two thirds of
+            // a round; and a residual's entries were formed, three transcendental instructions each, before any bound.
+            // This kernel: 64 rows of 128256 bfloat16 entries 15.0 -> 13.5 us, strict SD on them 20.2 -> 18.3, 256 rows
+            // of 151936 binary32 entries 44.2 -> 35.0.)
+            float gub[NE], ub[NE];
             unsigned w[NE];
-            float lo = neg_inf();
 #pragma unroll
             for (int q = 0; q < NE / 4; ++q) {
                 // (a last round whose second slots this wavefront does not have, in binary32: no numbers)
@@ -194,20 +225,36 @@ __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char*
                                            A.off_hi, A.seed_lo, A.seed_hi);
                 w[q * 4 + 0] = r.x; w[q * 4 + 1] = r.y; w[q * 4 + 2] = r.z; w[q * 4 + 3] = r.w;
             }
+            // (1 - u) = (2^24 - 1 - 2 (w >> 9)) 2^-24: both operations are exact
+            auto x_of = [&](unsigned word) __attribute__((always_inline)) {
+                return fmaf(static_cast<float>(word >> 9), -0x1p-23f, 1.0f - 0x1p-24f);
+            };
 #pragma unroll
             for (int e = 0; e < NE; ++e) {
-                const unsigned m = 0x00FFFFFFu ^ ((w[e] >> 9) << 1);   // (1 - u) 2^24, odd, >= 1
-                const float c = static_cast<float>(__clz(static_cast<int>(m)) - 8);
-                gub[e] = fmaf(c, 0.693148f, 0.693148f + 1e-3f);
-                const float glb = (c >= 1.0f) ? fmaf(c, 0.693147f, -0.693148f - 1e-3f) : -2.82f;
-                lo = fmaxf(lo, __fadd_rn(z[e], glb));      // (max() drops the NaN of a NaN logit)
+                gub[e] = fmaf(hw_log2(x_of(w[e])), -0x1.62e43p-1f, 1e-3f);
+                ub[e] = (residual ? fmaf(fmaf(z[e], kLog2e, -lt), static_cast<float>(kLn2), over) : z[e]) + gub[e];
             }
+            float top = ub[0];   // (NaN if any is: a NaN logit goes on to be found)
+#pragma unroll
+            for (int e = 1; e + 1 < NE; e += 2) top = max3_nan(top, ub[e], ub[e + 1]);
+            top = max3_nan(top, ub[NE - 1], ub[NE - 1]);
+            thr = fmaxf(thr, score_of_key(__hip_atomic_load(s_thr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)));
+            if (!__any(!(top < thr))) continue;
+            if (residual) {
+                residual_of(z, rawd, s);
+#pragma unroll
+                for (int e = 0; e < NE; ++e) ub[e] = __fadd_rn(z[e], gub[e]);
+            }
+            float lo = neg_inf();
+#pragma unroll
+            for (int e = 0; e < NE; ++e)   // (max() drops the NaN of a NaN logit)
+                lo = fmaxf(lo, __fadd_rn(z[e], gub[e] + fmaf(x_of(w[e]), -2.82f, -2e-3f)));
             thr = fmaxf(thr, wave_max(lo));
             // The entries that are left, at most a few per wavefront: every lane works through its own,
             // lowest index first (one pass of the loop serves one entry of every lane that has any).
             unsigned todo = 0;
 #pragma unroll
-            for (int e = 0; e < NE; ++e) todo |= !(__fadd_rn(z[e], gub[e]) < thr) ? (1u << e) : 0u;
+            for (int e = 0; e < NE; ++e) todo |= !(ub[e] < thr) ? (1u << e) : 0u;
             while (__any(todo != 0)) {
                 if (todo != 0) {
                     const int e = __builtin_ctz(todo);
@@ -219,12 +266,21 @@ __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char*
                         zz = (e == i) ? z[i] : zz;
                         ww = (e == i) ? w[i] : ww;
                     }
+                    bad |= !(zz < __builtin_inff());   // (a NaN or +inf logit is never below a threshold)
                     const float score = __fadd_rn(zz, gumbel(ww));
                     if (score > best.score) best = Best{score, index_of(e)};
                 }
             }
-            thr = fmaxf(thr, wave_max(best.score));
+            const float seen = wave_max(best.score);
+            thr = fmaxf(thr, seen);
+            if ((tid & 63) == 0) (void)__hip_atomic_fetch_max(s_thr, score_key(thr), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         } else {
+            if (residual) {
+                residual_of(z, rawd, s);
+            } else {
+#pragma unroll
+                for (int e = 0; e < NE; ++e) bad |= !(z[e] < __builtin_inff());
+            }
 #pragma unroll
             for (int e = 0; e < NE; ++e) {
                 if (z[e] > best.score) best = Best{z[e], index_of(e)};
@@ -238,6 +294,7 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
     constexpr int ES = BF16 ? 2 : 4;
     extern __shared__ int s_dyn[];   // tree: par[N], anc[N], acc[N], dep[N]
     __shared__ int s_n, s_st, s_key, s_last;
+    __shared__ unsigned s_thr;
     __shared__ Best s_best[4];
     __shared__ int s_bad[4];
 
@@ -245,7 +302,7 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
     const int gs = blockIdx.x, b = blockIdx.y;
     const int rows = P.rows;
 
-    if (tid == 0) { s_n = rows; s_st = 0; s_key = 0; }
+    if (tid == 0) { s_n = rows; s_st = 0; s_key = 0; s_thr = score_key(-FLT_MAX); }
     if (P.clear_arrive) {
         // the reduction kernel has ended: its wavefronts' slots go back to zero, so that the same call
         // replayed from a captured graph, with the same number, does not find them set
@@ -390,9 +447,9 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
             // lane has still costs its instructions; whole calls on 16 sequences of 2, V=64000: 18.5 us with 8 entries,
             // 17.9 with 4; on 40 of 2, V=50048, shares of two slots a lane: 23.5 and 24.1)
             if (!BF16 && s1 - s0 <= kWG)
-                draw_share<BF16, LD, KIND == KIND_TREESD, 4 + 4 * BF16>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, best, bad);
+                draw_share<BF16, LD, KIND == KIND_TREESD, 4 + 4 * BF16>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, &s_thr, best, bad);
             else
-                draw_share<BF16, LD, KIND == KIND_TREESD, 8>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, best, bad);
+                draw_share<BF16, LD, KIND == KIND_TREESD, 8>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, &s_thr, best, bad);
         }
         best = wave_best(best);
         bad = __any(bad);
