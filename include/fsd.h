@@ -33,7 +33,9 @@
  *     what an otherwise idle device holds at once.  So do the workgroups that
  *     share a sequence in two kernels after it: the walk of strict SD over a
  *     tree, and the selection of a warped call under top_p without top_k
- *     where it splits a long row.  If other work occupies the
+ *     where it splits a long row.  (The draw's workgroups wait for nobody but
+ *     the last of a sequence, which looks for the shares of those dispatched
+ *     before it, and so does not depend on what else is resident.)  If other work occupies the
  *     GPU while a call runs (another stream, another process), some of its
  *     workgroups may start late; every wait is bounded (see
  *     fsd_debug_set_spin_limit), and a wait that expires ends the call with

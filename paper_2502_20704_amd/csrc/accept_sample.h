@@ -40,13 +40,10 @@ struct Best { float score; int idx; };
 __device__ __forceinline__ Best better(Best a, Best b) {
     return (b.score > a.score || (b.score == a.score && b.idx < a.idx)) ? b : a;
 }
+// the best of the wavefront's 64: the maximum score, then the lowest index that has it (scores are never NaN)
 __device__ __forceinline__ Best wave_best(Best v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        Best other{__shfl_xor(v.score, o), __shfl_xor(v.idx, o)};
-        v = better(v, other);
-    }
-    return v;
+    const float top = wave_max(v.score);
+    return Best{top, wave_min(v.score == top ? v.idx : 0x7FFFFFFF)};
 }
 
 // what a draw needs beside the row: cut = the warpers' scale and threshold apply (FSD_SAMPLE only)
@@ -289,72 +286,138 @@ __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char*
     }
 }
 
+// A workgroup's share of a sequence's draw in one word that says by itself whether it has arrived: score, then the flag
+// of an unusable logit and the index plus one (all ones: no entry).  Never zero.
+__device__ __forceinline__ unsigned long long share_word(Best m, int bad) {
+    const unsigned at = m.idx == 0x7FFFFFFF ? 0x7FFFFFFFu : static_cast<unsigned>(m.idx) + 1u;
+    return (static_cast<unsigned long long>(__float_as_uint(m.score)) << 32) | (bad ? 0x80000000u : 0u) | at;
+}
+__device__ __forceinline__ Best share_best(unsigned long long w) {
+    const unsigned at = static_cast<unsigned>(w) & 0x7FFFFFFFu;
+    return Best{__uint_as_float(static_cast<unsigned>(w >> 32)), at == 0x7FFFFFFFu ? 0x7FFFFFFF : static_cast<int>(at) - 1};
+}
+// How often the sequence's last workgroup looks for a share.  The workgroups it waits for come before it in the grid
+// and wait for nobody, so they have started before it and end whatever else the device does.
+constexpr unsigned kShareLooks = 1u << 22;
+
+// What bounds it in calls of a few sequences is a chain of latencies: arguments, results of the reduction, row, variates,
+// share, merge, outputs.  So the arguments' cache lines are requested together, all words the acceptance needs in one
+// go, up to 64 positions or nodes are decided by every wavefront for itself (no barrier), the last workgroup of a sequence looks for
+// the others' shares (it used to be whoever counted itself last, one round trip more), and nothing is waited for that
+// the outputs do not need.  1 sequence of 4 positions, V=32000, binary32: 5.5 -> 4.0 us; of 8, V=128256, bfloat16: 5.8 -> 4.1;
+// 32 trees of 60 nodes 16.8 -> 9.7 (their path used to be written node by node, a load behind every store);
+// 64 sequences of 8 13.5 -> 12.0.
 template <bool BF16, int LD, int KIND>
 __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
     constexpr int ES = BF16 ? 2 : 4;
+    constexpr bool TREE = KIND == KIND_TREE, TREESD = KIND == KIND_TREESD, CHAIN = !TREE && !TREESD;
+    constexpr bool BY_RATIO = KIND == KIND_SD || KIND == KIND_RFSD;
     extern __shared__ int s_dyn[];   // tree: par[N], anc[N], acc[N], dep[N]
-    __shared__ int s_n, s_st, s_key, s_last;
+    __shared__ int s_n, s_st, s_key;
     __shared__ unsigned s_thr;
     __shared__ Best s_best[4];
     __shared__ int s_bad[4];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int gs = blockIdx.x, b = blockIdx.y;
     const int rows = P.rows;
-
-    if (tid == 0) { s_n = rows; s_st = 0; s_key = 0; s_thr = score_key(-FLT_MAX); }
-    if (P.clear_arrive) {
-        // the reduction kernel has ended: its wavefronts' slots go back to zero, so that the same call
-        // replayed from a captured graph, with the same number, does not find them set
-        uint4* const slots = reinterpret_cast<uint4*>(P.ws.arrive);
-        const long nthreads = static_cast<long>(gridDim.x) * gridDim.y * kWG;
-        for (long i = (static_cast<long>(b) * gridDim.x + gs) * kWG + tid; i < kMaxArrive / 2; i += nthreads)
-            slots[i] = make_uint4(0u, 0u, 0u, 0u);
-    }
-    __syncthreads();
+    // one argument from every cache line they lie in: loaded where they are used, each line would be a miss of its own
+    asm volatile("" ::"s"(P.rows), "s"(P.seed_lo), "s"(P.inv_temp), "s"(P.ws.div), "s"(P.ws.nonce));
 
     // ---- which positions are accepted
+    const bool few = rows <= 64;      // a lane per position or node, every wavefront for itself
+    const int pr = b * rows + (lane < rows ? lane : rows - 1);
+    const unsigned long long fail_word = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(P.ws.counters + 2), __ATOMIC_RELAXED, AGENT);
     int n = 0;         // accepted prefix length / path depth
     int sample_row = 0;
     int winner = -1;
     int nchain = 0;    // strict SD on a tree: rejected siblings whose draft rows shape the residual
-    if constexpr (KIND == KIND_CHAIN || KIND == KIND_SD || KIND == KIND_RFSD) {
+    int status = 0;
+    int my_par = -1, my_dep = 0, my_tok = 0;   // few: this lane's node (or position)
+    // Sec. 4 eq. 4 (NaN compares false); Sec. 3 eq. 1-2 in the log domain: min(1, p/q) > u  <=>  min(0, ln p - ln q) - ln u > 0;
+    // reducible FSD (Sec. 4.3): either rule accepts
+    auto accepted = [&](int i, float div, double ratio) __attribute__((always_inline)) -> bool {
+        bool ok = false;
+        if constexpr (KIND != KIND_SD) ok = div <= P.T;
+        if constexpr (BY_RATIO) {
+            const U4 r = philox4x32_10((static_cast<unsigned>(i) >> 2) | (1u << 30), static_cast<unsigned>(b),
+                                       P.off_lo, P.off_hi, P.seed_lo, P.seed_hi);
+            const unsigned wsel = (i & 3) == 0 ? r.x : (i & 3) == 1 ? r.y : (i & 3) == 2 ? r.z : r.w;
+            const double u = static_cast<double>(word_to_uniform(wsel));
+            const double thr = ratio < 0.0 ? ratio : 0.0;
+            ok = ok || (thr - log(u) > 0.0);
+        }
+        return ok;
+    };
+    if (tid == 0) { s_n = rows; s_st = 0; s_key = 0; s_thr = score_key(-FLT_MAX); }
+    if (!TREESD && few) {
+        const int st = P.ws.pst[pr];
+        float div = 0.0f;
+        double ratio = 0.0;
+        if constexpr (KIND != KIND_SD) div = P.ws.div[pr];
+        if constexpr (BY_RATIO) ratio = P.ws.lr[pr];
+        if constexpr (TREE) my_par = P.parent[pr];
+        my_tok = P.tokens[pr];   // (for the outputs)
+        __syncthreads();
+        const bool mine = lane < rows;
+        if (__any(mine && st != 0)) {
+            int bits = mine ? st : 0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) bits |= __shfl_xor(bits, o);
+            status = bits;
+        }
+        if constexpr (CHAIN) {
+            const unsigned long long no = __ballot(mine && !accepted(lane, div, ratio));
+            n = no ? static_cast<int>(__builtin_ctzll(no)) : rows;
+            sample_row = n;
+        } else {
+            const bool bad_parent = my_par < -1 || my_par >= lane;
+            if (__any(mine && bad_parent)) status |= FSD_ROW_BAD_PARENT;
+            if (bad_parent) my_par = -1;
+            // pointer jumping: after r rounds `at` names the 2^r-th ancestor, the rest covers that stretch:
+            // ancestor + 1 (8 bits), depth (8 bits), accepted
+            int at = (my_par + 1) | (1 << 8) | (accepted(lane, div, ratio) ? 1 << 16 : 0);
+            for (int span = 1; span < rows; span <<= 1) {
+                const int up = at & 0xFF, far = __shfl(at, up ? up - 1 : 0);
+                if (up) at = (far & 0xFF) | ((at & 0xFF00) + (far & 0xFF00)) | (at & far & (1 << 16));
+            }
+            my_dep = (at >> 8) & 0xFF;
+            const bool good = mine && (at >> 16);
+            if (__any(mine && my_dep > P.max_depth)) status |= FSD_ROW_TOO_DEEP;
+            const float deepest = wave_max(good ? static_cast<float>(my_dep) : 0.0f);   // deepest, then lowest index
+            if (deepest > 0.0f) {
+                n = static_cast<int>(deepest);
+                winner = static_cast<int>(__builtin_ctzll(__ballot(good && my_dep == n)));
+            }
+            sample_row = winner + 1;
+        }
+    } else if constexpr (CHAIN) {
+        __syncthreads();
         for (int i = tid; i < rows; i += kWG) {
-            const int pr = b * rows + i;
-            const int st = P.ws.pst[pr];
-            bool ok = false;
-            if constexpr (KIND == KIND_CHAIN || KIND == KIND_RFSD) {
-                ok = (P.ws.div[pr] <= P.T);   // Sec. 4 eq. 4 (NaN compares false)
-            }
-            if constexpr (KIND == KIND_SD || KIND == KIND_RFSD) {   // reducible FSD (Sec. 4.3): either rule accepts
-                // Sec. 3 eq. 1-2 in the log domain: min(1, p/q) > u  <=>  min(0, ln p - ln q) - ln u > 0
-                const double ratio = P.ws.lr[pr];
-                const U4 r = philox4x32_10((static_cast<unsigned>(i) >> 2) | (1u << 30), static_cast<unsigned>(b),
-                                           P.off_lo, P.off_hi, P.seed_lo, P.seed_hi);
-                const unsigned wsel = (i & 3) == 0 ? r.x : (i & 3) == 1 ? r.y : (i & 3) == 2 ? r.z : r.w;
-                const double u = static_cast<double>(word_to_uniform(wsel));
-                const double thr = ratio < 0.0 ? ratio : 0.0;
-                ok = ok || (thr - log(u) > 0.0);
-            }
+            const size_t at = static_cast<size_t>(b) * rows + i;
+            const int st = P.ws.pst[at];
+            const bool ok = accepted(i, KIND != KIND_SD ? P.ws.div[at] : 0.0f, BY_RATIO ? P.ws.lr[at] : 0.0);
             if (st) atomicOr(&s_st, st);
             if (!ok) atomicMin(&s_n, i);
         }
         __syncthreads();
         n = s_n;
         sample_row = n;
-    } else if constexpr (KIND == KIND_TREESD) {
+        status = s_st;
+    } else if constexpr (TREESD) {
         // the walk kernel has decided: depth, last node, and the residual chain the token comes from
         // (if the walk gave up on a bounded wait it may have written nothing: the header is then
         // whatever an earlier call left, so nothing in it is trusted)
         const int* hdr = P.ws.tsd + static_cast<size_t>(b) * (4 + rows);
-        const bool gave_up = failure_flagged(P.ws);
-        if (tid == 0) s_st = gave_up ? FSD_ROW_INTERNAL : hdr[0];
-        n = gave_up ? 0 : hdr[1];
-        sample_row = gave_up ? 0 : hdr[2] + 1;
-        nchain = gave_up ? 0 : hdr[3];
+        const int h0 = hdr[0], h1 = hdr[1], h2 = hdr[2], h3 = hdr[3];
+        const bool gave_up = fail_word == P.ws.nonce;
+        status = gave_up ? FSD_ROW_INTERNAL : h0;
+        n = gave_up ? 0 : h1;
+        sample_row = gave_up ? 0 : h2 + 1;
+        nchain = __builtin_amdgcn_readfirstlane(gave_up ? 0 : h3);
         if (n < 0 || n > P.max_depth || sample_row < 0 || sample_row > rows || nchain < 0 || nchain > rows) {
             n = 0; sample_row = 0; nchain = 0;
-            if (tid == 0) s_st = FSD_ROW_INTERNAL;
+            status = FSD_ROW_INTERNAL;
         }
         int* ch = s_dyn;
         float* iz = reinterpret_cast<float*>(s_dyn + rows);
@@ -371,14 +434,15 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
         int* anc = s_dyn + rows;
         int* acc = s_dyn + 2 * rows;
         int* dep = s_dyn + 3 * rows;
+        __syncthreads();
         for (int j = tid; j < rows; j += kWG) {
-            const int pr = b * rows + j;
-            int p = P.parent[pr];
+            const size_t at = static_cast<size_t>(b) * rows + j;
+            int p = P.parent[at];
             if (p < -1 || p >= j) { atomicOr(&s_st, FSD_ROW_BAD_PARENT); p = -1; }
-            const int st = P.ws.pst[pr];
+            const int st = P.ws.pst[at];
             if (st) atomicOr(&s_st, st);
             par[j] = p; anc[j] = p; dep[j] = 1;
-            acc[j] = (P.ws.div[pr] <= P.T) ? 1 : 0;
+            acc[j] = accepted(j, P.ws.div[at], 0.0) ? 1 : 0;
         }
         __syncthreads();
         // pointer jumping: after r rounds anc[j] is the 2^r-th ancestor, acc/dep cover that stretch
@@ -409,23 +473,30 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
         const int key = s_key;
         if (key) { n = key >> 11; winner = kMaxRows - 1 - (key & (kMaxRows - 1)); }
         sample_row = winner + 1;
+        status = s_st;
     }
-    int status = s_st;
     if (status & FSD_ROW_BAD_PARENT) status &= ~FSD_ROW_TOO_DEEP;   // depths mean nothing in a malformed tree
-    if (failure_flagged(P.ws)) status |= FSD_ROW_INTERNAL;   // a bounded wait of the reduction kernel expired
+    const bool failed = __any(fail_word == P.ws.nonce) != 0;
+    if (failed) status |= FSD_ROW_INTERNAL;   // a bounded wait of an earlier kernel expired
+
+    // (the same in every lane: scalars from here on)
+    status = __builtin_amdgcn_readfirstlane(status);
+    n = __builtin_amdgcn_readfirstlane(n);
+    sample_row = __builtin_amdgcn_readfirstlane(sample_row);
+    winner = __builtin_amdgcn_readfirstlane(winner);
 
     // ---- Gumbel-max over this workgroup's share of the sampled target row
     const char* trow = P.target + (static_cast<size_t>(b) * (rows + 1) + sample_row) * static_cast<size_t>(P.V) * ES;
     bool residual = false;
     const char* drow = nullptr;
     float lt = 0.0f, ld = 0.0f;
-    if constexpr (KIND == KIND_TREESD) {
+    if constexpr (TREESD) {
         if (nchain > 0 && !status) {
             residual = true;
             lt = static_cast<float>(P.ws.lse2[2 * (static_cast<size_t>(b) * rows + s_dyn[nchain - 1])]);
         }
     }
-    if constexpr (KIND == KIND_SD || KIND == KIND_RFSD) {
+    if constexpr (BY_RATIO) {
         if (n < rows) {   // rejected at n: the residual of Sec. 3 eq. 3 needs the draft row as well
             residual = true;
             drow = P.draft + (static_cast<size_t>(b) * rows + n) * static_cast<size_t>(P.V) * ES;
@@ -433,10 +504,12 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
             ld = static_cast<float>(P.ws.lse2[2 * (b * rows + n) + 1]);
         }
     }
+    const bool merges = gs == P.GS - 1;   // the sequence's last workgroup merges the shares and writes the outputs
     long s0 = static_cast<long>(gs) * P.sps;
     long s1 = (s0 + P.sps < P.nslots) ? s0 + P.sps : P.nslots;
-    bool alone = false;   // the last workgroup once more, over the whole row: see the end of the loop
-    for (;;) {
+    Best all{neg_inf(), 0x7FFFFFFF};   // the sequence's winner
+    int final_status = status;
+    auto share_of = [&](int& bd) __attribute__((always_inline)) -> Best {
         Best best{neg_inf(), 0x7FFFFFFF};
         int bad = 0;
         if (!status) {
@@ -447,128 +520,129 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
             // lane has still costs its instructions; whole calls on 16 sequences of 2, V=64000: 18.5 us with 8 entries,
             // 17.9 with 4; on 40 of 2, V=50048, shares of two slots a lane: 23.5 and 24.1)
             if (!BF16 && s1 - s0 <= kWG)
-                draw_share<BF16, LD, KIND == KIND_TREESD, 4 + 4 * BF16>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, &s_thr, best, bad);
+                draw_share<BF16, LD, TREESD, 4 + 4 * BF16>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, &s_thr, best, bad);
             else
-                draw_share<BF16, LD, KIND == KIND_TREESD, 8>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, &s_thr, best, bad);
+                draw_share<BF16, LD, TREESD, 8>(A, b, trow, residual, drow, lt, ld, C, s0, s1, tid, &s_thr, best, bad);
         }
         best = wave_best(best);
         bad = __any(bad);
         if (lane == 0) { s_best[wave] = best; s_bad[wave] = bad; }
         __syncthreads();
-        if (tid == 0) {
-            Best m = s_best[0];
-            int bd = s_bad[0];
-            for (int k = 1; k < 4; ++k) { m = better(m, s_best[k]); bd |= s_bad[k]; }
-            if (alone) {
-                s_key = m.idx;
-            } else {
-                // The share of this workgroup: two words that say by themselves whether they have arrived.  The
-                // sampler's shares are cleared with the exchange words at the start of the call and a posted
-                // word is never zero (the index goes out plus one, the flag with bit 1 set), so nothing has to
-                // order these stores before the count below: whoever merges looks until the words are there.
-                unsigned long long* slot = P.ws.spart + (static_cast<size_t>(b) * P.GS + gs) * 4;
-                __hip_atomic_store(slot + 0, (static_cast<unsigned long long>(__float_as_uint(m.score)) << 32) | (static_cast<unsigned>(m.idx) + 1u), __ATOMIC_RELAXED, AGENT);
-                __hip_atomic_store(slot + 1, static_cast<unsigned long long>(bd ? 3 : 2), __ATOMIC_RELAXED, AGENT);
-                const unsigned prev = __hip_atomic_fetch_add(P.ws.sdone + static_cast<size_t>(b) * kSdoneStride, 1u, __ATOMIC_RELAXED, AGENT);
-                s_last = (prev == static_cast<unsigned>(P.GS) - 1u) ? 1 : 0;
-            }
-        }
-        __syncthreads();
-        if (alone) break;
-        if (!s_last) return;
-
-        // ---- the last workgroup of the sequence merges the shares and writes the outputs
-        if (wave == 0) {   // one share per lane: the loads of all shares are in flight together
-            Best m{neg_inf(), 0x7FFFFFFF};
-            int bd = 0;
+        Best m = s_best[0];
+        bd = s_bad[0];
+#pragma unroll
+        for (int k = 1; k < 4; ++k) { m = better(m, s_best[k]); bd |= s_bad[k]; }
+        return m;
+    };
+    for (;;) {
+        int bd = 0;
+        const Best mine = share_of(bd);
+        if (!merges) {
+            // The sampler's shares are cleared with the exchange words at the start of the call, so nothing has to
+            // order this store: whoever merges looks until the word is there.
+            if (tid == 0)
+                __hip_atomic_store(P.ws.spart + static_cast<size_t>(b) * P.GS + gs, share_word(mine, bd), __ATOMIC_RELAXED, AGENT);
+        } else if (wave == 0) {
+            // one share per lane, this workgroup's own in the last (alone: nobody else's)
+            const unsigned long long* const slot = P.ws.spart + static_cast<size_t>(b) * P.GS;
+            unsigned long long w = share_word(mine, bd);
             bool late = false;
-            for (int k = lane; k < P.GS; k += 64) {
-                const unsigned long long* slot = P.ws.spart + (static_cast<size_t>(b) * P.GS + k) * 4;
-                // every workgroup of the sequence has counted itself, so its words are on their way: normally
-                // they are there at the first look (bounded wait otherwise)
-                unsigned long long w0 = 0, w1 = 0;
-                for (unsigned polls = 0;; ++polls) {
-                    w0 = __hip_atomic_load(slot + 0, __ATOMIC_RELAXED, AGENT);
-                    w1 = __hip_atomic_load(slot + 1, __ATOMIC_RELAXED, AGENT);
-                    if ((w0 != 0 && w1 != 0) || polls >= P.spin_limit) break;
+            if (s1 - s0 < P.nslots) {
+                const bool other = lane < gs;
+                for (unsigned looks = 0;; ++looks) {
+                    const unsigned long long v = __hip_atomic_load(slot + (other ? lane : 0), __ATOMIC_RELAXED, AGENT);
+                    late = __any(other && v == 0) != 0;
+                    if (!late || looks >= kShareLooks) { w = other ? v : w; break; }
                     __builtin_amdgcn_s_sleep(1);
                 }
-                if (w0 == 0 || w1 == 0) { late = true; continue; }
-                bd |= static_cast<int>(w1 & 1);
-                m = better(m, Best{__uint_as_float(static_cast<unsigned>(w0 >> 32)), static_cast<int>(static_cast<unsigned>(w0) - 1u)});
             }
-            m = wave_best(m);
-            bd = __any(bd);
-            late = __any(late);
-            if (lane == 0) {
-                int st = status;
-                if (late) st |= FSD_ROW_INTERNAL;   // a share never arrived (never expected)
-                if (!st && (bd || (m.idx == 0x7FFFFFFF && !residual))) st |= FSD_ROW_NONFINITE;
-                s_st = st;
-                s_key = m.idx;
-            }
+            all = wave_best(share_best(w));
+            bd = __any((w & 0x80000000u) != 0);
+            if (late) final_status |= FSD_ROW_INTERNAL;   // a share never arrived (never expected)
+            if (!final_status && (bd || (all.idx == 0x7FFFFFFF && !residual))) final_status |= FSD_ROW_NONFINITE;
         }
-        __syncthreads();
-        if (!residual || s_st || s_key != 0x7FFFFFFF) break;
-        // No entry has a positive part (p = q to rounding, which a genuine rejection all but excludes): the
-        // token is drawn from the row itself, by this workgroup alone.  (A rejected row is one the reduction
-        // has found usable: it has an entry above -inf.)
-        residual = false;
-        alone = true;
-        s0 = 0;
-        s1 = P.nslots;
-        __syncthreads();   // (s_st and s_key have been read)
-    }
-    __syncthreads();
-    status = s_st;
-    const int token = s_key;
-    if (status) n = 0;
-    const int width = (KIND == KIND_TREE || KIND == KIND_TREESD) ? P.max_depth + 1 : rows + 1;
-    int32_t* out = P.out_tokens + static_cast<size_t>(b) * width;
-    if constexpr (KIND == KIND_TREESD) {
-        // the walk has written the path and its tokens; add the drawn token, or take it all back
-        if (status) {
-            int32_t* pn = P.path_nodes + static_cast<size_t>(b) * P.max_depth;
-            for (int i = tid; i < P.max_depth; i += kWG) pn[i] = -1;
-            for (int i = tid; i < width; i += kWG) out[i] = -1;
-        } else if (tid == 0) {
-            out[n] = token;
-        }
-    } else if constexpr (KIND == KIND_TREE) {
-        int32_t* pn = P.path_nodes + static_cast<size_t>(b) * P.max_depth;
-        for (int i = tid; i < P.max_depth; i += kWG) pn[i] = -1;
-        for (int i = tid; i < width; i += kWG) out[i] = (i == n && !status) ? token : -1;
-        __syncthreads();
-        if (tid == 0 && !status) {
-            const int* par = s_dyn;
-            int jn = winner;
-            for (int i = n - 1; i >= 0 && jn >= 0; --i) {
-                pn[i] = jn;
-                out[i] = P.tokens[static_cast<size_t>(b) * rows + jn];
-                jn = par[jn];
-            }
-        }
-    } else {
-        for (int i = tid; i < width; i += kWG) {
-            int v = -1;
-            if (!status) {
-                if (i < n) v = P.tokens[static_cast<size_t>(b) * rows + i];
-                else if (i == n) v = token;
-            }
-            out[i] = v;
+        if constexpr (BY_RATIO || TREESD) {
+            if (!merges || !residual) break;
+            if (tid == 0) { s_st = final_status; s_key = all.idx; }
+            __syncthreads();
+            if (s_st || s_key != 0x7FFFFFFF) break;
+            // No entry has a positive part (p = q to rounding, which a genuine rejection all but excludes): the
+            // token is drawn from the row itself, by this workgroup alone.  (A rejected row is one the reduction
+            // has found usable: it has an entry above -inf.)
+            residual = false;
+            s0 = 0;
+            s1 = P.nslots;
+        } else {
+            break;
         }
     }
-    if (tid == 0) {
-        P.out_len[b] = n;
-        if (P.row_status) P.row_status[b] = status;
-        // The last workgroup of the last sequence to finish: every workgroup of this kernel has posted its
-        // share by now, and so has looked at the failure word, which nothing looks at after this kernel.
-        // It goes back to zero, so that the same call replayed from a captured graph, with the same
-        // number, does not find a failure of the last time.
-        const unsigned done = atomicAdd(P.ws.counters + 4, 1u);
-        if (done == gridDim.y - 1) {
-            __hip_atomic_store(reinterpret_cast<unsigned long long*>(P.ws.counters + 2), 0ull, __ATOMIC_RELAXED, AGENT);
+    if (merges && wave == 0) {
+        const int token = all.idx;
+        if (final_status) n = 0;
+        const int width = CHAIN ? rows + 1 : P.max_depth + 1;
+        int32_t* const out = P.out_tokens + static_cast<size_t>(b) * width;
+        if constexpr (TREESD) {
+            // the walk has written the path and its tokens; add the drawn token, or take it all back
+            if (final_status) {
+                int32_t* pn = P.path_nodes + static_cast<size_t>(b) * P.max_depth;
+                for (int i = lane; i < P.max_depth; i += 64) pn[i] = -1;
+                for (int i = lane; i < width; i += 64) out[i] = -1;
+            } else if (lane == 0) {
+                out[n] = token;
+            }
+        } else if constexpr (TREE) {
+            int32_t* const pn = P.path_nodes + static_cast<size_t>(b) * P.max_depth;
+            if (few) {
+                // the nodes of the path are the winner and its ancestors; a node's place is its depth
+                unsigned long long path = 0;
+                if (!final_status)
+                    for (int j = winner; j >= 0; j = __builtin_amdgcn_readlane(my_par, j)) path |= 1ull << j;
+                for (int i = n + lane; i < P.max_depth; i += 64) pn[i] = -1;
+                for (int i = n + lane; i < width; i += 64) out[i] = (i == n && !final_status) ? token : -1;
+                if ((path >> lane) & 1) { pn[my_dep - 1] = lane; out[my_dep - 1] = my_tok; }
+            } else {
+                for (int i = n + lane; i < P.max_depth; i += 64) pn[i] = -1;
+                for (int i = n + lane; i < width; i += 64) out[i] = (i == n && !final_status) ? token : -1;
+                if (lane == 0 && !final_status) {
+                    const int* par = s_dyn;
+                    int jn = winner;
+                    for (int i = n - 1; i >= 0 && jn >= 0; --i) {
+                        pn[i] = jn;
+                        out[i] = P.tokens[static_cast<size_t>(b) * rows + jn];
+                        jn = par[jn];
+                    }
+                }
+            }
+        } else {
+            for (int i = lane; i < width; i += 64) {
+                int v = -1;
+                if (!final_status) {
+                    if (i < n) v = few ? my_tok : P.tokens[static_cast<size_t>(b) * rows + i];
+                    else if (i == n) v = token;
+                }
+                out[i] = v;
+            }
         }
+        if (lane == 0) {
+            P.out_len[b] = n;
+            if (P.row_status) P.row_status[b] = final_status;
+            // A call that has failed (every workgroup of this kernel sees that): the last sequence to finish puts the
+            // failure word, which nothing looks at after this kernel, back to zero, so that the same call replayed from a captured
+            // graph, with the same number, does not find a failure of the last time.
+            if (failed) {
+                const unsigned done = atomicAdd(P.ws.counters + 4, 1u);
+                if (done == gridDim.y - 1)
+                    __hip_atomic_store(reinterpret_cast<unsigned long long*>(P.ws.counters + 2), 0ull, __ATOMIC_RELAXED, AGENT);
+            }
+        }
+    }
+    if (P.clear_arrive) {
+        // the reduction kernel has ended: its wavefronts' slots go back to zero, so that the same call
+        // replayed from a captured graph, with the same number, does not find them set
+        uint4* const slots = reinterpret_cast<uint4*>(P.ws.arrive);
+        const long nthreads = static_cast<long>(gridDim.x) * gridDim.y * kWG;
+        for (long i = (static_cast<long>(b) * gridDim.x + gs) * kWG + tid; i < kMaxArrive / 2; i += nthreads)
+            slots[i] = make_uint4(0u, 0u, 0u, 0u);
     }
 }
 

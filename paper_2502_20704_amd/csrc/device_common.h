@@ -19,7 +19,7 @@ constexpr int kWG = 256;          // threads per workgroup (4 wavefronts of 64)
 constexpr int kMaxRows = 2048;    // K or N
 constexpr int kSampleWGs = 1024;  // sampler workgroups aimed at per call (all sequences together): more cost
                                   // more in launch and posting than their parallelism returns
-constexpr int kSdoneStride = 64;  // 32-bit words between the sampler's per-sequence counters: one 256-byte
+constexpr int kSdoneStride = 64;  // 32-bit words between the selection's per-sequence counters: one 256-byte
                                   // line each, so that the counting atomics of different sequences do not
                                   // queue at one memory channel
 constexpr int kWalkShare = 8;     // workgroups that share a sequence's passes in the tree walk (at most)
@@ -104,6 +104,24 @@ __device__ __forceinline__ float wave_max(float v) {
         "s_nop 1"
         : "+v"(v));
     return lane_f(v, 63);
+}
+// minimum over the wavefront
+__device__ __forceinline__ int wave_min(int v) {
+    asm("s_nop 1\n\t"
+        "v_min_i32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_i32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_i32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_i32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_i32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_i32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "+v"(v));
+    return __builtin_amdgcn_readlane(v, 63);
 }
 // Sums over the wavefront in a fixed order: within rows of 16 lanes, then row 0 into row 1 and
 // row 2 into row 3, then rows 0-1 into rows 2-3; lane 63 holds the total.
@@ -343,8 +361,8 @@ __device__ __forceinline__ float gumbel(unsigned w) {
 // workspace view
 
 struct Ws {
-    unsigned* counters;  // 64 words (words 2-3: the failure word, see flag_failure; word 4: sequences the sampler has finished), then sdone
-    unsigned* sdone;     // [B][kSdoneStride], first word: sampler workgroups that posted
+    unsigned* counters;  // 64 words (words 2-3: the failure word, see flag_failure; word 4: sequences a failed call has finished), then sdone
+    unsigned* sdone;     // [B][kSdoneStride]: count and words of the workgroups that share a selection (warp_select.h)
     unsigned long long* part1;  // [R][G][n1] phase-1 words, dense: (kt,kd) | (St,Sd) in the two-phase modes (n1 = 2),
                                 // (kt,kd) | St | Sd | W in the single-pass ones (n1 = 4)
     double* part2;       // [R][G][n2] divergence words of the two-phase modes (n2 = 1, or 2 for TV and pointwise KL)
@@ -354,7 +372,7 @@ struct Ws {
     int* pst;            // [R] status bits per pair
     double* lse2;        // [R][2] log2-sum-exp2 of the target / draft row of the pair
     double* lr;          // [R] strict SD: ln p(x) - ln q(x)
-    unsigned long long* spart;  // [B][GS][4]
+    unsigned long long* spart;  // [B][GS] the sampler's shares (share_word in accept_sample.h)
     float* thr;          // [B] warpers: smallest kept scaled logit of the sampled row
     int* tsd;            // [B][4 + rows] strict SD on a tree, from the walk to the sampler: status, depth,
                          // last node (-1 = root), length of the residual chain, then the chain's nodes

@@ -470,7 +470,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     auto first_k = [&](unsigned long long) __attribute__((always_inline)) -> unsigned long long { return static_cast<unsigned long long>(P.top_k); };
 
     if constexpr (SPLIT) {
-        unsigned* const line = P.ws.sdone + static_cast<size_t>(b) * kSdoneStride;   // word 0 is the sampler's count
+        unsigned* const line = P.ws.sdone + static_cast<size_t>(b) * kSdoneStride;
         unsigned* const count = line + 1;
         char* const area = P.area + static_cast<size_t>(b) * P.seq_bytes;
         const int g = static_cast<int>(blockIdx.x), W = static_cast<int>(gridDim.x);

@@ -507,3 +507,45 @@ def test_routes_under_capture(torch_cuda):
         for w, k in zip(want, keep):
             for name, v in w.items():
                 assert np.array_equal(k["out"][name].cpu().numpy(), v, equal_nan=True), (rep, name)
+
+
+# up to 64 positions or nodes are decided by a wavefront, more by the workgroup; V: one, two and several shares of a draw
+@pytest.mark.parametrize("rows,V,dtype", [(1, 700, "bf16"), (2, 1025, "f32"), (63, 2056, "bf16"), (64, 4100, "bf16"), (64, 1028, "f32"),
+                                          (65, 4096, "bf16"), (65, 1029, "f32"), (130, 520, "f32")])
+def test_acceptance_around_a_wavefront_of_rows(torch_cuda, oracle, rows, V, dtype):
+    """Prefixes and paths that end at the first, an inner and the last position, or node 63, 64 and 65 of a tree; malformed
+    and too deep trees; a sequence with an unusable row beside good ones."""
+    rng = np.random.default_rng(rows * 1000 + V)
+    B, tol = 4, pu.rel_tol(dtype)
+    inp = _random_tree_inputs(rng, B, rows, V, dtype, noise=(0.2, 0.6))
+    inp["parent"][1] = np.arange(-1, rows - 1)                       # a chain: the deepest tree there is
+    chain = dict(target=inp["target"], draft=inp["draft"].copy(), cand=inp["node_tokens"])
+    chain["draft"][:] = chain["target"][:, :rows]                    # equal rows (accepted at any T >= 0) ...
+    for b, first in enumerate((0, rows // 2, rows - 1)):             # ... up to one that is not
+        chain["draft"][b, first] = chain["target"][b, first][::-1]
+    for mode in (fsd.SAMPLE, fsd.GREEDY):
+        print("acceptance", rows, V, dtype, mode, flush=True)
+        g = run_chain(torch_cuda, chain, 0.01, fsd.DIV_TV, mode, seed=5, offset=2)
+        o = oracle.verify_chain(chain["target"], chain["draft"], chain["cand"], 0.01, fsd.DIV_TV, mode, seed=5, offset=2)
+        assert list(o["accept_len"]) == [0, rows // 2, rows - 1, rows]
+        pu.check_chain(g, o, 0.01, tol, f"acceptance chain rows={rows} {dtype}", envelope=pu.Envelope(dtype))
+        for T in (-1.0, float(np.median(o["divs"])), 1e9):
+            g = run_tree(torch_cuda, inp, T, fsd.DIV_TV, rows, mode, seed=5, offset=2)
+            ot = oracle.verify_tree(inp["target"], inp["draft"], inp["node_tokens"], inp["parent"], rows, T, fsd.DIV_TV, mode, seed=5, offset=2)
+            pu.check_tree(g, ot, T, tol, f"acceptance tree rows={rows} {dtype} T={T}", envelope=pu.Envelope(dtype))
+    d = pu.to_dev(chain, ("target", "draft", "cand"))
+    out = fsd.sd_verify_chain(d["target"], d["draft"], d["cand"], seed=5, offset=2)
+    torch_cuda.cuda.synchronize()
+    o = oracle.sd_verify_chain(chain["target"], chain["draft"], chain["cand"], seed=5, offset=2)
+    check_sd(pu.host(out, pu.SD_KEYS), o, f"acceptance SD rows={rows} {dtype}")
+    if rows > 2:
+        bad = dict(inp, parent=inp["parent"].copy())
+        bad["parent"][0, rows - 1] = rows - 1                        # its own parent
+        g = run_tree(torch_cuda, bad, 1e9, fsd.DIV_TV, rows - 1, seed=5, offset=2)
+        o = oracle.verify_tree(bad["target"], bad["draft"], bad["node_tokens"], bad["parent"], rows - 1, 1e9, fsd.DIV_TV, seed=5, offset=2)
+        assert o["row_status"][0] == fsd.ROW_BAD_PARENT and o["row_status"][1] == fsd.ROW_TOO_DEEP
+        pu.check_tree(g, o, 1e9, tol, f"acceptance malformed rows={rows} {dtype}", envelope=pu.Envelope(dtype))
+        spoilt = dict(inp, draft=inp["draft"].copy())
+        spoilt["draft"][2, rows - 1, 1] = np.uint16(0x7FC0) if dtype == "bf16" else np.float32(np.nan)
+        g = run_tree(torch_cuda, spoilt, 1e9, fsd.DIV_TV, rows, seed=5, offset=2)
+        assert list(g["row_status"]) == [0, 0, fsd.ROW_NONFINITE, 0] and g["path_len"][2] == 0
