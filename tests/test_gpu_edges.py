@@ -544,7 +544,10 @@ def test_acceptance_around_a_wavefront_of_rows(torch_cuda, oracle, rows, V, dtyp
         g = run_tree(torch_cuda, bad, 1e9, fsd.DIV_TV, rows - 1, seed=5, offset=2)
         o = oracle.verify_tree(bad["target"], bad["draft"], bad["node_tokens"], bad["parent"], rows - 1, 1e9, fsd.DIV_TV, seed=5, offset=2)
         assert o["row_status"][0] == fsd.ROW_BAD_PARENT and o["row_status"][1] == fsd.ROW_TOO_DEEP
-        pu.check_tree(g, o, 1e9, tol, f"acceptance malformed rows={rows} {dtype}", envelope=pu.Envelope(dtype))
+        assert list(g["row_status"]) == list(o["row_status"])
+        assert (g["path_len"][:2] == 0).all() and (g["path_nodes"][:2] == -1).all() and (g["out_tokens"][:2] == -1).all()
+        pu.check_tree({k: v[2:] for k, v in g.items()}, {k: v[2:] for k, v in o.items()}, 1e9, tol,
+                      f"acceptance beside malformed rows={rows} {dtype}", envelope=pu.Envelope(dtype))
         spoilt = dict(inp, draft=inp["draft"].copy())
         spoilt["draft"][2, rows - 1, 1] = np.uint16(0x7FC0) if dtype == "bf16" else np.float32(np.nan)
         g = run_tree(torch_cuda, spoilt, 1e9, fsd.DIV_TV, rows, seed=5, offset=2)
