@@ -8,6 +8,11 @@ from __future__ import annotations
 import ctypes
 import os
 
+# torch before the library: the library then binds to the HIP runtime torch has loaded.  Loaded before torch it would
+# bring in the system's copy, and a process with two HIP runtimes has its device memory in one and this
+# library's launches in the other.
+import torch
+
 F32, BF16 = 0, 1
 DIV_KL, DIV_JS, DIV_TV = 0, 1, 2
 SAMPLE, GREEDY = 0, 1
@@ -33,11 +38,6 @@ def library() -> ctypes.CDLL:
             raise FileNotFoundError(
                 f"{LIB_PATH} is missing: build it with `python -m paper_2502_20704_amd.build` "
                 "(there is no CPU fallback)")
-        # torch first: the library then binds to the HIP runtime torch has loaded.  Loaded before torch
-        # it would bring in the system's copy, and a process with two HIP runtimes has its device
-        # memory in one and this library's launches in the other.
-        import torch  # noqa: F401
-
         L = ctypes.CDLL(LIB_PATH)
         c = ctypes
         vp, i32, u64, f32, sz = c.c_void_p, c.c_int, c.c_uint64, c.c_float, c.c_size_t
@@ -109,8 +109,6 @@ def fsd_workspace_bytes(B: int, rows_per_seq: int, V: int, dtype: int) -> int:
 
 
 def _dtype_code(t) -> int:
-    import torch
-
     if t.dtype == torch.float32:
         return F32
     if t.dtype == torch.bfloat16:
@@ -123,39 +121,37 @@ def _check(t, name, shape=None, dtype=None):
         raise ValueError(f"{name} must live on the GPU")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} has dtype {t.dtype}, expected {dtype}")
 
 
+# (Addresses go to ctypes as plain integers, which the argument types take: an object for each of a call's dozen, and a
+# torch.cuda.Stream for its stream, cost the host more than the two launches of a small call.  1 sequence of 4
+# positions, V=32000: host 13.2 -> 9.8 us a call, whole call 13.7 -> 11.9.)
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _workspace(workspace, need, device):
-    import torch
-
     if workspace is None:
         workspace = torch.empty(need + 256, dtype=torch.uint8, device=device)
     base = workspace.data_ptr()
     pad = (-base) % 256
-    return workspace, ctypes.c_void_p(base + pad), workspace.numel() - pad
+    return workspace, base + pad, workspace.numel() - pad
 
 
 def _stream(stream):
-    import torch
-
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())   # torch.cuda.current_stream().cuda_stream
 
 
 def fsd_verify_chain(target, draft, cand, T, div=DIV_JS, mode=SAMPLE, seed=0, offset=0, *, out=None,
                      workspace=None, stream=None):
     """target [B,K+1,V], draft [B,K,V], cand int32 [B,K] on the GPU -> dict of device tensors
     accept_len [B], out_tokens [B,K+1], divergences [B,K], row_status [B]."""
-    import torch
-
     B, K1, V = target.shape
     K = K1 - 1
     dt = _dtype_code(target)
@@ -186,8 +182,6 @@ STATIC_SCRATCH_BYTES = 4 << 20
 def fsd_verify_chain_static(target, draft, cand, T, div=DIV_JS, mode=SAMPLE, seed=0, offset=0, *, out, stream=None):
     """fsd_verify_chain on the library's own fixed scratch buffer: nothing is allocated, so the caller
     passes the output tensors (`out`: accept_len, out_tokens and optionally divergences, row_status)."""
-    import torch
-
     B, K1, V = target.shape
     K = K1 - 1
     dt = _dtype_code(target)
@@ -205,8 +199,6 @@ def fsd_verify_chain_static(target, draft, cand, T, div=DIV_JS, mode=SAMPLE, see
 def fsd_verify_chain_warped(target, draft, cand, T, div=DIV_JS, mode=SAMPLE, seed=0, offset=0, *,
                             temperature=1.0, top_k=0, top_p=1.0, out=None, workspace=None, stream=None):
     """fsd_verify_chain with temperature / top-k / top-p applied where the token is drawn."""
-    import torch
-
     B, K1, V = target.shape
     K = K1 - 1
     dt = _dtype_code(target)
@@ -236,8 +228,6 @@ def fsd_verify_tree(target, draft, node_tokens, parent, max_depth, T, div=DIV_JS
                     offset=0, *, out=None, workspace=None, stream=None):
     """target [B,N+1,V], draft [B,N,V], node_tokens / parent int32 [B,N] -> dict of device tensors
     path_len [B], path_nodes [B,max_depth], out_tokens [B,max_depth+1], divergences [B,N], row_status [B]."""
-    import torch
-
     B, N1, V = target.shape
     N = N1 - 1
     dt = _dtype_code(target)
@@ -268,8 +258,6 @@ def fsd_verify_tree(target, draft, node_tokens, parent, max_depth, T, div=DIV_JS
 def fsd_verify_tree_warped(target, draft, node_tokens, parent, max_depth, T, div=DIV_JS, mode=SAMPLE, seed=0,
                            offset=0, *, temperature=1.0, top_k=0, top_p=1.0, out=None, workspace=None, stream=None):
     """fsd_verify_tree with temperature / top-k / top-p applied where the token is drawn."""
-    import torch
-
     B, N1, V = target.shape
     N = N1 - 1
     dt = _dtype_code(target)
@@ -300,8 +288,6 @@ def fsd_verify_tree_warped(target, draft, node_tokens, parent, max_depth, T, div
 def sd_verify_chain(target, draft, cand, mode=SAMPLE, seed=0, offset=0, *, out=None, workspace=None,
                     stream=None):
     """strict speculative decoding on the chain tensors -> accept_len, out_tokens, log_ratio, row_status."""
-    import torch
-
     B, K1, V = target.shape
     K = K1 - 1
     dt = _dtype_code(target)
@@ -329,8 +315,6 @@ def sd_verify_tree(target, draft, node_tokens, parent, max_depth, mode=SAMPLE, s
                    workspace=None, stream=None):
     """strict speculative decoding over a token tree (tensors of fsd_verify_tree) -> path_len, path_nodes,
     out_tokens, log_ratio [B,N] (NaN for nodes never tried), row_status."""
-    import torch
-
     B, N1, V = target.shape
     N = N1 - 1
     dt = _dtype_code(target)
@@ -360,8 +344,6 @@ def sd_verify_tree(target, draft, node_tokens, parent, max_depth, mode=SAMPLE, s
 def rfsd_verify_chain(target, draft, cand, T, div=DIV_JS, mode=SAMPLE, seed=0, offset=0, *, out=None,
                       workspace=None, stream=None):
     """reducible FSD on the chain tensors -> accept_len, out_tokens, divergences, log_ratio, row_status."""
-    import torch
-
     B, K1, V = target.shape
     K = K1 - 1
     dt = _dtype_code(target)
@@ -390,8 +372,6 @@ def rfsd_verify_chain(target, draft, cand, T, div=DIV_JS, mode=SAMPLE, seed=0, o
 def fsd_calibrate_threshold(divergences, target_fraction: float, *, stream=None):
     """(T, accepted fraction) as 1-element device tensors: the smallest occurring threshold at which
     the chain rule accepts at least `target_fraction` of the candidate positions of `divergences`."""
-    import torch
-
     _check(divergences, "divergences", None, torch.float32)
     B, K = divergences.shape
     dev = divergences.device
@@ -432,8 +412,6 @@ def debug_set_selection_spin_limit(polls: int) -> int:
 
 def debug_warp_thresholds(out, B: int, rows: int, V: int, dtype_code: int):
     """the per-sequence cut fsd_verify_chain_warped left in its workspace (test hook), as a float32 tensor [B]"""
-    import torch
-
     L = library()
     L.fsd_debug_warp_threshold_offset.argtypes = [ctypes.c_int] * 4
     L.fsd_debug_warp_threshold_offset.restype = ctypes.c_size_t
