@@ -39,8 +39,9 @@
  *     GPU while a call runs (another stream, another process), some of its
  *     workgroups may start late; every wait is bounded (see
  *     fsd_debug_set_spin_limit), and a wait that expires ends the call with
- *     FSD_ROW_INTERNAL in row_status for every sequence (lengths 0, tokens -1)
- *     instead of hanging.  Run verify calls on a GPU that is theirs while they
+ *     FSD_ROW_INTERNAL in row_status for every sequence (lengths 0, tokens -1;
+ *     a plain FSD call on a few sequences, which is one kernel, for every
+ *     sequence it concerns) instead of hanging.  Run verify calls on a GPU that is theirs while they
  *     run, and treat FSD_ROW_INTERNAL as "call again".
  *   - Random numbers: Philox4x32-10 keyed by `seed`; `offset` selects the
  *     decode step (counter words 2,3), the sequence index is counter word 1 and

@@ -286,6 +286,43 @@ __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char*
     }
 }
 
+// The tree rule over at most 64 nodes, one per lane (the same in every lane but my_dep): depth and node of the deepest
+// accepted path, status bits of a malformed tree.  my_par: an invalid parent becomes -1.
+struct TreePick { int n, winner, my_dep, status; };
+__device__ __forceinline__ TreePick pick_path(int lane, int rows, int max_depth, int& my_par, bool accepted) {
+    TreePick r{0, -1, 0, 0};
+    const bool mine = lane < rows;
+    const bool bad_parent = my_par < -1 || my_par >= lane;
+    if (__any(mine && bad_parent)) r.status |= FSD_ROW_BAD_PARENT;
+    if (bad_parent) my_par = -1;
+    // pointer jumping: after r rounds `at` names the 2^r-th ancestor, the rest covers that stretch:
+    // ancestor + 1 (8 bits), depth (8 bits), accepted
+    int at = (my_par + 1) | (1 << 8) | (accepted ? 1 << 16 : 0);
+    for (int span = 1; span < rows; span <<= 1) {
+        const int up = at & 0xFF, far = __shfl(at, up ? up - 1 : 0);
+        if (up) at = (far & 0xFF) | ((at & 0xFF00) + (far & 0xFF00)) | (at & far & (1 << 16));
+    }
+    r.my_dep = (at >> 8) & 0xFF;
+    const bool good = mine && (at >> 16);
+    if (__any(mine && r.my_dep > max_depth)) r.status |= FSD_ROW_TOO_DEEP;
+    const float deepest = wave_max(good ? static_cast<float>(r.my_dep) : 0.0f);   // deepest, then lowest index
+    if (deepest > 0.0f) {
+        r.n = static_cast<int>(deepest);
+        r.winner = static_cast<int>(__builtin_ctzll(__ballot(good && r.my_dep == r.n)));
+    }
+    return r;
+}
+// a path of n nodes that ends at `winner` (-1: none) and the token behind it, a node per lane
+__device__ __forceinline__ void write_path(int lane, int max_depth, int winner, int n, int my_par, int my_dep, int my_tok, int token,
+                                           int32_t* pn, int32_t* out) {
+    // the nodes of the path are the winner and its ancestors; a node's place is its depth
+    unsigned long long path = 0;
+    for (int j = winner; j >= 0; j = __builtin_amdgcn_readlane(my_par, j)) path |= 1ull << j;
+    for (int i = n + lane; i < max_depth; i += 64) pn[i] = -1;
+    for (int i = n + lane; i <= max_depth; i += 64) out[i] = i == n ? token : -1;
+    if ((path >> lane) & 1) { pn[my_dep - 1] = lane; out[my_dep - 1] = my_tok; }
+}
+
 // A workgroup's share of a sequence's draw in one word that says by itself whether it has arrived: score, then the flag
 // of an unusable logit and the index plus one (all ones: no entry).  Never zero.
 __device__ __forceinline__ unsigned long long share_word(Best m, int bad) {
@@ -371,24 +408,11 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
             n = no ? static_cast<int>(__builtin_ctzll(no)) : rows;
             sample_row = n;
         } else {
-            const bool bad_parent = my_par < -1 || my_par >= lane;
-            if (__any(mine && bad_parent)) status |= FSD_ROW_BAD_PARENT;
-            if (bad_parent) my_par = -1;
-            // pointer jumping: after r rounds `at` names the 2^r-th ancestor, the rest covers that stretch:
-            // ancestor + 1 (8 bits), depth (8 bits), accepted
-            int at = (my_par + 1) | (1 << 8) | (accepted(lane, div, ratio) ? 1 << 16 : 0);
-            for (int span = 1; span < rows; span <<= 1) {
-                const int up = at & 0xFF, far = __shfl(at, up ? up - 1 : 0);
-                if (up) at = (far & 0xFF) | ((at & 0xFF00) + (far & 0xFF00)) | (at & far & (1 << 16));
-            }
-            my_dep = (at >> 8) & 0xFF;
-            const bool good = mine && (at >> 16);
-            if (__any(mine && my_dep > P.max_depth)) status |= FSD_ROW_TOO_DEEP;
-            const float deepest = wave_max(good ? static_cast<float>(my_dep) : 0.0f);   // deepest, then lowest index
-            if (deepest > 0.0f) {
-                n = static_cast<int>(deepest);
-                winner = static_cast<int>(__builtin_ctzll(__ballot(good && my_dep == n)));
-            }
+            const TreePick pick = pick_path(lane, rows, P.max_depth, my_par, accepted(lane, div, ratio));
+            n = pick.n;
+            winner = pick.winner;
+            my_dep = pick.my_dep;
+            status |= pick.status;
             sample_row = winner + 1;
         }
     } else if constexpr (CHAIN) {
@@ -593,13 +617,7 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
         } else if constexpr (TREE) {
             int32_t* const pn = P.path_nodes + static_cast<size_t>(b) * P.max_depth;
             if (few) {
-                // the nodes of the path are the winner and its ancestors; a node's place is its depth
-                unsigned long long path = 0;
-                if (!final_status)
-                    for (int j = winner; j >= 0; j = __builtin_amdgcn_readlane(my_par, j)) path |= 1ull << j;
-                for (int i = n + lane; i < P.max_depth; i += 64) pn[i] = -1;
-                for (int i = n + lane; i < width; i += 64) out[i] = (i == n && !final_status) ? token : -1;
-                if ((path >> lane) & 1) { pn[my_dep - 1] = lane; out[my_dep - 1] = my_tok; }
+                write_path(lane, P.max_depth, final_status ? -1 : winner, n, my_par, my_dep, my_tok, final_status ? -1 : token, pn, out);
             } else {
                 for (int i = n + lane; i < P.max_depth; i += 64) pn[i] = -1;
                 for (int i = n + lane; i < width; i += 64) out[i] = (i == n && !final_status) ? token : -1;

@@ -14,7 +14,8 @@
 //   accept_sample   (accept_sample.h) per sequence: the accepted prefix (Sec. 4, eq. 4) or accepted
 //                   tree path (Sec. 6.4) or the strict-SD acceptance (Sec. 3, eq. 1-2), then the extra
 //                   token by Gumbel-max over the vocabulary of one target row, split over GS workgroups.
-// and fsd_calibrate_threshold the kernels of calibrate.h.
+// The plain FSD calls on a few sequences launch small_call (small_call.h) alone, and fsd_calibrate_threshold the
+// kernels of calibrate.h.
 //
 // Nothing here is shared with the CPU oracle: Philox4x32-10 and the exact-operation logarithm
 // are implemented a second time from their published / stated definitions.
@@ -34,6 +35,7 @@
 #include "device_common.h"
 #include "pair_kernel.h"
 #include "accept_sample.h"
+#include "small_call.h"
 #include "tree_sd_walk.h"
 #include "warp_select.h"
 #include "calibrate.h"
@@ -169,7 +171,8 @@ unsigned g_selection_spin_limit = UINT_MAX;   // test hook: a smaller limit for 
 // The entropy form of JS (bfloat16 logits) carries an absolute error of a few 1e-7 whatever the
 // result: below this floor (nats) a pair is evaluated again in the pointwise form, so that what the
 // caller sees is within 2e-3 relative everywhere (with a margin of five to ten).
-float g_js_floor = 1e-3f;
+constexpr float kJsFloor = 1e-3f;
+float g_js_floor = kJsFloor;
 bool g_exact_js = false;   // test hook: bfloat16 JS in the pointwise form only
 bool g_self_clear = true;  // test hook: 0 = every call launches the clearing kernel
 #ifdef FSD_PHASE_TIMING
@@ -343,6 +346,63 @@ void launch_sample(int dtype, int load, int kind, dim3 grid, size_t lds, hipStre
         else if (load == LOAD_WIDE) launch_sample_k<false, LOAD_WIDE>(kind, grid, lds, st, P);
         else launch_sample_k<false, LOAD_ELEM>(kind, grid, lds, st, P);
     }
+}
+
+// ---- a plain FSD call on a few sequences in one launch (small_call.h): false (nothing launched) if it is not small.
+// Small is what its words have room for beside one draw from every target row: whole calls under JS that just are
+// (two kernels -> one, us): bfloat16 V=128256, 4 sequences of 8 20.0 -> 15.2, V=256000, 4 of 4 20.9 -> 16.8; binary32 V=128256,
+// 4 of 8 20.6 -> 18.8; V=32000, 8 of 8 15.8 -> 12.0.
+constexpr int kSmallPairs = 64;
+// Draws: workgroups aimed at, at most, and rounds one of them may take.  (Half as many, with twice the rounds: 1 sequence of 8,
+// V=128256 8.5 -> 9.2 us; twice as many: 4 of 8 15.2 -> 16.1.)
+constexpr long kSmallDraws = 1024, kSmallRounds = 4;
+// Two slots a lane while that leaves a wavefront a SIMD or less of its own, else four: half the words to read for
+// twice the work of a step.  Whole calls with two and four (us): V=32000, bfloat16, 512 wavefronts 7.41 and 7.58, 1024 9.15 and
+// 8.49; binary32, 504 6.90 and 6.80, 1008 7.67 and 7.06, 2016 10.7 and 8.3; V=32001 504 7.57 and 8.09, 1008 8.92 and 8.62.
+constexpr long kSmallWaves = 640;
+
+template <bool BF16, int NV, int MODE, int LD>
+bool launch_small_k(hipStream_t st, const SmallParams& P, int B, bool captured) {
+    static Residency cache[16] = {};
+    const Residency res = residency_of(small_call<BF16, NV, MODE, LD>, kWG, cache);
+    if (P.team_wgs > res.total) return false;   // (the members of a team wait for each other; they come first in the grid)
+    g_last_grid = P.team_wgs;
+    if (captured) {
+        // a replay has the number of the call that was recorded: what the replay before it left would count as its own
+        const long n16 = (static_cast<long>(P.npairs) * P.G * (4 + P.np) + static_cast<long>(P.draw_wgs) * 2 + 1) / 2;
+        hipLaunchKernelGGL(zero_counters, dim3(static_cast<unsigned>((n16 + 255) / 256)), dim3(256), 0, st,
+                           reinterpret_cast<uint4*>(P.words), n16);
+    }
+    hipLaunchKernelGGL((small_call<BF16, NV, MODE, LD>), dim3(static_cast<unsigned>(P.team_wgs + P.draw_wgs + B)), dim3(kWG), 0, st, P);
+    return true;
+}
+template <bool BF16, int NV, int LD>
+bool launch_small_m(int div, hipStream_t st, const SmallParams& P, int B, bool captured) {
+    return div == FSD_DIV_JS ? launch_small_k<BF16, NV, MODE_JS, LD>(st, P, B, captured)
+         : div == FSD_DIV_TV ? launch_small_k<BF16, NV, MODE_TV, LD>(st, P, B, captured) : launch_small_k<BF16, NV, MODE_KLP, LD>(st, P, B, captured);
+}
+template <bool BF16, int LD>
+bool launch_small(int div, hipStream_t st, SmallParams& P, int B, bool captured) {
+    constexpr int VE = Slot<BF16>::VE;
+    const long all = static_cast<long>(B) * (P.rows + 1), round = 8 / VE * kWG;
+    long GS = kSmallDraws / all;
+    if (GS > (P.nslots + round - 1) / round) GS = (P.nslots + round - 1) / round;
+    if (GS > 64) GS = 64;
+    if (GS < 1 || P.nslots > GS * round * kSmallRounds) return false;
+    P.GS = static_cast<int>(GS);
+    P.sps = static_cast<int>((P.nslots + GS - 1) / GS);
+    P.draw_wgs = static_cast<int>(all * GS);
+    P.np = small_share_words(div == FSD_DIV_JS ? MODE_JS : MODE_TV);
+    const auto team = [&](int NV) {   // false: too many members, or words
+        P.G = static_cast<int>(team_size(P.nslots, NV));
+        P.team_wgs = (P.npairs * P.G + kWG / 64 - 1) / (kWG / 64);
+        return P.G <= kSmallTeam && static_cast<long>(P.npairs) * P.G * (4 + P.np) + all * GS * 2 <= kMaxArrive;
+    };
+    const auto idle = [&] { return static_cast<long>(P.npairs) * P.G <= kSmallWaves; };
+    if (P.npairs > kSmallPairs) return false;
+    if (team(2) && idle() && launch_small_m<BF16, 2, LD>(div, st, P, B, captured)) return true;
+    if (team(4) && launch_small_m<BF16, 4, LD>(div, st, P, B, captured)) return true;
+    return team(8) && launch_small_m<BF16, 8, LD>(div, st, P, B, captured);
 }
 
 // The workgroups that share a sequence wait for each other, so the whole grid has to be resident:
@@ -540,11 +600,50 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     const Ws ws = carve(workspace, p, B, rows, p.G, n1, n2, zero_bytes);
     if (zero_bytes > p.zero_bytes) return FSD_ERR_WORKSPACE;   // the exchange words would run into what follows them (no shape here does)
 
+    const bool warped = (temperature != 1.0f) || (top_k > 0 && top_k < V) || (top_p < 1.0f);
+    // Plain FSD on a few sequences is one launch, unless a test or the profiler has asked for the kernels of a large call.
+    if ((kind == KIND_CHAIN || kind == KIND_TREE) && !(warped && mode == FSD_SAMPLE) && rows <= 64 && load != LOAD_ELEM && !g_shape_nv && !g_prof_on &&
+        g_self_clear && !(k1mode == MODE_JSE && g_js_floor != kJsFloor)) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        const bool captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
+        if (captured) (void)hipGetLastError();
+        SmallParams P;
+        P.target = static_cast<const char*>(target);
+        P.draft = static_cast<const char*>(draft);
+        P.tokens = tokens;
+        P.parent = tree ? parent : nullptr;
+        P.rows = rows;
+        P.npairs = R;
+        P.max_depth = max_depth;
+        P.V = V;
+        P.nslots = p.nslots;
+        P.T = T;
+        P.mode = mode;
+        P.seed_lo = static_cast<unsigned>(seed);
+        P.seed_hi = static_cast<unsigned>(seed >> 32);
+        P.off_lo = static_cast<unsigned>(offset);
+        P.off_hi = static_cast<unsigned>(offset >> 32);
+        P.spin_limit = g_spin_limit;
+        P.out_len = out_len;
+        P.out_tokens = out_tokens;
+        P.path_nodes = path_nodes;
+        P.row_status = row_status;
+        P.user_div = user_vals;
+        P.words = ws.arrive;
+        P.nonce = ws.nonce;
+        const bool launched =
+            dtype == FSD_BF16 ? (load == LOAD_ALIGNED ? launch_small<true, LOAD_ALIGNED>(div, st, P, B, captured)
+                                                      : launch_small<true, LOAD_WIDE>(div, st, P, B, captured))
+                              : (load == LOAD_ALIGNED ? launch_small<false, LOAD_ALIGNED>(div, st, P, B, captured)
+                                                      : launch_small<false, LOAD_WIDE>(div, st, P, B, captured));
+        if (launched)
+            return (hipGetLastError() == hipSuccess) ? FSD_OK : FSD_ERR_LAUNCH;
+    }
+
     // The calls have no clearing kernel: the reduction clears what it and the kernels after it need (see
     // clear_own_words in pair_kernel.h; C2: -3 us a call, C4: -2 us), unless there are more than 4 MB to
     // clear (inside the reduction kernel that costs what the kernel of its own costs, C3: 7.5 MB) or
     // the grid is too large for the arrival slots.
-    const bool warped = (temperature != 1.0f) || (top_k > 0 && top_k < V) || (top_p < 1.0f);
     const bool self_clear = g_self_clear && zero_bytes <= (4u << 20) && max_resident_wavefronts() <= kMaxArrive;
     if (!self_clear) {
         const long n16 = static_cast<long>(zero_bytes / 16);

@@ -291,6 +291,43 @@ __device__ __noinline__ float js_pointwise_slice(const char* tptr, const char* d
     return wave_sumf(acc);
 }
 
+// ---- an entry's terms, p and q up to a common factor
+__device__ __forceinline__ void tv_terms(float p, float q, float& A, float& Bn, float& MA) {
+    const float d = p - q, sum = p + q;
+    A += fmaxf(d, 0.0f);
+    Bn += fmaxf(-d, 0.0f);
+    MA += (d > 0.0f) ? sum : 0.0f;   // the other side's mass is what is left of 2
+}
+template <int MODE>   // MODE_JS: twice the divergence in units of ln 2 (MODE_KLP: the same scale)
+__device__ __forceinline__ void pointwise_term(float p, float q, float& acc) {
+    [[maybe_unused]] constexpr float kTiny = 2e-38f;   // floor of u and v under the logarithm (their weights are then zero or negligible)
+    const float d = p - q, sum = p + q;
+    // (JS) p = q = 0: 0 * inf = NaN, which max() drops (u = kTiny, v = 2, both weights zero)
+    const float inv = __builtin_amdgcn_rcpf(sum);
+    float u = fmaxf(fmaf(d, inv, 1.0f), kTiny), v = fmaxf(2.0f - u, kTiny);
+    if constexpr (MODE == MODE_KLP) {
+        // u = 1 + r and v = 2 - u carry an absolute error of 2^-23: harmless for JS, where a
+        // small u or v comes with a small weight, but KL weighs ln(u/v) with the larger of the
+        // two.  Far from p = q the smaller one is taken from its own quotient instead (a
+        // relative error); near p = q the exact complement is what keeps the first-order
+        // terms cancelling.
+        const float inv2 = inv + inv;
+        if (u < 0.5f) u = fmaxf(p * inv2, kTiny);
+        if (v < 0.5f) v = fmaxf(q * inv2, kTiny);
+    }
+    if constexpr (MODE == MODE_JS) {
+        // p ln(2p/s) + q ln(2q/s) = ln2 (p log2 u + q log2 v); the rounding of u = 1 + r
+        // cancels between the two terms because p/u = q/v
+        acc = fmaf(p, hw_log2(u), acc);
+        acc = fmaf(q, hw_log2(v), acc);
+    } else {
+        // p ln(p/q) + q - p = (s/2) [u ln(u/v) + v - u] >= 0 entry by entry (the added q - p
+        // sums to zero).  Written in (u, v) only, the rounding of u cancels between the
+        // two parts; p ln(u/v) - (p - q) would keep it to first order.
+        acc = fmaf(sum, fmaf(u, hw_log2(u) - hw_log2(v), (v - u) * kLog2e), acc);
+    }
+}
+
 template <int I> struct SetId { static constexpr int value = I; };
 template <bool B> struct BoolTag { static constexpr bool value = B; };
 
@@ -934,11 +971,7 @@ void pair_kernel(PairParams P) {
                 get4(S, c, t4, d4);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float p = t4[i], q = d4[i] * cq;
-                    const float d = p - q, sum = p + q;
-                    A += fmaxf(d, 0.0f);
-                    Bn += fmaxf(-d, 0.0f);
-                    MA += (d > 0.0f) ? sum : 0.0f;   // the other side's mass is what is left of 2
+                    tv_terms(t4[i], d4[i] * cq, A, Bn, MA);
                 }
             }
             // max() drops NaN: an unusable row (NaN factor) is made to reach the side selection
@@ -962,31 +995,7 @@ void pair_kernel(PairParams P) {
                 // floor under p and q instead
                 const float p = (MODE == MODE_KLP) ? fmaf(t4[i], ft, kTiny) : t4[i];
                 const float q = (MODE == MODE_KLP) ? fmaf(d4[i], fd, kTiny) : d4[i] * cq;
-                const float d = p - q, sum = p + q;
-                // (JS) p = q = 0: 0 * inf = NaN, which max() drops (u = kTiny, v = 2, both weights zero)
-                const float inv = __builtin_amdgcn_rcpf(sum);
-                float u = fmaxf(fmaf(d, inv, 1.0f), kTiny), v = fmaxf(2.0f - u, kTiny);
-                if constexpr (MODE == MODE_KLP) {
-                    // u = 1 + r and v = 2 - u carry an absolute error of 2^-23: harmless for JS, where a
-                    // small u or v comes with a small weight, but KL weighs ln(u/v) with the larger of the
-                    // two.  Far from p = q the smaller one is taken from its own quotient instead (a
-                    // relative error); near p = q the exact complement is what keeps the first-order
-                    // terms cancelling.
-                    const float inv2 = inv + inv;
-                    if (u < 0.5f) u = fmaxf(p * inv2, kTiny);
-                    if (v < 0.5f) v = fmaxf(q * inv2, kTiny);
-                }
-                if constexpr (MODE == MODE_JS) {
-                    // p ln(2p/s) + q ln(2q/s) = ln2 (p log2 u + q log2 v); the rounding of u = 1 + r
-                    // cancels between the two terms because p/u = q/v
-                    acc = fmaf(p, hw_log2(u), acc);
-                    acc = fmaf(q, hw_log2(v), acc);
-                } else {
-                    // p ln(p/q) + q - p = (s/2) [u ln(u/v) + v - u] >= 0 entry by entry (the added q - p
-                    // sums to zero).  Written in (u, v) only, the rounding of u cancels between the
-                    // two parts; p ln(u/v) - (p - q) would keep it to first order.
-                    acc = fmaf(sum, fmaf(u, hw_log2(u) - hw_log2(v), (v - u) * kLog2e), acc);
-                }
+                pointwise_term<MODE>(p, q, acc);
               }
             }
             acc = wave_sumf(acc);

@@ -1,0 +1,388 @@
+// FSD on a few sequences in one launch.
+// Part of libfsd (gfx950); included by fsd_kernels.hip, which holds the host side and the C ABI.
+#ifndef FSD_CSRC_SMALL_CALL_H_
+#define FSD_CSRC_SMALL_CALL_H_
+
+#include "accept_sample.h"
+#include "device_common.h"
+#include "pair_kernel.h"
+
+namespace {
+
+// ------------------------------------------------------------------------------------------
+// a small call: reduction, draw and acceptance in one kernel
+//
+// What bounds a call of a few sequences is not work but a chain: a kernel's start, the logits from memory, and a round
+// trip through the memory's side (1-1.5 us) wherever wavefronts meet.  In the two kernels of a large call it has six
+// such trips: the members' arrival, their sums, the divergence's shares, the rows' results from one kernel to the next, the sampled row, the
+// draw's shares.  Here it has two, the sums and the divergence's shares:
+//   - Every word says by itself whether it is this call's: half of it is half of the call's number.  So nothing is
+//     cleared and nobody's arrival is waited for.  (A replay of a captured call has the number of the call before: the
+//     host records a kernel before this one that clears the words.)
+//   - The draw needs the target row and the random numbers, which are the same for every row, but not the
+//     divergences.  While the teams work, workgroups that wait for nobody draw from all target rows; acceptance
+//     then only picks one.  (The chip is mostly idle in such a call.)
+//   - One workgroup a sequence, the last of the grid, reads the draws' and the members' words itself.
+// The teams' wavefronts hold NV slots of each row a lane, for one pair each: there is no second step and nothing to
+// overlap.  All divergences are evaluated pointwise, for bfloat16 too: half as much a lane as in the large shape.
+// NV is the least that leaves a team at most 64 members (one word of each a lane).
+struct SmallParams {
+    const char* target;
+    const char* draft;
+    const int32_t* tokens;
+    const int32_t* parent;  // tree only
+    int rows;               // K or N
+    int npairs;             // B * rows
+    int max_depth;          // tree only
+    long V;
+    long nslots;
+    int G;                  // wavefronts per pair
+    int np;                 // words of a member's share of the divergence
+    int team_wgs;           // the grid: the teams' workgroups, the draws' (GS for every target row), one per sequence
+    int draw_wgs;
+    int GS;
+    int sps;                // slots per draw
+    float T;
+    int mode;
+    unsigned seed_lo, seed_hi, off_lo, off_hi;
+    unsigned spin_limit;
+    int32_t* out_len;
+    int32_t* out_tokens;
+    int32_t* path_nodes;    // tree only
+    int32_t* row_status;    // optional
+    float* user_div;        // optional
+    unsigned long long* words;   // sums [pair][member][4], shares of the divergence [pair][member][np], draws [b][row][GS][2]
+    unsigned long long nonce;
+};
+
+constexpr int kSmallTeam = 64;
+// words of a divergence's share: JS a sum and a status; TV three sums, KL two and a mark, and a status
+constexpr int small_share_words(int mode) { return mode == MODE_JS ? 2 : 4; }
+
+__device__ __forceinline__ unsigned long long tagged(unsigned payload, unsigned long long nonce, int i) {
+    return ((i & 1) ? (nonce << 32) : (nonce & 0xFFFFFFFF00000000ull)) | payload;
+}
+__device__ __forceinline__ bool is_tagged(unsigned long long w, unsigned long long nonce, int i) {
+    return static_cast<unsigned>(w >> 32) == static_cast<unsigned>((i & 1) ? nonce : nonce >> 32);
+}
+// lane l reads the N words of entry l, entries `stride` words apart (lanes past the last one repeat it): false if a
+// word has not come within `limit` looks
+template <int N, int R>
+__device__ __forceinline__ bool await_tagged(const unsigned long long* (&at)[R], unsigned long long nonce, unsigned limit,
+                                             unsigned long long (&w)[R][N]) {
+    for (unsigned polls = 0;; ++polls) {
+        bool missing = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) w[r][i] = read64(at[r] + i);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) missing |= !is_tagged(w[r][i], nonce, i);
+        }
+        if (!__any(missing)) return true;
+        if (polls >= limit) return false;
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+
+template <bool BF16, int NV, int MODE, int LD>
+__device__ __forceinline__ void small_team(const SmallParams& P, int gwave) {
+    constexpr int VE = Slot<BF16>::VE, ES = BF16 ? 2 : 4, NE = NV * VE, NP = small_share_words(MODE);
+    constexpr float kTiny = 2e-38f;
+    const int lane = threadIdx.x & 63;
+    const int pair = gwave / P.G, member = gwave - pair * P.G;
+    if (pair >= P.npairs) return;
+    const int b = pair / P.rows, j = pair - b * P.rows;
+    int ctx = j;
+    if (P.parent) {
+        const int par = P.parent[pair];
+        ctx = (par >= -1 && par < j) ? par + 1 : 0;   // (small_finish reports an invalid one)
+    }
+    const char* const trow = P.target + (static_cast<size_t>(b) * (P.rows + 1) + ctx) * static_cast<size_t>(P.V) * ES;
+    const char* const drow = P.draft + static_cast<size_t>(pair) * static_cast<size_t>(P.V) * ES;
+    unsigned long long* const sums = P.words + static_cast<size_t>(pair) * P.G * 4;
+    unsigned long long* const shares = P.words + static_cast<size_t>(P.npairs) * P.G * 4 + static_cast<size_t>(pair) * P.G * NP;
+
+    const long s0 = static_cast<long>(member) * (64 * NV) + lane;
+    uint4 ra[NV], rb[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const long s = s0 + 64 * k, at = s < P.nslots ? s : P.nslots - 1;
+        ra[k] = load_slot<BF16, LD>(trow, at, P.V);
+        rb[k] = load_slot<BF16, LD, true>(drow, at, P.V);
+    }
+    // ---- maximum, then sums of 2^(z log2e - k) with k = ceil(max log2e)
+    float mt = neg_inf(), md = neg_inf();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const long s = s0 + 64 * k, at = s < P.nslots ? s : P.nslots - 1;
+        settle_slot<BF16, LD>(ra[k], at, P.V);
+        settle_slot<BF16, LD>(rb[k], at, P.V);
+        if (s >= P.nslots) { ra[k] = slot_neg_inf<BF16>(); rb[k] = slot_neg_inf<BF16>(); }
+        float a[VE], c[VE];
+        unpack<BF16>(ra[k], a);
+        unpack<BF16>(rb[k], c);
+#pragma unroll
+        for (int e = 0; e < VE; e += 2) {
+            mt = fmaxf(fmaxf(mt, a[e]), a[e + 1]);
+            md = fmaxf(fmaxf(md, c[e]), c[e + 1]);
+        }
+    }
+    wave_max2(mt, md);
+    const float kt = (mt == neg_inf()) ? 0.0f : ceilf(mt * kLog2e), kd = (md == neg_inf()) ? 0.0f : ceilf(md * kLog2e);
+    float et[NE], ed[NE], st = 0.0f, sd = 0.0f, wsum = 0.0f, dmax = neg_inf();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        float a[VE], c[VE];
+        unpack<BF16>(ra[k], a);
+        unpack<BF16>(rb[k], c);
+#pragma unroll
+        for (int e = 0; e < VE; ++e) {
+            const float xa = hw_exp2(fmaf(a[e], kLog2e, -kt)), xb = hw_exp2(fmaf(c[e], kLog2e, -kd));
+            et[k * VE + e] = xa;
+            ed[k * VE + e] = xb;
+            st += xa;
+            sd += xb;
+            if constexpr (MODE == MODE_KLP) {   // sum p (a - b) beside the pointwise terms (see pair_kernel)
+                const float diff = a[e] - c[e];
+                dmax = fmaxf(dmax, diff);       // +inf iff the draft masks an entry the target does not
+                wsum = fmaf(xa, __builtin_amdgcn_fmed3f(diff, -FLT_MAX, FLT_MAX), wsum);
+            }
+        }
+    }
+    wave_sumf2(st, sd);
+    if (lane < 4) {
+        const float mine = lane == 0 ? kt : lane == 1 ? kd : lane == 2 ? st : sd;
+        post64(sums + member * 4 + lane, tagged(__float_as_uint(mine), P.nonce, lane));
+    }
+    if constexpr (MODE == MODE_KLP) { wsum = wave_sumf(wsum); dmax = wave_max(dmax); }
+
+    // ---- the rows' normalisers relative to this wavefront's own references
+    const unsigned long long* at[1] = {sums + (lane < P.G ? lane : P.G - 1) * 4};
+    unsigned long long w[1][4];
+    const bool ok = await_tagged<4, 1>(at, P.nonce, P.spin_limit, w);
+    TeamNorm n{kt, kd, 0.0f, 0.0f, ok};
+    const unsigned long long packed[2] = {(w[0][1] << 32) | static_cast<unsigned>(w[0][0]), (w[0][3] << 32) | static_cast<unsigned>(w[0][2])};
+    merge_round(packed, lane < P.G, n);
+    const float rzt = __builtin_amdgcn_rcpf(n.zt), rzd = __builtin_amdgcn_rcpf(n.zd);
+    const float ft = ((st > 0.0f) || (st != st)) ? rzt : rzt * 0.0f, fd = ((sd > 0.0f) || (sd != sd)) ? rzd : rzd * 0.0f;
+
+    // ---- the divergence's terms (as in pair_kernel's phase 2)
+    const float ftc = fmaxf(ft, 0x1p-80f), fdc = fmaxf(fd, 0x1p-80f);   // max() drops NaN: see below
+    const float cq = (ftc == fdc) ? 1.0f : fdc * __builtin_amdgcn_rcpf(ftc);
+    const bool unusable = ft != ft || fd != fd;
+    float part[3] = {0.0f, 0.0f, 0.0f};
+    if constexpr (MODE == MODE_TV) {
+#pragma unroll
+        for (int i = 0; i < NE; ++i) tv_terms(et[i], ed[i] * cq, part[0], part[1], part[2]);
+        wave_sumf2(part[0], part[1]);
+        part[2] = wave_sumf(part[2]);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) part[i] = unusable ? ft + fd : part[i] * ftc;
+    } else {
+        float acc = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const float p = (MODE == MODE_KLP) ? fmaf(et[i], ft, kTiny) : et[i];
+            const float q = (MODE == MODE_KLP) ? fmaf(ed[i], fd, kTiny) : ed[i] * cq;
+            pointwise_term<MODE>(p, q, acc);
+        }
+        acc = wave_sumf(acc);
+        if constexpr (MODE != MODE_KLP) acc *= ftc;
+        if (unusable) acc = ft + fd;
+        if constexpr (MODE == MODE_KLP) {
+            if (dmax == __builtin_inff()) acc += __builtin_inff();   // NaN stays NaN
+            const float dl = ((kt - hw_log2(ft)) - (kd - hw_log2(fd))) * static_cast<float>(kLn2);
+            const bool sat = (ft > 0.0f) && dmax > neg_inf() && (fd == 0.0f || dmax - dl > 80.0f);
+            part[1] = wsum * ft;
+            part[2] = sat ? 1.0f : 0.0f;
+        }
+        part[0] = acc;
+    }
+    if (lane < NP) {
+        const float val = (lane == 0 || NP == 2) ? part[0] : lane == 1 ? part[1] : part[2];
+        const unsigned mine = lane == NP - 1 ? (ok ? 0u : static_cast<unsigned>(FSD_ROW_INTERNAL)) : __float_as_uint(val);
+        post64(shares + member * NP + lane, tagged(mine, P.nonce, lane));
+    }
+}
+
+struct SmallShared {
+    unsigned thr;
+    Best best[4];
+    int bad[4];
+    float div[64];
+    int status[64];
+    Best drawn[65];
+    int drawn_status[65];
+};
+
+// the best score of a share of one target row, whichever row the token will come from
+template <bool BF16, int LD>
+__device__ __forceinline__ void small_draw(const SmallParams& P, int row_of_all, int g, SmallShared& s) {
+    constexpr int ES = BF16 ? 2 : 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = row_of_all / (P.rows + 1);
+    if (tid == 0) s.thr = score_key(-FLT_MAX);
+    __syncthreads();
+    const char* const trow = P.target + static_cast<size_t>(row_of_all) * static_cast<size_t>(P.V) * ES;
+    const long s0 = static_cast<long>(g) * P.sps, s1 = (s0 + P.sps < P.nslots) ? s0 + P.sps : P.nslots;
+    const DrawArgs A{P.V, P.mode, P.seed_lo, P.seed_hi, P.off_lo, P.off_hi, false, neg_inf(), 1.0f};
+    const DrawChain C{nullptr, 0, 0, nullptr};
+    Best best{neg_inf(), 0x7FFFFFFF};
+    int bad = 0;
+    draw_share<BF16, LD, false, 8>(A, b, trow, false, nullptr, 0.0f, 0.0f, C, s0, s1, tid, &s.thr, best, bad);
+    best = wave_best(best);
+    bad = __any(bad);
+    if (lane == 0) { s.best[wave] = best; s.bad[wave] = bad; }
+    __syncthreads();
+    if (tid < 2) {
+        Best m = s.best[0];
+        int bd = s.bad[0];
+#pragma unroll
+        for (int k = 1; k < 4; ++k) { m = better(m, s.best[k]); bd |= s.bad[k]; }
+        const unsigned long long share = share_word(m, bd);
+        unsigned long long* const at = P.words + static_cast<size_t>(P.npairs) * P.G * (4 + P.np) +
+                                       (static_cast<size_t>(row_of_all) * P.GS + g) * 2;
+        post64(at + tid, tagged(tid ? static_cast<unsigned>(share) : static_cast<unsigned>(share >> 32), P.nonce, tid));
+    }
+}
+
+// a sequence's divergences, its accepted prefix and its token
+template <int MODE>
+__device__ __forceinline__ void small_finish(const SmallParams& P, int b, SmallShared& s) {
+    constexpr int NP = small_share_words(MODE);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rows = P.rows;
+    const size_t mine_at = static_cast<size_t>(b) * rows + (lane < rows ? lane : rows - 1);
+    const int token_in = P.tokens[mine_at];
+    int my_par = P.parent ? P.parent[mine_at] : -1;
+    // the draws first: they are there long before the divergences
+    const unsigned long long* const draws = P.words + static_cast<size_t>(P.npairs) * P.G * (4 + NP);
+    for (int r = wave; r <= rows; r += 4) {
+        const unsigned long long* at[1] = {draws + ((static_cast<size_t>(b) * (rows + 1) + r) * P.GS + (lane < P.GS ? lane : P.GS - 1)) * 2};
+        unsigned long long w[1][2];
+        const bool there = await_tagged<2, 1>(at, P.nonce, kShareLooks, w);
+        const unsigned long long share = (w[0][0] << 32) | static_cast<unsigned>(w[0][1]);
+        const Best m = wave_best(share_best(share));
+        const int st = !there ? FSD_ROW_INTERNAL : (__any((share & 0x80000000u) != 0) || m.idx == 0x7FFFFFFF) ? FSD_ROW_NONFINITE : 0;
+        if (lane == 0) { s.drawn[r] = m; s.drawn_status[r] = st; }
+    }
+    // four rows a wavefront at a time
+    const unsigned long long* const sums = P.words;
+    const unsigned long long* const shares = P.words + static_cast<size_t>(P.npairs) * P.G * 4;
+    const bool in = lane < P.G;
+    for (int base = wave; base < rows; base += 16) {
+        const unsigned long long* at[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int r = base + 4 * k < rows ? base + 4 * k : base;
+            at[k] = shares + ((static_cast<size_t>(b) * rows + r) * P.G + (in ? lane : P.G - 1)) * NP;
+        }
+        unsigned long long w[4][NP];
+        const bool there = await_tagged<NP, 4>(at, P.nonce, P.spin_limit, w);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int r = base + 4 * k;
+            if (r >= rows) break;
+            const int pair = b * rows + r;
+            int status = (!there || __any(static_cast<unsigned>(w[k][NP - 1]) != 0)) ? FSD_ROW_INTERNAL : 0;
+            const double first = wave_sum(in ? static_cast<double>(lo_f(w[k][0])) : 0.0);
+            double value;
+            if constexpr (MODE == MODE_TV) {   // the lighter side (see pair_kernel)
+                const double other = wave_sum(in ? static_cast<double>(lo_f(w[k][1])) : 0.0);
+                const double mass = wave_sum(in ? static_cast<double>(lo_f(w[k][2])) : 0.0);
+                value = (mass != mass) ? __builtin_nan("") : (mass <= 1.0 ? first : other);
+            } else {
+                value = 0.5 * kLn2 * first;
+            }
+            if (value != value) status |= FSD_ROW_NONFINITE;   // NaN / +inf logits, or a row without mass
+            if (value < 0.0) value = 0.0;
+            if (status) value = __builtin_nan("");
+            if constexpr (MODE == MODE_KLP) {
+                // terms that leave binary32's range: the log-domain value where it is larger by more than its rounding
+                if (!status && value < __builtin_inf() && __any(in && lo_f(w[k][2]) > 0.0f)) {
+                    const double logs = wave_sum(in ? static_cast<double>(lo_f(w[k][1])) : 0.0);
+                    const unsigned long long* p1[1] = {sums + (static_cast<size_t>(pair) * P.G + (in ? lane : P.G - 1)) * 4};
+                    unsigned long long u[1][4];
+                    if (!await_tagged<4, 1>(p1, P.nonce, P.spin_limit, u)) status |= FSD_ROW_INTERNAL;
+                    const float kt = lo_f(u[0][0]), kd = lo_f(u[0][1]);
+                    const double St = in ? static_cast<double>(lo_f(u[0][2])) : 0.0, Sd = in ? static_cast<double>(lo_f(u[0][3])) : 0.0;
+                    const float Kt = wave_max((St > 0.0) ? kt : neg_inf()), Kd = wave_max((Sd > 0.0) ? kd : neg_inf());
+                    const double Zt = wave_sum((St > 0.0) ? ldexp(St, kdiff(kt, Kt)) : 0.0), Zd = wave_sum((Sd > 0.0) ? ldexp(Sd, kdiff(kd, Kd)) : 0.0);
+                    const double dl = ((static_cast<double>(Kt) + log2(Zt)) - (static_cast<double>(Kd) + log2(Zd))) * kLn2;
+                    const double v = logs - dl;
+                    if (v == v && v - value > 4e-7 * (fabs(logs) + fabs(dl))) value = v;
+                    if (status) value = __builtin_nan("");
+                }
+            }
+            if (lane == 0) {
+                s.div[r] = static_cast<float>(value);
+                s.status[r] = status;
+                if (P.user_div) P.user_div[pair] = static_cast<float>(value);
+            }
+        }
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    const bool mine = lane < rows;
+    const float div = mine ? s.div[lane] : 0.0f;
+    int status = mine ? s.status[lane] : 0;
+    if (__any(status != 0)) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) status |= __shfl_xor(status, o);
+    }
+    const bool accepted = div <= P.T;   // Sec. 4 eq. 4 (NaN compares false)
+    int n, row, winner = -1, my_dep = 0;
+    if (P.parent) {
+        const TreePick pick = pick_path(lane, rows, P.max_depth, my_par, accepted);
+        status |= pick.status;
+        if (status & FSD_ROW_BAD_PARENT) status &= ~FSD_ROW_TOO_DEEP;   // depths mean nothing in a malformed tree
+        n = pick.n;
+        winner = pick.winner;
+        my_dep = pick.my_dep;
+        row = winner + 1;
+    } else {
+        const unsigned long long no = __ballot(mine && !accepted);
+        n = no ? static_cast<int>(__builtin_ctzll(no)) : rows;
+        row = n;
+    }
+    const int token = s.drawn[row].idx;
+    if (!status) status = s.drawn_status[row];
+    if (status) n = 0;
+    if (P.parent) {
+        write_path(lane, P.max_depth, status ? -1 : winner, n, my_par, my_dep, token_in, status ? -1 : token,
+                   P.path_nodes + static_cast<size_t>(b) * P.max_depth, P.out_tokens + static_cast<size_t>(b) * (P.max_depth + 1));
+    } else {
+        int32_t* const out = P.out_tokens + static_cast<size_t>(b) * (rows + 1);
+        for (int i = lane; i <= rows; i += 64) {
+            int v = -1;
+            if (!status) v = i < n ? token_in : i == n ? token : -1;
+            out[i] = v;
+        }
+    }
+    if (lane == 0) {
+        P.out_len[b] = n;
+        if (P.row_status) P.row_status[b] = status;
+    }
+}
+
+template <bool BF16, int NV, int MODE, int LD>
+__global__ __launch_bounds__(kWG) void small_call(SmallParams P) {
+    __shared__ SmallShared s;
+    const int wg = static_cast<int>(blockIdx.x);
+    if (wg < P.team_wgs) {
+        small_team<BF16, NV, MODE, LD>(P, wg * (kWG / 64) + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
+    } else if (wg < P.team_wgs + P.draw_wgs) {
+        const int d = wg - P.team_wgs, row = d / P.GS;
+        small_draw<BF16, LD>(P, row, d - row * P.GS, s);
+    } else {
+        small_finish<MODE>(P, wg - P.team_wgs - P.draw_wgs, s);
+    }
+}
+
+}  // namespace
+
+#endif  // FSD_CSRC_SMALL_CALL_H_
