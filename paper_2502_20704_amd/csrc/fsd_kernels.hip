@@ -348,14 +348,21 @@ void launch_sample(int dtype, int load, int kind, dim3 grid, size_t lds, hipStre
     }
 }
 
-// ---- a plain FSD call on a few sequences in one launch (small_call.h): false (nothing launched) if it is not small.
-// Small is what its words have room for beside one draw from every target row: whole calls under JS that just are
-// (two kernels -> one, us): bfloat16 V=128256, 4 sequences of 8 20.0 -> 15.2, V=256000, 4 of 4 20.9 -> 16.8; binary32 V=128256,
-// 4 of 8 20.6 -> 18.8; V=32000, 8 of 8 15.8 -> 12.0.
-constexpr int kSmallPairs = 64;
-// Draws: workgroups aimed at, at most, and rounds one of them may take.  (Half as many, with twice the rounds: 1 sequence of 8,
-// V=128256 8.5 -> 9.2 us; twice as many: 4 of 8 15.2 -> 16.1.)
-constexpr long kSmallDraws = 1024, kSmallRounds = 4;
+// ---- small calls (small_call.h): every pair's wavefronts at once, one step each
+// Pairs times vocabulary up to which one step of the whole device beats the persistent teams, which load a
+// pair behind the other.  Whole calls, persistent and one step (us): JS, bfloat16 V=64000, 64 pairs 18.0 and 15.0, 96 18.4 and
+// 17.1, V=128256, 64 pairs 21.3 and 22.3, 80 24.4 and 26.3; binary32 V=64000, 64 pairs 18.4 and 16.9, 96 22.2 and 21.9, V=128256,
+// 64 25.6 and 28.2.  TV, bfloat16 V=64000, 64 pairs 16.4 and 15.1, 96 16.7 and 17.2; binary32 V=64000, 80 21.3 and 21.0, 96
+// 21.8 and 22.4.  KL, binary32 V=64000, 96 pairs 26.1 and 23.0; bfloat16 KL has a single pass in large calls, V=32000, 32 pairs 11.8
+// and 9.5, 64 11.9 and 12.4.
+constexpr long small_entries(int dtype, int div) {
+    return div == FSD_DIV_TV ? 9L << 19 : (div == FSD_DIV_KL && dtype == FSD_BF16) ? 9L << 17 : 6L << 20;
+}
+// Draws of all target rows in the same launch: entries of those rows, at most (the draw of one row a sequence behind the
+// reduction, and of all beside it, us: binary32 V=128256, 36 rows 17.1 and 19.2, V=64000, 72 16.9 and 17.7, V=32000, 112
+// 16.0 and 14.8; bfloat16 V=128256, 36 15.8 and 16.2, V=32000, 72 12.6 and 11.1), workgroups aimed at, at most, and rounds one
+// of them may take (half the workgroups, with twice the rounds: 1 sequence of 8, V=128256 8.5 -> 9.2; twice as many: 4 of 8 15.2 -> 16.1).
+constexpr long kSmallDrawn = 4L << 20, kSmallDraws = 1024, kSmallRounds = 4;
 // Two slots a lane while that leaves a wavefront a SIMD or less of its own, else four: half the words to read for
 // twice the work of a step.  Whole calls with two and four (us): V=32000, bfloat16, 512 wavefronts 7.41 and 7.58, 1024 9.15 and
 // 8.49; binary32, 504 6.90 and 6.80, 1008 7.67 and 7.06, 2016 10.7 and 8.3; V=32001 504 7.57 and 8.09, 1008 8.92 and 8.62.
@@ -367,13 +374,14 @@ bool launch_small_k(hipStream_t st, const SmallParams& P, int B, bool captured) 
     const Residency res = residency_of(small_call<BF16, NV, MODE, LD>, kWG, cache);
     if (P.team_wgs > res.total) return false;   // (the members of a team wait for each other; they come first in the grid)
     g_last_grid = P.team_wgs;
+    const int finish = P.draw_wgs ? B : (P.npairs + kSmallFinish - 1) / kSmallFinish;
     if (captured) {
         // a replay has the number of the call that was recorded: what the replay before it left would count as its own
         const long n16 = (static_cast<long>(P.npairs) * P.G * (4 + P.np) + static_cast<long>(P.draw_wgs) * 2 + 1) / 2;
         hipLaunchKernelGGL(zero_counters, dim3(static_cast<unsigned>((n16 + 255) / 256)), dim3(256), 0, st,
                            reinterpret_cast<uint4*>(P.words), n16);
     }
-    hipLaunchKernelGGL((small_call<BF16, NV, MODE, LD>), dim3(static_cast<unsigned>(P.team_wgs + P.draw_wgs + B)), dim3(kWG), 0, st, P);
+    hipLaunchKernelGGL((small_call<BF16, NV, MODE, LD>), dim3(static_cast<unsigned>(P.team_wgs + P.draw_wgs + finish)), dim3(kWG), 0, st, P);
     return true;
 }
 template <bool BF16, int NV, int LD>
@@ -381,28 +389,34 @@ bool launch_small_m(int div, hipStream_t st, const SmallParams& P, int B, bool c
     return div == FSD_DIV_JS ? launch_small_k<BF16, NV, MODE_JS, LD>(st, P, B, captured)
          : div == FSD_DIV_TV ? launch_small_k<BF16, NV, MODE_TV, LD>(st, P, B, captured) : launch_small_k<BF16, NV, MODE_KLP, LD>(st, P, B, captured);
 }
+enum { SMALL_NONE = 0, SMALL_REDUCED = 1, SMALL_DONE = 2 };   // launched: nothing, the reduction alone, the whole call
 template <bool BF16, int LD>
-bool launch_small(int div, hipStream_t st, SmallParams& P, int B, bool captured) {
+int launch_small(int div, hipStream_t st, SmallParams& P, int B, int plan_G, bool whole, bool captured) {
     constexpr int VE = Slot<BF16>::VE;
+    P.np = small_share_words(div == FSD_DIV_JS ? MODE_JS : MODE_TV);
     const long all = static_cast<long>(B) * (P.rows + 1), round = 8 / VE * kWG;
-    long GS = kSmallDraws / all;
+    long GS = whole && P.rows <= 64 && all * P.V <= kSmallDrawn ? kSmallDraws / all : 0;
     if (GS > (P.nslots + round - 1) / round) GS = (P.nslots + round - 1) / round;
     if (GS > 64) GS = 64;
-    if (GS < 1 || P.nslots > GS * round * kSmallRounds) return false;
-    P.GS = static_cast<int>(GS);
-    P.sps = static_cast<int>((P.nslots + GS - 1) / GS);
-    P.draw_wgs = static_cast<int>(all * GS);
-    P.np = small_share_words(div == FSD_DIV_JS ? MODE_JS : MODE_TV);
-    const auto team = [&](int NV) {   // false: too many members, or words
+    if (P.nslots > GS * round * kSmallRounds) GS = 0;
+    const auto launch = [&](int NV) {
         P.G = static_cast<int>(team_size(P.nslots, NV));
+        const long words = static_cast<long>(P.npairs) * P.G * (4 + P.np);
         P.team_wgs = (P.npairs * P.G + kWG / 64 - 1) / (kWG / 64);
-        return P.G <= kSmallTeam && static_cast<long>(P.npairs) * P.G * (4 + P.np) + all * GS * 2 <= kMaxArrive;
+        if (P.G > kSmallTeam) return false;
+        // the words lie in the place of the arrival slots, or, more of them, in that of the exchange words
+        const bool few = words + all * GS * 2 <= kMaxArrive;
+        if (!few && P.G * (4 + P.np) > plan_G * 8) return false;
+        P.words = few ? P.ws.arrive : P.ws.part1;
+        P.GS = few ? static_cast<int>(GS) : 0;
+        P.draw_wgs = static_cast<int>(all) * P.GS;
+        P.sps = P.GS ? static_cast<int>((P.nslots + P.GS - 1) / P.GS) : 0;
+        return NV == 2 ? launch_small_m<BF16, 2, LD>(div, st, P, B, captured)
+             : NV == 4 ? launch_small_m<BF16, 4, LD>(div, st, P, B, captured) : launch_small_m<BF16, 8, LD>(div, st, P, B, captured);
     };
-    const auto idle = [&] { return static_cast<long>(P.npairs) * P.G <= kSmallWaves; };
-    if (P.npairs > kSmallPairs) return false;
-    if (team(2) && idle() && launch_small_m<BF16, 2, LD>(div, st, P, B, captured)) return true;
-    if (team(4) && launch_small_m<BF16, 4, LD>(div, st, P, B, captured)) return true;
-    return team(8) && launch_small_m<BF16, 8, LD>(div, st, P, B, captured);
+    const bool two = P.npairs * team_size(P.nslots, 2) <= kSmallWaves;
+    if ((two && launch(2)) || launch(4) || launch(8)) return P.draw_wgs ? SMALL_DONE : SMALL_REDUCED;
+    return SMALL_NONE;
 }
 
 // The workgroups that share a sequence wait for each other, so the whole grid has to be resident:
@@ -601,9 +615,12 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     if (zero_bytes > p.zero_bytes) return FSD_ERR_WORKSPACE;   // the exchange words would run into what follows them (no shape here does)
 
     const bool warped = (temperature != 1.0f) || (top_k > 0 && top_k < V) || (top_p < 1.0f);
-    // Plain FSD on a few sequences is one launch, unless a test or the profiler has asked for the kernels of a large call.
-    if ((kind == KIND_CHAIN || kind == KIND_TREE) && !(warped && mode == FSD_SAMPLE) && rows <= 64 && load != LOAD_ELEM && !g_shape_nv && !g_prof_on &&
-        g_self_clear && !(k1mode == MODE_JSE && g_js_floor != kJsFloor)) {
+    // Small calls: the reduction in one step, or the whole of a plain FSD call on a few sequences in one launch, unless a test or the
+    // profiler has asked for the kernels of a large call.  (Reducible FSD under bfloat16 KL takes its normalisers from
+    // the single-pass kernel, whose sums are kept in float64.)
+    bool reduced = false;
+    if ((kind == KIND_CHAIN || kind == KIND_TREE || kind == KIND_RFSD) && load != LOAD_ELEM && !g_shape_nv && !g_prof_on && g_self_clear &&
+        static_cast<long>(R) * V <= small_entries(dtype, div) && !(kind == KIND_RFSD && k1mode == MODE_KL) && !(k1mode == MODE_JSE && g_js_floor != kJsFloor)) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         const bool captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
         if (captured) (void)hipGetLastError();
@@ -629,15 +646,22 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         P.path_nodes = path_nodes;
         P.row_status = row_status;
         P.user_div = user_vals;
-        P.words = ws.arrive;
         P.nonce = ws.nonce;
-        const bool launched =
-            dtype == FSD_BF16 ? (load == LOAD_ALIGNED ? launch_small<true, LOAD_ALIGNED>(div, st, P, B, captured)
-                                                      : launch_small<true, LOAD_WIDE>(div, st, P, B, captured))
-                              : (load == LOAD_ALIGNED ? launch_small<false, LOAD_ALIGNED>(div, st, P, B, captured)
-                                                      : launch_small<false, LOAD_WIDE>(div, st, P, B, captured));
-        if (launched)
-            return (hipGetLastError() == hipSuccess) ? FSD_OK : FSD_ERR_LAUNCH;
+        P.ws = ws;
+        P.user_ratio = user_ratio;
+        P.want_ratio = (kind == KIND_RFSD) ? 1 : 0;
+        P.clear_a = reinterpret_cast<uint4*>(ws.counters + 4);
+        P.clear_a16 = static_cast<long>((p.n_counters - 4) * 4 / 16);
+        P.clear_b = reinterpret_cast<uint4*>(ws.spart);
+        P.clear_b16 = static_cast<long>((p.off_part1 - p.off_spart) / 16);
+        const bool whole = kind != KIND_RFSD && !(warped && mode == FSD_SAMPLE);
+        const int launched =
+            dtype == FSD_BF16 ? (load == LOAD_ALIGNED ? launch_small<true, LOAD_ALIGNED>(div, st, P, B, plan_G, whole, captured)
+                                                      : launch_small<true, LOAD_WIDE>(div, st, P, B, plan_G, whole, captured))
+                              : (load == LOAD_ALIGNED ? launch_small<false, LOAD_ALIGNED>(div, st, P, B, plan_G, whole, captured)
+                                                      : launch_small<false, LOAD_WIDE>(div, st, P, B, plan_G, whole, captured));
+        if (launched == SMALL_DONE) return (hipGetLastError() == hipSuccess) ? FSD_OK : FSD_ERR_LAUNCH;
+        reduced = launched == SMALL_REDUCED;
     }
 
     // The calls have no clearing kernel: the reduction clears what it and the kernels after it need (see
@@ -645,7 +669,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     // clear (inside the reduction kernel that costs what the kernel of its own costs, C3: 7.5 MB) or
     // the grid is too large for the arrival slots.
     const bool self_clear = g_self_clear && zero_bytes <= (4u << 20) && max_resident_wavefronts() <= kMaxArrive;
-    if (!self_clear) {
+    if (!self_clear && !reduced) {
         const long n16 = static_cast<long>(zero_bytes / 16);
         hipLaunchKernelGGL(zero_counters, dim3(static_cast<unsigned>((n16 + 255) / 256)), dim3(256), 0, st,
                            reinterpret_cast<uint4*>(ws.counters), n16);
@@ -679,7 +703,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     pp.want_ratio = (kind == KIND_RFSD) ? 1 : 0;
     pp.js_floor = g_js_floor;
     pp.ws = ws;
-    launch_pair(dtype, p.NV, k1mode, load, st, pp);
+    if (!reduced) launch_pair(dtype, p.NV, k1mode, load, st, pp);
 
     SampleParams sp;
     sp.target = static_cast<const char*>(target);
@@ -706,7 +730,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     sp.spin_limit = g_spin_limit;
     sp.thr = nullptr;
     sp.inv_temp = 1.0f;
-    sp.clear_arrive = self_clear ? 1 : 0;
+    sp.clear_arrive = (self_clear && !reduced) ? 1 : 0;
     if (warped && mode == FSD_SAMPLE) {
         // warpers: one more kernel finds, per sequence, the smallest kept scaled logit
         WarpParams wp;

@@ -22,7 +22,9 @@ namespace {
 //   - The draw needs the target row and the random numbers, which are the same for every row, but not the
 //     divergences.  While the teams work, workgroups that wait for nobody draw from all target rows; acceptance
 //     then only picks one.  (The chip is mostly idle in such a call.)
-//   - One workgroup a sequence, the last of the grid, reads the draws' and the members' words itself.
+//   - One workgroup a sequence (16 pairs, if there are no draws), the last of the grid, reads the draws' and the members' words itself.
+// Where the draws of all rows would be too much, or need what this kernel does not have (reducible FSD, the warpers), it leaves
+// the results to the kernels that follow, as pair_kernel does.
 // The teams' wavefronts hold NV slots of each row a lane, for one pair each: there is no second step and nothing to
 // overlap.  All divergences are evaluated pointwise, for bfloat16 too: half as much a lane as in the large shape.
 // NV is the least that leaves a team at most 64 members (one word of each a lane).
@@ -39,7 +41,7 @@ struct SmallParams {
     int G;                  // wavefronts per pair
     int np;                 // words of a member's share of the divergence
     int team_wgs;           // the grid: the teams' workgroups, the draws' (GS for every target row), one per sequence
-    int draw_wgs;
+    int draw_wgs;           // 0: the draw follows in kernels of its own, the results go to the workspace (ws)
     int GS;
     int sps;                // slots per draw
     float T;
@@ -53,9 +55,18 @@ struct SmallParams {
     float* user_div;        // optional
     unsigned long long* words;   // sums [pair][member][4], shares of the divergence [pair][member][np], draws [b][row][GS][2]
     unsigned long long nonce;
+    // without draws: where the results go, what the kernels that follow need cleared (16-byte units)
+    Ws ws;
+    float* user_ratio;      // optional, reducible FSD only
+    int want_ratio;         // reducible FSD: ln p(x) - ln q(x) at the candidate token as well
+    uint4* clear_a;
+    long clear_a16;
+    uint4* clear_b;
+    long clear_b16;
 };
 
 constexpr int kSmallTeam = 64;
+constexpr int kSmallFinish = 16;   // pairs of a finishing workgroup where the reduction alone is asked for: four a wavefront
 // words of a divergence's share: JS a sum and a status; TV three sums, KL two and a mark, and a status
 constexpr int small_share_words(int mode) { return mode == MODE_JS ? 2 : 4; }
 
@@ -250,18 +261,27 @@ __device__ __forceinline__ void small_draw(const SmallParams& P, int row_of_all,
     }
 }
 
-// a sequence's divergences, its accepted prefix and its token
-template <int MODE>
-__device__ __forceinline__ void small_finish(const SmallParams& P, int b, SmallShared& s) {
+// a sequence's divergences, its accepted prefix or path and its token
+template <bool BF16, int MODE>
+__device__ __forceinline__ void small_finish(const SmallParams& P, int wg, SmallShared& s) {
     constexpr int NP = small_share_words(MODE);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = P.rows;
-    const size_t mine_at = static_cast<size_t>(b) * rows + (lane < rows ? lane : rows - 1);
+    // this workgroup's pairs: a sequence's, or, where only the reduction is asked for, a fixed number
+    const int b = wg;
+    const int pair0 = P.draw_wgs ? b * rows : wg * kSmallFinish, pair1 = P.draw_wgs ? pair0 + rows : min(pair0 + kSmallFinish, P.npairs);
+    const size_t mine_at = static_cast<size_t>(P.draw_wgs ? b : 0) * rows + (lane < rows ? lane : rows - 1);
     const int token_in = P.tokens[mine_at];
     int my_par = P.parent ? P.parent[mine_at] : -1;
+    if (P.draw_wgs == 0) {
+        const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+        const long step = static_cast<long>((P.npairs + kSmallFinish - 1) / kSmallFinish) * kWG;
+        for (long i = static_cast<long>(wg) * kWG + tid; i < P.clear_a16; i += step) P.clear_a[i] = zero;
+        for (long i = static_cast<long>(wg) * kWG + tid; i < P.clear_b16; i += step) P.clear_b[i] = zero;
+    }
     // the draws first: they are there long before the divergences
     const unsigned long long* const draws = P.words + static_cast<size_t>(P.npairs) * P.G * (4 + NP);
-    for (int r = wave; r <= rows; r += 4) {
+    for (int r = wave; r <= rows && P.draw_wgs; r += 4) {
         const unsigned long long* at[1] = {draws + ((static_cast<size_t>(b) * (rows + 1) + r) * P.GS + (lane < P.GS ? lane : P.GS - 1)) * 2};
         unsigned long long w[1][2];
         const bool there = await_tagged<2, 1>(at, P.nonce, kShareLooks, w);
@@ -270,24 +290,23 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int b, SmallS
         const int st = !there ? FSD_ROW_INTERNAL : (__any((share & 0x80000000u) != 0) || m.idx == 0x7FFFFFFF) ? FSD_ROW_NONFINITE : 0;
         if (lane == 0) { s.drawn[r] = m; s.drawn_status[r] = st; }
     }
-    // four rows a wavefront at a time
+    // four pairs a wavefront at a time
     const unsigned long long* const sums = P.words;
     const unsigned long long* const shares = P.words + static_cast<size_t>(P.npairs) * P.G * 4;
     const bool in = lane < P.G;
-    for (int base = wave; base < rows; base += 16) {
+    for (int base = pair0 + wave; base < pair1; base += 16) {
         const unsigned long long* at[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int r = base + 4 * k < rows ? base + 4 * k : base;
-            at[k] = shares + ((static_cast<size_t>(b) * rows + r) * P.G + (in ? lane : P.G - 1)) * NP;
+            const int pair = base + 4 * k < pair1 ? base + 4 * k : base;
+            at[k] = shares + (static_cast<size_t>(pair) * P.G + (in ? lane : P.G - 1)) * NP;
         }
         unsigned long long w[4][NP];
         const bool there = await_tagged<NP, 4>(at, P.nonce, P.spin_limit, w);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int r = base + 4 * k;
-            if (r >= rows) break;
-            const int pair = b * rows + r;
+            const int pair = base + 4 * k;
+            if (pair >= pair1) break;
             int status = (!there || __any(static_cast<unsigned>(w[k][NP - 1]) != 0)) ? FSD_ROW_INTERNAL : 0;
             const double first = wave_sum(in ? static_cast<double>(lo_f(w[k][0])) : 0.0);
             double value;
@@ -301,30 +320,58 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int b, SmallS
             if (value != value) status |= FSD_ROW_NONFINITE;   // NaN / +inf logits, or a row without mass
             if (value < 0.0) value = 0.0;
             if (status) value = __builtin_nan("");
-            if constexpr (MODE == MODE_KLP) {
-                // terms that leave binary32's range: the log-domain value where it is larger by more than its rounding
-                if (!status && value < __builtin_inf() && __any(in && lo_f(w[k][2]) > 0.0f)) {
+            bool log_domain = false;   // KL terms that leave binary32's range
+            if constexpr (MODE == MODE_KLP) log_domain = !status && value < __builtin_inf() && __any(in && lo_f(w[k][2]) > 0.0f);
+            double lse2_t = 0.0, lse2_d = 0.0;
+            if (P.want_ratio || log_domain) {
+                const unsigned long long* p1[1] = {sums + (static_cast<size_t>(pair) * P.G + (in ? lane : P.G - 1)) * 4};
+                unsigned long long u[1][4];
+                if (!await_tagged<4, 1>(p1, P.nonce, P.spin_limit, u)) status |= FSD_ROW_INTERNAL;
+                const float kt = lo_f(u[0][0]), kd = lo_f(u[0][1]);
+                const double St = in ? static_cast<double>(lo_f(u[0][2])) : 0.0, Sd = in ? static_cast<double>(lo_f(u[0][3])) : 0.0;
+                const float Kt = wave_max((St > 0.0) ? kt : neg_inf()), Kd = wave_max((Sd > 0.0) ? kd : neg_inf());
+                const double Zt = wave_sum((St > 0.0) ? ldexp(St, kdiff(kt, Kt)) : 0.0), Zd = wave_sum((Sd > 0.0) ? ldexp(Sd, kdiff(kd, Kd)) : 0.0);
+                lse2_t = static_cast<double>(Kt) + log2(Zt);
+                lse2_d = static_cast<double>(Kd) + log2(Zd);
+                if constexpr (MODE == MODE_KLP) {
+                    // the log-domain value where it is larger by more than its own rounding can explain
                     const double logs = wave_sum(in ? static_cast<double>(lo_f(w[k][1])) : 0.0);
-                    const unsigned long long* p1[1] = {sums + (static_cast<size_t>(pair) * P.G + (in ? lane : P.G - 1)) * 4};
-                    unsigned long long u[1][4];
-                    if (!await_tagged<4, 1>(p1, P.nonce, P.spin_limit, u)) status |= FSD_ROW_INTERNAL;
-                    const float kt = lo_f(u[0][0]), kd = lo_f(u[0][1]);
-                    const double St = in ? static_cast<double>(lo_f(u[0][2])) : 0.0, Sd = in ? static_cast<double>(lo_f(u[0][3])) : 0.0;
-                    const float Kt = wave_max((St > 0.0) ? kt : neg_inf()), Kd = wave_max((Sd > 0.0) ? kd : neg_inf());
-                    const double Zt = wave_sum((St > 0.0) ? ldexp(St, kdiff(kt, Kt)) : 0.0), Zd = wave_sum((Sd > 0.0) ? ldexp(Sd, kdiff(kd, Kd)) : 0.0);
-                    const double dl = ((static_cast<double>(Kt) + log2(Zt)) - (static_cast<double>(Kd) + log2(Zd))) * kLn2;
-                    const double v = logs - dl;
-                    if (v == v && v - value > 4e-7 * (fabs(logs) + fabs(dl))) value = v;
-                    if (status) value = __builtin_nan("");
+                    const double dl = (lse2_t - lse2_d) * kLn2, v = logs - dl;
+                    if (log_domain && v == v && v - value > 4e-7 * (fabs(logs) + fabs(dl))) value = v;
                 }
+                if (status) value = __builtin_nan("");
+            }
+            if (P.draw_wgs == 0 && lane == 0) {
+                if (P.want_ratio) {
+                    const int x = P.tokens[pair];
+                    double ratio = __builtin_nan("");
+                    if (x < 0 || x >= P.V) {
+                        status |= FSD_ROW_BAD_TOKEN;
+                    } else if (!(status & FSD_ROW_NONFINITE)) {
+                        constexpr int ES = BF16 ? 2 : 4;
+                        const double lp = static_cast<double>(load_elem<BF16>(P.target + (static_cast<size_t>(pair) + pair / rows) * P.V * ES, x)) - lse2_t * kLn2;
+                        const double lq = static_cast<double>(load_elem<BF16>(P.draft + static_cast<size_t>(pair) * P.V * ES, x)) - lse2_d * kLn2;
+                        ratio = (lp == -__builtin_inf()) ? -__builtin_inf() : lp - lq;
+                    }
+                    P.ws.lr[pair] = ratio;
+                    if (P.user_ratio) P.user_ratio[pair] = static_cast<float>(ratio);
+                }
+                P.ws.div[pair] = static_cast<float>(value);
+                P.ws.lse2[2 * pair] = lse2_t;
+                P.ws.lse2[2 * pair + 1] = lse2_d;
+                P.ws.pst[pair] = status;
+                if (status & FSD_ROW_INTERNAL) flag_failure(P.ws);
             }
             if (lane == 0) {
-                s.div[r] = static_cast<float>(value);
-                s.status[r] = status;
+                if (P.draw_wgs) {
+                    s.div[pair - pair0] = static_cast<float>(value);
+                    s.status[pair - pair0] = status;
+                }
                 if (P.user_div) P.user_div[pair] = static_cast<float>(value);
             }
         }
     }
+    if (P.draw_wgs == 0) return;
     __syncthreads();
     if (wave != 0) return;
     const bool mine = lane < rows;
@@ -379,7 +426,7 @@ __global__ __launch_bounds__(kWG) void small_call(SmallParams P) {
         const int d = wg - P.team_wgs, row = d / P.GS;
         small_draw<BF16, LD>(P, row, d - row * P.GS, s);
     } else {
-        small_finish<MODE>(P, wg - P.team_wgs - P.draw_wgs, s);
+        small_finish<BF16, MODE>(P, wg - P.team_wgs - P.draw_wgs, s);
     }
 }
 

@@ -555,15 +555,17 @@ def test_acceptance_around_a_wavefront_of_rows(torch_cuda, oracle, rows, V, dtyp
 
 
 # a call in one launch: 2, 4 and 8 slots a lane and the team's limit of 64, the wavefronts up to which it takes 2, rows and pairs
-# up to 64, one entry behind a slot, and one size beyond each
+# up to 64, one entry behind a slot, the entries up to which a reduction takes one step, and one size beyond each
 @pytest.mark.parametrize("B,K,V,dtype", [
     (1, 2, 65536, "bf16"), (1, 2, 65537, "bf16"), (1, 2, 131073, "bf16"), (1, 1, 262144, "bf16"), (1, 1, 262145, "bf16"),
     (1, 2, 32768, "f32"), (1, 2, 32769, "f32"), (1, 2, 65537, "f32"), (1, 1, 131072, "f32"), (1, 1, 131073, "f32"),
     (4, 5, 32000, "bf16"), (3, 7, 32001, "bf16"), (2, 5, 32001, "f32"), (3, 4, 32000, "f32"), (2, 16, 40001, "bf16"),
-    (1, 64, 520, "bf16"), (1, 65, 520, "bf16"), (64, 1, 1025, "f32"), (13, 5, 1025, "f32"), (3, 1, 8, "bf16"), (3, 1, 5, "f32")])
-def test_calls_in_one_launch(torch_cuda, oracle, B, K, V, dtype):
-    """Chains, and trees of the same sizes, under every divergence; masked entries, and a row that cannot be used where
-    there is a second sequence."""
+    (1, 64, 520, "bf16"), (1, 65, 520, "bf16"), (64, 1, 1025, "f32"), (13, 5, 1025, "f32"), (3, 1, 8, "bf16"), (3, 1, 5, "f32"),
+    (2, 130, 603, "f32"), (3, 17, 20000, "bf16"), (8, 2, 262144, "bf16"), (8, 2, 262145, "bf16"), (4, 9, 131072, "bf16"),
+    (4, 9, 131073, "bf16")])
+def test_small_calls(torch_cuda, oracle, B, K, V, dtype):
+    """Chains, and trees of the same sizes, under every divergence, and reducible FSD; masked entries, and a row that
+    cannot be used where there is a second sequence."""
     rng = np.random.default_rng(V + 64 * K + B)
     inp = _random_tree_inputs(rng, B, K, V, dtype, noise=(0.3, 0.8))
     if V > 100:
@@ -583,3 +585,6 @@ def test_calls_in_one_launch(torch_cuda, oracle, B, K, V, dtype):
             g = run_tree(torch_cuda, inp, T, div, K, mode, seed=3, offset=6)
             o = oracle.verify_tree(inp["target"], inp["draft"], inp["node_tokens"], inp["parent"], K, T, div, mode, seed=3, offset=6)
             pu.check_tree(g, o, T, tol, what + " tree", envelope=env)
+        g = run_rfsd(torch_cuda, chain, T, div, seed=3, offset=6)
+        o = oracle.rfsd_verify_chain(chain["target"], chain["draft"], chain["cand"], T, div, seed=3, offset=6)
+        check_rfsd(g, o, T, tol, f"small reducible B={B} K={K} V={V} {dtype} div={div}", envelope=env)
