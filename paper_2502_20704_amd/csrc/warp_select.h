@@ -70,12 +70,15 @@ constexpr float kWarpRange = 28.0f;   // what lies further below the maximum wei
 // usual settings (top-k of at most kWarpFastK, or top-p alone).  One workgroup's time is a compute unit
 // reading and passing over a whole row while most of the device is idle, so up to eight share a row and what is left
 // for one of them is the select (rows of 128256 bfloat16 entries: 64 of them under temperature 0.7, top-k 50, top-p 0.9
-// take 23 us with four workgroups each, 30 with one; 8 of them under top-p 0.95 30 us with eight, 49 with one):
+// take 23 us with four workgroups each, 30 with one; 8 of them under top-p 0.95 25 us with eight, 49 with one):
 //   top-k   every workgroup leaves the entries at or above the k-th largest of its own threads' maxima (the
 //           row's k largest are among them) and counts itself; whoever counts last selects from all of them.
 //   top-p   the workgroups agree on the row's range (one word each, zero until posted; the wait is bounded, and
 //           all are resident, which the host checks), add their histograms of values in memory and count
-//           themselves; whoever counts last finds the bin of the crossing, gathers it from the row and selects.
+//           themselves.  When all have (the same kind of wait) every one finds the bin of the crossing and leaves the entries its own
+//           share has of it, and counts itself again; whoever counts last then selects from those.  (It used to gather the
+//           bin from the row alone, a pass over the whole of it in one compute unit; that is left for bins with more
+//           entries than the lists hold.  8 rows of 128256 bfloat16 entries under top-p 0.95: 30 -> 25 us.)
 // Words and counts lie in the sequence's counter line, which every call clears.  What is left for others is stored
 // with device-scope stores and performed (s_waitcnt) before the count.
 constexpr int kWarpShare = 8;
@@ -475,17 +478,41 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         char* const area = P.area + static_cast<size_t>(b) * P.seq_bytes;
         const int g = static_cast<int>(blockIdx.x), W = static_cast<int>(gridDim.x);
         // everything this workgroup has stored is performed, then it counts itself: true for the last one
-        auto count_self = [&]() __attribute__((always_inline)) -> bool {
+        auto count_self = [&](unsigned* at) __attribute__((always_inline)) -> bool {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            if (tid == 0) s_bin = (__hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, AGENT) == static_cast<unsigned>(W) - 1u) ? 1 : 0;
+            if (tid == 0) s_bin = (__hip_atomic_fetch_add(at, 1u, __ATOMIC_RELAXED, AGENT) == static_cast<unsigned>(W) - 1u) ? 1 : 0;
             __syncthreads();
             const bool last = s_bin != 0;
             __syncthreads();   // (s_bin is used again)
             return last;
         };
+        // this workgroup's keys (s_lkey, s_nlist) for whoever counts last: lists of cap keys, each behind its length
+        auto leave_list = [&](unsigned* lists, int cap, unsigned* at) __attribute__((always_inline)) -> bool {
+            const int left = s_nlist;
+            for (int i = tid; i < left && i < cap; i += kWarpWG)
+                __hip_atomic_store(lists + g * (cap + 1) + 1 + i, s_lkey[i], __ATOMIC_RELAXED, AGENT);
+            if (tid == 0) __hip_atomic_store(lists + g * (cap + 1), static_cast<unsigned>(left), __ATOMIC_RELAXED, AGENT);
+            return count_self(at);
+        };
+        // all lists into s_lkey: false if one was too long.  (A stretch of threads per list: all are read at once; at most
+        // kSplitBytes / 4 <= kWarpList keys.)
+        auto read_lists = [&](const unsigned* lists, int cap) __attribute__((always_inline)) -> bool {
+            if (tid == 0) s_nlist = 0;
+            __syncthreads();
+            const int per = kWarpWG / W, w = tid / per;
+            bool too_long = false;
+            if (w < W) {
+                const int n = static_cast<int>(__hip_atomic_load(lists + w * (cap + 1), __ATOMIC_RELAXED, AGENT));
+                too_long = n > cap;
+                for (int i = tid - w * per; i < n && !too_long; i += per) {
+                    const unsigned key = __hip_atomic_load(lists + w * (cap + 1) + 1 + i, __ATOMIC_RELAXED, AGENT);
+                    s_lkey[atomicAdd(&s_nlist, 1)] = key;
+                }
+            }
+            return __syncthreads_or(too_long) == 0;
+        };
         if (want_k) {
-            // lists of cap keys, each behind its length
             const int cap = static_cast<int>(kSplitBytes / 4) / W - 1;
             unsigned* const lists = reinterpret_cast<unsigned*>(area);
             s_tmax[tid] = ordered_key(tmax);
@@ -500,25 +527,8 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
                 }
             });
             __syncthreads();
-            const int left = s_nlist;
-            for (int i = tid; i < left && i < cap; i += kWarpWG)
-                __hip_atomic_store(lists + g * (cap + 1) + 1 + i, s_lkey[i], __ATOMIC_RELAXED, AGENT);
-            if (tid == 0) __hip_atomic_store(lists + g * (cap + 1), static_cast<unsigned>(left), __ATOMIC_RELAXED, AGENT);
-            if (!count_self()) return;
-            if (tid == 0) s_nlist = 0;
-            __syncthreads();
-            // (a stretch of threads per list: all lists are read at once; at most kSplitBytes / 4 <= kWarpList keys)
-            const int per = kWarpWG / W, w = tid / per;
-            bool too_long = false;
-            if (w < W) {
-                const int n = static_cast<int>(__hip_atomic_load(lists + w * (cap + 1), __ATOMIC_RELAXED, AGENT));
-                too_long = n > cap;
-                for (int i = tid - w * per; i < n && !too_long; i += per) {
-                    const unsigned key = __hip_atomic_load(lists + w * (cap + 1) + 1 + i, __ATOMIC_RELAXED, AGENT);
-                    s_lkey[atomicAdd(&s_nlist, 1)] = key;
-                }
-            }
-            const bool fits = __syncthreads_or(too_long) == 0;
+            if (!leave_list(lists, cap, count)) return;
+            const bool fits = read_lists(lists, cap);
             whole = true;
             if (fits) {
                 const int n = s_nlist;
@@ -585,8 +595,23 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
             __syncthreads();
             const unsigned long long mine = s_bins[tid];
             if (mine) (void)__hip_atomic_fetch_add(bins + tid, mine, __ATOMIC_RELAXED, AGENT);
-            if (!count_self()) return;
-            whole = true;
+            if (!count_self(count)) {
+                if (tid == 0) {
+                    bool all = false;
+                    for (unsigned polls = 0;; ++polls) {
+                        all = __hip_atomic_load(count, __ATOMIC_RELAXED, AGENT) >= static_cast<unsigned>(W);
+                        if (all || polls >= P.spin_limit) break;
+                        __builtin_amdgcn_s_sleep(1);
+                    }
+                    s_bin = all ? 0 : 1;
+                }
+                __syncthreads();
+                if (s_bin != 0) {
+                    if (tid == 0) { flag_failure(P.ws); P.thr[b] = neg_inf(); }
+                    return;
+                }
+                __syncthreads();   // (s_bin is used again)
+            }
             // running sums from the top, one bin per thread
             const unsigned long long h = read64(bins + tid);
             unsigned long long v = h;
@@ -607,7 +632,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
             if (tid < kSplitBins - 1 && above < need && above + h >= need) { s_bin = tid; s_need = need - above; }
             __syncthreads();
             const int chosen = s_bin;
-            if (chosen >= 0) {
+            auto gather = [&]() __attribute__((always_inline)) {
                 const Interval near = bin_interval(top, scale, chosen);
                 for_each([&](float sv, unsigned key) {
                     if (sv >= near.lo && sv <= near.hi && bin_of(sv) == chosen && weight(sv, key)) {
@@ -616,6 +641,19 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
                     }
                 });
                 __syncthreads();
+            };
+            // (behind the histogram: what is left of the sequence's memory)
+            unsigned* const lists = reinterpret_cast<unsigned*>(bins + kSplitBins);
+            const int cap = static_cast<int>((kSplitBytes - kSplitBins * 8) / 4) / W - 1;
+            if (chosen >= 0) gather();
+            if (!leave_list(lists, cap, line + 2 + 2 * kWarpShare)) return;
+            if (chosen >= 0) {
+                if (!read_lists(lists, cap)) {
+                    whole = true;
+                    if (tid == 0) s_nlist = 0;
+                    __syncthreads();
+                    gather();
+                }
                 const int nl = s_nlist;
                 if (nl <= kWarpList) {
                     lds_select(s_lkey, nl, weight, [](unsigned long long) {});
@@ -627,6 +665,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
                 if (tid == 0) P.thr[b] = t_p;
                 return;
             }
+            whole = true;
             __syncthreads();
         }
     }
