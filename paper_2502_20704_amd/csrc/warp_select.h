@@ -3,6 +3,7 @@
 #ifndef FSD_CSRC_WARP_SELECT_H_
 #define FSD_CSRC_WARP_SELECT_H_
 
+#include "accept_sample.h"
 #include "device_common.h"
 #include "pair_kernel.h"
 
@@ -107,9 +108,32 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
 
     // ---- the row the token will be drawn from: the first rejected position, or the row after the last
     // (chain); the row after the deepest node whose ancestors are all accepted, lowest index on ties (tree)
+    int from = 0;
     if (tid == 0) { s_n = P.rows; s_st = 0; s_match = 0u; }
     __syncthreads();
-    if (P.parent == nullptr) {
+    if (P.rows <= 64) {
+        // a lane per position or node, every wavefront for itself, all words requested together (see accept_sample): the
+        // pointer jumping by all sixteen wavefronts, two barriers a round, and the failure word behind it took 2.5 us of the
+        // kernel on trees of 60 nodes (24.5 -> 22.0) and about 1 us of a whole call on chains of 8 (93.9 -> 92.7)
+        const int pr = b * P.rows + (lane < P.rows ? lane : P.rows - 1);
+        const int st = P.ws.pst[pr];
+        const float div = P.ws.div[pr];
+        int my_par = P.parent ? P.parent[pr] : -1;
+        const bool failed = failure_flagged(P.ws);
+        const bool mine = lane < P.rows, ok = div <= P.T;
+        bool stop = failed || __any(mine && st != 0);
+        if (P.parent == nullptr) {
+            const unsigned long long no = __ballot(mine && !ok);
+            from = no ? static_cast<int>(__builtin_ctzll(no)) : P.rows;
+        } else {
+            const TreePick pick = pick_path(lane, P.rows, kMaxRows, my_par, ok);
+            stop |= (pick.status & FSD_ROW_BAD_PARENT) != 0;   // accept_sample reports it
+            from = pick.winner + 1;
+        }
+        from = __builtin_amdgcn_readfirstlane(from);
+        if (stop && tid == 0) s_st = 1;
+        __syncthreads();
+    } else if (P.parent == nullptr) {
         for (int i = tid; i < P.rows; i += kWarpWG) {
             const int pr = b * P.rows + i;
             if (P.ws.pst[pr]) atomicOr(&s_st, 1);
@@ -160,11 +184,16 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         if (tid == 0) s_n = key ? (kMaxRows - 1 - static_cast<int>(key & (kMaxRows - 1))) + 1 : 0;
         __syncthreads();
     }
-    if (s_st || failure_flagged(P.ws)) {   // nothing will be drawn for this sequence
+    if (P.rows > 64) {
+        if (failure_flagged(P.ws) && tid == 0) s_st = 1;
+        from = s_n;
+        __syncthreads();
+    }
+    if (s_st) {   // nothing will be drawn for this sequence
         if (tid == 0) P.thr[b] = neg_inf();
         return;
     }
-    const char* row = P.target + (static_cast<size_t>(b) * (P.rows + 1) + s_n) * static_cast<size_t>(P.V) * ES;
+    const char* row = P.target + (static_cast<size_t>(b) * (P.rows + 1) + from) * static_cast<size_t>(P.V) * ES;
 
     constexpr int NK = SPLIT ? kSplitKeep : kWarpKeep;
     // this workgroup's share of the row
