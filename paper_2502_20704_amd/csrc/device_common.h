@@ -380,7 +380,8 @@ struct Ws {
     unsigned long long* wz;     // [B][rows][kWalkShare] the walk's partial normalisers, one round per rejection
     unsigned long long* arrive; // [kMaxArrive] a call without a clearing kernel: wavefront i of the reduction kernel
                                 // writes the call's number here once it has cleared its words (never cleared
-                                // by a kernel before the reduction: only a word equal to the number counts)
+                                // by a kernel before the reduction: only a word equal to the number counts).  A small
+                                // call (small_call.h) keeps its own words here, each with half of its number
     unsigned long long nonce;   // the call's number: never 0, different for every call of the process
 };
 

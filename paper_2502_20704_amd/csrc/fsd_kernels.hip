@@ -594,6 +594,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         if (k1mode == MODE_JSE) p.spm = 64 * p.NV;
     }
     if (dtype == FSD_F32 && load != LOAD_ELEM && !g_shape_nv) {
+        // (Of what small_call does not take, strict SD above all.)
         // A call whose pairs all fit the device at once is one step per wavefront, and its time the chain of that
         // step: half the slots per lane (twice the members, who post at most twice what the workspace is laid
         // out for) shorten it.  One sequence of 4 positions, V=32000: 15.5 -> 14.1 us a call; 8 positions, V=128256:
