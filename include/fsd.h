@@ -308,7 +308,8 @@ int fsd_calibrate_threshold(const float* divergences, int B, int K, float target
  * fsd_profile_enable(1) every verify call launches that kernel with a pair of
  * events that take the start and the end of its dispatch on the call's stream
  * (what a kernel trace shows; up to 4096 pairs are kept; later calls are
- * not recorded).  fsd_profile_collect waits for the recorded events, returns
+ * not recorded).  Small calls, which otherwise take another kernel (see
+ * fsd_debug_set_small_calls), launch it as well while this is on.  fsd_profile_collect waits for the recorded events, returns
  * the number of pairs and their mean / minimum duration in milliseconds, and
  * forgets them.  Not thread-safe; meant for a single benchmarking thread.
  */
@@ -354,6 +355,16 @@ int fsd_debug_set_shape(int wavefronts, int slots_per_thread);
 /* Test hook: grid size (workgroups) of the last vocabulary-reduction launch and
  * the number of its workgroups the device can hold at once, which caps it. */
 void fsd_debug_last_launch(int* grid, int* resident);
+
+/* Test hooks of the route a call takes.  Small FSD calls (pairs times vocabulary
+ * up to a few million, none of the hooks above changed from its default) have all their pairs reduced
+ * in one step of the whole device, and where the draw is small too are one launch;
+ * fsd_debug_set_small_calls(0) sends them the way of the larger ones (persistent
+ * teams, then the sampler, both at their own shapes) and returns the previous setting.
+ * fsd_debug_last_route: of the last verify call, 0 = persistent teams, 1 = the
+ * one-step reduction with the sampler behind it, 2 = one launch. */
+int fsd_debug_set_small_calls(int on);
+int fsd_debug_last_route(void);
 
 /* Test hook: workgroups a sequence of the last warped call's selection of kept
  * logits (1: one works alone). */

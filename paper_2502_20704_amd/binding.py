@@ -89,6 +89,10 @@ def library() -> ctypes.CDLL:
         L.fsd_debug_set_selection_spin_limit.restype = c.c_uint
         L.fsd_debug_last_selection.argtypes = []
         L.fsd_debug_last_selection.restype = i32
+        L.fsd_debug_set_small_calls.argtypes = [i32]
+        L.fsd_debug_set_small_calls.restype = i32
+        L.fsd_debug_last_route.argtypes = []
+        L.fsd_debug_last_route.restype = i32
         L.fsd_debug_set_self_clear.argtypes = [i32]
         L.fsd_debug_set_self_clear.restype = i32
         L.fsd_debug_set_spin_limit.argtypes = [c.c_uint]
@@ -424,6 +428,16 @@ def debug_warp_thresholds(out, B: int, rows: int, V: int, dtype_code: int):
 def debug_last_selection() -> int:
     """workgroups a sequence of the last warped call's selection (test hook)"""
     return int(library().fsd_debug_last_selection())
+
+
+def debug_set_small_calls(on: bool) -> bool:
+    """Test hook: False sends small FSD calls the way of the larger ones; returns the previous setting."""
+    return bool(library().fsd_debug_set_small_calls(1 if on else 0))
+
+
+def debug_last_route() -> int:
+    """route of the last verify call (test hook): 0 persistent teams, 1 one-step reduction, 2 one launch"""
+    return int(library().fsd_debug_last_route())
 
 
 def debug_set_js_floor(floor_nats: float) -> float:

@@ -175,6 +175,7 @@ constexpr float kJsFloor = 1e-3f;
 float g_js_floor = kJsFloor;
 bool g_exact_js = false;   // test hook: bfloat16 JS in the pointwise form only
 bool g_self_clear = true;  // test hook: 0 = every call launches the clearing kernel
+bool g_small_calls = true; // test hook: 0 = no call takes small_call
 #ifdef FSD_PHASE_TIMING
 unsigned long long* g_dbg = nullptr;
 #endif
@@ -390,6 +391,7 @@ bool launch_small_m(int div, hipStream_t st, const SmallParams& P, int B, bool c
          : div == FSD_DIV_TV ? launch_small_k<BF16, NV, MODE_TV, LD>(st, P, B, captured) : launch_small_k<BF16, NV, MODE_KLP, LD>(st, P, B, captured);
 }
 enum { SMALL_NONE = 0, SMALL_REDUCED = 1, SMALL_DONE = 2 };   // launched: nothing, the reduction alone, the whole call
+std::atomic<int> g_last_route{SMALL_NONE};   // of the last verify call (see fsd_debug_last_route)
 template <bool BF16, int LD>
 int launch_small(int div, hipStream_t st, SmallParams& P, int B, int plan_G, bool whole, bool captured) {
     constexpr int VE = Slot<BF16>::VE;
@@ -619,8 +621,8 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     // Small calls: the reduction in one step, or the whole of a plain FSD call on a few sequences in one launch, unless a test or the
     // profiler has asked for the kernels of a large call.  (Reducible FSD under bfloat16 KL takes its normalisers from
     // the single-pass kernel, whose sums are kept in float64.)
-    bool reduced = false;
-    if ((kind == KIND_CHAIN || kind == KIND_TREE || kind == KIND_RFSD) && load != LOAD_ELEM && !g_shape_nv && !g_prof_on && g_self_clear &&
+    int launched = SMALL_NONE;
+    if ((kind == KIND_CHAIN || kind == KIND_TREE || kind == KIND_RFSD) && load != LOAD_ELEM && g_small_calls && !g_shape_nv && !g_prof_on && g_self_clear &&
         static_cast<long>(R) * V <= small_entries(dtype, div) && !(kind == KIND_RFSD && k1mode == MODE_KL) && !(k1mode == MODE_JSE && g_js_floor != kJsFloor)) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         const bool captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
@@ -656,14 +658,15 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         P.clear_b = reinterpret_cast<uint4*>(ws.spart);
         P.clear_b16 = static_cast<long>((p.off_part1 - p.off_spart) / 16);
         const bool whole = kind != KIND_RFSD && !(warped && mode == FSD_SAMPLE);
-        const int launched =
+        launched =
             dtype == FSD_BF16 ? (load == LOAD_ALIGNED ? launch_small<true, LOAD_ALIGNED>(div, st, P, B, plan_G, whole, captured)
                                                       : launch_small<true, LOAD_WIDE>(div, st, P, B, plan_G, whole, captured))
                               : (load == LOAD_ALIGNED ? launch_small<false, LOAD_ALIGNED>(div, st, P, B, plan_G, whole, captured)
                                                       : launch_small<false, LOAD_WIDE>(div, st, P, B, plan_G, whole, captured));
-        if (launched == SMALL_DONE) return (hipGetLastError() == hipSuccess) ? FSD_OK : FSD_ERR_LAUNCH;
-        reduced = launched == SMALL_REDUCED;
     }
+    g_last_route.store(launched, std::memory_order_relaxed);
+    if (launched == SMALL_DONE) return (hipGetLastError() == hipSuccess) ? FSD_OK : FSD_ERR_LAUNCH;
+    const bool reduced = launched == SMALL_REDUCED;
 
     // The calls have no clearing kernel: the reduction clears what it and the kernels after it need (see
     // clear_own_words in pair_kernel.h; C2: -3 us a call, C4: -2 us), unless there are more than 4 MB to
@@ -997,6 +1000,14 @@ size_t fsd_debug_warp_threshold_offset(int B, int rows_per_seq, int V, int dtype
 void fsd_debug_last_launch(int* grid, int* resident) {
     if (grid) *grid = g_last_grid;
     if (resident) *resident = g_last_total;
+}
+
+int fsd_debug_last_route(void) { return g_last_route.load(std::memory_order_relaxed); }
+
+int fsd_debug_set_small_calls(int on) {
+    const int prev = g_small_calls ? 1 : 0;
+    g_small_calls = (on != 0);
+    return prev;
 }
 
 int fsd_debug_last_selection(void) { return g_last_selection.load(std::memory_order_relaxed); }

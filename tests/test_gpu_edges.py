@@ -10,6 +10,7 @@ from tests.test_gpu_parity import (_random_tree_inputs, check_rfsd, check_sd, ch
                                    run_rfsd, run_sd_tree, run_tree, run_warped)
 
 pytestmark = pytest.mark.gpu
+both_routes = pytest.mark.usefixtures("route")   # see conftest.py
 
 
 @pytest.fixture(scope="module")
@@ -52,6 +53,7 @@ def test_selection_by_value(torch_cuda, oracle, V, dtype):
 
 
 # entries a team member holds: 3072 (bfloat16 JS, TV), 2048 (the other kernels); a slot: 8 or 4
+@both_routes
 @pytest.mark.parametrize("V", [3, 7, 8, 9, 15, 2047, 2049, 3071, 3073, 6151])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_ragged_rows(torch_cuda, oracle, V, dtype):
@@ -83,6 +85,7 @@ def test_ragged_rows(torch_cuda, oracle, V, dtype):
     check_sd_tree(g, o, f"ragged SD tree V={V} {dtype}", tin)
 
 
+@both_routes
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_rows_on_odd_addresses(torch_cuda, oracle, dtype):
     """Tensors whose first row starts one element past a 16-byte boundary (V a multiple of the slot)."""
@@ -103,6 +106,7 @@ def test_rows_on_odd_addresses(torch_cuda, oracle, dtype):
                        envelope=pu.Envelope(dtype))
 
 
+@both_routes
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_every_call_on_odd_addresses(torch_cuda, oracle, dtype):
     """The entry points beside the plain chain call, on tensors whose first row starts one element past a 16-byte
@@ -443,6 +447,7 @@ def test_shares_of_a_draw(torch_cuda, oracle, share, dtype):
 
 
 # 5 wavefronts a compute unit (1280 on 256 of them) with 1024 entries of a binary32 row each
+@both_routes
 @pytest.mark.parametrize("B,K,V", [(1, 4, 32000), (10, 4, 32000), (11, 4, 32000), (1, 8, 128256), (1, 1, 262144), (1, 1, 262145), (40, 8, 4096)])
 @pytest.mark.parametrize("div", [fsd.DIV_JS, fsd.DIV_TV, fsd.DIV_KL])
 def test_small_binary32_calls(torch_cuda, oracle, B, K, V, div):
@@ -510,6 +515,7 @@ def test_routes_under_capture(torch_cuda):
 
 
 # up to 64 positions or nodes are decided by a wavefront, more by the workgroup; V: one, two and several shares of a draw
+@both_routes
 @pytest.mark.parametrize("rows,V,dtype", [(1, 700, "bf16"), (2, 1025, "f32"), (63, 2056, "bf16"), (64, 4100, "bf16"), (64, 1028, "f32"),
                                           (65, 4096, "bf16"), (65, 1029, "f32"), (130, 520, "f32")])
 def test_acceptance_around_a_wavefront_of_rows(torch_cuda, oracle, rows, V, dtype):
@@ -555,15 +561,17 @@ def test_acceptance_around_a_wavefront_of_rows(torch_cuda, oracle, rows, V, dtyp
 
 
 # a call in one launch: 2, 4 and 8 slots a lane and the team's limit of 64, the wavefronts up to which it takes 2, rows and pairs
-# up to 64, one entry behind a slot, the entries up to which a reduction takes one step, and one size beyond each
-@pytest.mark.parametrize("B,K,V,dtype", [
-    (1, 2, 65536, "bf16"), (1, 2, 65537, "bf16"), (1, 2, 131073, "bf16"), (1, 1, 262144, "bf16"), (1, 1, 262145, "bf16"),
-    (1, 2, 32768, "f32"), (1, 2, 32769, "f32"), (1, 2, 65537, "f32"), (1, 1, 131072, "f32"), (1, 1, 131073, "f32"),
-    (4, 5, 32000, "bf16"), (3, 7, 32001, "bf16"), (2, 5, 32001, "f32"), (3, 4, 32000, "f32"), (2, 16, 40001, "bf16"),
-    (1, 64, 520, "bf16"), (1, 65, 520, "bf16"), (64, 1, 1025, "f32"), (13, 5, 1025, "f32"), (3, 1, 8, "bf16"), (3, 1, 5, "f32"),
-    (2, 130, 603, "f32"), (3, 17, 20000, "bf16"), (8, 2, 262144, "bf16"), (8, 2, 262145, "bf16"), (4, 9, 131072, "bf16"),
-    (4, 9, 131073, "bf16")])
-def test_small_calls(torch_cuda, oracle, B, K, V, dtype):
+# up to 64, one entry behind a slot, the entries up to which a reduction takes one step, and one size beyond each.  Routes under JS,
+# TV and KL: 2 one launch, 1 the one-step reduction with the sampler behind it, 0 the persistent teams
+@pytest.mark.parametrize("B,K,V,dtype,routes", [
+    (1, 2, 65536, "bf16", "222"), (1, 2, 65537, "bf16", "222"), (1, 2, 131073, "bf16", "222"), (1, 1, 262144, "bf16", "222"),
+    (1, 1, 262145, "bf16", "000"), (1, 2, 32768, "f32", "222"), (1, 2, 32769, "f32", "222"), (1, 2, 65537, "f32", "222"),
+    (1, 1, 131072, "f32", "222"), (1, 1, 131073, "f32", "000"), (4, 5, 32000, "bf16", "222"), (3, 7, 32001, "bf16", "222"),
+    (2, 5, 32001, "f32", "222"), (3, 4, 32000, "f32", "222"), (2, 16, 40001, "bf16", "220"), (1, 64, 520, "bf16", "222"),
+    (1, 65, 520, "bf16", "111"), (64, 1, 1025, "f32", "222"), (13, 5, 1025, "f32", "222"), (3, 1, 8, "bf16", "222"),
+    (3, 1, 5, "f32", "222"), (2, 130, 603, "f32", "111"), (3, 17, 20000, "bf16", "222"), (8, 2, 262144, "bf16", "110"),
+    (8, 2, 262145, "bf16", "000"), (4, 9, 131072, "bf16", "110"), (4, 9, 131073, "bf16", "100")])
+def test_small_calls(torch_cuda, oracle, B, K, V, dtype, routes):
     """Chains, and trees of the same sizes, under every divergence, and reducible FSD; masked entries, and a row that
     cannot be used where there is a second sequence."""
     rng = np.random.default_rng(V + 64 * K + B)
@@ -576,15 +584,18 @@ def test_small_calls(torch_cuda, oracle, B, K, V, dtype):
             inp["target"][B - 1, 0, V // 2] = 0x7FC0 if dtype == "bf16" else np.float32(np.nan)
     chain = dict(target=inp["target"], draft=inp["draft"], cand=inp["node_tokens"])
     tol, env = pu.rel_tol(dtype), pu.Envelope(dtype)
-    for div, T in ((fsd.DIV_JS, 0.06), (fsd.DIV_TV, 0.25), (fsd.DIV_KL, 0.2)):
+    for div, T, way in zip((fsd.DIV_JS, fsd.DIV_TV, fsd.DIV_KL), (0.06, 0.25, 0.2), map(int, routes)):
         for mode in (fsd.SAMPLE, fsd.GREEDY):
             what = f"one launch B={B} K={K} V={V} {dtype} div={div} mode={mode}"
             g = run_chain(torch_cuda, chain, T, div, mode, seed=3, offset=6)
+            assert fsd.debug_last_route() == way, what
             o = oracle.verify_chain(chain["target"], chain["draft"], chain["cand"], T, div, mode, seed=3, offset=6)
             pu.check_chain(g, o, T, tol, what, envelope=env)
             g = run_tree(torch_cuda, inp, T, div, K, mode, seed=3, offset=6)
+            assert fsd.debug_last_route() == way, what
             o = oracle.verify_tree(inp["target"], inp["draft"], inp["node_tokens"], inp["parent"], K, T, div, mode, seed=3, offset=6)
             pu.check_tree(g, o, T, tol, what + " tree", envelope=env)
         g = run_rfsd(torch_cuda, chain, T, div, seed=3, offset=6)
+        assert fsd.debug_last_route() == (way > 0 and not (dtype == "bf16" and div == fsd.DIV_KL))
         o = oracle.rfsd_verify_chain(chain["target"], chain["draft"], chain["cand"], T, div, seed=3, offset=6)
         check_rfsd(g, o, T, tol, f"small reducible B={B} K={K} V={V} {dtype} div={div}", envelope=env)

@@ -7,6 +7,8 @@ from paper_2502_20704_amd import synth
 from tests import parity_util as pu
 
 pytestmark = pytest.mark.gpu
+both_routes = pytest.mark.usefixtures("route")   # see conftest.py
+small_and_large = pytest.mark.usefixtures("small_and_large")
 
 
 @pytest.fixture(scope="module")
@@ -48,6 +50,7 @@ SMALL = [  # (B, K, V, dtype, kind, sigma): aligned and ragged V, one slot to se
 ]
 
 
+@both_routes
 @pytest.mark.parametrize("B,K,V,dtype,kind,sigma", SMALL)
 @pytest.mark.parametrize("div", [fsd.DIV_KL, fsd.DIV_JS, fsd.DIV_TV])
 def test_chain_small(torch_cuda, oracle, B, K, V, dtype, kind, sigma, div):
@@ -72,6 +75,7 @@ def test_maximum_vocabulary(torch_cuda, oracle, dtype):
     assert fsd.fsd_workspace_bytes(1, 2, vmax + 1, fsd.BF16 if dtype == "bf16" else fsd.F32) == 0
 
 
+@both_routes
 def test_third_model_family_vocabulary(torch_cuda, oracle):
     """V = 256 000 (the largest vocabulary among the paper's model pairs), 125 wavefronts per pair."""
     inp = synth.chain_inputs(4, 4, 256000, "bf16", "peaked", (0.25, 4.0), seed=62)
@@ -81,6 +85,7 @@ def test_third_model_family_vocabulary(torch_cuda, oracle):
         pu.check_chain(g, o, 0.1, 2e-3, f"V=256000 div={div}")
 
 
+@both_routes
 def test_many_short_sequences(torch_cuda, oracle):
     """far more row pairs than resident teams, smallest team size"""
     inp = synth.chain_inputs(700, 5, 1000, "bf16", "gauss2", (0.25, 2.0), seed=63)
@@ -90,6 +95,7 @@ def test_many_short_sequences(torch_cuda, oracle):
         pu.check_chain(g, o, 0.05, 2e-3, f"B=700 div={div}")
 
 
+@small_and_large
 def test_chain_greedy_and_determinism(torch_cuda, oracle):
     inp = synth.chain_inputs(6, 5, 12345, "bf16", "peaked", 1.0, seed=3)
     g = run_chain(torch_cuda, inp, 0.05, fsd.DIV_JS, mode=fsd.GREEDY)
@@ -103,6 +109,7 @@ def test_chain_greedy_and_determinism(torch_cuda, oracle):
                                   b[k].view(np.uint32) if b[k].dtype == np.float32 else b[k]), k
 
 
+@small_and_large
 def test_identical_rows_threshold_zero(torch_cuda, oracle):
     """identical logits and T = 0 accept every candidate, for all three divergences."""
     for dtype, V in (("f32", 32000), ("bf16", 128256), ("bf16", 999)):
@@ -116,6 +123,7 @@ def test_identical_rows_threshold_zero(torch_cuda, oracle):
             pu.check_chain(g, o, 0.0, pu.rel_tol(dtype), "identical")
 
 
+@small_and_large
 def test_masked_entries_and_closed_form(torch_cuda, oracle):
     """-inf logits are legal; uniform vs half-uniform has JS = 3/4 ln(4/3), TV = 1/2, KL = +inf."""
     V = 128256
@@ -146,6 +154,7 @@ def test_masked_entries_and_closed_form(torch_cuda, oracle):
             pu.check_chain(g, o, 0.5, pu.rel_tol(dtype), f"masked {dtype} div={div}")
 
 
+@small_and_large
 def test_wide_dynamic_range_across_the_team(torch_cuda, oracle):
     """slices of one row whose maxima lie hundreds of units apart: the wavefronts of a team then hold
     reference exponents more than 127 apart, sums relative to the lower ones overflow, and their
@@ -170,6 +179,7 @@ def test_wide_dynamic_range_across_the_team(torch_cuda, oracle):
             assert (g["divergences"][1] == 0).all()
 
 
+@small_and_large
 def test_mass_in_opposite_halves(torch_cuda, oracle):
     """target and draft put their mass on different halves of the vocabulary, `gap` units apart: in
     every slice one side's normalising factor vanishes (or nearly) while the other's does not.  JS goes
@@ -194,6 +204,7 @@ def test_mass_in_opposite_halves(torch_cuda, oracle):
                 pu.check_chain(g, o, 0.3, pu.rel_tol(dtype), f"opposite halves gap={gap} {dtype} div={div}")
 
 
+@small_and_large
 def test_exponentials_in_the_subnormal_range(torch_cuda, oracle):
     """logits spread evenly over 120 units: next to its largest entry every slice has entries whose
     exponential lies in binary32's subnormal range (87 to 103 below) or underflows altogether, on one
@@ -216,6 +227,7 @@ def test_exponentials_in_the_subnormal_range(torch_cuda, oracle):
             pu.check_chain(g, o, 0.3, pu.rel_tol(dtype), f"subnormal range {dtype} div={div}")
 
 
+@small_and_large
 def test_accuracy_envelope_on_nearly_identical_rows(torch_cuda, oracle):
     """The kernels evaluate p and q in binary32, so a divergence carries an absolute error of about 1e-7
     times the mass involved, whatever its size: the relative bar (1e-5 binary32 logits, 2e-3 bfloat16)
@@ -247,6 +259,7 @@ def test_accuracy_envelope_on_nearly_identical_rows(torch_cuda, oracle):
     assert seen_small > 100          # the regime below the floors was exercised
 
 
+@small_and_large
 def test_nonfinite_rows_are_flagged(torch_cuda, oracle):
     inp = synth.chain_inputs(4, 3, 3000, "f32", "gauss2", 1.0, seed=2)
     inp["target"][0, 1, 77] = np.nan
@@ -262,6 +275,7 @@ def test_nonfinite_rows_are_flagged(torch_cuda, oracle):
 
 # ------------------------------------------------------------------- benchmark configurations
 
+@both_routes
 def test_config_c0(torch_cuda, oracle):
     inp = synth.config_inputs("C0", seed=0)
     for div in (fsd.DIV_KL, fsd.DIV_JS, fsd.DIV_TV):
@@ -272,6 +286,7 @@ def test_config_c0(torch_cuda, oracle):
             print("C0", div, T, r, flush=True)
 
 
+@both_routes
 def test_config_c1_sweep(torch_cuda, oracle):
     for sigma in synth.CONFIGS["C1"]["sigma"]:
         inp = synth.config_inputs("C1", seed=0, sigma=sigma)
@@ -367,6 +382,7 @@ def run_rfsd(torch_cuda, inp, T, div, mode=None, seed=0, offset=0):
     return pu.host(out, pu.RFSD_KEYS)
 
 
+@both_routes
 def test_rfsd_small(torch_cuda, oracle):
     for (B, K, V, dtype, kind, sigma) in SMALL[:7]:
         inp = synth.chain_inputs(B, K, V, dtype, kind, sigma, seed=31)
@@ -380,6 +396,7 @@ def test_rfsd_small(torch_cuda, oracle):
                 check_rfsd(g, o, T, tol, f"rFSD B={B} K={K} V={V} {dtype} div={div} mode={mode}")
 
 
+@both_routes
 def test_rfsd_reduces_to_strict_sd_and_to_fsd(torch_cuda, oracle):
     """Sec. 4.3: with T = 0 the rule is strict SD's (bit-identical outputs); with a threshold nothing
     exceeds it is FSD's."""
@@ -451,6 +468,7 @@ WARPS = [dict(temperature=0.7), dict(top_k=1), dict(top_k=40), dict(top_p=0.9), 
          dict(temperature=1.3, top_k=50, top_p=0.8), dict(temperature=0.5, top_k=100000, top_p=0.95)]
 
 
+@both_routes
 def test_warpers_small(torch_cuda, oracle):
     for (B, K, V, dtype, kind, sigma) in SMALL[:7]:
         inp = synth.chain_inputs(B, K, V, dtype, kind, sigma, seed=71)
@@ -496,6 +514,7 @@ def test_warpers_selection_edge_cases(torch_cuda, oracle):
             check_warped(g, o, 0.1, pu.rel_tol(dtype), f"selection edge cases {dtype} {kw}")
 
 
+@both_routes
 def test_tree_warpers(torch_cuda, oracle):
     """the tree call with warpers: the cut and the token against the oracle on random trees; off = the plain call"""
     rng = np.random.default_rng(91)
@@ -624,6 +643,7 @@ def test_config_c4_tree_full(torch_cuda, oracle):
 
 # ----------------------------------------------------------------------------------- trees
 
+@both_routes
 def test_tree_small_random(torch_cuda, oracle):
     rng = np.random.default_rng(5)
     for trial, (N, V, dtype) in enumerate([(10, 8, "f32"), (33, 1000, "bf16"), (60, 4097, "f32"), (200, 512, "bf16"),
@@ -648,6 +668,7 @@ def test_tree_small_random(torch_cuda, oracle):
                 pu.check_tree(g, o, T, pu.rel_tol(dtype), f"tree N={N} V={V} T={T} div={div}")
 
 
+@both_routes
 def test_tree_runs_of_pairs_with_idle_teams(torch_cuda, oracle):
     """At the full vocabulary a team is 13 workgroups and about 39 teams are resident; a tree call hands
     each team a run of consecutive pairs.  111 pairs make runs of 3 that use up the pairs before the
@@ -663,6 +684,7 @@ def test_tree_runs_of_pairs_with_idle_teams(torch_cuda, oracle):
             pu.check_tree(g, o, T, pu.rel_tol("bf16"), f"tree runs N={N} div={div}")
 
 
+@both_routes
 def test_chain_shaped_tree_equals_chain(torch_cuda):
     inp = synth.chain_inputs(4, 6, 9000, "bf16", "peaked", 1.0, seed=4)
     parent = np.broadcast_to(np.arange(-1, 5, dtype=np.int32), (4, 6)).copy()
@@ -675,6 +697,7 @@ def test_chain_shaped_tree_equals_chain(torch_cuda):
         assert np.array_equal(c["divergences"], t["divergences"])
 
 
+@small_and_large
 def test_tree_bad_parent_and_depth(torch_cuda, oracle):
     inp = synth.chain_inputs(2, 4, 500, "f32", "gauss2", 1.0, seed=4)
     parent = np.array([[-1, 0, 2, 1], [-1, 0, 1, 2]], dtype=np.int32)
@@ -689,6 +712,7 @@ def test_tree_bad_parent_and_depth(torch_cuda, oracle):
 def test_reduction_kernel_shapes_agree(torch_cuda, oracle):
     """the tuning hook: every shape of the reduction kernel gives the same decisions and tokens, and
     divergences that differ only by the rounding order of the partial sums"""
+    prev = fsd.debug_set_small_calls(False)   # the default shape of the same kernel is what they are compared with
     try:
         for dtype, shapes in (("bf16", (2, 4, 5)), ("f32", (2, 4, 8))):
             inp = synth.chain_inputs(3, 4, 40000, dtype, "peaked", 1.0, seed=91)
@@ -708,6 +732,7 @@ def test_reduction_kernel_shapes_agree(torch_cuda, oracle):
                     assert np.allclose(g["divergences"], ref["divergences"], rtol=2e-6, atol=atol), what
     finally:
         fsd.debug_set_shape(0, 0)
+        fsd.debug_set_small_calls(prev)
 
 
 def _js_inputs():
@@ -736,7 +761,8 @@ JS_FLOOR = 1e-3   # the library's default floor of the entropy form (nats)
 
 def test_js_bf16_both_evaluations(torch_cuda, oracle):
     """bfloat16 JS: the entropy form alone (floor 0), the pointwise second evaluation alone (floor +inf), the
-    pointwise kernel, and the default mix, each against the oracle.  The entropy form is held to its absolute
+    pointwise kernel, the default mix, and what the library takes for calls of these sizes (the one-step reduction,
+    pointwise, up to some million entries), each against the oracle.  The entropy form is held to its absolute
     error, everything else to the relative bar."""
     try:
         for name, t, d, cand in _js_inputs():
@@ -744,11 +770,14 @@ def test_js_bf16_both_evaluations(torch_cuda, oracle):
             inp = dict(target=t, draft=d, cand=cand)
             fin = np.isfinite(o["divs"])
             for what, floor, exact in (("entropy form", 0.0, False), ("second evaluation", float("inf"), False),
-                                       ("pointwise kernel", None, True), ("default", None, False)):
+                                       ("pointwise kernel", None, True), ("default", None, False), ("own route", None, False)):
+                fsd.debug_set_small_calls(what == "own route")
                 prev = fsd.debug_set_js_floor(floor) if floor is not None else None
                 fsd.debug_set_exact_js(exact)
                 print(f"{name}: {what}", flush=True)
                 g = run_chain(torch_cuda, inp, 0.1, fsd.DIV_JS, seed=3, offset=2)
+                # (teams of more than 64 wavefronts have no other route)
+                assert (fsd.debug_last_route() != 0) == (what == "own route" and t.shape[2] <= 262144), f"{name} {what}"
                 if prev is not None:
                     fsd.debug_set_js_floor(prev)
                 fsd.debug_set_exact_js(False)
@@ -766,8 +795,10 @@ def test_js_bf16_both_evaluations(torch_cuda, oracle):
     finally:
         fsd.debug_set_exact_js(False)
         fsd.debug_set_js_floor(JS_FLOOR)
+        fsd.debug_set_small_calls(True)
 
 
+@both_routes
 def test_js_bf16_second_evaluation_in_a_tree(torch_cuda, oracle):
     """the second evaluation where pairs share target rows: a tree whose drafts are close to their targets, so
     that most nodes fall below the floor, with the floor at its default and at +inf"""
@@ -784,6 +815,7 @@ def test_js_bf16_second_evaluation_in_a_tree(torch_cuda, oracle):
         fsd.debug_set_js_floor(JS_FLOOR)
 
 
+@small_and_large
 def test_js_bf16_siblings_share_their_target_row(torch_cuda, oracle):
     """a tree's children follow each other and share their parent's target row, whose exponentials and sums the
     entropy-form kernel takes over from the previous pair: wide trees (many siblings), masked entries in target
@@ -803,6 +835,7 @@ def test_js_bf16_siblings_share_their_target_row(torch_cuda, oracle):
 
 # ------------------------------------------------------------------ random shapes
 
+@both_routes
 def test_random_small_shapes(torch_cuda, oracle):
     """200 random draws of (B, K, V, dtype, input kind, noise, masks, divergence, T): the chain call, and in
     turn reducible FSD, strict SD and a random tree over the same rows, each against the oracle."""
@@ -1041,6 +1074,7 @@ def test_sd_tree_bounded_wait_expires_cleanly(torch_cuda, oracle):
     check_sd_tree(g, o, "after restoring the poll budget")
 
 
+@both_routes
 def test_random_small_shapes_warped_and_tree_sd(torch_cuda, oracle):
     """150 random draws: the chain call with a random set of warpers, and strict SD over a random tree
     (or star), each against the oracle."""
@@ -1162,6 +1196,7 @@ def test_bounded_wait_expires_cleanly(torch_cuda, oracle):
     pu.check_chain(g, o, 0.1, 2e-3, "after restoring the poll budget")
 
 
+@both_routes
 def test_calls_without_a_clearing_kernel_on_dirty_workspaces(torch_cuda, oracle):
     """The plain calls do not launch a kernel to clear their workspace: the reduction kernel's wavefronts
     clear their own exchange words and announce themselves with the call's number.  Whatever the
@@ -1274,6 +1309,7 @@ def test_calls_without_a_clearing_kernel_on_dirty_workspaces(torch_cuda, oracle)
         fsd.debug_set_self_clear(True)
 
 
+@both_routes
 def test_many_calls_on_one_workspace_repeat_bit_for_bit(torch_cuda):
     """1200 calls of four shapes, three divergences and strict SD, mixed, on ONE workspace that starts
     full of random bytes: every call must give, bit for bit, what the first call of its kind gave.
