@@ -440,6 +440,12 @@ void pair_kernel(PairParams P) {
                                       // and of p and q where both are normalised (KL)
     constexpr int kWavesPerWG = kWG / 64;
 
+    // IEEE handling of signalling NaNs off (bit 9 of the mode register): a maximum with one is the other operand.  The
+    // maximum pass over packed bfloat16 words reads every word whose upper logit is masked as one, and with it on the maximum of the words
+    // before such a word was lost (sparse rows: a reference exponent too low, and infinite exponentials where the row's
+    // largest logits lay 88 above it).  Nothing else here sees one but from an unusable row.
+    if constexpr (BF16) __builtin_amdgcn_s_setreg(1 | (9 << 6) | (0 << 11), 0);
+
     // the wavefront's number as a scalar: everything derived from it (member, slot range, exchange
     // addresses) then lives in scalar registers
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));

@@ -599,3 +599,30 @@ def test_small_calls(torch_cuda, oracle, B, K, V, dtype, routes):
         assert fsd.debug_last_route() == (way > 0 and not (dtype == "bf16" and div == fsd.DIV_KL))
         o = oracle.rfsd_verify_chain(chain["target"], chain["draft"], chain["cand"], T, div, seed=3, offset=6)
         check_rfsd(g, o, T, tol, f"small reducible B={B} K={K} V={V} {dtype} div={div}", envelope=env)
+
+
+@both_routes
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("base", [150.0, 0.0])
+@pytest.mark.parametrize("V,kept", [(40000, 600), (40000, 40), (40003, 20000), (8200, 2)])
+def test_sparse_rows(torch_cuda, oracle, dtype, base, V, kept):
+    """All but a few entries of every row masked, at places that the two models share, and the rest far above and around
+    zero: a lane's, a wavefront's largest logit stands between masked ones, or there is none."""
+    B, K = 2, 3
+    rng = np.random.default_rng(kept)
+    inp = synth.chain_inputs(B, K, V, "f32", "gauss2", 0.7, seed=kept)
+    t, d = inp["target"] + np.float32(base), inp["draft"] + np.float32(base)
+    for b in range(B):
+        at = rng.permutation(V)[kept:]
+        t[b, :, at] = -np.inf
+        d[b, :, at] = -np.inf
+    if dtype == "bf16":
+        t, d = synth.to_bf16_bits(t), synth.to_bf16_bits(d)
+    case = dict(target=t, draft=d, cand=inp["cand"])
+    for div, T in ((fsd.DIV_JS, 0.06), (fsd.DIV_TV, 0.25), (fsd.DIV_KL, 0.25)):
+        what = f"{dtype} V={V} kept={kept} base={base} div={div}"
+        print(what, flush=True)
+        g = run_chain(torch_cuda, case, T, div, seed=5, offset=2)
+        o = oracle.verify_chain(t, d, inp["cand"], T, div, seed=5, offset=2)
+        assert (o["row_status"] == 0).all()
+        pu.check_chain(g, o, T, pu.rel_tol(dtype), what, envelope=pu.Envelope(dtype))
