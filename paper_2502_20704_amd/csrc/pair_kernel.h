@@ -66,6 +66,13 @@ __device__ __forceinline__ unsigned fbits(float x) {              // never 0
 // to another is an exact scaling by a power of two.
 __device__ __forceinline__ int kdiff(float k, float M) { return static_cast<int>(k - M); }
 
+// A slice's reference exponent from its largest logit.  A slice without mass (masked by -inf, or by a finite value so low
+// that its exponent is not finite) has one far below any other: the row's sum relative to it is then infinite, its
+// factor 1 / sum is 0 and so are its entries.  (It used to be 0: where all of the row's logits lay below -88 the sum relative to
+// it was 0 and the row taken for one without mass; and a slice of the lowest finite values got infinite exponentials.)
+constexpr float kNoMass = -0x1p126f;
+__device__ __forceinline__ float reference_exponent(float largest) { return fmaxf(ceilf(largest * kLog2e), kNoMass); }
+
 // two binary32 values in one exchange word (never 0: +0.0 in the low half is posted as -0.0)
 __device__ __forceinline__ unsigned long long pack2(float lo, float hi) {
     return static_cast<unsigned long long>(fbits(lo)) | (static_cast<unsigned long long>(__float_as_uint(hi)) << 32);
@@ -1144,8 +1151,8 @@ void pair_kernel(PairParams P) {
             }
             PT(0);   // load wait + max pass
             if constexpr (SAME) md = wave_max(md); else wave_max2(mt, md);
-            kt = SAME ? (SHARE_SUM ? last_kt : due.kt) : ((mt == neg_inf()) ? 0.0f : ceilf(mt * kLog2e));
-            kd = (md == neg_inf()) ? 0.0f : ceilf(md * kLog2e);
+            kt = SAME ? (SHARE_SUM ? last_kt : due.kt) : reference_exponent(mt);
+            kd = reference_exponent(md);
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
                 float a[VE], c[VE];

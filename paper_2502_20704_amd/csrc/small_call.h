@@ -143,7 +143,7 @@ __device__ __forceinline__ void small_team(const SmallParams& P, int gwave) {
         }
     }
     wave_max2(mt, md);
-    const float kt = (mt == neg_inf()) ? 0.0f : ceilf(mt * kLog2e), kd = (md == neg_inf()) ? 0.0f : ceilf(md * kLog2e);
+    const float kt = reference_exponent(mt), kd = reference_exponent(md);
     float et[NE], ed[NE], st = 0.0f, sd = 0.0f, wsum = 0.0f, dmax = neg_inf();
 #pragma unroll
     for (int k = 0; k < NV; ++k) {

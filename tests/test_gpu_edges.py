@@ -601,13 +601,50 @@ def test_small_calls(torch_cuda, oracle, B, K, V, dtype, routes):
         check_rfsd(g, o, T, tol, f"small reducible B={B} K={K} V={V} {dtype} div={div}", envelope=env)
 
 
+# a wavefront's slice of the small calls is 512 or 1024 entries, of the large ones at most 3072; a row that is not 16-byte aligned
 @both_routes
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("base", [150.0, 0.0])
+@pytest.mark.parametrize("V", [20000, 20001])
+@pytest.mark.parametrize("base", [-200.0, 0.0])
+def test_slices_without_mass(torch_cuda, oracle, dtype, V, base):
+    """Whole slices masked, by -inf and by the type's lowest value, in the target's rows, the draft's or both, and in the
+    rest of the row logits far below and around zero: a slice without mass is weightless whatever the others' level."""
+    B, K = 2, 3
+    lowest = np.float32(-3.3895314e38) if dtype == "bf16" else np.finfo(np.float32).min
+    for value in (-np.inf, lowest):
+        for where in ("target", "draft", "both"):
+            inp = synth.chain_inputs(B, K, V, "f32", "gauss2", 0.7, seed=V % 31)
+            t, d = inp["target"] + np.float32(base), inp["draft"] + np.float32(base)
+            if where != "draft":
+                t[:, :, 6000:14000] = value
+            if where != "target":
+                d[:, :, 6000:14000] = value
+            if dtype == "bf16":
+                t, d = synth.to_bf16_bits(t), synth.to_bf16_bits(d)
+            case = dict(target=t, draft=d, cand=inp["cand"])
+            what = f"{dtype} V={V} base={base} {where} masked by {value}"
+            print(what, flush=True)
+            for div, T in ((fsd.DIV_JS, 0.2), (fsd.DIV_TV, 0.4), (fsd.DIV_KL, 0.8)):
+                if div == fsd.DIV_KL and where == "draft" and np.isfinite(value):
+                    continue   # (about 1e38, where sums leave binary32's range)
+                g = run_chain(torch_cuda, case, T, div, seed=5, offset=2)
+                o = oracle.verify_chain(t, d, inp["cand"], T, div, seed=5, offset=2)
+                assert (o["row_status"] == 0).all()
+                pu.check_chain(g, o, T, pu.rel_tol(dtype), f"{what} div={div}", envelope=pu.Envelope(dtype))
+            o = oracle.sd_verify_chain(t, d, inp["cand"], seed=5, offset=2)
+            dev = pu.to_dev(case, ("target", "draft", "cand"))
+            out = fsd.sd_verify_chain(dev["target"], dev["draft"], dev["cand"], seed=5, offset=2)
+            torch_cuda.cuda.synchronize()
+            check_sd(pu.host(out, pu.SD_KEYS), o, what)
+
+
+@both_routes
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("base", [150.0, 0.0, -200.0])
 @pytest.mark.parametrize("V,kept", [(40000, 600), (40000, 40), (40003, 20000), (8200, 2)])
 def test_sparse_rows(torch_cuda, oracle, dtype, base, V, kept):
-    """All but a few entries of every row masked, at places that the two models share, and the rest far above and around
-    zero: a lane's, a wavefront's largest logit stands between masked ones, or there is none."""
+    """All but a few entries of every row masked, at places that the two models share, and the rest far above, around and far
+    below zero: a lane's, a wavefront's largest logit stands between masked ones, or there is none."""
     B, K = 2, 3
     rng = np.random.default_rng(kept)
     inp = synth.chain_inputs(B, K, V, "f32", "gauss2", 0.7, seed=kept)
