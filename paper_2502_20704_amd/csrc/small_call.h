@@ -67,8 +67,15 @@ struct SmallParams {
 
 constexpr int kSmallTeam = 64;
 constexpr int kSmallFinish = 16;   // pairs of a finishing workgroup where the reduction alone is asked for: four a wavefront
-// words of a divergence's share: JS a sum and a status; TV three sums, KL two and a mark, and a status
+// words of a divergence's share: JS a sum and a status; TV three sums, KL two and a mark, and a status; bfloat16 KL two sums
+// in float64, the mark and the status in the last bits of the first
 constexpr int small_share_words(int mode) { return mode == MODE_JS ? 2 : 4; }
+// Bfloat16 KL is made of float64 sums in large calls (pair_kernel's single pass): for results of order one its error is the
+// rounding of the result, and it grows in proportion as they get smaller.  The pointwise terms have no such error; so that they are
+// not behind for large results either, the rows' normalisers, the sums over a wavefront and the shares are float64 here,
+// and a share is corrected for the rounding of its factor, which all entries have in common.
+template <bool BF16, int MODE> constexpr bool kWideKl = BF16 && MODE == MODE_KLP;
+constexpr unsigned kSaturated = 1u, kLate = 2u;
 
 __device__ __forceinline__ unsigned long long tagged(unsigned payload, unsigned long long nonce, int i) {
     return ((i & 1) ? (nonce << 32) : (nonce & 0xFFFFFFFF00000000ull)) | payload;
@@ -103,6 +110,7 @@ template <bool BF16, int NV, int MODE, int LD>
 __device__ __forceinline__ void small_team(const SmallParams& P, int gwave) {
     constexpr int VE = Slot<BF16>::VE, ES = BF16 ? 2 : 4, NE = NV * VE, NP = small_share_words(MODE);
     constexpr float kTiny = 2e-38f;
+    constexpr bool WIDE = kWideKl<BF16, MODE>;
     const int lane = threadIdx.x & 63;
     const int pair = gwave / P.G, member = gwave - pair * P.G;
     if (pair >= P.npairs) return;
@@ -145,6 +153,7 @@ __device__ __forceinline__ void small_team(const SmallParams& P, int gwave) {
     wave_max2(mt, md);
     const float kt = reference_exponent(mt), kd = reference_exponent(md);
     float et[NE], ed[NE], st = 0.0f, sd = 0.0f, wsum = 0.0f, dmax = neg_inf();
+    [[maybe_unused]] double st64 = 0.0, sd64 = 0.0, wsum64 = 0.0;   // WIDE: binary32 sums of 16 entries, added up in float64
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
         float a[VE], c[VE];
@@ -163,21 +172,47 @@ __device__ __forceinline__ void small_team(const SmallParams& P, int gwave) {
                 wsum = fmaf(xa, __builtin_amdgcn_fmed3f(diff, -FLT_MAX, FLT_MAX), wsum);
             }
         }
+        if constexpr (WIDE) {
+            if (k & 1) {
+                st64 += static_cast<double>(st);
+                sd64 += static_cast<double>(sd);
+                wsum64 += static_cast<double>(wsum);
+                st = sd = wsum = 0.0f;
+            }
+        }
     }
-    wave_sumf2(st, sd);
+    if constexpr (WIDE) {
+        st64 = wave_sum(st64);
+        sd64 = wave_sum(sd64);
+        st = static_cast<float>(st64);
+        sd = static_cast<float>(sd64);
+    } else {
+        wave_sumf2(st, sd);
+    }
     if (lane < 4) {
         const float mine = lane == 0 ? kt : lane == 1 ? kd : lane == 2 ? st : sd;
         post64(sums + member * 4 + lane, tagged(__float_as_uint(mine), P.nonce, lane));
     }
-    if constexpr (MODE == MODE_KLP) { wsum = wave_sumf(wsum); dmax = wave_max(dmax); }
+    if constexpr (WIDE) wsum64 = wave_sum(wsum64);
+    else if constexpr (MODE == MODE_KLP) wsum = wave_sumf(wsum);
+    if constexpr (MODE == MODE_KLP) dmax = wave_max(dmax);
 
     // ---- the rows' normalisers relative to this wavefront's own references
     const unsigned long long* at[1] = {sums + (lane < P.G ? lane : P.G - 1) * 4};
     unsigned long long w[1][4];
     const bool ok = await_tagged<4, 1>(at, P.nonce, P.spin_limit, w);
     TeamNorm n{kt, kd, 0.0f, 0.0f, ok};
-    const unsigned long long packed[2] = {(w[0][1] << 32) | static_cast<unsigned>(w[0][0]), (w[0][3] << 32) | static_cast<unsigned>(w[0][2])};
-    merge_round(packed, lane < P.G, n);
+    [[maybe_unused]] double zt64 = 0.0;
+    if constexpr (WIDE) {
+        // (this wavefront's own sums as they were before they were rounded for the others)
+        const double mt64 = lane == member ? st64 : static_cast<double>(lo_f(w[0][2])), md64 = lane == member ? sd64 : static_cast<double>(lo_f(w[0][3]));
+        zt64 = wave_sum(lane < P.G ? ldexp(mt64, kdiff(lo_f(w[0][0]), kt)) : 0.0);
+        n.zt = static_cast<float>(zt64);
+        n.zd = static_cast<float>(wave_sum(lane < P.G ? ldexp(md64, kdiff(lo_f(w[0][1]), kd)) : 0.0));
+    } else {
+        const unsigned long long packed[2] = {(w[0][1] << 32) | static_cast<unsigned>(w[0][0]), (w[0][3] << 32) | static_cast<unsigned>(w[0][2])};
+        merge_round(packed, lane < P.G, n);
+    }
     const float rzt = __builtin_amdgcn_rcpf(n.zt), rzd = __builtin_amdgcn_rcpf(n.zd);
     const float ft = ((st > 0.0f) || (st != st)) ? rzt : rzt * 0.0f, fd = ((sd > 0.0f) || (sd != sd)) ? rzd : rzd * 0.0f;
 
@@ -186,6 +221,7 @@ __device__ __forceinline__ void small_team(const SmallParams& P, int gwave) {
     const float cq = (ftc == fdc) ? 1.0f : fdc * __builtin_amdgcn_rcpf(ftc);
     const bool unusable = ft != ft || fd != fd;
     float part[3] = {0.0f, 0.0f, 0.0f};
+    [[maybe_unused]] double share64 = 0.0;
     if constexpr (MODE == MODE_TV) {
 #pragma unroll
         for (int i = 0; i < NE; ++i) tv_terms(et[i], ed[i] * cq, part[0], part[1], part[2]);
@@ -195,27 +231,49 @@ __device__ __forceinline__ void small_team(const SmallParams& P, int gwave) {
         for (int i = 0; i < 3; ++i) part[i] = unusable ? ft + fd : part[i] * ftc;
     } else {
         float acc = 0.0f;
+        [[maybe_unused]] double acc64 = 0.0;
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
             const float p = (MODE == MODE_KLP) ? fmaf(et[i], ft, kTiny) : et[i];
             const float q = (MODE == MODE_KLP) ? fmaf(ed[i], fd, kTiny) : ed[i] * cq;
             pointwise_term<MODE>(p, q, acc);
+            if constexpr (WIDE) {
+                if (i % 16 == 15) { acc64 += static_cast<double>(acc); acc = 0.0f; }
+            }
         }
-        acc = wave_sumf(acc);
-        if constexpr (MODE != MODE_KLP) acc *= ftc;
-        if (unusable) acc = ft + fd;
+        if constexpr (WIDE) {
+            // in proportion to 1 / zt64 instead of its binary32 rounding ft (2^-22 apart at most, where ft is not 0)
+            double exact = 2.0 - zt64 * static_cast<double>(ft);
+            if (!(fabs(exact - 1.0) < 0x1p-20)) exact = 1.0;
+            share64 = unusable ? static_cast<double>(ft + fd) : wave_sum(acc64) * exact;
+            if (dmax == __builtin_inff()) share64 += __builtin_inf();   // NaN stays NaN
+            wsum64 = ft > 0.0f ? wsum64 * (static_cast<double>(ft) * exact) : 0.0;
+        } else {
+            acc = wave_sumf(acc);
+            if constexpr (MODE != MODE_KLP) acc *= ftc;
+            if (unusable) acc = ft + fd;
+            if constexpr (MODE == MODE_KLP) {
+                if (dmax == __builtin_inff()) acc += __builtin_inff();   // NaN stays NaN
+                part[1] = wsum * ft;
+            }
+            part[0] = acc;
+        }
         if constexpr (MODE == MODE_KLP) {
-            if (dmax == __builtin_inff()) acc += __builtin_inff();   // NaN stays NaN
             const float dl = ((kt - hw_log2(ft)) - (kd - hw_log2(fd))) * static_cast<float>(kLn2);
             const bool sat = (ft > 0.0f) && dmax > neg_inf() && (fd == 0.0f || dmax - dl > 80.0f);
-            part[1] = wsum * ft;
             part[2] = sat ? 1.0f : 0.0f;
         }
-        part[0] = acc;
     }
     if (lane < NP) {
-        const float val = (lane == 0 || NP == 2) ? part[0] : lane == 1 ? part[1] : part[2];
-        const unsigned mine = lane == NP - 1 ? (ok ? 0u : static_cast<unsigned>(FSD_ROW_INTERNAL)) : __float_as_uint(val);
+        unsigned mine;
+        if constexpr (WIDE) {
+            const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(lane < 2 ? share64 : wsum64));
+            mine = static_cast<unsigned>((lane & 1) ? bits >> 32 : bits);
+            if (lane == 0) mine = (mine & ~(kSaturated | kLate)) | (part[2] > 0.0f ? kSaturated : 0u) | (ok ? 0u : kLate);
+        } else {
+            const float val = (lane == 0 || NP == 2) ? part[0] : lane == 1 ? part[1] : part[2];
+            mine = lane == NP - 1 ? (ok ? 0u : static_cast<unsigned>(FSD_ROW_INTERNAL)) : __float_as_uint(val);
+        }
         post64(shares + member * NP + lane, tagged(mine, P.nonce, lane));
     }
 }
@@ -265,6 +323,7 @@ __device__ __forceinline__ void small_draw(const SmallParams& P, int row_of_all,
 template <bool BF16, int MODE>
 __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, SmallShared& s) {
     constexpr int NP = small_share_words(MODE);
+    constexpr bool WIDE = kWideKl<BF16, MODE>;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = P.rows;
     // this workgroup's pairs: a sequence's, or, where only the reduction is asked for, a fixed number
@@ -307,8 +366,15 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
         for (int k = 0; k < 4; ++k) {
             const int pair = base + 4 * k;
             if (pair >= pair1) break;
-            int status = (!there || __any(static_cast<unsigned>(w[k][NP - 1]) != 0)) ? FSD_ROW_INTERNAL : 0;
-            const double first = wave_sum(in ? static_cast<double>(lo_f(w[k][0])) : 0.0);
+            const bool late = WIDE ? (w[k][0] & kLate) != 0 : static_cast<unsigned>(w[k][NP - 1]) != 0;
+            int status = (!there || __any(late)) ? FSD_ROW_INTERNAL : 0;
+            // (a float64 number from its two words)
+            [[maybe_unused]] auto wide = [&](int i, unsigned drop) __attribute__((always_inline)) {
+                return __longlong_as_double(static_cast<long long>((w[k][i + 1] << 32) | (static_cast<unsigned>(w[k][i]) & ~drop)));
+            };
+            double first;
+            if constexpr (WIDE) first = wave_sum(in ? wide(0, kSaturated | kLate) : 0.0);
+            else first = wave_sum(in ? static_cast<double>(lo_f(w[k][0])) : 0.0);
             double value;
             if constexpr (MODE == MODE_TV) {   // the lighter side (see pair_kernel)
                 const double other = wave_sum(in ? static_cast<double>(lo_f(w[k][1])) : 0.0);
@@ -321,7 +387,8 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
             if (value < 0.0) value = 0.0;
             if (status) value = __builtin_nan("");
             bool log_domain = false;   // KL terms that leave binary32's range
-            if constexpr (MODE == MODE_KLP) log_domain = !status && value < __builtin_inf() && __any(in && lo_f(w[k][2]) > 0.0f);
+            if constexpr (MODE == MODE_KLP)
+                log_domain = !status && value < __builtin_inf() && __any(in && (WIDE ? (w[k][0] & kSaturated) != 0 : lo_f(w[k][2]) > 0.0f));
             double lse2_t = 0.0, lse2_d = 0.0;
             if (P.want_ratio || log_domain) {
                 const unsigned long long* p1[1] = {sums + (static_cast<size_t>(pair) * P.G + (in ? lane : P.G - 1)) * 4};
@@ -335,7 +402,9 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
                 lse2_d = static_cast<double>(Kd) + log2(Zd);
                 if constexpr (MODE == MODE_KLP) {
                     // the log-domain value where it is larger by more than its own rounding can explain
-                    const double logs = wave_sum(in ? static_cast<double>(lo_f(w[k][1])) : 0.0);
+                    double logs;
+                    if constexpr (WIDE) logs = wave_sum(in ? wide(2, 0u) : 0.0);
+                    else logs = wave_sum(in ? static_cast<double>(lo_f(w[k][1])) : 0.0);
                     const double dl = (lse2_t - lse2_d) * kLn2, v = logs - dl;
                     if (log_domain && v == v && v - value > 4e-7 * (fabs(logs) + fabs(dl))) value = v;
                 }

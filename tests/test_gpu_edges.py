@@ -663,3 +663,29 @@ def test_sparse_rows(torch_cuda, oracle, dtype, base, V, kept):
         o = oracle.verify_chain(t, d, inp["cand"], T, div, seed=5, offset=2)
         assert (o["row_status"] == 0).all()
         pu.check_chain(g, o, T, pu.rel_tol(dtype), what, envelope=pu.Envelope(dtype))
+
+
+# flat and Zipf-shaped rows from one wavefront's to 64 wavefronts', KL from 0.4 to 3
+@pytest.mark.parametrize("kind,sigma,V", [("gauss2", 1.0, 32000), ("gauss2", 1.0, 128256), ("gauss2", 1.0, 250000), ("gauss2", 2.5, 8003),
+                                          ("zipf", 2.5, 1000)])
+def test_small_kl_is_as_exact_as_in_large_calls(torch_cuda, oracle, kind, sigma, V):
+    """Bfloat16 KL against 64 bits in small calls and, the same rows, in the kernel of large ones, whose sums are float64: the rms
+    error is no larger.  (Two estimates from 160 pairs or more scatter by 6 % each: 1.2 is two deviations of their ratio.  With
+    binary32 sums in the small calls the ratio was 1.3 to 2.2 here.)"""
+    K = 4
+    B = max(1, min(40, 1100000 // (K * V)))
+    err = {True: [], False: []}
+    try:
+        for seed in range(-(-160 // (B * K))):
+            inp = synth.chain_inputs(B, K, V, "bf16", kind, sigma, seed=seed)
+            o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], 0.1, fsd.DIV_KL)
+            for small in err:
+                fsd.debug_set_small_calls(small)
+                g = run_chain(torch_cuda, inp, 0.1, fsd.DIV_KL)
+                assert (fsd.debug_last_route() > 0) == small
+                err[small].append((g["divergences"].astype(np.float64) - o["divs"]) / o["divs"])
+    finally:
+        fsd.debug_set_small_calls(True)
+    rms = {small: float(np.sqrt(np.mean(np.concatenate(e) ** 2))) for small, e in err.items()}
+    print(kind, sigma, V, "rms error against 64 bits: small calls", rms[True], "large", rms[False], flush=True)
+    assert rms[True] <= 1.2 * rms[False]
