@@ -375,7 +375,7 @@ bool launch_small_k(hipStream_t st, const SmallParams& P, int B, bool captured) 
     const Residency res = residency_of(small_call<BF16, NV, MODE, LD>, kWG, cache);
     if (P.team_wgs > res.total) return false;   // (the members of a team wait for each other; they come first in the grid)
     g_last_grid = P.team_wgs;
-    const int finish = P.draw_wgs ? B : (P.npairs + kSmallFinish - 1) / kSmallFinish;
+    const int finish = P.draw_wgs ? B : (P.npairs + P.finish - 1) / P.finish;
     if (captured) {
         // a replay has the number of the call that was recorded: what the replay before it left would count as its own
         const long n16 = (static_cast<long>(P.npairs) * P.G * (4 + P.np) + static_cast<long>(P.draw_wgs) * 2 + 1) / 2;
@@ -653,6 +653,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         P.ws = ws;
         P.user_ratio = user_ratio;
         P.want_ratio = (kind == KIND_RFSD) ? 1 : 0;
+        P.finish = small_finish_pairs(kind == KIND_RFSD);
         P.clear_a = reinterpret_cast<uint4*>(ws.counters + 4);
         P.clear_a16 = static_cast<long>((p.n_counters - 4) * 4 / 16);
         P.clear_b = reinterpret_cast<uint4*>(ws.spart);

@@ -44,6 +44,7 @@ struct SmallParams {
     int draw_wgs;           // 0: the draw follows in kernels of its own, the results go to the workspace (ws)
     int GS;
     int sps;                // slots per draw
+    int finish;             // without draws: pairs of a finishing workgroup
     float T;
     int mode;
     unsigned seed_lo, seed_hi, off_lo, off_hi;
@@ -66,7 +67,11 @@ struct SmallParams {
 };
 
 constexpr int kSmallTeam = 64;
-constexpr int kSmallFinish = 16;   // pairs of a finishing workgroup where the reduction alone is asked for: four a wavefront
+// Pairs of a finishing workgroup where the reduction alone is asked for: four a wavefront, or one where reducible FSD asks for the
+// candidate's log-ratio too, a chain of its own (two merges and logarithms in float64) for every pair.  Whole calls of reducible FSD, the
+// persistent teams, four pairs and one (us): JS, bfloat16 B=4 K=8 V=32000 17.5, 20.1 and 14.0, V=128256 20.7, 25.5 and 18.3; binary32 B=4
+// K=8 V=32000 15.3, 19.9 and 13.5, B=8 17.3, 23.6 and 16.4.
+constexpr int small_finish_pairs(bool want_ratio) { return want_ratio ? 4 : 16; }
 // words of a divergence's share: JS a sum and a status; TV three sums, KL two and a mark, and a status; bfloat16 KL two sums
 // in float64, the mark and the status in the last bits of the first
 constexpr int small_share_words(int mode) { return mode == MODE_JS ? 2 : 4; }
@@ -328,13 +333,13 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
     const int rows = P.rows;
     // this workgroup's pairs: a sequence's, or, where only the reduction is asked for, a fixed number
     const int b = wg;
-    const int pair0 = P.draw_wgs ? b * rows : wg * kSmallFinish, pair1 = P.draw_wgs ? pair0 + rows : min(pair0 + kSmallFinish, P.npairs);
+    const int pair0 = P.draw_wgs ? b * rows : wg * P.finish, pair1 = P.draw_wgs ? pair0 + rows : min(pair0 + P.finish, P.npairs);
     const size_t mine_at = static_cast<size_t>(P.draw_wgs ? b : 0) * rows + (lane < rows ? lane : rows - 1);
     const int token_in = P.tokens[mine_at];
     int my_par = P.parent ? P.parent[mine_at] : -1;
     if (P.draw_wgs == 0) {
         const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
-        const long step = static_cast<long>((P.npairs + kSmallFinish - 1) / kSmallFinish) * kWG;
+        const long step = static_cast<long>((P.npairs + P.finish - 1) / P.finish) * kWG;
         for (long i = static_cast<long>(wg) * kWG + tid; i < P.clear_a16; i += step) P.clear_a[i] = zero;
         for (long i = static_cast<long>(wg) * kWG + tid; i < P.clear_b16; i += step) P.clear_b[i] = zero;
     }
@@ -353,12 +358,37 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
     const unsigned long long* const sums = P.words;
     const unsigned long long* const shares = P.words + static_cast<size_t>(P.npairs) * P.G * 4;
     const bool in = lane < P.G;
+    // log2-sum-exp2 of a pair's rows from the team's sums, in float64
+    auto row_logs = [&](int pair, double& lse2_t, double& lse2_d) __attribute__((always_inline)) -> bool {
+        const unsigned long long* p1[1] = {sums + (static_cast<size_t>(pair) * P.G + (in ? lane : P.G - 1)) * 4};
+        unsigned long long u[1][4];
+        const bool there = await_tagged<4, 1>(p1, P.nonce, P.spin_limit, u);
+        const float kt = lo_f(u[0][0]), kd = lo_f(u[0][1]);
+        const double St = in ? static_cast<double>(lo_f(u[0][2])) : 0.0, Sd = in ? static_cast<double>(lo_f(u[0][3])) : 0.0;
+        const float Kt = wave_max((St > 0.0) ? kt : neg_inf()), Kd = wave_max((Sd > 0.0) ? kd : neg_inf());
+        const double Zt = wave_sum((St > 0.0) ? ldexp(St, kdiff(kt, Kt)) : 0.0), Zd = wave_sum((Sd > 0.0) ? ldexp(Sd, kdiff(kd, Kd)) : 0.0);
+        lse2_t = static_cast<double>(Kt) + log2(Zt);
+        lse2_d = static_cast<double>(Kd) + log2(Zd);
+        return there;
+    };
     for (int base = pair0 + wave; base < pair1; base += 16) {
         const unsigned long long* at[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int pair = base + 4 * k < pair1 ? base + 4 * k : base;
             at[k] = shares + (static_cast<size_t>(pair) * P.G + (in ? lane : P.G - 1)) * NP;
+        }
+        // what reducible FSD's log-ratio takes is there before the shares are
+        double log_p = 0.0, log_q = 0.0, first_t = 0.0, first_d = 0.0;
+        bool first_ok = true;
+        int x = 0;
+        if (P.want_ratio) {   // (one pair a wavefront)
+            constexpr int ES = BF16 ? 2 : 4;
+            x = P.tokens[base];
+            const long at_x = (x < 0 || x >= P.V) ? 0 : x;
+            log_p = static_cast<double>(load_elem<BF16>(P.target + (static_cast<size_t>(base) + base / rows) * P.V * ES, at_x));
+            log_q = static_cast<double>(load_elem<BF16>(P.draft + static_cast<size_t>(base) * P.V * ES, at_x));
+            first_ok = row_logs(base, first_t, first_d);
         }
         unsigned long long w[4][NP];
         const bool there = await_tagged<NP, 4>(at, P.nonce, P.spin_limit, w);
@@ -389,17 +419,9 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
             bool log_domain = false;   // KL terms that leave binary32's range
             if constexpr (MODE == MODE_KLP)
                 log_domain = !status && value < __builtin_inf() && __any(in && (WIDE ? (w[k][0] & kSaturated) != 0 : lo_f(w[k][2]) > 0.0f));
-            double lse2_t = 0.0, lse2_d = 0.0;
+            double lse2_t = first_t, lse2_d = first_d;
             if (P.want_ratio || log_domain) {
-                const unsigned long long* p1[1] = {sums + (static_cast<size_t>(pair) * P.G + (in ? lane : P.G - 1)) * 4};
-                unsigned long long u[1][4];
-                if (!await_tagged<4, 1>(p1, P.nonce, P.spin_limit, u)) status |= FSD_ROW_INTERNAL;
-                const float kt = lo_f(u[0][0]), kd = lo_f(u[0][1]);
-                const double St = in ? static_cast<double>(lo_f(u[0][2])) : 0.0, Sd = in ? static_cast<double>(lo_f(u[0][3])) : 0.0;
-                const float Kt = wave_max((St > 0.0) ? kt : neg_inf()), Kd = wave_max((Sd > 0.0) ? kd : neg_inf());
-                const double Zt = wave_sum((St > 0.0) ? ldexp(St, kdiff(kt, Kt)) : 0.0), Zd = wave_sum((Sd > 0.0) ? ldexp(Sd, kdiff(kd, Kd)) : 0.0);
-                lse2_t = static_cast<double>(Kt) + log2(Zt);
-                lse2_d = static_cast<double>(Kd) + log2(Zd);
+                if (!(P.want_ratio ? first_ok : row_logs(pair, lse2_t, lse2_d))) status |= FSD_ROW_INTERNAL;
                 if constexpr (MODE == MODE_KLP) {
                     // the log-domain value where it is larger by more than its own rounding can explain
                     double logs;
@@ -412,14 +434,11 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
             }
             if (P.draw_wgs == 0 && lane == 0) {
                 if (P.want_ratio) {
-                    const int x = P.tokens[pair];
                     double ratio = __builtin_nan("");
                     if (x < 0 || x >= P.V) {
                         status |= FSD_ROW_BAD_TOKEN;
                     } else if (!(status & FSD_ROW_NONFINITE)) {
-                        constexpr int ES = BF16 ? 2 : 4;
-                        const double lp = static_cast<double>(load_elem<BF16>(P.target + (static_cast<size_t>(pair) + pair / rows) * P.V * ES, x)) - lse2_t * kLn2;
-                        const double lq = static_cast<double>(load_elem<BF16>(P.draft + static_cast<size_t>(pair) * P.V * ES, x)) - lse2_d * kLn2;
+                        const double lp = log_p - lse2_t * kLn2, lq = log_q - lse2_d * kLn2;
                         ratio = (lp == -__builtin_inf()) ? -__builtin_inf() : lp - lq;
                     }
                     P.ws.lr[pair] = ratio;
