@@ -31,7 +31,8 @@ struct SampleParams {
     const float* thr;         // optional [B]: warpers, smallest kept scaled logit of the sampled row
     float inv_temp;           // warpers: binary32(1 / temperature), 1 otherwise
     unsigned spin_limit;      // bounded wait for the other workgroups' shares
-    int clear_arrive;         // a call without a clearing kernel: the arrival slots are cleared here (see pair_kernel.h)
+    uint4* clear;             // words of the reduction that count by the call's number (its arrival slots, see pair_kernel.h; the
+    long clear16;             // words of a captured small_call), in 16-byte units: they go back to zero here
     Ws ws;
 };
 
@@ -654,14 +655,11 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
             }
         }
     }
-    if (P.clear_arrive) {
-        // the reduction kernel has ended: its wavefronts' slots go back to zero, so that the same call
-        // replayed from a captured graph, with the same number, does not find them set
-        uint4* const slots = reinterpret_cast<uint4*>(P.ws.arrive);
-        const long nthreads = static_cast<long>(gridDim.x) * gridDim.y * kWG;
-        for (long i = (static_cast<long>(b) * gridDim.x + gs) * kWG + tid; i < kMaxArrive / 2; i += nthreads)
-            slots[i] = make_uint4(0u, 0u, 0u, 0u);
-    }
+    // The reduction kernel has ended: its words go back to zero, so that the same call replayed from a captured graph, with the
+    // same number, does not find them set.
+    const long nthreads = static_cast<long>(gridDim.x) * gridDim.y * kWG;
+    for (long i = (static_cast<long>(b) * gridDim.x + gs) * kWG + tid; i < P.clear16; i += nthreads)
+        P.clear[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 }  // namespace

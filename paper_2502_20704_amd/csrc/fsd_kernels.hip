@@ -370,23 +370,24 @@ constexpr long kSmallDrawn = 4L << 20, kSmallDraws = 1024, kSmallRounds = 4;
 constexpr long kSmallWaves = 640;
 
 template <bool BF16, int NV, int MODE, int LD>
-bool launch_small_k(hipStream_t st, const SmallParams& P, int B, bool captured) {
+bool launch_small_k(hipStream_t st, SmallParams& P, int B, bool captured) {
     static Residency cache[16] = {};
     const Residency res = residency_of(small_call<BF16, NV, MODE, LD>, kWG, cache);
     if (P.team_wgs > res.total) return false;   // (the members of a team wait for each other; they come first in the grid)
     g_last_grid = P.team_wgs;
     const int finish = P.draw_wgs ? B : (P.npairs + P.finish - 1) / P.finish;
-    if (captured) {
-        // a replay has the number of the call that was recorded: what the replay before it left would count as its own
-        const long n16 = (static_cast<long>(P.npairs) * P.G * (4 + P.np) + static_cast<long>(P.draw_wgs) * 2 + 1) / 2;
-        hipLaunchKernelGGL(zero_counters, dim3(static_cast<unsigned>((n16 + 255) / 256)), dim3(256), 0, st,
-                           reinterpret_cast<uint4*>(P.words), n16);
+    P.words16 = (static_cast<long>(P.npairs) * P.G * (4 + P.np) + static_cast<long>(P.draw_wgs) * 2 + 1) / 2;
+    if (captured && P.draw_wgs) {
+        // A replay has the number of the call that was recorded: what the replay before it left would count as its own.  (Where
+        // the sampler follows it clears the words, see run: whatever this kernel's wavefronts had to post is there by then.)
+        hipLaunchKernelGGL(zero_counters, dim3(static_cast<unsigned>((P.words16 + 255) / 256)), dim3(256), 0, st,
+                           reinterpret_cast<uint4*>(P.words), P.words16);
     }
     hipLaunchKernelGGL((small_call<BF16, NV, MODE, LD>), dim3(static_cast<unsigned>(P.team_wgs + P.draw_wgs + finish)), dim3(kWG), 0, st, P);
     return true;
 }
 template <bool BF16, int NV, int LD>
-bool launch_small_m(int div, hipStream_t st, const SmallParams& P, int B, bool captured) {
+bool launch_small_m(int div, hipStream_t st, SmallParams& P, int B, bool captured) {
     return div == FSD_DIV_JS ? launch_small_k<BF16, NV, MODE_JS, LD>(st, P, B, captured)
          : div == FSD_DIV_TV ? launch_small_k<BF16, NV, MODE_TV, LD>(st, P, B, captured) : launch_small_k<BF16, NV, MODE_KLP, LD>(st, P, B, captured);
 }
@@ -622,6 +623,8 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     // profiler has asked for the kernels of a large call.  (Reducible FSD under bfloat16 KL takes its normalisers from
     // the single-pass kernel, whose sums are kept in float64.)
     int launched = SMALL_NONE;
+    uint4* clear_last = nullptr;   // what the sampler clears once the reduction has ended (see SampleParams)
+    long clear_last16 = 0;
     if ((kind == KIND_CHAIN || kind == KIND_TREE || kind == KIND_RFSD) && load != LOAD_ELEM && g_small_calls && !g_shape_nv && !g_prof_on && g_self_clear &&
         static_cast<long>(R) * V <= small_entries(dtype, div) && !(kind == KIND_RFSD && k1mode == MODE_KL) && !(k1mode == MODE_JSE && g_js_floor != kJsFloor)) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -664,6 +667,10 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
                                                       : launch_small<true, LOAD_WIDE>(div, st, P, B, plan_G, whole, captured))
                               : (load == LOAD_ALIGNED ? launch_small<false, LOAD_ALIGNED>(div, st, P, B, plan_G, whole, captured)
                                                       : launch_small<false, LOAD_WIDE>(div, st, P, B, plan_G, whole, captured));
+        if (launched == SMALL_REDUCED && captured) {
+            clear_last = reinterpret_cast<uint4*>(P.words);
+            clear_last16 = P.words16;
+        }
     }
     g_last_route.store(launched, std::memory_order_relaxed);
     if (launched == SMALL_DONE) return (hipGetLastError() == hipSuccess) ? FSD_OK : FSD_ERR_LAUNCH;
@@ -674,6 +681,10 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     // clear (inside the reduction kernel that costs what the kernel of its own costs, C3: 7.5 MB) or
     // the grid is too large for the arrival slots.
     const bool self_clear = g_self_clear && zero_bytes <= (4u << 20) && max_resident_wavefronts() <= kMaxArrive;
+    if (self_clear && !reduced) {
+        clear_last = reinterpret_cast<uint4*>(ws.arrive);
+        clear_last16 = kMaxArrive / 2;
+    }
     if (!self_clear && !reduced) {
         const long n16 = static_cast<long>(zero_bytes / 16);
         hipLaunchKernelGGL(zero_counters, dim3(static_cast<unsigned>((n16 + 255) / 256)), dim3(256), 0, st,
@@ -735,7 +746,8 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     sp.spin_limit = g_spin_limit;
     sp.thr = nullptr;
     sp.inv_temp = 1.0f;
-    sp.clear_arrive = (self_clear && !reduced) ? 1 : 0;
+    sp.clear = clear_last;
+    sp.clear16 = clear_last16;
     if (warped && mode == FSD_SAMPLE) {
         // warpers: one more kernel finds, per sequence, the smallest kept scaled logit
         WarpParams wp;

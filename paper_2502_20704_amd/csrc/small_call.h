@@ -17,8 +17,8 @@ namespace {
 // such trips: the members' arrival, their sums, the divergence's shares, the rows' results from one kernel to the next, the sampled row, the
 // draw's shares.  Here it has two, the sums and the divergence's shares:
 //   - Every word says by itself whether it is this call's: half of it is half of the call's number.  So nothing is
-//     cleared and nobody's arrival is waited for.  (A replay of a captured call has the number of the call before: the
-//     host records a kernel before this one that clears the words.)
+//     cleared and nobody's arrival is waited for.  (A replay of a captured call has the number of the replay before: there
+//     the words are cleared, by a kernel before this one or by the sampler behind it.)
 //   - The draw needs the target row and the random numbers, which are the same for every row, but not the
 //     divergences.  While the teams work, workgroups that wait for nobody draw from all target rows; acceptance
 //     then only picks one.  (The chip is mostly idle in such a call.)
@@ -54,6 +54,7 @@ struct SmallParams {
     int32_t* path_nodes;    // tree only
     int32_t* row_status;    // optional
     float* user_div;        // optional
+    long words16;                // the words below in 16-byte units, rounded up
     unsigned long long* words;   // sums [pair][member][4], shares of the divergence [pair][member][np], draws [b][row][GS][2]
     unsigned long long nonce;
     // without draws: where the results go, what the kernels that follow need cleared (16-byte units)

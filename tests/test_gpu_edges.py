@@ -514,6 +514,82 @@ def test_routes_under_capture(torch_cuda):
                 assert np.array_equal(k["out"][name].cpu().numpy(), v, equal_nan=True), (rep, name)
 
 
+def test_replays_on_other_inputs(torch_cuda):
+    """A replay has the number of the call that was recorded, and so had the replay before it: its words must not count
+    again.  Other logits and tokens between the replays, on the recorded call's own workspace, and an eager call on that
+    workspace before the last two: every replay equals, bit for bit, an eager call on the same inputs elsewhere.  One launch, the one-step
+    reduction with its words in the arrival slots and in the place of the exchange words, the persistent teams, and the
+    calls with kernels between reduction and draw."""
+    torch = torch_cuda
+    warp = dict(temperature=0.8, top_k=40, top_p=0.9)
+    calls = [  # call, B, rows, V, dtype, divergence, more arguments, route
+        ("chain", 2, 4, 32000, torch.float32, fsd.DIV_JS, {}, 2), ("chain", 3, 7, 32001, torch.bfloat16, fsd.DIV_TV, {}, 2),
+        ("chain", 3, 5, 20000, torch.bfloat16, fsd.DIV_KL, {}, 2), ("tree", 2, 9, 9000, torch.bfloat16, fsd.DIV_JS, {}, 2),
+        ("rfsd", 2, 5, 32000, torch.bfloat16, fsd.DIV_JS, {}, 1), ("chain", 16, 5, 64000, torch.bfloat16, fsd.DIV_JS, {}, 1),
+        ("chain", 600, 5, 1500, torch.float32, fsd.DIV_KL, {}, 1), ("warped", 3, 4, 40004, torch.bfloat16, fsd.DIV_JS, warp, 1),
+        ("warped", 4, 13, 40004, torch.bfloat16, fsd.DIV_JS, dict(top_p=0.9), 1),
+        ("chain", 16, 5, 128259, torch.bfloat16, fsd.DIV_JS, {}, 0), ("sd", 3, 5, 32000, torch.float32, None, {}, 0),
+        ("sd_tree", 2, 9, 9000, torch.bfloat16, None, {}, 0)]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+
+    def inputs(call, B, rows, V, dtype):
+        d = dict(target=torch.randn((B, rows + 1, V), generator=gen, device="cuda").mul_(3).to(dtype))
+        # (the next row's noise differs from set to set: other divergences, lengths and tokens)
+        spread = 0.2 + 1.5 * torch.rand((B, rows, 1), generator=gen, device="cuda")
+        d["draft"] = (d["target"][:, :rows].float() + spread * torch.randn((B, rows, V), generator=gen, device="cuda")).to(dtype)
+        d["tokens"] = torch.randint(0, V, (B, rows), generator=gen, device="cuda", dtype=torch.int32)
+        if "tree" in call:
+            d["parent"] = torch.tensor([[-1] + [int(torch.randint(-1, j, (1,))) for j in range(1, rows)] for _ in range(B)],
+                                       dtype=torch.int32, device="cuda")
+        return d
+
+    def run(call, d, div, more, **keep):
+        rnd = dict(seed=4, offset=9, **keep)
+        rows, T = d["draft"].shape[1], {fsd.DIV_JS: 0.05, fsd.DIV_TV: 0.2, fsd.DIV_KL: 0.2}.get(div)
+        if call == "chain":
+            return fsd.fsd_verify_chain(d["target"], d["draft"], d["tokens"], T, div, **rnd)
+        if call == "warped":
+            return fsd.fsd_verify_chain_warped(d["target"], d["draft"], d["tokens"], T, div, **more, **rnd)
+        if call == "rfsd":
+            return fsd.rfsd_verify_chain(d["target"], d["draft"], d["tokens"], T, div, **rnd)
+        if call == "tree":
+            return fsd.fsd_verify_tree(d["target"], d["draft"], d["tokens"], d["parent"], rows, T, div, **rnd)
+        if call == "sd":
+            return fsd.sd_verify_chain(d["target"], d["draft"], d["tokens"], **rnd)
+        return fsd.sd_verify_tree(d["target"], d["draft"], d["tokens"], d["parent"], rows, **rnd)
+
+    for call, B, rows, V, dtype, div, more, route in calls:
+        print("replays", call, B, rows, V, dtype, div, more, flush=True)
+        sets = [inputs(call, B, rows, V, dtype) for _ in range(3)]
+        own = {k: v.clone() for k, v in sets[0].items()}
+        first = run(call, own, div, more)
+        assert fsd.debug_last_route() == route
+        out = {k: torch.empty_like(v) for k, v in first.items() if k != "_workspace"}
+        names = list(out)
+        ws = torch.empty_like(first["_workspace"]).random_(0, 256)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            run(call, own, div, more, out=out, workspace=ws)
+        seen = []
+        for rep in range(6):
+            for k, v in sets[rep % 3].items():
+                own[k].copy_(v)
+            for k in names:
+                out[k].fill_(-7)
+            want = run(call, sets[rep % 3], div, more)
+            if rep >= 4:
+                run(call, sets[(rep + 1) % 3], div, more, workspace=ws)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for k in names:
+                assert np.array_equal(out[k].cpu().numpy(), want[k].cpu().numpy(), equal_nan=True), (call, rep, k)
+            seen.append(out["out_tokens"].cpu().numpy())
+        assert not np.array_equal(seen[0], seen[1]) and np.array_equal(seen[0], seen[3])
+
+
 # up to 64 positions or nodes are decided by a wavefront, more by the workgroup; V: one, two and several shares of a draw
 @both_routes
 @pytest.mark.parametrize("rows,V,dtype", [(1, 700, "bf16"), (2, 1025, "f32"), (63, 2056, "bf16"), (64, 4100, "bf16"), (64, 1028, "f32"),
