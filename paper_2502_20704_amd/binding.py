@@ -8,10 +8,7 @@ from __future__ import annotations
 import ctypes
 import os
 
-# torch before the library: the library then binds to the HIP runtime torch has loaded.  Loaded before torch it would
-# bring in the system's copy, and a process with two HIP runtimes has its device memory in one and this
-# library's launches in the other.
-import torch
+torch = None   # imported with the first use (see _use_torch): building the library and making inputs need none
 
 F32, BF16 = 0, 1
 DIV_KL, DIV_JS, DIV_TV = 0, 1, 2
@@ -30,6 +27,13 @@ class FsdError(RuntimeError):
         super().__init__(f"{where}: {msg} (status {status})")
 
 
+def _use_torch():
+    global torch
+    import torch as module
+
+    torch = module
+
+
 def library() -> ctypes.CDLL:
     """The loaded C ABI.  Raises if libfsd.so has not been built (python -m paper_2502_20704_amd.build)."""
     global _lib
@@ -38,6 +42,10 @@ def library() -> ctypes.CDLL:
             raise FileNotFoundError(
                 f"{LIB_PATH} is missing: build it with `python -m paper_2502_20704_amd.build` "
                 "(there is no CPU fallback)")
+        # torch before the library: the library then binds to the HIP runtime torch has loaded.  Loaded before torch it would
+        # bring in the system's copy, and a process with two HIP runtimes has its device memory in one and this
+        # library's launches in the other.
+        _use_torch()
         L = ctypes.CDLL(LIB_PATH)
         c = ctypes
         vp, i32, u64, f32, sz = c.c_void_p, c.c_int, c.c_uint64, c.c_float, c.c_size_t
@@ -113,6 +121,8 @@ def fsd_workspace_bytes(B: int, rows_per_seq: int, V: int, dtype: int) -> int:
 
 
 def _dtype_code(t) -> int:
+    if torch is None:
+        _use_torch()
     if t.dtype == torch.float32:
         return F32
     if t.dtype == torch.bfloat16:
@@ -376,6 +386,8 @@ def rfsd_verify_chain(target, draft, cand, T, div=DIV_JS, mode=SAMPLE, seed=0, o
 def fsd_calibrate_threshold(divergences, target_fraction: float, *, stream=None):
     """(T, accepted fraction) as 1-element device tensors: the smallest occurring threshold at which
     the chain rule accepts at least `target_fraction` of the candidate positions of `divergences`."""
+    if torch is None:
+        _use_torch()
     _check(divergences, "divergences", None, torch.float32)
     B, K = divergences.shape
     dev = divergences.device

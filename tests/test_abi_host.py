@@ -3,6 +3,8 @@ declares, plans workspaces, and turns bad arguments into error codes before anyt
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -38,6 +40,14 @@ def test_workspace_planning():
     assert fsd.fsd_workspace_bytes(1, 8, 1000, 7) == 0
     assert fsd.fsd_workspace_bytes(1, 8, int(fsd.library().fsd_max_vocab(fsd.F32)) + 1, fsd.F32) == 0
     assert fsd.fsd_workspace_bytes(1, 4097, 1000, fsd.F32) == 0
+
+
+def test_import_without_torch():
+    """Building the library and making inputs take neither torch nor the library."""
+    code = ("import sys, paper_2502_20704_amd as fsd; from paper_2502_20704_amd import binding, build, synth; "
+            "synth.chain_inputs(1, 2, 100, 'bf16', 'peaked', 1.0, seed=1); assert fsd.DIV_JS == 1; "
+            "sys.exit('torch' in sys.modules)")
+    assert subprocess.run([sys.executable, "-c", code], cwd=ROOT).returncode == 0
 
 
 FAKE = ctypes.c_void_p(0x1000)      # never dereferenced: every case below fails validation first
