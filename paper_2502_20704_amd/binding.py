@@ -159,7 +159,10 @@ def _workspace(workspace, need, device):
 def _stream(stream):
     if stream is not None:
         return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())   # torch.cuda.current_stream().cuda_stream
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:   # (not part of torch's public interface)
+        return torch.cuda.current_stream().cuda_stream
 
 
 def fsd_verify_chain(target, draft, cand, T, div=DIV_JS, mode=SAMPLE, seed=0, offset=0, *, out=None,

@@ -5,6 +5,7 @@ import os
 import re
 import subprocess
 import sys
+import types
 
 import pytest
 
@@ -48,6 +49,15 @@ def test_import_without_torch():
             "synth.chain_inputs(1, 2, 100, 'bf16', 'peaked', 1.0, seed=1); assert fsd.DIV_JS == 1; "
             "sys.exit('torch' in sys.modules)")
     assert subprocess.run([sys.executable, "-c", code], cwd=ROOT).returncode == 0
+
+
+def test_stream_of_a_torch_without_the_short_way(monkeypatch):
+    from paper_2502_20704_amd import binding
+
+    stream = types.SimpleNamespace(cuda_stream=77)
+    monkeypatch.setattr(binding, "torch", types.SimpleNamespace(
+        _C=types.SimpleNamespace(), cuda=types.SimpleNamespace(current_stream=lambda: stream)))
+    assert binding._stream(None) == 77 and binding._stream(types.SimpleNamespace(cuda_stream=5)) == 5
 
 
 FAKE = ctypes.c_void_p(0x1000)      # never dereferenced: every case below fails validation first
