@@ -1176,24 +1176,44 @@ def test_calls_can_be_captured_in_a_graph(torch_cuda):
             assert np.array_equal(got_sd[k], want_sd[k], equal_nan=True), (rep, k)
 
 
+# (sequences, rows, V, tree, small route, the call's route)
+@pytest.mark.parametrize("B,K,V,tree,small,route", [
+    (4, 4, 128256, False, True, 2), (3, 6, 64000, True, True, 2), (16, 5, 64000, False, True, 1), (8, 10, 64000, True, True, 1),
+    (4, 4, 128256, False, False, 0), (3, 6, 64000, True, False, 0)])
+def test_bounded_wait_expires_cleanly(torch_cuda, oracle, B, K, V, tree, small, route):
+    """With a zero poll budget a workgroup may give up waiting for its team: the kernel still ends.  A sequence is
+    flagged FSD_ROW_INTERNAL, with empty outputs, or right; where a kernel follows the reduction all are flagged if one is.  The
+    next call, with the budget restored, is right."""
+    inp = synth.chain_inputs(B, K, V, "bf16", "peaked", 1.0, seed=6)
+    parent = np.array([[-1, 0, 1, 0, 3, 2, 5, -1, 7, 7][:K]] * B, dtype=np.int32)
+    tin = dict(target=inp["target"], draft=inp["draft"], node_tokens=inp["cand"], parent=parent)
+    length, check = ("path_len", pu.check_tree) if tree else ("accept_len", pu.check_chain)
+    if tree:
+        o = oracle.verify_tree(inp["target"], inp["draft"], inp["cand"], parent, K, 0.1, fsd.DIV_JS)
+    else:
+        o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], 0.1, fsd.DIV_JS)
 
-def test_bounded_wait_expires_cleanly(torch_cuda, oracle):
-    """with a zero poll budget a workgroup may give up waiting for its team: the kernel still ends,
-    and the call either is correct throughout or flags FSD_ROW_INTERNAL on every sequence."""
-    inp = synth.chain_inputs(4, 4, 128256, "bf16", "peaked", 1.0, seed=6)
-    o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], 0.1, fsd.DIV_JS)
-    prev = fsd.debug_set_spin_limit(0)
+    def call():
+        g = run_tree(torch_cuda, tin, 0.1, fsd.DIV_JS, K) if tree else run_chain(torch_cuda, inp, 0.1, fsd.DIV_JS)
+        assert fsd.debug_last_route() == route
+        return g
+
+    prev_small, prev = fsd.debug_set_small_calls(small), fsd.debug_set_spin_limit(0)
     try:
-        g = run_chain(torch_cuda, inp, 0.1, fsd.DIV_JS)
+        g = call()
+        fsd.debug_set_spin_limit(prev)
+        after = call()
     finally:
         fsd.debug_set_spin_limit(prev)
-    if (g["row_status"] == 0).all():
-        pu.check_chain(g, o, 0.1, 2e-3, "zero poll budget, nothing expired")
-    else:
-        assert ((g["row_status"] & fsd.ROW_INTERNAL) != 0).all()
-        assert (g["accept_len"] == 0).all() and (g["out_tokens"] == -1).all()
-    g = run_chain(torch_cuda, inp, 0.1, fsd.DIV_JS)
-    pu.check_chain(g, o, 0.1, 2e-3, "after restoring the poll budget")
+        fsd.debug_set_small_calls(prev_small)
+    bad = (g["row_status"] & fsd.ROW_INTERNAL) != 0
+    assert ((g["row_status"] == 0) | bad).all() and (route == 2 or bad.all() or not bad.any())
+    assert (g[length][bad] == 0).all() and (g["out_tokens"][bad] == -1).all()
+    if tree:
+        assert (g["path_nodes"][bad] == -1).all()
+    if not bad.all():
+        check({k: v[~bad] for k, v in g.items()}, {k: v[~bad] for k, v in o.items()}, 0.1, 2e-3, "zero poll budget, not flagged")
+    check(after, o, 0.1, 2e-3, "after restoring the poll budget")
 
 
 @both_routes
