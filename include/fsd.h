@@ -37,8 +37,8 @@
  *     the last of a sequence, which looks for the shares of those dispatched
  *     before it, and so does not depend on what else is resident.)  If other work occupies the
  *     GPU while a call runs (another stream, another process), some of its
- *     workgroups may start late; every wait is bounded (see
- *     fsd_debug_set_spin_limit), and a wait that expires ends the call with
+ *     workgroups may start late; every wait is bounded (by
+ *     1<<22 polls; see fsd_debug_set_spin_limit), and a wait that expires ends the call with
  *     FSD_ROW_INTERNAL in row_status for every sequence (lengths 0, tokens -1;
  *     a plain FSD call on a few sequences, which is one kernel, for every
  *     sequence it concerns) instead of hanging.  Run verify calls on a GPU that is theirs while they
@@ -318,7 +318,9 @@ int fsd_profile_collect(float* mean_ms, float* min_ms);
 
 /* Test hook: number of polls a wavefront spends waiting for the words of those
  * it shares a row pair or a sequence with before it gives up and the call
- * flags FSD_ROW_INTERNAL (default 1<<22).  Returns the previous value. */
+ * flags FSD_ROW_INTERNAL (default 1<<22).  It governs the waits of workgroups that have to be resident together; the
+ * look for the shares of a draw, which are there whatever else is resident, has a fixed bound of its own
+ * (1<<22).  Returns the previous value. */
 unsigned fsd_debug_set_spin_limit(unsigned polls);
 
 /* Test hook: a smaller number of polls for one of these waits alone, that of the

@@ -30,7 +30,6 @@ struct SampleParams {
     int32_t* row_status;      // optional
     const float* thr;         // optional [B]: warpers, smallest kept scaled logit of the sampled row
     float inv_temp;           // warpers: binary32(1 / temperature), 1 otherwise
-    unsigned spin_limit;      // bounded wait for the other workgroups' shares
     uint4* clear;             // words of the reduction that count by the call's number (its arrival slots, see pair_kernel.h; the
     long clear16;             // words of a captured small_call), in 16-byte units: they go back to zero here
     Ws ws;

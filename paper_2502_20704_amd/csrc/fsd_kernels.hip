@@ -97,6 +97,7 @@ bool make_plan(int B, int rows, long V, int dtype, Plan& p) {
     p.off_counters = o; p.n_counters = 64 + static_cast<size_t>(B) * kSdoneStride; o = align_up(o + p.n_counters * 4, 256);
     p.off_state = o; o = align_up(o + R * 8, 256);
     p.off_wz = o; o = align_up(o + R * kWalkShare * 8, 256);
+    // (a share is one word of 8 bytes; it used to be 32 bytes, and the size that callers are told stays what it was)
     p.off_spart = o; o = align_up(o + static_cast<size_t>(B) * p.GS * 32, 256);
     // the two exchange arrays: 8 words of 8 bytes for every member of the plan's team, twice what the mode that posts
     // most (4 words a member) needs of it, so that a shape may have twice the members (small binary32 calls do).  A call
@@ -660,7 +661,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         P.clear_a = reinterpret_cast<uint4*>(ws.counters + 4);
         P.clear_a16 = static_cast<long>((p.n_counters - 4) * 4 / 16);
         P.clear_b = reinterpret_cast<uint4*>(ws.spart);
-        P.clear_b16 = static_cast<long>((p.off_part1 - p.off_spart) / 16);
+        P.clear_b16 = (static_cast<long>(B) * p.GS + 1) / 2;
         const bool whole = kind != KIND_RFSD && !(warped && mode == FSD_SAMPLE);
         launched =
             dtype == FSD_BF16 ? (load == LOAD_ALIGNED ? launch_small<true, LOAD_ALIGNED>(div, st, P, B, plan_G, whole, captured)
@@ -699,7 +700,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     pp.clear_a16 = static_cast<long>((p.n_counters - 4) * 4 / 16);
     // (the walk's shares lie right before the sampler's: strict SD over a tree has both cleared)
     pp.clear_b = reinterpret_cast<uint4*>(kind == KIND_TREESD ? reinterpret_cast<char*>(ws.wz) : reinterpret_cast<char*>(ws.spart));
-    pp.clear_b16 = static_cast<long>((p.off_part1 - (kind == KIND_TREESD ? p.off_wz : p.off_spart)) / 16);
+    pp.clear_b16 = static_cast<long>((p.off_spart - (kind == KIND_TREESD ? p.off_wz : p.off_spart)) / 16) + (static_cast<long>(B) * p.GS + 1) / 2;
     pp.target = static_cast<const char*>(target);
     pp.draft = static_cast<const char*>(draft);
     pp.parent = tree ? parent : nullptr;
@@ -743,7 +744,6 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     sp.path_nodes = path_nodes;
     sp.row_status = row_status;
     sp.ws = ws;
-    sp.spin_limit = g_spin_limit;
     sp.thr = nullptr;
     sp.inv_temp = 1.0f;
     sp.clear = clear_last;

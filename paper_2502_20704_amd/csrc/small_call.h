@@ -27,7 +27,8 @@ namespace {
 // the results to the kernels that follow, as pair_kernel does.
 // The teams' wavefronts hold NV slots of each row a lane, for one pair each: there is no second step and nothing to
 // overlap.  All divergences are evaluated pointwise, for bfloat16 too: half as much a lane as in the large shape.
-// NV is the least that leaves a team at most 64 members (one word of each a lane).
+// NV is 2 where that makes few wavefronts (kSmallWaves), else 4, and the next larger one where a team would have more than 64
+// members (one word of each a lane), the words would not fit the workspace or the teams the device.
 struct SmallParams {
     const char* target;
     const char* draft;
@@ -89,8 +90,8 @@ __device__ __forceinline__ unsigned long long tagged(unsigned payload, unsigned 
 __device__ __forceinline__ bool is_tagged(unsigned long long w, unsigned long long nonce, int i) {
     return static_cast<unsigned>(w >> 32) == static_cast<unsigned>((i & 1) ? nonce : nonce >> 32);
 }
-// lane l reads the N words of entry l, entries `stride` words apart (lanes past the last one repeat it): false if a
-// word has not come within `limit` looks
+// every lane reads the N words at each of its R places (lanes without an entry of their own repeat another's): false if one of the
+// wavefront's words has not come within `limit` looks
 template <int N, int R>
 __device__ __forceinline__ bool await_tagged(const unsigned long long* (&at)[R], unsigned long long nonce, unsigned limit,
                                              unsigned long long (&w)[R][N]) {
