@@ -345,16 +345,27 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
         for (long i = static_cast<long>(wg) * kWG + tid; i < P.clear_a16; i += step) P.clear_a[i] = zero;
         for (long i = static_cast<long>(wg) * kWG + tid; i < P.clear_b16; i += step) P.clear_b[i] = zero;
     }
-    // the draws first: they are there long before the divergences
+    // the draws first: they are there long before the divergences.  (Four rows a wavefront at a time: each on its own, the
+    // round trips of a tree's rows were the longest part of its call.)
     const unsigned long long* const draws = P.words + static_cast<size_t>(P.npairs) * P.G * (4 + NP);
-    for (int r = wave; r <= rows && P.draw_wgs; r += 4) {
-        const unsigned long long* at[1] = {draws + ((static_cast<size_t>(b) * (rows + 1) + r) * P.GS + (lane < P.GS ? lane : P.GS - 1)) * 2};
-        unsigned long long w[1][2];
-        const bool there = await_tagged<2, 1>(at, P.nonce, kShareLooks, w);
-        const unsigned long long share = (w[0][0] << 32) | static_cast<unsigned>(w[0][1]);
-        const Best m = wave_best(share_best(share));
-        const int st = !there ? FSD_ROW_INTERNAL : (__any((share & 0x80000000u) != 0) || m.idx == 0x7FFFFFFF) ? FSD_ROW_NONFINITE : 0;
-        if (lane == 0) { s.drawn[r] = m; s.drawn_status[r] = st; }
+    for (int base = wave; base <= rows && P.draw_wgs; base += 16) {
+        const unsigned long long* at[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int r = base + 4 * k <= rows ? base + 4 * k : base;
+            at[k] = draws + ((static_cast<size_t>(b) * (rows + 1) + r) * P.GS + (lane < P.GS ? lane : P.GS - 1)) * 2;
+        }
+        unsigned long long w[4][2];
+        const bool there = await_tagged<2, 4>(at, P.nonce, kShareLooks, w);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int r = base + 4 * k;
+            if (r > rows) break;
+            const unsigned long long share = (w[k][0] << 32) | static_cast<unsigned>(w[k][1]);
+            const Best m = wave_best(share_best(share));
+            const int st = !there ? FSD_ROW_INTERNAL : (__any((share & 0x80000000u) != 0) || m.idx == 0x7FFFFFFF) ? FSD_ROW_NONFINITE : 0;
+            if (lane == 0) { s.drawn[r] = m; s.drawn_status[r] = st; }
+        }
     }
     // four pairs a wavefront at a time
     const unsigned long long* const sums = P.words;
