@@ -364,7 +364,8 @@ void fsd_debug_last_launch(int* grid, int* resident);
  * fsd_debug_set_small_calls(0) sends them the way of the larger ones (persistent
  * teams, then the sampler, both at their own shapes) and returns the previous setting.
  * fsd_debug_last_route: of the last verify call, 0 = persistent teams, 1 = the
- * one-step reduction with the sampler behind it, 2 = one launch. */
+ * one-step reduction with the sampler behind it, 2 = one launch.  (A call that is being captured may take 1
+ * where it takes 2 otherwise; the results are the same.) */
 int fsd_debug_set_small_calls(int on);
 int fsd_debug_last_route(void);
 

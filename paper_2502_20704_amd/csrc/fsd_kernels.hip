@@ -351,20 +351,47 @@ void launch_sample(int dtype, int load, int kind, dim3 grid, size_t lds, hipStre
 }
 
 // ---- small calls (small_call.h): every pair's wavefronts at once, one step each
-// Pairs times vocabulary up to which one step of the whole device beats the persistent teams, which load a
-// pair behind the other.  Whole calls, persistent and one step (us): JS, bfloat16 V=64000, 64 pairs 18.0 and 15.0, 96 18.4 and
-// 17.1, V=128256, 64 pairs 21.3 and 22.3, 80 24.4 and 26.3; binary32 V=64000, 64 pairs 18.4 and 16.9, 96 22.2 and 21.9, V=128256,
-// 64 25.6 and 28.2.  TV, bfloat16 V=64000, 64 pairs 16.4 and 15.1, 96 16.7 and 17.2; binary32 V=64000, 80 21.3 and 21.0, 96
-// 21.8 and 22.4.  KL, binary32 V=64000, 96 pairs 26.1 and 23.0; bfloat16 KL has a single pass in large calls, V=32000, 32 pairs 11.8
-// and 9.5, 64 11.9 and 12.4.
-constexpr long small_entries(int dtype, int div) {
-    return div == FSD_DIV_TV ? 9L << 19 : (div == FSD_DIV_KL && dtype == FSD_BF16) ? 9L << 17 : 6L << 20;
+// Which of its forms a call may take, each where it is the fastest.  Whole calls (us) by the persistent teams, by the reduction in one
+// step with the sampler behind it, and in one launch; (n) is n sequences of 8 unless said otherwise, [n] one tree of n nodes.
+//   reduction  one step of the whole device, until the members' words cost more than the teams' second step.
+//     JS   bfloat16 V=32000 [60] 16.7 14.6, 3 of 60 19.9 19.2; V=64000 (8) 18.6 16.6, (12) 19.6 19.6; V=128256 [30] 18.4 17.1, [36] 19.0 19.5, (4)
+//          18.9 17.3, (6) 20.1 20.9
+//          binary32 V=32000 [30] 13.8 13.8, [60] 15.1 15.5, 2 of 60 19.2 18.0; V=64000 (4) 15.4 16.1, (6) 18.6 17.8, (12) 23.4 23.0; V=128256 (3) 18.8
+//          18.0, (4) 19.8 19.7, (5) 22.4 23.8.  (From 1 to 2 million entries the teams' one step is the faster one.)
+//     TV   bfloat16 V=32000 [60] 15.7 14.9; V=64000 (4) 14.9 14.6, (6) 15.2 16.2; V=128256 (2) 15.1 15.2, (3) 15.6 16.4
+//          binary32 V=32000 [30] 13.6 14.5, [60] 15.1 16.1, 2 of 60 18.7 18.2; V=64000 (4) 15.2 17.2, (8) 19.4 19.2; V=128256 (3) 18.6 18.6, (4) 19.4 20.5
+//     KL   binary32 V=32000 [60] 16.5 15.8; V=64000 (6) 21.0 18.7, (12) 27.1 24.6; V=128256 (4) 22.0 21.7, (6) 26.8 27.2; bfloat16 has a single pass in large
+//          calls: V=32000 [30] 13.3 14.9
+//     Reducible FSD: JS bfloat16 V=64000 (12) 20.5 19.3, V=128256 (4) 19.6 17.1, (6) 20.9 21.0; TV V=64000 (8) 19.5 17.2, V=128256 (5) 20.3 20.9.
+//   one launch draws from all rows, and one workgroup a sequence reads all its words: worth less the more of both there is.
+//     JS   bfloat16 V=128256 (2) 16.4 14.4 11.3, (3) 16.8 15.9 14.8, (4) 18.9 17.3 17.7; [16] 16.7 14.8 12.2, [30] 18.4 17.1 18.6; V=32000 [30] 16.3 14.4
+//          11.9, [60] 16.7 14.6 17.0; V=64000 [30] 16.7 14.7 12.8
+//          binary32 V=32000 [30] 13.8 13.8 11.8, [60] 15.1 15.5 18.9; V=64000 [30] 15.0 15.9 16.1; V=128256 [16] 15.6 15.5 14.8, (3) 18.8 18.0 17.4
+//     KL   bfloat16 V=32000, 8 of 5 12.9 14.4 10.3, 12 of 5 13.0 14.6 14.2, [16] 13.2 14.1 10.4, [30] 13.3 14.9 14.5
+//   replays    of one launch have a kernel before it that clears its words, 2 us: the larger ones take the reduction instead, in the same
+//          shape, so that a replay gives what the eager call gives.  JS, V=32000 8 of 5 bfloat16 15.3 13.0 11.6, binary32 13.4 13.8
+//          11.9, 12 of 5 binary32 14.2 15.3 15.1; V=64000 [30] bfloat16 16.3 14.2 15.0; V=128256 (3) 16.4 16.0 16.5; KL binary32 V=64000 (6) 20.9 19.1
+//          20.5; but TV binary32 V=64000 (4) 14.6 17.5 15.3.
+struct SmallForms { bool reduction, whole, whole_replayed; };
+SmallForms small_forms(int kind, int dtype, int div, int B, int rows, long V) {
+    constexpr long M = 1L << 20;
+    const bool bf16 = dtype == FSD_BF16, tv = div == FSD_DIV_TV, single_pass = bf16 && div == FSD_DIV_KL, long_rows = V > 3L << 15;
+    const long entries = static_cast<long>(B) * rows * V, drawn = static_cast<long>(B) * (rows + 1) * V, bytes = drawn * (bf16 ? 2 : 4);
+    const bool ratio = kind == KIND_RFSD;
+    SmallForms f{false, false, false};
+    if (single_pass) f.reduction = false;   // (reducible FSD: its normalisers' sums are float64 there)
+    else if (ratio) f.reduction = entries <= (tv ? 9 * M / 2 : 6 * M);
+    else if (tv) f.reduction = bf16 ? entries <= 2 * M : (entries > 2 * M && entries <= 9 * M / 2 && !long_rows);
+    else if (div == FSD_DIV_KL) f.reduction = entries <= 6 * M;
+    else f.reduction = entries <= (long_rows ? 4 * M : 6 * M) && (bf16 || entries <= M || entries > 2 * M);
+    const long most = single_pass ? 40 * M : 120 * M;   // rows times bytes drawn from
+    f.whole = !ratio && rows <= 32 && entries <= (single_pass ? 9 * M / 8 : 6 * M) && drawn <= 4 * M && rows * bytes <= most;
+    f.whole_replayed = (tv && !bf16) || (bytes <= 6 * M && rows * bytes <= 60 * M);
+    return f;
 }
-// Draws of all target rows in the same launch: entries of those rows, at most (the draw of one row a sequence behind the
-// reduction, and of all beside it, us: binary32 V=128256, 36 rows 17.1 and 19.2, V=64000, 72 16.9 and 17.7, V=32000, 112
-// 16.0 and 14.8; bfloat16 V=128256, 36 15.8 and 16.2, V=32000, 72 12.6 and 11.1), workgroups aimed at, at most, and rounds one
+// Draws of all target rows in the same launch: workgroups aimed at, at most, and rounds one
 // of them may take (half the workgroups, with twice the rounds: 1 sequence of 8, V=128256 8.5 -> 9.2; twice as many: 4 of 8 15.2 -> 16.1).
-constexpr long kSmallDrawn = 4L << 20, kSmallDraws = 1024, kSmallRounds = 4;
+constexpr long kSmallDraws = 1024, kSmallRounds = 4;
 // Two slots a lane while that leaves a wavefront a SIMD or less of its own, else four: half the words to read for
 // twice the work of a step.  Whole calls with two and four (us): V=32000, bfloat16, 512 wavefronts 7.41 and 7.58, 1024 9.15 and
 // 8.49; binary32, 504 6.90 and 6.80, 1008 7.67 and 7.06, 2016 10.7 and 8.3; V=32001 504 7.57 and 8.09, 1008 8.92 and 8.62.
@@ -395,11 +422,11 @@ bool launch_small_m(int div, hipStream_t st, SmallParams& P, int B, bool capture
 enum { SMALL_NONE = 0, SMALL_REDUCED = 1, SMALL_DONE = 2 };   // launched: nothing, the reduction alone, the whole call
 std::atomic<int> g_last_route{SMALL_NONE};   // of the last verify call (see fsd_debug_last_route)
 template <bool BF16, int LD>
-int launch_small(int div, hipStream_t st, SmallParams& P, int B, int plan_G, bool whole, bool captured) {
+int launch_small(int div, hipStream_t st, SmallParams& P, int B, int plan_G, SmallForms may, bool captured) {
     constexpr int VE = Slot<BF16>::VE;
     P.np = small_share_words(div == FSD_DIV_JS ? MODE_JS : MODE_TV);
     const long all = static_cast<long>(B) * (P.rows + 1), round = 8 / VE * kWG;
-    long GS = whole && P.rows <= 64 && all * P.V <= kSmallDrawn ? kSmallDraws / all : 0;
+    long GS = may.whole ? kSmallDraws / all : 0;
     if (GS > (P.nslots + round - 1) / round) GS = (P.nslots + round - 1) / round;
     if (GS > 64) GS = 64;
     if (P.nslots > GS * round * kSmallRounds) GS = 0;
@@ -415,6 +442,8 @@ int launch_small(int div, hipStream_t st, SmallParams& P, int B, int plan_G, boo
         P.GS = few ? static_cast<int>(GS) : 0;
         P.draw_wgs = static_cast<int>(all) * P.GS;
         P.sps = P.GS ? static_cast<int>((P.nslots + P.GS - 1) / P.GS) : 0;
+        if (!P.GS && !may.reduction) return false;
+        if (captured && !may.whole_replayed) P.draw_wgs = P.GS = 0;
         return NV == 2 ? launch_small_m<BF16, 2, LD>(div, st, P, B, captured)
              : NV == 4 ? launch_small_m<BF16, 4, LD>(div, st, P, B, captured) : launch_small_m<BF16, 8, LD>(div, st, P, B, captured);
     };
@@ -598,12 +627,12 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         if (k1mode == MODE_JSE) p.spm = 64 * p.NV;
     }
     if (dtype == FSD_F32 && load != LOAD_ELEM && !g_shape_nv) {
-        // (Of what small_call does not take, strict SD above all.)
+        // (Of what small_call does not take: strict SD above all, and the calls its rule leaves to the teams.)
         // A call whose pairs all fit the device at once is one step per wavefront, and its time the chain of that
         // step: half the slots per lane (twice the members, who post at most twice what the workspace is laid
-        // out for) shorten it.  One sequence of 4 positions, V=32000: 15.5 -> 14.1 us a call; 8 positions, V=128256:
-        // 15.9 -> 15.5; 4 sequences of 5, V=64000, KL: 17.5 -> 16.8.  The line is drawn at the most wavefronts it was
-        // measured to help with (1280; at 2384, more than one step, 21.9 -> 22.6).
+        // out for) shorten it.  Strict SD: one sequence of 4 positions, V=32000: 13.8 -> 12.8 us a call; 8 of 4 14.1 -> 12.9; one of 8, V=128256
+        // 14.6 -> 14.4; 4 of 5, V=64000 14.3 -> 13.6.  The line is drawn at the most wavefronts it was
+        // measured to help with (1280; TV and JS at 2384, more than one step, 21.9 -> 22.6).
         const long G4 = team_size(p.nslots, 4);
         if (G4 <= kMaxTeam && static_cast<long>(R) * G4 * 32 <= 5 * max_resident_wavefronts()) {
             p.NV = 4;
@@ -621,16 +650,21 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
 
     const bool warped = (temperature != 1.0f) || (top_k > 0 && top_k < V) || (top_p < 1.0f);
     // Small calls: the reduction in one step, or the whole of a plain FSD call on a few sequences in one launch, unless a test or the
-    // profiler has asked for the kernels of a large call.  (Reducible FSD under bfloat16 KL takes its normalisers from
-    // the single-pass kernel, whose sums are kept in float64.)
+    // profiler has asked for the kernels of a large call
     int launched = SMALL_NONE;
     uint4* clear_last = nullptr;   // what the sampler clears once the reduction has ended (see SampleParams)
     long clear_last16 = 0;
+    bool captured = false;
+    SmallForms may{false, false, false};
     if ((kind == KIND_CHAIN || kind == KIND_TREE || kind == KIND_RFSD) && load != LOAD_ELEM && g_small_calls && !g_shape_nv && !g_prof_on && g_self_clear &&
-        static_cast<long>(R) * V <= small_entries(dtype, div) && !(kind == KIND_RFSD && k1mode == MODE_KL) && !(k1mode == MODE_JSE && g_js_floor != kJsFloor)) {
+        static_cast<long>(R) * V <= 6L << 20 && !(k1mode == MODE_JSE && g_js_floor != kJsFloor)) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        const bool captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
+        captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
         if (captured) (void)hipGetLastError();
+        may = small_forms(kind, dtype, div, B, rows, V);
+        if (warped && mode == FSD_SAMPLE) may.whole = false;
+    }
+    if (may.whole || may.reduction) {
         SmallParams P;
         P.target = static_cast<const char*>(target);
         P.draft = static_cast<const char*>(draft);
@@ -662,12 +696,11 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         P.clear_a16 = static_cast<long>((p.n_counters - 4) * 4 / 16);
         P.clear_b = reinterpret_cast<uint4*>(ws.spart);
         P.clear_b16 = (static_cast<long>(B) * p.GS + 1) / 2;
-        const bool whole = kind != KIND_RFSD && !(warped && mode == FSD_SAMPLE);
         launched =
-            dtype == FSD_BF16 ? (load == LOAD_ALIGNED ? launch_small<true, LOAD_ALIGNED>(div, st, P, B, plan_G, whole, captured)
-                                                      : launch_small<true, LOAD_WIDE>(div, st, P, B, plan_G, whole, captured))
-                              : (load == LOAD_ALIGNED ? launch_small<false, LOAD_ALIGNED>(div, st, P, B, plan_G, whole, captured)
-                                                      : launch_small<false, LOAD_WIDE>(div, st, P, B, plan_G, whole, captured));
+            dtype == FSD_BF16 ? (load == LOAD_ALIGNED ? launch_small<true, LOAD_ALIGNED>(div, st, P, B, plan_G, may, captured)
+                                                      : launch_small<true, LOAD_WIDE>(div, st, P, B, plan_G, may, captured))
+                              : (load == LOAD_ALIGNED ? launch_small<false, LOAD_ALIGNED>(div, st, P, B, plan_G, may, captured)
+                                                      : launch_small<false, LOAD_WIDE>(div, st, P, B, plan_G, may, captured));
         if (launched == SMALL_REDUCED && captured) {
             clear_last = reinterpret_cast<uint4*>(P.words);
             clear_last16 = P.words16;

@@ -518,11 +518,14 @@ def test_replays_on_other_inputs(torch_cuda):
     """A replay has the number of the call that was recorded, and so had the replay before it: its words must not count
     again.  Other logits and tokens between the replays, on the recorded call's own workspace, and an eager call on that
     workspace before the last two: every replay equals, bit for bit, an eager call on the same inputs elsewhere.  One launch, the one-step
-    reduction with its words in the arrival slots and in the place of the exchange words, the persistent teams, and the
-    calls with kernels between reduction and draw."""
+    reduction with its words in the arrival slots and in the place of the exchange words, calls in one launch whose replays take the
+    reduction, the persistent teams, and the calls with kernels between reduction and draw."""
     torch = torch_cuda
     warp = dict(temperature=0.8, top_k=40, top_p=0.9)
-    calls = [  # call, B, rows, V, dtype, divergence, more arguments, route
+    calls = [  # call, B, rows, V, dtype, divergence, more arguments, route, and the recorded call's where it is another
+        ("chain", 3, 8, 128256, torch.bfloat16, fsd.DIV_JS, {}, (2, 1)), ("chain", 12, 5, 32000, torch.float32, fsd.DIV_JS, {}, (2, 1)),
+        ("tree", 1, 30, 32001, torch.float32, fsd.DIV_KL, {}, (2, 1)), ("tree", 1, 16, 32000, torch.bfloat16, fsd.DIV_KL, {}, 2),
+        ("chain", 4, 8, 64000, torch.float32, fsd.DIV_TV, {}, 2),
         ("chain", 2, 4, 32000, torch.float32, fsd.DIV_JS, {}, 2), ("chain", 3, 7, 32001, torch.bfloat16, fsd.DIV_TV, {}, 2),
         ("chain", 3, 5, 20000, torch.bfloat16, fsd.DIV_KL, {}, 2), ("tree", 2, 9, 9000, torch.bfloat16, fsd.DIV_JS, {}, 2),
         ("rfsd", 2, 5, 32000, torch.bfloat16, fsd.DIV_JS, {}, 1), ("chain", 16, 5, 64000, torch.bfloat16, fsd.DIV_JS, {}, 1),
@@ -564,7 +567,8 @@ def test_replays_on_other_inputs(torch_cuda):
         sets = [inputs(call, B, rows, V, dtype) for _ in range(3)]
         own = {k: v.clone() for k, v in sets[0].items()}
         first = run(call, own, div, more)
-        assert fsd.debug_last_route() == route
+        eager, recorded = route if isinstance(route, tuple) else (route, route)
+        assert fsd.debug_last_route() == eager
         out = {k: torch.empty_like(v) for k, v in first.items() if k != "_workspace"}
         names = list(out)
         ws = torch.empty_like(first["_workspace"]).random_(0, 256)
@@ -572,6 +576,7 @@ def test_replays_on_other_inputs(torch_cuda):
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph):
             run(call, own, div, more, out=out, workspace=ws)
+        assert fsd.debug_last_route() == recorded
         seen = []
         for rep in range(6):
             for k, v in sets[rep % 3].items():
@@ -636,17 +641,22 @@ def test_acceptance_around_a_wavefront_of_rows(torch_cuda, oracle, rows, V, dtyp
         assert list(g["row_status"]) == [0, 0, fsd.ROW_NONFINITE, 0] and g["path_len"][2] == 0
 
 
-# a call in one launch: 2, 4 and 8 slots a lane and the team's limit of 64, the wavefronts up to which it takes 2, rows and pairs
-# up to 64, one entry behind a slot, the entries up to which a reduction takes one step, and one size beyond each.  Routes under JS,
-# TV and KL: 2 one launch, 1 the one-step reduction with the sampler behind it, 0 the persistent teams
+# A call in one launch: 2, 4 and 8 slots a lane and the team's limit of 64, the wavefronts up to which it takes 2, one entry behind a
+# slot; the rows, entries and bytes up to which a call takes a form, and one beyond.  Routes under JS, TV and KL, then those of
+# reducible FSD: 2 one launch, 1 the one-step reduction with the sampler behind it, 0 the persistent teams
 @pytest.mark.parametrize("B,K,V,dtype,routes", [
-    (1, 2, 65536, "bf16", "222"), (1, 2, 65537, "bf16", "222"), (1, 2, 131073, "bf16", "222"), (1, 1, 262144, "bf16", "222"),
-    (1, 1, 262145, "bf16", "000"), (1, 2, 32768, "f32", "222"), (1, 2, 32769, "f32", "222"), (1, 2, 65537, "f32", "222"),
-    (1, 1, 131072, "f32", "222"), (1, 1, 131073, "f32", "000"), (4, 5, 32000, "bf16", "222"), (3, 7, 32001, "bf16", "222"),
-    (2, 5, 32001, "f32", "222"), (3, 4, 32000, "f32", "222"), (2, 16, 40001, "bf16", "220"), (1, 64, 520, "bf16", "222"),
-    (1, 65, 520, "bf16", "111"), (64, 1, 1025, "f32", "222"), (13, 5, 1025, "f32", "222"), (3, 1, 8, "bf16", "222"),
-    (3, 1, 5, "f32", "222"), (2, 130, 603, "f32", "111"), (3, 17, 20000, "bf16", "222"), (8, 2, 262144, "bf16", "110"),
-    (8, 2, 262145, "bf16", "000"), (4, 9, 131072, "bf16", "110"), (4, 9, 131073, "bf16", "100")])
+    (1, 2, 65536, "bf16", "222110"), (1, 2, 65537, "bf16", "222110"), (1, 2, 131073, "bf16", "222110"), (1, 1, 262144, "bf16", "222110"),
+    (1, 1, 262145, "bf16", "000000"), (1, 2, 32768, "f32", "222111"), (1, 2, 32769, "f32", "222111"), (1, 2, 65537, "f32", "222111"),
+    (1, 1, 131072, "f32", "222111"), (1, 1, 131073, "f32", "000000"), (4, 5, 32000, "bf16", "222110"), (3, 7, 32001, "bf16", "222110"),
+    (2, 5, 32001, "f32", "222111"), (3, 4, 32000, "f32", "222111"), (2, 16, 40001, "bf16", "220110"), (1, 32, 520, "bf16", "222110"),
+    (1, 33, 520, "bf16", "110110"), (1, 64, 520, "bf16", "110110"), (1, 65, 520, "bf16", "110110"), (1, 32, 520, "f32", "222111"), (1, 65, 520, "f32", "101111"), (64, 1, 1025, "f32", "222111"),
+    (13, 5, 1025, "f32", "222111"), (3, 1, 8, "bf16", "222110"), (3, 1, 5, "f32", "222111"), (2, 130, 603, "f32", "101111"),
+    (3, 17, 20000, "bf16", "222110"), (3, 19, 20000, "bf16", "220110"), (1, 30, 63550, "bf16", "220110"), (1, 30, 70000, "bf16", "100110"),
+    (1, 33, 63550, "bf16", "110110"), (1, 33, 63551, "bf16", "100110"), (1, 33, 31775, "f32", "101111"), (1, 33, 31776, "f32", "001111"),
+    (1, 33, 63550, "f32", "001111"), (1, 33, 63551, "f32", "111111"), (1, 33, 98304, "f32", "111111"), (1, 33, 98305, "f32", "101111"),
+    (1, 48, 98304, "f32", "111111"), (1, 49, 98300, "f32", "101101"), (8, 2, 262144, "bf16", "100110"), (8, 2, 262145, "bf16", "000000"),
+    (4, 8, 131072, "bf16", "100110"), (4, 9, 131072, "bf16", "000110"), (4, 9, 131073, "bf16", "000100"), (1, 64, 98304, "bf16", "100100"),
+    (1, 65, 98304, "bf16", "000000")])
 def test_small_calls(torch_cuda, oracle, B, K, V, dtype, routes):
     """Chains, and trees of the same sizes, under every divergence, and reducible FSD; masked entries, and a row that
     cannot be used where there is a second sequence."""
@@ -660,7 +670,8 @@ def test_small_calls(torch_cuda, oracle, B, K, V, dtype, routes):
             inp["target"][B - 1, 0, V // 2] = 0x7FC0 if dtype == "bf16" else np.float32(np.nan)
     chain = dict(target=inp["target"], draft=inp["draft"], cand=inp["node_tokens"])
     tol, env = pu.rel_tol(dtype), pu.Envelope(dtype)
-    for div, T, way in zip((fsd.DIV_JS, fsd.DIV_TV, fsd.DIV_KL), (0.06, 0.25, 0.2), map(int, routes)):
+    ways = list(map(int, routes))
+    for div, T, way, reducible in zip((fsd.DIV_JS, fsd.DIV_TV, fsd.DIV_KL), (0.06, 0.25, 0.2), ways[:3], ways[3:]):
         for mode in (fsd.SAMPLE, fsd.GREEDY):
             what = f"one launch B={B} K={K} V={V} {dtype} div={div} mode={mode}"
             g = run_chain(torch_cuda, chain, T, div, mode, seed=3, offset=6)
@@ -672,7 +683,7 @@ def test_small_calls(torch_cuda, oracle, B, K, V, dtype, routes):
             o = oracle.verify_tree(inp["target"], inp["draft"], inp["node_tokens"], inp["parent"], K, T, div, mode, seed=3, offset=6)
             pu.check_tree(g, o, T, tol, what + " tree", envelope=env)
         g = run_rfsd(torch_cuda, chain, T, div, seed=3, offset=6)
-        assert fsd.debug_last_route() == (way > 0 and not (dtype == "bf16" and div == fsd.DIV_KL))
+        assert fsd.debug_last_route() == reducible
         o = oracle.rfsd_verify_chain(chain["target"], chain["draft"], chain["cand"], T, div, seed=3, offset=6)
         check_rfsd(g, o, T, tol, f"small reducible B={B} K={K} V={V} {dtype} div={div}", envelope=env)
 
