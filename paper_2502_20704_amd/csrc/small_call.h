@@ -384,8 +384,16 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
         lse2_d = static_cast<double>(Kd) + log2(Zd);
         return there;
     };
+    // a share's first sum, or KL's second (WIDE: float64 in two words, whose last bits in the first are marks)
+    auto number = [](const unsigned long long (&v)[NP], int i) __attribute__((always_inline)) -> double {
+        if constexpr (WIDE)
+            return __longlong_as_double(static_cast<long long>((v[2 * i + 1] << 32) | (static_cast<unsigned>(v[2 * i]) & ~(i ? 0u : kSaturated | kLate))));
+        else
+            return static_cast<double>(lo_f(v[i]));
+    };
     for (int base = pair0 + wave; base < pair1; base += 16) {
         const unsigned long long* at[4];
+        [[maybe_unused]] unsigned again = 0;   // pairs whose KL has terms that leave binary32's range
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int pair = base + 4 * k < pair1 ? base + 4 * k : base;
@@ -411,13 +419,7 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
             if (pair >= pair1) break;
             const bool late = WIDE ? (w[k][0] & kLate) != 0 : static_cast<unsigned>(w[k][NP - 1]) != 0;
             int status = (!there || __any(late)) ? FSD_ROW_INTERNAL : 0;
-            // (a float64 number from its two words)
-            [[maybe_unused]] auto wide = [&](int i, unsigned drop) __attribute__((always_inline)) {
-                return __longlong_as_double(static_cast<long long>((w[k][i + 1] << 32) | (static_cast<unsigned>(w[k][i]) & ~drop)));
-            };
-            double first;
-            if constexpr (WIDE) first = wave_sum(in ? wide(0, kSaturated | kLate) : 0.0);
-            else first = wave_sum(in ? static_cast<double>(lo_f(w[k][0])) : 0.0);
+            const double first = wave_sum(in ? number(w[k], 0) : 0.0);
             double value;
             if constexpr (MODE == MODE_TV) {   // the lighter side (see pair_kernel)
                 const double other = wave_sum(in ? static_cast<double>(lo_f(w[k][1])) : 0.0);
@@ -428,38 +430,27 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
             }
             if (value != value) status |= FSD_ROW_NONFINITE;   // NaN / +inf logits, or a row without mass
             if (value < 0.0) value = 0.0;
-            if (status) value = __builtin_nan("");
-            bool log_domain = false;   // KL terms that leave binary32's range
-            if constexpr (MODE == MODE_KLP)
-                log_domain = !status && value < __builtin_inf() && __any(in && (WIDE ? (w[k][0] & kSaturated) != 0 : lo_f(w[k][2]) > 0.0f));
-            double lse2_t = first_t, lse2_d = first_d;
-            if (P.want_ratio || log_domain) {
-                if (!(P.want_ratio ? first_ok : row_logs(pair, lse2_t, lse2_d))) status |= FSD_ROW_INTERNAL;
-                if constexpr (MODE == MODE_KLP) {
-                    // the log-domain value where it is larger by more than its own rounding can explain
-                    double logs;
-                    if constexpr (WIDE) logs = wave_sum(in ? wide(2, 0u) : 0.0);
-                    else logs = wave_sum(in ? static_cast<double>(lo_f(w[k][1])) : 0.0);
-                    const double dl = (lse2_t - lse2_d) * kLn2, v = logs - dl;
-                    if (log_domain && v == v && v - value > 4e-7 * (fabs(logs) + fabs(dl))) value = v;
-                }
-                if (status) value = __builtin_nan("");
+            if (P.want_ratio && !first_ok) status |= FSD_ROW_INTERNAL;
+            if constexpr (MODE == MODE_KLP) {
+                const bool saturated = __any(in && (WIDE ? (w[k][0] & kSaturated) != 0 : lo_f(w[k][2]) > 0.0f));
+                if (!status && value < __builtin_inf() && saturated) again |= 1u << k;
             }
+            if (status) value = __builtin_nan("");
             if (P.draw_wgs == 0 && lane == 0) {
                 if (P.want_ratio) {
                     double ratio = __builtin_nan("");
                     if (x < 0 || x >= P.V) {
                         status |= FSD_ROW_BAD_TOKEN;
                     } else if (!(status & FSD_ROW_NONFINITE)) {
-                        const double lp = log_p - lse2_t * kLn2, lq = log_q - lse2_d * kLn2;
+                        const double lp = log_p - first_t * kLn2, lq = log_q - first_d * kLn2;
                         ratio = (lp == -__builtin_inf()) ? -__builtin_inf() : lp - lq;
                     }
                     P.ws.lr[pair] = ratio;
                     if (P.user_ratio) P.user_ratio[pair] = static_cast<float>(ratio);
                 }
                 P.ws.div[pair] = static_cast<float>(value);
-                P.ws.lse2[2 * pair] = lse2_t;
-                P.ws.lse2[2 * pair + 1] = lse2_d;
+                P.ws.lse2[2 * pair] = first_t;
+                P.ws.lse2[2 * pair + 1] = first_d;
                 P.ws.pst[pair] = status;
                 if (status & FSD_ROW_INTERNAL) flag_failure(P.ws);
             }
@@ -469,6 +460,34 @@ __device__ __forceinline__ void small_finish(const SmallParams& P, int wg, Small
                     s.status[pair - pair0] = status;
                 }
                 if (P.user_div) P.user_div[pair] = static_cast<float>(value);
+            }
+        }
+        if constexpr (MODE == MODE_KLP) {
+            // The log-domain value where it is larger by more than its own rounding can explain.  (One pair after the other, behind the
+            // others' code, which its logarithms in float64 made half as long again: bfloat16 KL, 5 sequences of 1, V=64896 8.0 -> 7.6 us a call, one of 9,
+            // V=130176 10.7 -> 10.4; binary32 KL 1 %.)
+            for (again = __builtin_amdgcn_readfirstlane(again); again != 0; again &= again - 1) {
+                const int pair = base + 4 * __builtin_ctz(again);
+                const unsigned long long* p[1] = {shares + (static_cast<size_t>(pair) * P.G + (in ? lane : P.G - 1)) * NP};
+                unsigned long long v[1][NP];
+                double lse2_t = first_t, lse2_d = first_d;
+                bool ok = await_tagged<NP, 1>(p, P.nonce, P.spin_limit, v);
+                if (!P.want_ratio) ok = row_logs(pair, lse2_t, lse2_d) && ok;
+                const double first = wave_sum(in ? number(v[0], 0) : 0.0), logs = wave_sum(in ? number(v[0], 1) : 0.0);
+                const double dl = (lse2_t - lse2_d) * kLn2, log_value = logs - dl;
+                double value = fmax(0.5 * kLn2 * first, 0.0);
+                if (log_value - value > 4e-7 * (fabs(logs) + fabs(dl))) value = log_value;
+                if (!ok) value = __builtin_nan("");
+                if (lane == 0) {
+                    if (P.draw_wgs) {
+                        s.div[pair - pair0] = static_cast<float>(value);
+                        if (!ok) s.status[pair - pair0] = FSD_ROW_INTERNAL;
+                    } else {
+                        P.ws.div[pair] = static_cast<float>(value);
+                        if (!ok) { P.ws.pst[pair] = FSD_ROW_INTERNAL; flag_failure(P.ws); }
+                    }
+                    if (P.user_div) P.user_div[pair] = static_cast<float>(value);
+                }
             }
         }
     }
