@@ -355,11 +355,13 @@ void launch_sample(int dtype, int load, int kind, dim3 grid, size_t lds, hipStre
 // step with the sampler behind it, and in one launch; (n) is n sequences of 8 unless said otherwise, [n] one tree of n nodes.
 //   reduction  one step of the whole device, until the members' words cost more than the teams' second step.
 //     JS   bfloat16 V=32000 [60] 16.7 14.6, 3 of 60 19.9 19.2; V=64000 (8) 18.6 16.6, (12) 19.6 19.6; V=128256 [30] 18.4 17.1, [36] 19.0 19.5, (4)
-//          18.9 17.3, (6) 20.1 20.9
+//          18.9 17.3, (5) 19.7 19.1, (6) 20.1 20.9; V=256000, 5 of 4 21.3 20.7; V=210901, 2 of 14 23.6 21.7
 //          binary32 V=32000 [30] 13.8 13.8, [60] 15.1 15.5, 2 of 60 19.2 18.0; V=64000 (4) 15.4 16.1, (6) 18.6 17.8, (12) 23.4 23.0; V=128256 (3) 18.8
-//          18.0, (4) 19.8 19.7, (5) 22.4 23.8.  (From 1 to 2 million entries the teams' one step is the faster one.)
-//     TV   bfloat16 V=32000 [60] 15.7 14.9; V=64000 (4) 14.9 14.6, (6) 15.2 16.2; V=128256 (2) 15.1 15.2, (3) 15.6 16.4
-//          binary32 V=32000 [30] 13.6 14.5, [60] 15.1 16.1, 2 of 60 18.7 18.2; V=64000 (4) 15.2 17.2, (8) 19.4 19.2; V=128256 (3) 18.6 18.6, (4) 19.4 20.5
+//          18.0, (4) 19.8 19.7, (5) 22.4 23.8.  (From 1 million entries on, where the teams need one step, about 2 million, that is the faster one.)
+//     TV   bfloat16 V=32000 [60] 15.7 14.9; V=64000 (4) 14.9 14.6, (6) 15.2 16.2; V=128256 (2) 15.1 15.2, (3) 15.6 16.4; V=200000, 4 of 4 18.1 17.6,
+//          6 of 4 19.6 20.1; rows that are not 16-byte aligned V=40265, 21 of 4 19.7 17.6, V=235817, 2 of 9 22.3 19.1
+//          binary32 V=32000 [30] 13.6 14.5, [60] 15.1 16.1, 2 of 60 18.7 18.2; V=64000 (4) 15.2 17.2, (8) 19.4 19.2; V=128256 (3) 18.6 18.6, (4) 19.4 20.5;
+//          V=98752 [41], three steps of the teams, 21.5 20.6
 //     KL   binary32 V=32000 [60] 16.5 15.8; V=64000 (6) 21.0 18.7, (12) 27.1 24.6; V=128256 (4) 22.0 21.7, (6) 26.8 27.2; bfloat16 has a single pass in large
 //          calls: V=32000 [30] 13.3 14.9
 //     Reducible FSD: JS bfloat16 V=64000 (12) 20.5 19.3, V=128256 (4) 19.6 17.1, (6) 20.9 21.0; TV V=64000 (8) 19.5 17.2, V=128256 (5) 20.3 20.9.
@@ -373,18 +375,24 @@ void launch_sample(int dtype, int load, int kind, dim3 grid, size_t lds, hipStre
 //          11.9, 12 of 5 binary32 14.2 15.3 15.1; V=64000 [30] bfloat16 16.3 14.2 15.0; V=128256 (3) 16.4 16.0 16.5; KL binary32 V=64000 (6) 20.9 19.1
 //          20.5; but TV binary32 V=64000 (4) 14.6 17.5 15.3.
 struct SmallForms { bool reduction, whole, whole_replayed; };
-SmallForms small_forms(int kind, int dtype, int div, int B, int rows, long V) {
+SmallForms small_forms(int kind, int dtype, int div, int B, int rows, long V, bool aligned) {
     constexpr long M = 1L << 20;
-    const bool bf16 = dtype == FSD_BF16, tv = div == FSD_DIV_TV, single_pass = bf16 && div == FSD_DIV_KL, long_rows = V > 3L << 15;
+    const bool bf16 = dtype == FSD_BF16, tv = div == FSD_DIV_TV, js = div == FSD_DIV_JS, single_pass = bf16 && div == FSD_DIV_KL, long_rows = V > 3L << 15;
     const long entries = static_cast<long>(B) * rows * V, drawn = static_cast<long>(B) * (rows + 1) * V, bytes = drawn * (bf16 ? 2 : 4);
     const bool ratio = kind == KIND_RFSD;
     SmallForms f{false, false, false};
     if (single_pass) f.reduction = false;   // (reducible FSD: its normalisers' sums are float64 there)
     else if (ratio) f.reduction = entries <= (tv ? 9 * M / 2 : 6 * M);
-    else if (tv) f.reduction = bf16 ? entries <= 2 * M : (entries > 2 * M && entries <= 9 * M / 2 && !long_rows);
+    else if (bf16 && js) f.reduction = entries <= (!long_rows || V > 1L << 17 || !aligned ? 6 * M : kind == KIND_CHAIN ? 5 * M : 4 * M);   // (4 slots a lane, many members)
+    else if (bf16) f.reduction = entries <= (!aligned ? 9 * M / 2 : V > 1L << 17 ? 15 * M / 4 : 2 * M);
     else if (div == FSD_DIV_KL) f.reduction = entries <= 6 * M;
-    else f.reduction = entries <= (long_rows ? 4 * M : 6 * M) && (bf16 || entries <= M || entries > 2 * M);
-    const long most = single_pass ? 40 * M : 120 * M;   // rows times bytes drawn from
+    else {
+        // pairs that the binary32 teams take in a step (8 slots a lane, a wavefront a SIMD)
+        const long step = max_resident_wavefronts() / 8 / team_size((V + 3) / 4, 8), pairs = static_cast<long>(B) * rows;
+        if (js) f.reduction = entries <= (long_rows ? 4 * M : 6 * M) && (entries <= M || pairs > step);
+        else f.reduction = entries <= (long_rows ? 4 * M : 9 * M / 2) && pairs > (long_rows ? 2 * step : step);
+    }
+    const long most = single_pass ? 40 * M : js && !bf16 ? 144 * M : 120 * M;   // rows times bytes drawn from
     f.whole = !ratio && rows <= 32 && entries <= (single_pass ? 9 * M / 8 : 6 * M) && drawn <= 4 * M && rows * bytes <= most;
     f.whole_replayed = (tv && !bf16) || (bytes <= 6 * M && rows * bytes <= 60 * M);
     return f;
@@ -430,6 +438,7 @@ int launch_small(int div, hipStream_t st, SmallParams& P, int B, int plan_G, Sma
     if (GS > (P.nslots + round - 1) / round) GS = (P.nslots + round - 1) / round;
     if (GS > 64) GS = 64;
     if (P.nslots > GS * round * kSmallRounds) GS = 0;
+    bool no_room = false;   // (one launch in a larger shape than its teams need is slower than the teams: 7 sequences of 11, V=47744 TV 18.6 and 16.6)
     const auto launch = [&](int NV) {
         P.G = static_cast<int>(team_size(P.nslots, NV));
         const long words = static_cast<long>(P.npairs) * P.G * (4 + P.np);
@@ -442,13 +451,13 @@ int launch_small(int div, hipStream_t st, SmallParams& P, int B, int plan_G, Sma
         P.GS = few ? static_cast<int>(GS) : 0;
         P.draw_wgs = static_cast<int>(all) * P.GS;
         P.sps = P.GS ? static_cast<int>((P.nslots + P.GS - 1) / P.GS) : 0;
-        if (!P.GS && !may.reduction) return false;
+        if (!P.GS && !may.reduction) { no_room = true; return false; }
         if (captured && !may.whole_replayed) P.draw_wgs = P.GS = 0;
         return NV == 2 ? launch_small_m<BF16, 2, LD>(div, st, P, B, captured)
              : NV == 4 ? launch_small_m<BF16, 4, LD>(div, st, P, B, captured) : launch_small_m<BF16, 8, LD>(div, st, P, B, captured);
     };
     const bool two = P.npairs * team_size(P.nslots, 2) <= kSmallWaves;
-    if ((two && launch(2)) || launch(4) || launch(8)) return P.draw_wgs ? SMALL_DONE : SMALL_REDUCED;
+    if ((two && launch(2)) || launch(4) || (!no_room && launch(8))) return P.draw_wgs ? SMALL_DONE : SMALL_REDUCED;
     return SMALL_NONE;
 }
 
@@ -661,7 +670,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
         if (captured) (void)hipGetLastError();
-        may = small_forms(kind, dtype, div, B, rows, V);
+        may = small_forms(kind, dtype, div, B, rows, V, load == LOAD_ALIGNED);
         if (warped && mode == FSD_SAMPLE) may.whole = false;
     }
     if (may.whole || may.reduction) {
