@@ -30,9 +30,9 @@ namespace {
 // and then phase 2 of pair j - LAG from an older set of kept exponentials (LAG = 1, or 2 where
 // the registers allow a third set).  Memory operations return in the order they were issued,
 // which fixes the order of the requests in a step (see `step`): small exchange words first, the
-// next pair's logits as soon as phase 1 has consumed the registers (a whole step ahead where a
-// second set of logit registers fits), and nothing after that waits on memory unless a team
-// member is late.  The bfloat16 two-phase kernels (two wavefronts per SIMD) are bound by
+// next pair's logits as soon as phase 1 has consumed their registers (in the bfloat16 two-phase kernels
+// slot by slot; a whole step ahead where a second set of logit registers fits), and nothing after that
+// waits on memory unless a team member is late.  The bfloat16 two-phase kernels (two wavefronts per SIMD) are bound by
 // vector-ALU issue; the binary32 ones (one wavefront per SIMD) by the exposed latencies, which the
 // longer lag and the earlier prefetch hide.  The single-pass modes (bfloat16 KL, the normalisers
 // of strict SD) have no phase 2.  Waiting is bounded (spin_limit polls, then FSD_ROW_INTERNAL),
@@ -93,10 +93,15 @@ __device__ __forceinline__ unsigned long long* word_at(unsigned long long* p, un
 __device__ __forceinline__ const unsigned long long* word_at(const unsigned long long* p, unsigned i) {
     return reinterpret_cast<const unsigned long long*>(reinterpret_cast<const char*>(p) + i * 8u);
 }
-template <int N>
+// FRESH: the offsets are formed again at every request, from a lane number that the hoisting of loop invariants does
+// not see (kept, they take registers, and two each: the compiler only adds a 32-bit offset to a scalar pointer where
+// it sees in the same block that it is one).
+template <int N, bool FRESH = false>
 __device__ __forceinline__ void request_n(const unsigned long long* p, int GW, int base, unsigned long long (&w)[N],
                                           bool spread = true) {
-    const int m = base + static_cast<int>(threadIdx.x & 63);
+    int lane = static_cast<int>(threadIdx.x & 63);
+    if constexpr (FRESH) asm volatile("" : "+v"(lane));
+    const int m = base + lane;
     const int mm = spread ? ((m < GW) ? m : GW - 1) : 0;
     const unsigned long long* const mine = word_at(p, static_cast<unsigned>(mm * N));
 #pragma unroll
@@ -335,6 +340,45 @@ __device__ __forceinline__ void pointwise_term(float p, float q, float& acc) {
     }
 }
 
+// Largest of a lane's bfloat16 logits, two at a time as they lie in their words: bfloat16 numbers order like their bit
+// patterns as signed 16-bit integers, but for two negative ones, which order the other way round.  So the result is the
+// maximum where it is not negative, and otherwise some negative value; a wavefront whose largest is negative (all
+// of its slice is) looks again with packed_max_negative, where the smallest pattern is the largest number.  A masked entry is
+// -inf or a low value and never the maximum; a NaN or +inf may be, in a row that is unusable then.  One instruction a word, where
+// a shift and two halves of v_max3_f32 took two (72 instructions fewer a step of 96 logits, which alone changed no call's time,
+// and 3 to 36 registers fewer, which is what lets the requests of the next pair's logits move up: see EARLY).
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+template <int NV>
+__device__ __forceinline__ float packed_max(const uint4 (&r)[NV]) {
+    const auto words = [](unsigned w) { return __builtin_bit_cast(s16x2, w); };
+    s16x2 m0 = words(r[0].x), m1 = words(r[0].y), m2 = words(r[0].z), m3 = words(r[0].w);
+#pragma unroll
+    for (int k = 1; k < NV; ++k) {
+        m0 = __builtin_elementwise_max(m0, words(r[k].x));
+        m1 = __builtin_elementwise_max(m1, words(r[k].y));
+        m2 = __builtin_elementwise_max(m2, words(r[k].z));
+        m3 = __builtin_elementwise_max(m3, words(r[k].w));
+    }
+    m0 = __builtin_elementwise_max(m0, m2);
+    m1 = __builtin_elementwise_max(m1, m3);
+    const unsigned w = __builtin_bit_cast(unsigned, __builtin_elementwise_max(m0, m1));
+    const int lo = static_cast<int>(w << 16), hi = static_cast<int>(w & 0xFFFF0000u);
+    return __int_as_float(lo > hi ? lo : hi);
+}
+template <int NV>
+__device__ __forceinline__ float packed_max_negative(const uint4 (&r)[NV]) {
+    const auto words = [](unsigned w) { return __builtin_bit_cast(u16x2, w); };
+    u16x2 m = words(0xFFFFFFFFu);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        m = __builtin_elementwise_min(__builtin_elementwise_min(m, words(r[k].x)), words(r[k].y));
+        m = __builtin_elementwise_min(__builtin_elementwise_min(m, words(r[k].z)), words(r[k].w));
+    }
+    const unsigned w = __builtin_bit_cast(unsigned, m), lo = w << 16, hi = w & 0xFFFF0000u;
+    return __uint_as_float(lo < hi ? lo : hi);
+}
+
 template <int I> struct SetId { static constexpr int value = I; };
 template <bool B> struct BoolTag { static constexpr bool value = B; };
 
@@ -442,17 +486,19 @@ void pair_kernel(PairParams P) {
     // words requested a whole step before they are used.)
     constexpr int LAG = (TWO_PHASE && !BF16 && NV == 8) ? 2 : 1;
     constexpr int NB = LAG + 1;                      // sets of kept exponentials
+    // EARLY: the next pair's logits are requested slot by slot, each as soon as the exponentials of this pair's slot have
+    // been formed, so that they are on their way for half a phase longer than if all were asked for behind the post (which cost
+    // C2's kernel 7 us of 61 in waits for logits, and C4's 20 of 167: both measured with the reads replaced by
+    // cached ones).  The exchange words are asked for right before the first of these requests, not at the top of the step: more members have
+    // posted by then, so fewer wavefronts have to ask again, behind the prefetch.  Whole calls (us), all requests
+    // behind the post, slot by slot, and with the words behind the first slot's exponentials: C2 72.9, 70.0, 69.6; C4 186.6, 184.1, 180.3;
+    // behind the second or third slot's 69.7 and 181.1, 69.8 and 181.8.  TV: C2 74.3 -> 72.0, C4 201 -> 198.  The
+    // single-pass modes do not gain (strict SD at C2 66.5 -> 67.8).
+    constexpr bool EARLY = BF16 && TWO_PHASE;
     constexpr int NC = (NE + 3) / 4;                 // chunks of four per row
     constexpr float kTiny = 2e-38f;   // floor of u and v under the logarithm (their weights are then zero or negligible),
                                       // and of p and q where both are normalised (KL)
     constexpr int kWavesPerWG = kWG / 64;
-
-    // IEEE handling of signalling NaNs off (bit 9 of the mode register): a maximum with one is the other operand.  The
-    // maximum pass over packed bfloat16 words reads every word whose upper logit is masked as one, and with it on the maximum of the words
-    // before such a word was lost (sparse rows: a reference exponent too low, and infinite exponentials where the row's
-    // largest logits lay 88 above it).  Nothing else here sees one but from an unusable row.  (As the builtin, which tells
-    // the compiler that the mode changes, it cost the kernel on trees 0.6 %: C4 188.4 -> 189.5 us a call.)
-    if constexpr (BF16) asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 9, 1), 0" ::: "memory");
 
     // the wavefront's number as a scalar: everything derived from it (member, slot range, exchange
     // addresses) then lives in scalar registers
@@ -466,8 +512,9 @@ void pair_kernel(PairParams P) {
     // chunks there: that is what lets them hold 6 slots per lane (96 logits a step) in 256 registers,
     // and with two workgroups of 80 KB it takes all of a compute unit's LDS.  (TV at 5 slots per lane,
     // a shape of the tuning hook, keeps one.)
-    // (The least that leaves no register spilled on aligned rows.  Unaligned rows need a few registers more, for the
-    // slot at the end of the row: JS spills 6, TV 5, the entropy form on trees 3.)
+    // (The least that leaves no register of a step spilled in the entropy form, but for one address of a branch that only a
+    // wait that has expired takes.  JS and TV have 30 registers to spare with it; with 3 chunks in LDS JS takes the same time and
+    // TV is slower, C2 72.0 -> 73.6 us a call.)
     constexpr int NL = (JSE || (BF16 && NV == 6 && TWO_PHASE)) ? 5 : (BF16 && NV == 5 && MODE == MODE_TV) ? 1 : 0;
     __shared__ float4 lds_keep[NL ? NB * NL * 2 * kWG : 1];
     auto put4 = [&](auto S, int c, const float (&t4)[4], const float (&d4)[4]) __attribute__((always_inline)) {
@@ -568,9 +615,9 @@ void pair_kernel(PairParams P) {
     // target rows of the pair in work, of the one before it and of the one requested last (entropy-form JS on
     // a tree: a pair whose target row is its predecessor's takes over that row's exponentials and sums)
     const char *tp_prev = nullptr, *tp_cur = nullptr, *tp_next = nullptr;
-    auto load_item = [&](uint4 (&ra)[NV], uint4 (&rb)[NV], int pair, bool wanted = true) __attribute__((always_inline)) {
-        const char *tptr, *dptr;
-        // the requests come in the order of the team's pairs (the last one may be repeated)
+    // the rows of the pair whose logits are requested next: the requests come in the order of the team's pairs (the
+    // last one may be repeated)
+    auto next_rows = [&](int pair, const char*& tptr, const char*& dptr) __attribute__((always_inline)) {
         while (load_pair < pair) {
             load_pair += pstep;
             load_j += step_j;
@@ -578,6 +625,24 @@ void pair_kernel(PairParams P) {
             if (load_j >= P.rows) { load_j -= P.rows; ++load_b; }
         }
         row_ptrs_bj(pair, load_b, load_j, tptr, dptr);
+    };
+    // slot k of both rows, for the lane whose first slot is `first` (not wanted: one cached slot for all lanes)
+    auto load_one = [&](uint4& a, uint4& b, int k, const char* tptr, const char* dptr, bool wanted, int first) __attribute__((always_inline)) {
+        if constexpr (LD == LOAD_WIDE) {
+            // (one minimum keeps a lane inside the slice and inside the row)
+            const unsigned off = static_cast<unsigned>(first) * 16u + 1024u * k, limit = wanted ? off_last : 0u;
+            a = load_16<LD, !TSHARED>(tptr, off < limit ? off : limit);
+            b = load_16<LD, true>(dptr, off < limit ? off : limit);
+        } else {
+            const int sk = first + 64 * k;
+            const long sl = wanted ? (sk < sl_end ? sk : sl_last) : 0;
+            a = load_slot<BF16, LD, !TSHARED>(tptr, sl, P.V);
+            b = load_slot<BF16, LD, true>(dptr, sl, P.V);
+        }
+    };
+    auto load_item = [&](uint4 (&ra)[NV], uint4 (&rb)[NV], int pair, bool wanted = true) __attribute__((always_inline)) {
+        const char *tptr, *dptr;
+        next_rows(pair, tptr, dptr);
         [[maybe_unused]] const bool again = tptr == tp_next;   // the row requested last
         tp_next = tptr;
         // A draft row is read once.  So is a target row of a chain (but for the one the token is drawn
@@ -607,28 +672,20 @@ void pair_kernel(PairParams P) {
             return;
         }
 #pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            if constexpr (LD == LOAD_WIDE) {
-                // (one minimum keeps a lane inside the slice and inside the row; not wanted: one cached slot)
-                const unsigned off = static_cast<unsigned>(first) * 16u + 1024u * k, limit = wanted ? off_last : 0u;
-                ra[k] = load_16<LD, !TSHARED>(tptr, off < limit ? off : limit);
-                rb[k] = load_16<LD, true>(dptr, off < limit ? off : limit);
-            } else {
-                const int sk = first + 64 * k;
-                const long sl = wanted ? (sk < sl_end ? sk : sl_last) : 0;   // not wanted: one cached slot for all lanes
-                ra[k] = load_slot<BF16, LD, !TSHARED>(tptr, sl, P.V);
-                rb[k] = load_slot<BF16, LD, true>(dptr, sl, P.V);
-            }
-        }
+        for (int k = 0; k < NV; ++k) load_one(ra[k], rb[k], k, tptr, dptr, wanted, first);
     };
+    // (EARLY, the kernels short of scalar registers: the bounds are hidden from the hoisting of loop invariants, which kept a
+    // mask for every slot across the loop, spilled to lanes of a vector register.  The binary32 kernels, one wavefront a SIMD, are
+    // 1 to 2 % faster with the masks kept.)
     auto fill_unowned = [&](uint4 (&ra)[NV], uint4 (&rb)[NV]) __attribute__((always_inline)) {
+        int first = sl0, end = sl_end;
         if constexpr (LD == LOAD_WIDE) {
             // the slot that reaches past the end of the row belongs to one lane of the team's last member
             if (s1 > s0 && s1 * VE > P.V) {
-                asm volatile("");   // stays a branch
+                if constexpr (EARLY) asm volatile("" : "+v"(first), "+s"(end)); else asm volatile("");   // stays a branch
 #pragma unroll
                 for (int k = 0; k < NV; ++k) {
-                    if (sl0 + 64 * k == sl_end - 1) {
+                    if ((EARLY ? first : sl0) + 64 * k == (EARLY ? end : sl_end) - 1) {
                         settle_slot<BF16, LD>(ra[k], sl_end - 1, P.V, JSE ? kJsFill : slot_neg_inf<BF16>().x);
                         settle_slot<BF16, LD>(rb[k], sl_end - 1, P.V, JSE ? kJsFill : slot_neg_inf<BF16>().x);
                     }
@@ -636,21 +693,23 @@ void pair_kernel(PairParams P) {
             }
         }
         if (fill_needed) {
+            int from = static_cast<int>(s0);
+            if constexpr (EARLY) asm volatile("" : "+v"(first), "+s"(end), "+s"(from));
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
                 // first the question that has one answer for the whole wavefront (does slot k reach past
                 // the slice at all?): a scalar branch skips the full slots, and only the one or two at the
                 // end of the slice go through the per-lane selection
-                if (s0 + 64 * (k + 1) > s1) {
+                if (EARLY ? from + 64 * (k + 1) > end : s0 + 64 * (k + 1) > s1) {
                     if constexpr (JSE) {
                         // (a finite logit far below everything: exponential 0 and e x = 0, where -inf gives NaN)
                         asm volatile("");   // stays a branch: only a team's last member with slots has such lanes
-                        if (sl0 + 64 * k >= sl_end) {
+                        if ((EARLY ? first : sl0) + 64 * k >= (EARLY ? end : sl_end)) {
                             ra[k] = make_uint4(kJsFill, kJsFill, kJsFill, kJsFill);
                             rb[k] = make_uint4(kJsFill, kJsFill, kJsFill, kJsFill);
                         }
                     } else {
-                        if (sl0 + 64 * k >= sl_end) { ra[k] = slot_neg_inf<BF16>(); rb[k] = slot_neg_inf<BF16>(); }
+                        if ((EARLY ? first : sl0) + 64 * k >= (EARLY ? end : sl_end)) { ra[k] = slot_neg_inf<BF16>(); rb[k] = slot_neg_inf<BF16>(); }
                     }
                 }
             }
@@ -1069,9 +1128,9 @@ void pair_kernel(PairParams P) {
     // what can overlap: the small exchange words (the previous pair's team words, and the words of a
     // pair this wavefront has to finish) are requested first, at the top of the step, where they sit
     // behind the logits that are about to be used anyway; the logits of the next pair are requested
-    // once phase 1 has consumed the registers (in the two-phase modes after this wavefront's sums are
-    // posted: the team's next step waits for every member's post, so nothing that can wait comes
-    // before it); and nothing after that waits on memory unless a team member is late (then the
+    // once phase 1 has consumed the registers (EARLY: slot by slot, with the words before the first of them; in the binary32
+    // two-phase modes after this wavefront's sums are posted: the team's next step waits for every member's post, so nothing
+    // that can wait comes before it); and nothing after that waits on memory unless a team member is late (then the
     // words are asked for again, behind the prefetch).
     // (ra, rb) hold the logits of `pair`, the next pair's go to (rna, rnb).  Where registers allow
     // (DEEP) these are different sets and the next pair is requested at the top of the step, a whole
@@ -1088,17 +1147,19 @@ void pair_kernel(PairParams P) {
         // overlaps with the memory latency and does not need it.
         __builtin_amdgcn_s_setprio(3);
         asm volatile("" ::: "memory");
-        if constexpr (TWO_PHASE)
-        {
-            const unsigned long long* const p1 = part1 + words_at(due.pair >= 0 ? due.pair : pair, N1);
-            request_n<2>(p1, GW, 0, w);
-            request_n<2>(p1, GW, 64, w2, GW > 64);
-        }
-        request_n<FW>(finw + words_at(fpair >= 0 ? fpair : pair, FW), GW, 0, fw, fpair >= 0);
+        auto request_words = [&]() __attribute__((always_inline)) {
+            if constexpr (TWO_PHASE) {
+                const unsigned long long* const p1 = part1 + words_at(due.pair >= 0 ? due.pair : pair, N1);
+                request_n<2, EARLY>(p1, GW, 0, w);
+                request_n<2, EARLY>(p1, GW, 64, w2, GW > 64);
+            }
+            request_n<FW, EARLY>(finw + words_at(fpair >= 0 ? fpair : pair, FW), GW, 0, fw, fpair >= 0);
+        };
+        if constexpr (!EARLY) request_words();
         if constexpr (DEEP) {
             // this pair's logits arrived in (ra, rb) during the last step; ask for the next pair's now
-            const bool more = pair + pstep < pair_end;
-            load_item(rna, rnb, more ? pair + pstep : pair, more);
+            const bool deep_more = pair + pstep < pair_end;
+            load_item(rna, rnb, deep_more ? pair + pstep : pair, deep_more);
         }
         asm volatile("" ::: "memory");
         fill_unowned(ra, rb);
@@ -1112,31 +1173,18 @@ void pair_kernel(PairParams P) {
         tp_cur = tp_next;
         const bool same_target = (SHARE || SHARE_SUM) && iter > 0 && tp_cur == tp_prev;
         float kt, kd, st = 0.0f, sd = 0.0f, wacc = 0.0f, dmax = JSE ? 0.0f : neg_inf();
+        const bool more = pair + pstep < pair_end;
+        [[maybe_unused]] const char *next_t = nullptr, *next_d = nullptr;
+        if constexpr (EARLY) {
+            next_rows(more ? pair + pstep : pair, next_t, next_d);
+            tp_next = next_t;
+        }
         auto phase1 = [&](auto SAME_T) __attribute__((always_inline)) {
             constexpr bool SAME = decltype(SAME_T)::value;
             float mt = neg_inf(), md = neg_inf();
             if constexpr (BF16) {
-                // A 32-bit word holds two bfloat16 logits.  Read as binary32 it is its upper logit plus a
-                // perturbation below that logit's last place, so the maximum over the words as they are has
-                // the largest upper logit in its upper half: only the lower logits need a shift.  (A word
-                // whose upper logit is +-inf or NaN reads as NaN and is dropped: a masked entry is never
-                // the maximum, and the exponential pass still sees the +inf or NaN that spoils a row.)
-                float th = neg_inf(), tl = neg_inf(), dh = neg_inf(), dl = neg_inf();
-#pragma unroll
-                for (int k = 0; k < NV; ++k) {
-                    if constexpr (!SAME) {
-                        th = fmaxf(fmaxf(th, __uint_as_float(ra[k].x)), __uint_as_float(ra[k].y));
-                        th = fmaxf(fmaxf(th, __uint_as_float(ra[k].z)), __uint_as_float(ra[k].w));
-                        tl = fmaxf(fmaxf(tl, __uint_as_float(ra[k].x << 16)), __uint_as_float(ra[k].y << 16));
-                        tl = fmaxf(fmaxf(tl, __uint_as_float(ra[k].z << 16)), __uint_as_float(ra[k].w << 16));
-                    }
-                    dh = fmaxf(fmaxf(dh, __uint_as_float(rb[k].x)), __uint_as_float(rb[k].y));
-                    dh = fmaxf(fmaxf(dh, __uint_as_float(rb[k].z)), __uint_as_float(rb[k].w));
-                    dl = fmaxf(fmaxf(dl, __uint_as_float(rb[k].x << 16)), __uint_as_float(rb[k].y << 16));
-                    dl = fmaxf(fmaxf(dl, __uint_as_float(rb[k].z << 16)), __uint_as_float(rb[k].w << 16));
-                }
-                if constexpr (!SAME) mt = fmaxf(__uint_as_float(__float_as_uint(th) & 0xFFFF0000u), tl);
-                md = fmaxf(__uint_as_float(__float_as_uint(dh) & 0xFFFF0000u), dl);
+                if constexpr (!SAME) mt = packed_max<NV>(ra);
+                md = packed_max<NV>(rb);
             } else {
 #pragma unroll
                 for (int k = 0; k < NV; ++k) {
@@ -1152,6 +1200,14 @@ void pair_kernel(PairParams P) {
             }
             PT(0);   // load wait + max pass
             if constexpr (SAME) md = wave_max(md); else wave_max2(mt, md);
+            if constexpr (BF16) {
+                const int sign_t = SAME ? 0 : __float_as_int(mt), sign_d = __float_as_int(md);
+                if ((sign_t | sign_d) < 0) {
+                    asm volatile("");   // stays a branch
+                    if (sign_t < 0) mt = wave_max(packed_max_negative<NV>(ra));
+                    if (sign_d < 0) md = wave_max(packed_max_negative<NV>(rb));
+                }
+            }
             kt = SAME ? (SHARE_SUM ? last_kt : due.kt) : reference_exponent(mt);
             kd = reference_exponent(md);
 #pragma unroll
@@ -1205,6 +1261,17 @@ void pair_kernel(PairParams P) {
                         put4(SC, k * (VE / 4) + h, t4, d4);
                     }
                 }
+                if constexpr (EARLY) {
+                    // (both arms of the branch on a shared target row make the same requests in the same order, so the
+                    // compiler's count of what is in flight stays exact)
+                    asm volatile("" ::: "memory");
+                    if (k == 0) request_words();
+                    asm volatile("" ::: "memory");
+                    int first = sl0;
+                    if constexpr (RECOMPUTE_SLOTS) asm volatile("" : "+v"(first));
+                    load_one(rna[k], rnb[k], k, next_t, next_d, more, first);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
         };
         if constexpr (SHARE || SHARE_SUM) {
@@ -1241,10 +1308,9 @@ void pair_kernel(PairParams P) {
         asm volatile("" ::: "memory");
         // ---- the registers that held the logits are free: fetch the next pair (the request is
         // unconditional: the last step asks for one slot of its own pair, which the caches hold).  In the
-        // two-phase modes only after the post below: every member's post is what the whole team's next
-        // step waits for (bfloat16 JS: C2 -2 %, C4 -4 % against the request first).
+        // binary32 two-phase modes only after the post below: every member's post is what the whole team's next
+        // step waits for.
         if constexpr (!DEEP && !TWO_PHASE) {
-            const bool more = pair + pstep < pair_end;
             load_item(rna, rnb, more ? pair + pstep : pair, more);
             __builtin_amdgcn_s_setprio(0);
         }
@@ -1284,8 +1350,7 @@ void pair_kernel(PairParams P) {
         if (pl < N1) post64(post_at, mine);
         asm volatile("" ::: "memory");
         if constexpr (TWO_PHASE) {
-            if constexpr (!DEEP) {
-                const bool more = pair + pstep < pair_end;
+            if constexpr (!DEEP && !EARLY) {
                 load_item(rna, rnb, more ? pair + pstep : pair, more);
             }
             __builtin_amdgcn_s_setprio(0);   // only now does the priority drop

@@ -778,3 +778,46 @@ def test_small_kl_is_as_exact_as_in_large_calls(torch_cuda, oracle, kind, sigma,
     rms = {small: float(np.sqrt(np.mean(np.concatenate(e) ** 2))) for small, e in err.items()}
     print(kind, sigma, V, "rms error against 64 bits: small calls", rms[True], "large", rms[False], flush=True)
     assert rms[True] <= 1.2 * rms[False]
+
+
+@pytest.mark.parametrize("V", [5, 3071, 6145, 20000])
+@pytest.mark.parametrize("kind", ["log-probabilities", "one slice", "signed zeros", "masked"])
+def test_largest_logit_is_negative(torch_cuda, oracle, V, kind):
+    """Bfloat16 rows in the kernels of large calls where a wavefront's largest logit is negative, whose packed maximum is taken
+    in a second look: all of the row, all but one slice of it, beside signed zeros, between masked entries; a chain, a tree
+    whose siblings share target rows, and strict SD."""
+    B, K = 2, 5
+    rng = np.random.default_rng(V)
+    inp = synth.chain_inputs(B, K, V, "f32", "gauss2", 0.7, seed=V)
+    t, d = inp["target"], inp["draft"]
+    # (masked at the same places: with 3e38 in the draft alone KL is of that size, past binary32's largest number in a sum of logits)
+    masked = rng.permutation(V)[: V // 2]
+    for x in (t, d):
+        x -= x.max(-1, keepdims=True) + np.float32(1.0)
+        if kind == "one slice":
+            x[..., -min(V, 70):] += np.float32(9.0)
+        elif kind == "signed zeros":
+            x[..., rng.permutation(V)[: V // 3 + 1]] = -0.0
+            x[..., rng.permutation(V)[: V // 3]] = 0.0 if V % 2 else -0.0
+        elif kind == "masked":
+            x[..., masked] = -np.inf if V % 2 else np.float32(-3.0e38)
+    t, d = synth.to_bf16_bits(t), synth.to_bf16_bits(d)
+    case = dict(target=t, draft=d, cand=inp["cand"])
+    parent = np.broadcast_to(np.array([-1, -1, 0, 0, 2], dtype=np.int32), (B, K)).copy()
+    env = pu.Envelope("bf16")
+    prev = fsd.debug_set_small_calls(False)
+    try:
+        for div, T in ((fsd.DIV_JS, 0.06), (fsd.DIV_TV, 0.25), (fsd.DIV_KL, 0.25)):
+            what = f"{kind} V={V} div={div}"
+            print(what, flush=True)
+            g = run_chain(torch_cuda, case, T, div, seed=5, offset=2)
+            pu.check_chain(g, oracle.verify_chain(t, d, inp["cand"], T, div, seed=5, offset=2), T, pu.rel_tol("bf16"), what, envelope=env)
+            g = run_tree(torch_cuda, dict(target=t, draft=d, node_tokens=inp["cand"], parent=parent), T, div, 4, seed=5, offset=2)
+            o = oracle.verify_tree(t, d, inp["cand"], parent, 4, T, div, oracle.SAMPLE, seed=5, offset=2)
+            pu.check_tree(g, o, T, pu.rel_tol("bf16"), f"tree {what}", envelope=env)
+        dev = pu.to_dev(case, ("target", "draft", "cand"))
+        out = fsd.sd_verify_chain(dev["target"], dev["draft"], dev["cand"], seed=5, offset=2)
+        torch_cuda.cuda.synchronize()
+        check_sd(pu.host(out, pu.SD_KEYS), oracle.sd_verify_chain(t, d, inp["cand"], seed=5, offset=2), f"SD {kind} V={V}")
+    finally:
+        fsd.debug_set_small_calls(prev)
