@@ -28,7 +28,8 @@ struct SampleParams {
     int32_t* out_tokens;
     int32_t* path_nodes;      // tree only
     int32_t* row_status;      // optional
-    const float* thr;         // optional [B]: warpers, smallest kept scaled logit of the sampled row
+    int cut;                  // warpers: the scale and the threshold below apply (FSD_SAMPLE only)
+    const float* thr;         // optional [B]: warpers, smallest kept scaled logit of the sampled row (nullptr: all are kept)
     float inv_temp;           // warpers: binary32(1 / temperature), 1 otherwise
     uint4* clear;             // words of the reduction that count by the call's number (its arrival slots, see pair_kernel.h; the
     long clear16;             // words of a captured small_call), in 16-byte units: they go back to zero here
@@ -75,6 +76,7 @@ __device__ __forceinline__ float max3_nan(float a, float b, float c) {   // the 
 
 // The best score over slots [s0, s1) of the row, dealt to the workgroup's threads: of the row's entries or, with
 // `residual`, of the positive part of p - q.  bad: a NaN or +inf logit was seen.  s_thr: the workgroup's shared score.
+// STRIDE: the workgroup's threads.
 //
 // What bounds it: vector-ALU issue, most of it the random numbers (ten rounds of two 64-bit products per four entries);
 // in small calls the chain from the row's first load to its last score.  Beside the random numbers an entry costs a
@@ -85,13 +87,13 @@ __device__ __forceinline__ float max3_nan(float a, float b, float c) {   // the 
 // round's rows, the draft's too, before it works on this one's.  (The residual's draw used to score the row's own
 // entries along with it, for the case that no entry has any positive part; that case is now a second pass of the last
 // workgroup.  With the earlier request of the draft row: strict SD on 64 rows of 128256 bfloat16 entries 23.1 -> 20.0 us.)
-template <bool BF16, int LD, bool TREESD, int NE>
+template <bool BF16, int LD, bool TREESD, int NE, int STRIDE = kWG>
 __device__ __forceinline__ void draw_share(const DrawArgs& A, int b, const char* trow, bool residual, const char* drow,
                                            float lt, float ld, [[maybe_unused]] const DrawChain& C, long s0, long s1, int tid,
                                            unsigned* s_thr, Best& best, int& bad) {
     constexpr int VE = Slot<BF16>::VE;
     [[maybe_unused]] constexpr int ES = BF16 ? 2 : 4;
-    constexpr int NS = NE / VE, STRIDE = kWG;
+    constexpr int NS = NE / VE;
     // a score the winner is known to reach (see the bounds below), from the lowest finite one up: an entry
     // without mass, masked or cut off by the warpers, stays below
     float thr = -FLT_MAX;
@@ -323,6 +325,12 @@ __device__ __forceinline__ void write_path(int lane, int max_depth, int winner, 
     if ((path >> lane) & 1) { pn[my_dep - 1] = lane; out[my_dep - 1] = my_tok; }
 }
 
+// the tokens of a chain of at most 64 positions, one a lane: n accepted ones, the drawn token, padding (all of it padding
+// if the sequence has failed)
+__device__ __forceinline__ void write_chain(int lane, int rows, int n, bool failed, int my_tok, int token, int32_t* out) {
+    for (int i = lane; i <= rows; i += 64) out[i] = (failed || i > n) ? -1 : (i == n) ? token : my_tok;
+}
+
 // A workgroup's share of a sequence's draw in one word that says by itself whether it has arrived: score, then the flag
 // of an unusable logit and the index plus one (all ones: no entry).  Never zero.
 __device__ __forceinline__ unsigned long long share_word(Best m, int bad) {
@@ -333,6 +341,19 @@ __device__ __forceinline__ Best share_best(unsigned long long w) {
     const unsigned at = static_cast<unsigned>(w) & 0x7FFFFFFFu;
     return Best{__uint_as_float(static_cast<unsigned>(w >> 32)), at == 0x7FFFFFFFu ? 0x7FFFFFFF : static_cast<int>(at) - 1};
 }
+// A call that has failed (every workgroup of the last kernel sees that): the last sequence to finish puts the
+// failure word, which nothing looks at after that kernel, back to zero, so that the same call replayed from a captured
+// graph, with the same number, does not find a failure of the last time.  (gridDim.y: the sequences.)
+__device__ __forceinline__ void sequence_of_failed_call_done(const Ws& w) {
+    const unsigned done = atomicAdd(w.counters + 4, 1u);
+    if (done == gridDim.y - 1) __hip_atomic_store(reinterpret_cast<unsigned long long*>(w.counters + 2), 0ull, __ATOMIC_RELAXED, AGENT);
+}
+// The reduction kernel has ended: its words go back to zero, so that the same call replayed from a captured graph, with the
+// same number, does not find them set.
+__device__ __forceinline__ void clear_words(uint4* words, long n16, long thread, long nthreads) {
+    for (long i = thread; i < n16; i += nthreads) words[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 // How often the sequence's last workgroup looks for a share.  The workgroups it waits for come before it in the grid
 // and wait for nobody, so they have started before it and end whatever else the device does.
 constexpr unsigned kShareLooks = 1u << 22;
@@ -537,8 +558,8 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
         Best best{neg_inf(), 0x7FFFFFFF};
         int bad = 0;
         if (!status) {
-            const bool cut = P.thr != nullptr && P.mode == FSD_SAMPLE;
-            const DrawArgs A{P.V, P.mode, P.seed_lo, P.seed_hi, P.off_lo, P.off_hi, cut, cut ? P.thr[b] : neg_inf(), P.inv_temp};
+            const bool cut = P.cut && P.mode == FSD_SAMPLE;
+            const DrawArgs A{P.V, P.mode, P.seed_lo, P.seed_hi, P.off_lo, P.off_hi, cut, (cut && P.thr) ? P.thr[b] : neg_inf(), P.inv_temp};
             const DrawChain C{P.draft + static_cast<size_t>(b) * rows * static_cast<size_t>(P.V) * ES, rows, nchain, s_dyn};
             // binary32: a share of one slot a lane takes 4 entries a round, any longer one 8 (a second slot that no
             // lane has still costs its instructions; whole calls on 16 sequences of 2, V=64000: 18.5 us with 8 entries,
@@ -631,11 +652,13 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
                     }
                 }
             }
+        } else if (few) {
+            write_chain(lane, rows, n, final_status != 0, my_tok, token, out);
         } else {
             for (int i = lane; i < width; i += 64) {
                 int v = -1;
                 if (!final_status) {
-                    if (i < n) v = few ? my_tok : P.tokens[static_cast<size_t>(b) * rows + i];
+                    if (i < n) v = P.tokens[static_cast<size_t>(b) * rows + i];
                     else if (i == n) v = token;
                 }
                 out[i] = v;
@@ -644,21 +667,10 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
         if (lane == 0) {
             P.out_len[b] = n;
             if (P.row_status) P.row_status[b] = final_status;
-            // A call that has failed (every workgroup of this kernel sees that): the last sequence to finish puts the
-            // failure word, which nothing looks at after this kernel, back to zero, so that the same call replayed from a captured
-            // graph, with the same number, does not find a failure of the last time.
-            if (failed) {
-                const unsigned done = atomicAdd(P.ws.counters + 4, 1u);
-                if (done == gridDim.y - 1)
-                    __hip_atomic_store(reinterpret_cast<unsigned long long*>(P.ws.counters + 2), 0ull, __ATOMIC_RELAXED, AGENT);
-            }
+            if (failed) sequence_of_failed_call_done(P.ws);
         }
     }
-    // The reduction kernel has ended: its words go back to zero, so that the same call replayed from a captured graph, with the
-    // same number, does not find them set.
-    const long nthreads = static_cast<long>(gridDim.x) * gridDim.y * kWG;
-    for (long i = (static_cast<long>(b) * gridDim.x + gs) * kWG + tid; i < P.clear16; i += nthreads)
-        P.clear[i] = make_uint4(0u, 0u, 0u, 0u);
+    clear_words(P.clear, P.clear16, (static_cast<long>(b) * gridDim.x + gs) * kWG + tid, static_cast<long>(gridDim.x) * gridDim.y * kWG);
 }
 
 }  // namespace

@@ -519,9 +519,9 @@ constexpr long split_least(bool bf16, bool aligned, bool top_k) {
 // if it takes fewer workgroups than that for their lists to hold a large top-k.  (A list that overflows costs the last
 // workgroup the whole row again: 8 rows of 128256 bfloat16 entries, top-k 512: 69 us a call with eight workgroups a
 // row, 55 with one, 49 with four.)
-template <bool BF16, int LD>
-bool launch_warp_split(int B, hipStream_t st, const WarpParams& P) {
-    const bool want_k = P.top_k > 0 && P.top_k < P.V;
+template <bool BF16, int LD, int SHARED>
+bool launch_warp_split_k(int B, hipStream_t st, WarpParams& P) {
+    constexpr bool want_k = SHARED == SPLIT_TOP_K;
     if (P.V < split_least(BF16, LD == LOAD_ALIGNED, want_k)) return false;
     static std::atomic<long> resident[16] = {};
     int dev = 0;
@@ -530,7 +530,7 @@ bool launch_warp_split(int B, hipStream_t st, const WarpParams& P) {
     long total = resident[dev].load(std::memory_order_relaxed);
     if (total == 0) {
         int per_cu = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, warp_select<BF16, LD, true, true>, kWarpWG, 0) != hipSuccess) per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, warp_select<BF16, LD, true, SHARED>, kWarpWG, 0) != hipSuccess) per_cu = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
         (void)hipGetLastError();
         total = static_cast<long>(per_cu) * cus;
@@ -542,16 +542,29 @@ bool launch_warp_split(int B, hipStream_t st, const WarpParams& P) {
     const long by_work = (P.nslots + kWarpWG - 1) / kWarpWG;
     if (W > by_work) W = by_work;
     if (want_k) {
-        const auto fits = [&](long w) {
+        const auto needed = [&](long w) {
             const long share = (P.nslots + w - 1) / w;
-            return list_keys(P.top_k, share < kWarpWG ? share : kWarpWG) <= static_cast<long>(kSplitBytes / 4) / w - 1;
+            return list_keys(P.top_k, share < kWarpWG ? share : kWarpWG);
         };
-        while (W >= 2 && !fits(W)) --W;
+        while (W >= 2 && needed(W) > kSplitKeys / W - 1) --W;
+        // the draw in the same launch needs the places of the keys as well, twice the memory; where a sequence has that (fewer
+        // than 8 rows of the usual vocabularies under a top-k of hundreds do not), a list has as many entries as one of keys alone
+        if (P.draw && W >= 2) {
+            const long words = static_cast<long>(P.seq_bytes / 8);
+            P.list_keys = static_cast<int>((words < kSplitKeys ? words : kSplitKeys) / W - 1);
+            if (needed(W) > P.list_keys) P.draw = 0;
+        }
+        if (!P.draw && W >= 2) P.list_keys = static_cast<int>(kSplitKeys / W - 1);
     }
     if (W < 2 || (P.nslots + W - 1) / W > static_cast<long>(kSplitKeep) * kWarpWG) return false;
     g_last_selection.store(static_cast<int>(W), std::memory_order_relaxed);
-    hipLaunchKernelGGL((warp_select<BF16, LD, true, true>), dim3(static_cast<unsigned>(W), static_cast<unsigned>(B)), dim3(kWarpWG), 0, st, P);
+    hipLaunchKernelGGL((warp_select<BF16, LD, true, SHARED>), dim3(static_cast<unsigned>(W), static_cast<unsigned>(B)), dim3(kWarpWG), 0, st, P);
     return true;
+}
+
+template <bool BF16, int LD>
+bool launch_warp_split(int B, hipStream_t st, WarpParams& P) {
+    return P.top_k > 0 && P.top_k < P.V ? launch_warp_split_k<BF16, LD, SPLIT_TOP_K>(B, st, P) : launch_warp_split_k<BF16, LD, SPLIT_TOP_P>(B, st, P);
 }
 
 // how the kernels fetch a slot of these rows (see load_slot)
@@ -786,6 +799,7 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
     sp.path_nodes = path_nodes;
     sp.row_status = row_status;
     sp.ws = ws;
+    sp.cut = 0;
     sp.thr = nullptr;
     sp.inv_temp = 1.0f;
     sp.clear = clear_last;
@@ -811,7 +825,20 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         wp.area = reinterpret_cast<char*>(ws.part1);
         wp.seq_bytes = static_cast<size_t>(rows) * plan_G * 64;
         wp.spin_limit = g_spin_limit < g_selection_spin_limit ? g_spin_limit : g_selection_spin_limit;
+        wp.list_keys = 0;
+        wp.tokens = tokens;
+        wp.max_depth = max_depth;
+        wp.seed_lo = sp.seed_lo; wp.seed_hi = sp.seed_hi; wp.off_lo = sp.off_lo; wp.off_hi = sp.off_hi;
+        wp.out_len = out_len;
+        wp.out_tokens = out_tokens;
+        wp.path_nodes = path_nodes;
+        wp.row_status = row_status;
+        wp.clear = clear_last;
+        wp.clear16 = clear_last16;
         const bool want_k = top_k > 0 && top_k < V, want_p = top_p < 1.0f;
+        // the draw with the selection (by several workgroups a row), but for a recorded call whose reduction has words to be cleared
+        // where the lists go
+        wp.draw = (want_k && rows <= 64 && (clear_last == nullptr || clear_last == reinterpret_cast<uint4*>(ws.arrive))) ? 1 : 0;
         const auto warp = [&](auto kernel) {
             g_last_selection.store(1, std::memory_order_relaxed);
             hipLaunchKernelGGL(kernel, dim3(B), dim3(kWarpWG), 0, st, wp);
@@ -823,8 +850,9 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
                                                                       : launch_warp_split<true, LOAD_WIDE>(B, st, wp))
                                               : (load == LOAD_ALIGNED ? launch_warp_split<false, LOAD_ALIGNED>(B, st, wp)
                                                                       : launch_warp_split<false, LOAD_WIDE>(B, st, wp)));
-        if (split) {
-            // (launched)
+        if (split && wp.draw) return (hipGetLastError() == hipSuccess) ? FSD_OK : FSD_ERR_LAUNCH;   // (it has drawn the token as well)
+        if (split || (!want_k && !want_p)) {
+            // launched, or nothing to select: temperature alone keeps everything
         } else if (dtype == FSD_BF16) {
             if (keep) warp(warp_select<true, LOAD_ALIGNED, true>);
             else if (load == LOAD_ALIGNED) warp(warp_select<true, LOAD_ALIGNED, false>);
@@ -835,7 +863,8 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
             else if (load == LOAD_WIDE) warp(warp_select<false, LOAD_WIDE, false>);
             else warp(warp_select<false, LOAD_ELEM, false>);
         }
-        sp.thr = ws.thr;
+        if (want_k || want_p) sp.thr = ws.thr;
+        sp.cut = 1;
         sp.inv_temp = wp.inv_temp;
     }
     if (kind == KIND_TREESD) {

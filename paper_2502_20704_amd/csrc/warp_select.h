@@ -17,7 +17,8 @@ namespace {
 //   top-p   the largest t with sum_{s >= t} e^(s - max) >= top_p sum_{kept} e^(s - max), by the same
 //           select on weights; the weights are 2^40 fixed-point integers, so that the sums do not
 //           depend on the order of the atomic additions (results are the same run to run).
-// Ties at either threshold are kept.  accept_sample then drops every entry below the threshold.
+// Ties at either threshold are kept.  accept_sample then drops every entry below the threshold; or (P.draw) this kernel, which
+// has everything top-k kept in LDS by then, draws the token itself and writes the outputs.
 // What bounds it: the passes over the row (range, sums or per-thread maxima, gathering) on few compute units, the
 // selects in LDS, which are chains of barriers, and with SPLIT the round trips between the workgroups.
 
@@ -27,6 +28,18 @@ __device__ __forceinline__ unsigned ordered_key(float x) {
 }
 __device__ __forceinline__ float key_value(unsigned k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
+}
+
+// the bitwise or over the wavefront
+__device__ __forceinline__ unsigned wave_or(unsigned v) {
+    v |= static_cast<unsigned>(dpp_i<kDppSwap1>(static_cast<int>(v)));
+    v |= static_cast<unsigned>(dpp_i<kDppSwap2>(static_cast<int>(v)));
+    v |= static_cast<unsigned>(dpp_i<kDppHalfMirror>(static_cast<int>(v)));
+    v |= static_cast<unsigned>(dpp_i<kDppMirror>(static_cast<int>(v)));
+    unsigned all = 0u;
+#pragma unroll
+    for (int row = 0; row < 64; row += 16) all |= static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(v), row));
+    return all;
 }
 
 struct WarpParams {
@@ -43,7 +56,20 @@ struct WarpParams {
     // SPLIT: memory of a sequence's workgroups, seq_bytes each (the exchange words of the reduction, which has ended)
     char* area;
     size_t seq_bytes;
+    int list_keys;        // entries a workgroup's list has room for under top-k (see launch_warp_split)
     unsigned spin_limit;
+    // 1 (SPLIT under top-k, at most 64 rows, lists with room for the places as well): this kernel draws the token and writes
+    // the call's outputs, no accept_sample follows
+    int draw;
+    const int32_t* tokens;
+    int max_depth;        // tree only
+    unsigned seed_lo, seed_hi, off_lo, off_hi;
+    int32_t* out_len;
+    int32_t* out_tokens;
+    int32_t* path_nodes;  // tree only
+    int32_t* row_status;  // optional
+    uint4* clear;         // see SampleParams
+    long clear16;
     Ws ws;
 };
 
@@ -73,7 +99,12 @@ constexpr float kWarpRange = 28.0f;   // what lies further below the maximum wei
 // for one of them is the select (rows of 128256 bfloat16 entries: 64 of them under temperature 0.7, top-k 50, top-p 0.9
 // take 23 us with four workgroups each, 30 with one; 8 of them under top-p 0.95 25 us with eight, 49 with one):
 //   top-k   every workgroup leaves the entries at or above the k-th largest of its own threads' maxima (the
-//           row's k largest are among them) and counts itself; whoever counts last selects from all of them.
+//           row's k largest are among them) and counts itself; whoever counts last selects from all of them, a few
+//           hundred for the usual k, and with their places in the row draws the token from what is kept: no
+//           second kernel, whose start and passes over rows of which it drops nearly all cost more than the selection's end.
+//           Up to 1024 of them stand in the registers of every wavefront, and the wavefronts look for the cut together, each
+//           counting the entries above a candidate of its own: 4 bits a round with one barrier (count_select).  (A
+//           select by 8-bit digits in LDS has seven barriers a digit and its additions queue at a few words.)
 //   top-p   the workgroups agree on the row's range (one word each, zero until posted; the wait is bounded, and
 //           all are resident, which the host checks), add their histograms of values in memory and count
 //           themselves.  When all have (the same kind of wait) every one finds the bin of the crossing and leaves the entries its own
@@ -85,10 +116,17 @@ constexpr float kWarpRange = 28.0f;   // what lies further below the maximum wei
 constexpr int kWarpShare = 8;
 constexpr int kSplitKeep = 5;
 constexpr int kSplitBins = kWarpWG;
-constexpr size_t kSplitBytes = 16384;   // a sequence's lists: 4096 keys; or its histogram
+constexpr size_t kSplitBytes = 16384;   // a sequence's memory, at least; under top-p 1024 bins and lists of 2048 keys
+constexpr int kSplitKeys = 4096;        // keys and lengths of a sequence's lists under top-k, at most
+constexpr int kCountKeys = 1024;        // keys count_select takes
+constexpr int kRankKeys = 192;          // keys whose weights are summed up by rank, all pairs of them
 
-template <bool BF16, int LD, bool KEEP, bool SPLIT = false>
+// (two kernels, one under top-k and one under top-p alone: what they have in common is the row and the general selects, and with the
+// one's registers and code in the other the top-p calls took 2 us longer)
+enum { SPLIT_NONE = 0, SPLIT_TOP_K = 1, SPLIT_TOP_P = 2 };
+template <bool BF16, int LD, bool KEEP, int SHARED = SPLIT_NONE>
 __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
+    constexpr bool SPLIT = SHARED != SPLIT_NONE, BY_K = SHARED == SPLIT_TOP_K;
     constexpr int VE = Slot<BF16>::VE;
     constexpr int ES = BF16 ? 2 : 4;
     __shared__ unsigned long long s_hist[256];
@@ -103,12 +141,17 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     __shared__ unsigned s_prefix, s_mask, s_match;
     __shared__ unsigned long long s_need;
     __shared__ float s_max, s_min;
+    __shared__ unsigned s_round[2][kWarpWG / 64], s_score;
+    __shared__ unsigned long long s_above[kRankKeys + 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b = SPLIT ? blockIdx.y : blockIdx.x;
 
     // ---- the row the token will be drawn from: the first rejected position, or the row after the last
     // (chain); the row after the deepest node whose ancestors are all accepted, lowest index on ties (tree)
     int from = 0;
+    // P.draw: what the outputs need
+    [[maybe_unused]] int status = 0, n_acc = 0, winner = -1, my_par = -1, my_dep = 0, my_tok = 0;
+    [[maybe_unused]] bool failed = false;
     if (tid == 0) { s_n = P.rows; s_st = 0; s_match = 0u; }
     __syncthreads();
     if (P.rows <= 64) {
@@ -118,20 +161,34 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         const int pr = b * P.rows + (lane < P.rows ? lane : P.rows - 1);
         const int st = P.ws.pst[pr];
         const float div = P.ws.div[pr];
-        int my_par = P.parent ? P.parent[pr] : -1;
-        const bool failed = failure_flagged(P.ws);
+        if (P.parent) my_par = P.parent[pr];
+        if (BY_K && P.draw) my_tok = P.tokens[pr];
+        failed = failure_flagged(P.ws);
         const bool mine = lane < P.rows, ok = div <= P.T;
-        bool stop = failed || __any(mine && st != 0);
+        if (__any(mine && st != 0)) {
+            status = mine ? st : 0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) status |= __shfl_xor(status, o);
+        }
         if (P.parent == nullptr) {
             const unsigned long long no = __ballot(mine && !ok);
-            from = no ? static_cast<int>(__builtin_ctzll(no)) : P.rows;
+            from = n_acc = no ? static_cast<int>(__builtin_ctzll(no)) : P.rows;
         } else {
-            const TreePick pick = pick_path(lane, P.rows, kMaxRows, my_par, ok);
-            stop |= (pick.status & FSD_ROW_BAD_PARENT) != 0;   // accept_sample reports it
-            from = pick.winner + 1;
+            // (a path that is too deep is for whoever writes the outputs to report: a malformed tree stops both)
+            const TreePick pick = pick_path(lane, P.rows, BY_K && P.draw ? P.max_depth : kMaxRows, my_par, ok);
+            status |= pick.status;
+            if (status & FSD_ROW_BAD_PARENT) status &= ~FSD_ROW_TOO_DEEP;
+            n_acc = pick.n;
+            winner = pick.winner;
+            my_dep = pick.my_dep;
+            from = winner + 1;
         }
+        if (failed) status |= FSD_ROW_INTERNAL;
         from = __builtin_amdgcn_readfirstlane(from);
-        if (stop && tid == 0) s_st = 1;
+        status = __builtin_amdgcn_readfirstlane(status);
+        n_acc = __builtin_amdgcn_readfirstlane(n_acc);
+        winner = __builtin_amdgcn_readfirstlane(winner);
+        if (status && tid == 0) s_st = 1;
         __syncthreads();
     } else if (P.parent == nullptr) {
         for (int i = tid; i < P.rows; i += kWarpWG) {
@@ -189,8 +246,31 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         from = s_n;
         __syncthreads();
     }
+    // P.draw: the outputs of the sequence, by one wavefront
+    [[maybe_unused]] auto write_outputs = [&](int final_status, int token) __attribute__((always_inline)) {
+        const int n = final_status ? 0 : n_acc;
+        if (P.parent == nullptr) {
+            write_chain(lane, P.rows, n, final_status != 0, my_tok, token, P.out_tokens + static_cast<size_t>(b) * (P.rows + 1));
+        } else {
+            write_path(lane, P.max_depth, final_status ? -1 : winner, n, my_par, my_dep, my_tok, final_status ? -1 : token,
+                       P.path_nodes + static_cast<size_t>(b) * P.max_depth, P.out_tokens + static_cast<size_t>(b) * (P.max_depth + 1));
+        }
+        if (lane == 0) {
+            P.out_len[b] = n;
+            if (P.row_status) P.row_status[b] = final_status;
+            if (failed) sequence_of_failed_call_done(P.ws);
+        }
+    };
+    if constexpr (BY_K) {
+        if (P.draw)
+            clear_words(P.clear, P.clear16, (static_cast<long>(b) * gridDim.x + blockIdx.x) * kWarpWG + tid,
+                        static_cast<long>(gridDim.x) * gridDim.y * kWarpWG);
+    }
     if (s_st) {   // nothing will be drawn for this sequence
         if (tid == 0) P.thr[b] = neg_inf();
+        if constexpr (BY_K) {
+            if (P.draw && blockIdx.x == 0 && wave == 0) write_outputs(status, -1);
+        }
         return;
     }
     const char* row = P.target + (static_cast<size_t>(b) * (P.rows + 1) + from) * static_cast<size_t>(P.V) * ES;
@@ -209,7 +289,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
             kept[c] = load_slot<BF16, LD>(row, sl < sl_hi ? sl : P.nslots - 1, P.V);
         }
     }
-    // one pass over the row: f(scaled logit, key) for every entry
+    // one pass over the row: f(scaled logit, key, place in the row) for every entry
     auto for_slot = [&](const uint4& raw, long sl, auto&& f) __attribute__((always_inline)) {
         float z[VE];
         unpack<BF16>(raw, z);
@@ -217,11 +297,11 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         for (int e = 0; e < VE; ++e) {
             if (LD == LOAD_ALIGNED || sl * VE + e < P.V) {   // aligned rows have no ragged last slot
                 const float sv = __fmul_rn(z[e], P.inv_temp);
-                f(sv, ordered_key(sv));
+                f(sv, ordered_key(sv), static_cast<int>(sl * VE + e));
             }
         }
     };
-    auto for_each = [&](auto&& f) __attribute__((always_inline)) {
+    auto for_each_at = [&](auto&& f) __attribute__((always_inline)) {
         if constexpr (KEEP) {
             if (!SPLIT || !whole) {
 #pragma unroll
@@ -258,6 +338,9 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
             }
         }
     };
+    auto for_each = [&](auto&& f) __attribute__((always_inline)) {
+        for_each_at([&](float sv, unsigned key, int) __attribute__((always_inline)) { f(sv, key); });
+    };
     // the row's maximum (s_max) and its smallest entry above -inf (s_min), from every thread's own
     auto block_range = [&](float m, float lo) __attribute__((always_inline)) {
         float neg = -lo;
@@ -273,15 +356,43 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         }
         __syncthreads();
     };
+    const bool want_k = BY_K || (!SPLIT && P.top_k > 0 && P.top_k < P.V), want_p = (SPLIT && !BY_K) || P.top_p < 1.0f;
+    int bad = 0;   // P.draw: this thread has seen a NaN or +inf (or a logit that the temperature makes one)
     auto row_range = [&]() __attribute__((always_inline)) {
         float m = neg_inf(), lo = __builtin_inff();
         for_each([&](float sv, unsigned) {
             m = fmaxf(m, sv);
             lo = fminf(lo, (sv > neg_inf()) ? sv : __builtin_inff());
+            if constexpr (BY_K) bad |= !(sv < __builtin_inff());
         });
-        block_range(m, lo);
+        if (!BY_K || whole) block_range(m, lo);   // (under top-k nobody asks for the share's range)
         return m;   // this thread's maximum
     };
+    // The need-th largest of n <= kCountKeys keys in LDS, or its digits down to bit `down_to` (the result is then the largest
+    // multiple of 2^down_to with need keys at or above it): every wavefront holds all keys, 16 a lane, and in a round
+    // tries the value that extends the digits found so far by its own number.
+    auto count_select = [&](const unsigned* keys, int n, unsigned need, int down_to) __attribute__((always_inline)) -> unsigned {
+        constexpr int PER = kCountKeys / 64;
+        unsigned r[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) r[i] = (i * 64 + lane < n) ? keys[i * 64 + lane] : 0u;
+        unsigned found = 0u;
+        for (int shift = 28; shift >= down_to; shift -= 4) {
+            const unsigned least = found | (static_cast<unsigned>(wave) << shift);
+            unsigned count = 0u;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                if (i * 64 < n) count += static_cast<unsigned>(__popcll(__ballot(r[i] >= least)));
+            }
+            unsigned* const round = s_round[(shift >> 2) & 1];   // (the other one may still be read)
+            if (lane == 0) round[wave] = count;
+            __syncthreads();
+            const unsigned long long enough = __ballot(round[lane & 15] >= need) & 0xFFFFull;   // (for all up to some number)
+            found |= static_cast<unsigned>(enough ? 63 - __builtin_clzll(enough) : 0) << shift;
+        }
+        return found;
+    };
+    static_assert(kWarpWG / 64 == 16, "a digit of 4 bits a round");
     // Histogram additions of one thread, merged while consecutive entries fall in the same bin (the
     // leading digit of nearly every entry of a row is the same: adding them one by one would
     // serialise the whole workgroup on one LDS word).  s_hist takes the weights (1 per entry for
@@ -337,9 +448,25 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     // wgt(sv, key) gives an entry's weight (0 = not taking part); first_total, called with the
     // total weight of the first histogram, may set s_need.  down_to: the last digit's shift (16: the upper half of
     // the key, a lower bound of it).
+    // Digits in which all keys agree are theirs without a pass: a list's keys lie close together, and those of bfloat16 logits end in
+    // zeros.  (A pass is six barriers.)
     auto lds_select = [&](const unsigned* keys, int n, auto&& wgt, auto&& first_total, int down_to = 0) __attribute__((always_inline)) {
-        if (tid == 0) { s_prefix = 0u; s_mask = 0u; }
+        const unsigned first = keys[0];
+        unsigned differ = 0u;
+        for (int i = tid; i < n; i += kWarpWG) differ |= keys[i] ^ first;
+        differ = wave_or(differ);
+        if (tid == 0) s_match = 0u;
+        __syncthreads();
+        if (lane == 0 && differ) atomicOr(&s_match, differ);
+        __syncthreads();
+        differ = s_match;
+        unsigned same = 0u;
+#pragma unroll
+        for (int shift = 0; shift < 32; shift += 8) same |= ((differ >> shift) & 255u) ? 0u : 255u << shift;
+        if (tid == 0) { s_prefix = first & same & (~0u << down_to); s_mask = same; }
+        bool started = false;
         for (int shift = 24; shift >= down_to; shift -= 8) {
+            if ((same >> shift) & 255u) continue;
             if (tid < 256) { s_hist[tid] = 0ull; s_cnt[tid] = 0u; }
             __syncthreads();
             const unsigned prefix = s_prefix, mask = s_mask;
@@ -354,9 +481,11 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
                     }
                 }
             }
-            if (shift == 24) pick_from_top(shift, first_total);
+            if (!started) pick_from_top(shift, first_total);
             else pick_from_top(shift, [](unsigned long long) {});
+            started = true;
         }
+        __syncthreads();   // (no digit may have differed)
     };
     // The same select over the whole row (the general path): every digit is a pass over the row
     // until the entries that still share the prefix fit the list; then they are gathered there and
@@ -474,13 +603,8 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         return true;
     };
 
-    const bool want_k = P.top_k > 0 && P.top_k < P.V, want_p = P.top_p < 1.0f;
     bool done_k = !want_k, done_p = !want_p;
     float t_k = neg_inf(), t_p = neg_inf();
-    if (!want_k && !want_p) {   // temperature alone: everything is kept
-        if (tid == 0) P.thr[b] = neg_inf();
-        return;
-    }
     const float tmax = row_range();
     float cmax = s_max * kLog2e;
     auto one = [&](float, unsigned) __attribute__((always_inline)) -> unsigned long long { return 1ull; };
@@ -500,6 +624,27 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         return n ? n : 1ull;
     };
     auto first_k = [&](unsigned long long) __attribute__((always_inline)) -> unsigned long long { return static_cast<unsigned long long>(P.top_k); };
+
+    // ---- any setting from the whole row: by value, or by digits where that does not settle it
+    auto select_from_row = [&]() __attribute__((always_inline)) {
+        if (!done_k) {
+            if (!bin_select(one, first_k)) {
+                __syncthreads();
+                if (tid == 0) s_need = static_cast<unsigned long long>(P.top_k);
+                __syncthreads();
+                row_select(one, [](unsigned long long) {});
+            }
+            t_k = key_value(s_prefix);
+            __syncthreads();
+        }
+        if (!done_p) {
+            if (!bin_select(weight, nucleus_need)) {
+                __syncthreads();
+                row_select(weight, [&](unsigned long long Z) { s_need = nucleus_need(Z); });
+            }
+            t_p = key_value(s_prefix);
+        }
+    };
 
     if constexpr (SPLIT) {
         unsigned* const line = P.ws.sdone + static_cast<size_t>(b) * kSdoneStride;
@@ -527,57 +672,190 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         // all lists into s_lkey: false if one was too long.  (A stretch of threads per list: all are read at once; at most
         // kSplitBytes / 4 <= kWarpList keys.)
         auto read_lists = [&](const unsigned* lists, int cap) __attribute__((always_inline)) -> bool {
+            const int per = kWarpWG / W, w = tid / per, j0 = tid - w * per;
+            const unsigned* const mine = lists + (w < W ? w : 0) * (cap + 1) + 1;
+            unsigned key = __hip_atomic_load(mine + (j0 < cap ? j0 : 0), __ATOMIC_RELAXED, AGENT);
+            int lens[kWarpShare], at0 = 0, my_n = 0, n = 0;
+            bool fits = true;
+#pragma unroll
+            for (int q = 0; q < kWarpShare; ++q)
+                lens[q] = static_cast<int>(__hip_atomic_load(lists + (q < W ? q : 0) * (cap + 1), __ATOMIC_RELAXED, AGENT));
+#pragma unroll
+            for (int q = 0; q < kWarpShare; ++q) {
+                if (q >= W) break;
+                fits &= lens[q] <= cap;
+                if (q == w) { at0 = n; my_n = lens[q]; }
+                n += lens[q];
+            }
+            if (!fits) return false;
+            for (int j = j0; j < my_n; j += per) {
+                if (j != j0) key = __hip_atomic_load(mine + j, __ATOMIC_RELAXED, AGENT);
+                s_lkey[at0 + j] = key;
+            }
+            if (tid == 0) s_nlist = n;
+            __syncthreads();
+            return true;
+        };
+        if constexpr (BY_K) {
+            // a list: its length, with the flag of an unusable logit, and the keys, or (P.draw) the length and pairs of key and
+            // place in the row
+            const int cap = P.list_keys;
+            unsigned long long* const pairs = reinterpret_cast<unsigned long long*>(area);
+            unsigned* const keys = reinterpret_cast<unsigned*>(area);
+            unsigned* const s_place = reinterpret_cast<unsigned*>(s_bins);   // where in the row a key of s_lkey lies
+            static_assert(sizeof(s_bins) >= kSplitKeys * 4 && kSplitKeys <= kWarpList, "the lists fit");
+            const unsigned k = static_cast<unsigned>(P.top_k);
+            s_tmax[tid] = ordered_key(tmax);
             if (tid == 0) s_nlist = 0;
             __syncthreads();
-            const int per = kWarpWG / W, w = tid / per;
-            bool too_long = false;
-            if (w < W) {
-                const int n = static_cast<int>(__hip_atomic_load(lists + w * (cap + 1), __ATOMIC_RELAXED, AGENT));
-                too_long = n > cap;
-                for (int i = tid - w * per; i < n && !too_long; i += per) {
-                    const unsigned key = __hip_atomic_load(lists + w * (cap + 1) + 1 + i, __ATOMIC_RELAXED, AGENT);
-                    s_lkey[atomicAdd(&s_nlist, 1)] = key;
-                }
-            }
-            return __syncthreads_or(too_long) == 0;
-        };
-        if (want_k) {
-            const int cap = static_cast<int>(kSplitBytes / 4) / W - 1;
-            unsigned* const lists = reinterpret_cast<unsigned*>(area);
-            s_tmax[tid] = ordered_key(tmax);
-            if (tid == 0) { s_need = static_cast<unsigned long long>(P.top_k); s_nlist = 0; }
-            __syncthreads();
-            lds_select(s_tmax, kWarpWG, one, [](unsigned long long) {}, 16);   // (any bound with k entries at or above it)
-            const unsigned low = s_prefix;
-            for_each([&](float, unsigned key) {
+            const unsigned low = count_select(s_tmax, kWarpWG, k, 16);   // (any bound with k entries at or above it)
+            for_each_at([&](float, unsigned key, int place) {
                 if (key >= low) {
                     const int at = atomicAdd(&s_nlist, 1);
-                    if (at < cap) s_lkey[at] = key;
+                    if (at < cap) { s_lkey[at] = key; s_place[at] = static_cast<unsigned>(place); }
                 }
             });
-            __syncthreads();
-            if (!leave_list(lists, cap, count)) return;
-            const bool fits = read_lists(lists, cap);
+            const bool any_bad = __syncthreads_or(bad) != 0;
+            const int left = s_nlist;
+            const unsigned head_word = (any_bad ? 0x80000000u : 0u) | static_cast<unsigned>(left);
+            if (P.draw) {
+                unsigned long long* const at = pairs + g * (cap + 1);
+                for (int i = tid; i < left && i < cap; i += kWarpWG) post64(at + 1 + i, (static_cast<unsigned long long>(s_lkey[i]) << 32) | s_place[i]);
+                if (tid == 0) post64(at, head_word);
+            } else {
+                unsigned* const at = keys + g * (cap + 1);
+                for (int i = tid; i < left && i < cap; i += kWarpWG) __hip_atomic_store(at + 1 + i, s_lkey[i], __ATOMIC_RELAXED, AGENT);
+                if (tid == 0) __hip_atomic_store(at, head_word, __ATOMIC_RELAXED, AGENT);
+            }
+            if (!count_self(count)) return;
+            // the lists one after the other into s_lkey and s_place, a stretch of threads each; an entry is asked for together
+            // with the lengths, before it is known to be one
+            const int per = kWarpWG / W, w = tid / per, j0 = tid - w * per;
+            const int mine = (w < W ? w : 0) * (cap + 1) + 1;
+            auto entry_at = [&](int j) __attribute__((always_inline)) -> unsigned long long {   // key, place
+                if (P.draw) return read64(pairs + mine + j);
+                return static_cast<unsigned long long>(__hip_atomic_load(keys + mine + j, __ATOMIC_RELAXED, AGENT)) << 32;
+            };
+            unsigned long long entry = entry_at(j0 < cap ? j0 : 0);
+            int n = 0, at0 = 0, my_n = 0;
+            bool fits = true, row_bad = false;
+            unsigned head[kWarpShare];   // (all of them asked for in one go)
+#pragma unroll
+            for (int q = 0; q < kWarpShare; ++q) {
+                const int from_list = (q < W ? q : 0) * (cap + 1);
+                head[q] = P.draw ? static_cast<unsigned>(read64(pairs + from_list)) : __hip_atomic_load(keys + from_list, __ATOMIC_RELAXED, AGENT);
+            }
+#pragma unroll
+            for (int q = 0; q < kWarpShare; ++q) {
+                if (q >= W) break;
+                const int len = static_cast<int>(head[q] & 0x7FFFFFFFu);
+                fits &= len <= cap;
+                row_bad |= (head[q] >> 31) != 0;
+                if (q == w) { at0 = n; my_n = len; }
+                n += len;
+            }
             whole = true;
+            float cut = 0.0f;
             if (fits) {
-                const int n = s_nlist;
-                if (tid == 0) s_need = static_cast<unsigned long long>(P.top_k);
-                unsigned top = 0u;
-                for (int i = tid; i < n; i += kWarpWG) top = s_lkey[i] > top ? s_lkey[i] : top;
-                block_range(key_value(top), 0.0f);   // (a thread without a key brings the NaN of key 0, which max() drops)
-                cmax = s_max * kLog2e;
-                lds_select(s_lkey, n, one, [](unsigned long long) {});
-                t_k = key_value(s_prefix);
+                for (int j = j0; j < my_n; j += per) {
+                    if (j != j0) entry = entry_at(j);
+                    s_lkey[at0 + j] = static_cast<unsigned>(entry >> 32);
+                    s_place[at0 + j] = static_cast<unsigned>(entry);
+                }
                 __syncthreads();
-                if (want_p) {
+                bool have_p = !want_p;
+                if (n <= kCountKeys) {
+                    if (tid == 0) { s_nlist = 0; s_match = 0u; s_prefix = ~0u; }
+                    if (tid <= kRankKeys) s_above[tid] = 0ull;
+                    t_k = key_value(count_select(s_lkey, n, k, 0));
+                    if (want_p) {
+                        // what top-k keeps, with its weights: an entry is kept if those above it weigh less than is needed
+                        const unsigned key = tid < n ? s_lkey[tid] : 0u;
+                        const float sv = key_value(key), m = wave_max(sv);   // (0: a NaN, which max() drops)
+                        if (lane == 0 && m == m) atomicMax(&s_match, ordered_key(m));
+                        __syncthreads();
+                        cmax = key_value(s_match) * kLog2e;
+                        if (sv >= t_k) {
+                            const int at = atomicAdd(&s_nlist, 1);
+                            if (at < kRankKeys) { s_tmax[at] = key; s_hist[at] = weight(sv, key); }
+                        }
+                        __syncthreads();
+                        const int kept_k = s_nlist;
+                        have_p = kept_k <= kRankKeys;
+                        if (have_p) {
+                            // (all pairs: 64 entries a wavefront, and a sixteenth of those they are compared with)
+                            unsigned long long all = 0ull;
+                            for (int i0 = 0; i0 < kept_k; i0 += 64) {
+                                const int i = i0 + lane;
+                                const unsigned own = s_tmax[i < kept_k ? i : 0];
+                                unsigned long long above = 0ull;
+                                for (int j = wave; j < kept_k; j += kWarpWG / 64) {
+                                    const unsigned long long w = s_hist[j];
+                                    if (i0 == 0) all += w;
+                                    above += s_tmax[j] > own ? w : 0ull;
+                                }
+                                if (i < kept_k && above) atomicAdd(&s_above[i], above);
+                            }
+                            if (lane == 0) atomicAdd(&s_above[kRankKeys], all);
+                            __syncthreads();
+                            if (tid < kept_k && s_above[tid] < nucleus_need(s_above[kRankKeys])) atomicMin(&s_prefix, s_tmax[tid]);
+                            __syncthreads();
+                            t_p = key_value(s_prefix);
+                        }
+                    }
+                } else {
+                    if (tid == 0) s_need = static_cast<unsigned long long>(P.top_k);
+                    unsigned top = 0u;
+                    for (int i = tid; i < n; i += kWarpWG) top = s_lkey[i] > top ? s_lkey[i] : top;
+                    block_range(key_value(top), 0.0f);   // (a thread without a key brings the NaN of key 0, which max() drops)
+                    cmax = s_max * kLog2e;
+                    lds_select(s_lkey, n, one, [](unsigned long long) {});
+                    t_k = key_value(s_prefix);
+                }
+                if (!have_p) {
+                    __syncthreads();
                     lds_select(s_lkey, n, weight, [&](unsigned long long Z) { s_need = nucleus_need(Z); });
                     t_p = key_value(s_prefix);
                 }
-                if (tid == 0) P.thr[b] = fmaxf(t_k, t_p);
-                return;
+                cut = fmaxf(t_k, t_p);
+            } else {
+                // too long a list (a great many equal entries): the whole row, by this workgroup alone
+                row_range();
+                cmax = s_max * kLog2e;
+                select_from_row();
+                cut = fmaxf(t_k, t_p);
             }
-            row_range();
-            cmax = s_max * kLog2e;
+            if (tid == 0) P.thr[b] = cut;
+            if (!P.draw) return;
+            Best best{neg_inf(), 0x7FFFFFFF};
+            if (fits) {
+                for (int i = tid; i < n; i += kWarpWG) {
+                    const float sv = key_value(s_lkey[i]);
+                    if (!(sv >= cut)) continue;
+                    const unsigned place = s_place[i];
+                    const U4 v = philox4x32_10(place >> 2, static_cast<unsigned>(b), P.off_lo, P.off_hi, P.seed_lo, P.seed_hi);
+                    const unsigned word = (place & 3) == 0 ? v.x : (place & 3) == 1 ? v.y : (place & 3) == 2 ? v.z : v.w;
+                    best = better(best, Best{__fadd_rn(sv, gumbel(word)), static_cast<int>(place)});
+                }
+            } else {
+                if (tid == 0) s_score = score_key(-FLT_MAX);
+                __syncthreads();
+                const DrawArgs A{P.V, FSD_SAMPLE, P.seed_lo, P.seed_hi, P.off_lo, P.off_hi, true, cut, P.inv_temp};
+                draw_share<BF16, LD, false, 8, kWarpWG>(A, b, row, false, nullptr, 0.0f, 0.0f, DrawChain{nullptr, 0, 0, nullptr}, 0, P.nslots, tid,
+                                                        &s_score, best, bad);
+                row_bad |= __syncthreads_or(bad) != 0;
+            }
+            best = wave_best(best);
+            __syncthreads();
+            if (lane == 0) { s_red[wave] = best.score; s_cnt[wave] = static_cast<unsigned>(best.idx); }
+            __syncthreads();
+            if (wave == 0) {
+                const int from_wave = lane < kWarpWG / 64 ? lane : 0;
+                best = wave_best(Best{s_red[from_wave], static_cast<int>(s_cnt[from_wave])});
+                const bool none = best.idx == 0x7FFFFFFF || best.score == neg_inf();
+                write_outputs((row_bad || none) ? FSD_ROW_NONFINITE : 0, best.idx);
+            }
+            return;
         } else {
             unsigned long long* const bins = reinterpret_cast<unsigned long long*>(area);
             unsigned long long* const words = reinterpret_cast<unsigned long long*>(line + 2);
@@ -734,24 +1012,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         __syncthreads();
     }
 
-    // ---- any other setting: by value, or by digits where that does not settle it
-    if (!done_k) {
-        if (!bin_select(one, first_k)) {
-            __syncthreads();
-            if (tid == 0) s_need = static_cast<unsigned long long>(P.top_k);
-            __syncthreads();
-            row_select(one, [](unsigned long long) {});
-        }
-        t_k = key_value(s_prefix);
-        __syncthreads();
-    }
-    if (!done_p) {
-        if (!bin_select(weight, nucleus_need)) {
-            __syncthreads();
-            row_select(weight, [&](unsigned long long Z) { s_need = nucleus_need(Z); });
-        }
-        t_p = key_value(s_prefix);
-    }
+    select_from_row();
     if (tid == 0) P.thr[b] = fmaxf(t_k, t_p);
 }
 

@@ -821,3 +821,51 @@ def test_largest_logit_is_negative(torch_cuda, oracle, V, kind):
         check_sd(pu.host(out, pu.SD_KEYS), oracle.sd_verify_chain(t, d, inp["cand"], seed=5, offset=2), f"SD {kind} V={V}")
     finally:
         fsd.debug_set_small_calls(prev)
+
+
+# 1: one entry; 192, 193: the most that is summed up by rank, one more; 500: more candidates than are counted in registers;
+# 64, 65 rows: the most a lane each, one more (the draw is then a kernel of its own)
+@pytest.mark.parametrize("rows,k", [(13, 1), (13, 2), (13, 192), (13, 193), (13, 500), (64, 40), (65, 40)])
+@pytest.mark.parametrize("V,dtype", [(40000, "bf16"), (40003, "f32")])
+def test_draw_with_the_selection(torch_cuda, oracle, rows, k, V, dtype):
+    """Top-k by several workgroups a row, where the token is drawn by whoever selects: random rows, rows of a few hundred values (ties
+    at the cut, and at the nucleus' end), all but 300 entries masked, and the row after the last candidate."""
+    B = 4
+    rng = np.random.default_rng(rows + k)
+    t = (rng.standard_normal((B, rows + 1, V), dtype=np.float32) * np.float32(3))
+    t[1] = np.round(t[1] * 16) / 16
+    t[2, :, rng.permutation(V)[300:]] = -np.inf
+    d = (t[:, :rows] + rng.standard_normal((B, rows, V), dtype=np.float32) * np.float32(0.3))
+    d[3] = t[3, :rows]                                                  # everything accepted
+    inp = dict(target=t, draft=d, cand=rng.integers(0, V, (B, rows)).astype(np.int32))
+    if dtype == "bf16":
+        inp.update(target=synth.to_bf16_bits(t), draft=synth.to_bf16_bits(d))
+    for kw in (dict(top_k=k), dict(top_k=k, top_p=0.7, temperature=1.3), dict(top_k=k, top_p=0.05), dict(temperature=0.6)):
+        what = f"draw with the selection rows={rows} V={V} {dtype} {kw}"
+        print(what, flush=True)
+        g = run_warped(torch_cuda, inp, 0.005, fsd.DIV_TV, fsd.SAMPLE, 9, 4, **kw)
+        assert "top_k" not in kw or fsd.debug_last_selection() > 1
+        o = oracle.verify_chain_warped(inp["target"], inp["draft"], inp["cand"], 0.005, fsd.DIV_TV, fsd.SAMPLE, 9, 4, **kw)
+        check_warped(g, o, 0.005, pu.rel_tol(dtype), what, cut_active="top_k" in kw, envelope=pu.Envelope(dtype))
+
+
+def test_draw_with_the_selection_over_malformed_trees(torch_cuda, oracle):
+    """A tree with a parent behind its child, one deeper than the call allows and one as it should be: what the draw with the selection
+    reports, and that it leaves nothing of the first two."""
+    B, N, V, depth = 3, 14, 40000, 4
+    inp = _random_tree_inputs(np.random.default_rng(3), B, N, V, "bf16")
+    inp["parent"][:] = np.where(np.arange(N) < 4, -1, np.arange(N) % 4)
+    inp["parent"][0, 6] = 9
+    inp["parent"][1, 4:9] = np.arange(3, 8)
+    d = pu.to_dev(inp, ("target", "draft", "node_tokens", "parent"))
+    kw = dict(top_k=50, top_p=0.9)
+    out = fsd.fsd_verify_tree_warped(d["target"], d["draft"], d["node_tokens"], d["parent"], depth, 0.12, fsd.DIV_JS, fsd.SAMPLE, 5, 2, **kw)
+    assert fsd.debug_last_selection() > 1
+    torch_cuda.cuda.synchronize()
+    g = pu.host(out, pu.TREE_KEYS)
+    o = oracle.verify_tree_warped(inp["target"], inp["draft"], inp["node_tokens"], inp["parent"], depth, 0.12, fsd.DIV_JS, fsd.SAMPLE, 5, 2, **kw)
+    assert list(o["row_status"]) == [fsd.ROW_BAD_PARENT, fsd.ROW_TOO_DEEP, 0]
+    # (the divergences of a malformed tree's nodes are nobody's: the paths and tokens are what is compared)
+    for key in ("row_status", "path_len", "path_nodes", "out_tokens"):
+        assert (g[key] == o[key]).all(), key
+    assert (g["path_len"][:2] == 0).all() and (g["out_tokens"][:2] == -1).all() and (g["path_nodes"][:2] == -1).all()
