@@ -411,8 +411,12 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     // From the top: the digit at which the accumulated histogram reaches s_need; updates prefix and
     // need and leaves the number of entries that share the new prefix in s_match.  The 256 sums from
     // the top come from a parallel scan (a single thread walking the bins costs more than a pass
-    // over the row); need_of(total), if given, first derives s_need from the histogram's total.
+    // over the row); need_of(total), if given, first derives s_need from the histogram's total.  What is needed has been read by
+    // all four wavefronts, and a barrier lies between, before the one that finds its bin writes the rest: a wavefront
+    // that read the rest in its place could find a second bin, and the digits of both would end up in the prefix.
+    struct AsNeeded {};   // (s_need as it stands)
     auto pick_from_top = [&](int shift, auto&& need_of) __attribute__((always_inline)) {
+        constexpr bool DERIVED = !std::is_same_v<std::decay_t<decltype(need_of)>, AsNeeded>;
         __syncthreads();
         unsigned long long h = 0, v = 0;
         if (tid < 256) {
@@ -425,14 +429,19 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
             }
             if (lane == 0) s_wtot[wave] = v;
         }
+        unsigned long long need = DERIVED ? 0ull : s_need;
         __syncthreads();
         if (tid < 256) {
             for (int w = wave + 1; w < 4; ++w) v += s_wtot[w];   // v = everything in bins >= tid
-            if (tid == 0) need_of(v);
         }
-        __syncthreads();
+        if constexpr (DERIVED) {
+            if (tid == 0) need_of(v);
+            __syncthreads();
+            need = s_need;
+            __syncthreads();
+        }
         if (tid < 256) {
-            const unsigned long long need = s_need, above = v - h;
+            const unsigned long long above = v - h;
             const bool here = (v >= need && above < need) || (tid == 0 && v < need);
             if (here) {
                 s_prefix |= static_cast<unsigned>(tid) << shift;
@@ -463,7 +472,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         unsigned same = 0u;
 #pragma unroll
         for (int shift = 0; shift < 32; shift += 8) same |= ((differ >> shift) & 255u) ? 0u : 255u << shift;
-        if (tid == 0) { s_prefix = first & same & (~0u << down_to); s_mask = same; }
+        if (tid == 0) { s_prefix = first & same & (~0u << down_to); s_mask = same & (~0u << down_to); }
         bool started = false;
         for (int shift = 24; shift >= down_to; shift -= 8) {
             if ((same >> shift) & 255u) continue;
@@ -482,7 +491,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
                 }
             }
             if (!started) pick_from_top(shift, first_total);
-            else pick_from_top(shift, [](unsigned long long) {});
+            else pick_from_top(shift, AsNeeded{});
             started = true;
         }
         __syncthreads();   // (no digit may have differed)
@@ -521,7 +530,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
                 run_flush(run);
             }
             if (shift == 24) pick_from_top(shift, first_total);
-            else pick_from_top(shift, [](unsigned long long) {});
+            else pick_from_top(shift, AsNeeded{});
             if (!listed && shift >= 16 && s_match <= static_cast<unsigned>(kWarpList)) {
                 if (tid == 0) s_nlist = 0;
                 __syncthreads();
@@ -599,7 +608,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         __syncthreads();
         const int nl = s_nlist;
         if (nl > kWarpList) return false;
-        lds_select(s_lkey, nl, wgt, [](unsigned long long) {});
+        lds_select(s_lkey, nl, wgt, AsNeeded{});
         return true;
     };
 
@@ -632,7 +641,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
                 __syncthreads();
                 if (tid == 0) s_need = static_cast<unsigned long long>(P.top_k);
                 __syncthreads();
-                row_select(one, [](unsigned long long) {});
+                row_select(one, AsNeeded{});
             }
             t_k = key_value(s_prefix);
             __syncthreads();
@@ -809,7 +818,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
                     for (int i = tid; i < n; i += kWarpWG) top = s_lkey[i] > top ? s_lkey[i] : top;
                     block_range(key_value(top), 0.0f);   // (a thread without a key brings the NaN of key 0, which max() drops)
                     cmax = s_max * kLog2e;
-                    lds_select(s_lkey, n, one, [](unsigned long long) {});
+                    lds_select(s_lkey, n, one, AsNeeded{});
                     t_k = key_value(s_prefix);
                 }
                 if (!have_p) {
@@ -963,7 +972,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
                 }
                 const int nl = s_nlist;
                 if (nl <= kWarpList) {
-                    lds_select(s_lkey, nl, weight, [](unsigned long long) {});
+                    lds_select(s_lkey, nl, weight, AsNeeded{});
                     t_p = key_value(s_prefix);
                     done_p = true;
                 }
@@ -986,7 +995,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         s_tmax[tid] = ordered_key(tmax);
         if (tid == 0) { s_need = static_cast<unsigned long long>(P.top_k); s_nlist = 0; }
         __syncthreads();
-        lds_select(s_tmax, kWarpWG, one, [](unsigned long long) {}, 16);   // (any bound with k entries at or above it)
+        lds_select(s_tmax, kWarpWG, one, AsNeeded{}, 16);   // (any bound with k entries at or above it)
         const unsigned low = s_prefix;   // at most the key of L
         for_each([&](float, unsigned key) {
             if (key >= low) {
@@ -999,7 +1008,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         if (nl <= kWarpList) {
             if (tid == 0) s_need = static_cast<unsigned long long>(P.top_k);
             __syncthreads();
-            lds_select(s_lkey, nl, one, [](unsigned long long) {});
+            lds_select(s_lkey, nl, one, AsNeeded{});
             t_k = key_value(s_prefix);
             done_k = true;
             __syncthreads();

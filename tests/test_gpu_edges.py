@@ -849,6 +849,21 @@ def test_draw_with_the_selection(torch_cuda, oracle, rows, k, V, dtype):
         check_warped(g, o, 0.005, pu.rel_tol(dtype), what, cut_active="top_k" in kw, envelope=pu.Envelope(dtype))
 
 
+@pytest.mark.parametrize("V,kw", [(9000, dict(top_k=300)), (9000, dict(top_k=300, top_p=0.6)), (3000, dict(top_k=700)), (64, dict(top_k=40))])
+def test_cut_digits_in_several_quarters(torch_cuda, oracle, V, kw):
+    """Logits over [2, 8): their second digit takes all 256 values, and the entries above the bin of the cut lie in the bins of other
+    wavefronts.  Many sequences at once, one workgroup each."""
+    B = 300
+    rng = np.random.default_rng(V)
+    t = rng.uniform(2.0, 8.0, (B, 2, V)).astype(np.float32)
+    d = (t[:, :1] + rng.standard_normal((B, 1, V), dtype=np.float32) * np.float32(0.3))
+    inp = dict(target=t, draft=d, cand=rng.integers(0, V, (B, 1)).astype(np.int32))
+    g = run_warped(torch_cuda, inp, 0.01, fsd.DIV_TV, fsd.SAMPLE, 9, 4, **kw)
+    assert fsd.debug_last_selection() <= 1
+    o = oracle.verify_chain_warped(inp["target"], inp["draft"], inp["cand"], 0.01, fsd.DIV_TV, fsd.SAMPLE, 9, 4, **kw)
+    check_warped(g, o, 0.01, pu.rel_tol("f32"), f"cuts V={V} {kw}", envelope=pu.Envelope("f32"))
+
+
 def test_draw_with_the_selection_over_malformed_trees(torch_cuda, oracle):
     """A tree with a parent behind its child, one deeper than the call allows and one as it should be: what the draw with the selection
     reports, and that it leaves nothing of the first two."""
