@@ -262,7 +262,7 @@ void launch_pair_a(int load, hipStream_t st, const PairParams& P) {
     // a tree (shared target rows) has variants of its own, for 16-byte aligned rows and, on others, for the
     // library's own shapes of large calls.  (A small binary32 call, 4 slots, is one step per wavefront and has no sibling
     // to share with: 1 tree of 16 nodes, V=32001, with and without 16.4 us JS, 31.7 strict SD; of 8, V=128001 34.6 and 33.7.)
-    constexpr bool kOwn = BF16 ? (NV == 4 || NV == 6) : (NV == 8);
+    constexpr bool kOwn = BF16 ? (NV == 4 || NV == 6) : (NV >= 8);
     const bool shared = P.parent != nullptr;
     if (load == LOAD_ALIGNED) {
         if (shared) launch_pair_k<BF16, NV, MODE, LOAD_ALIGNED, true>(st, P);
@@ -320,6 +320,11 @@ void launch_pair(int dtype, int NV, int mode, int load, hipStream_t st, const Pa
     } else {
         if (NV == 2) launch_pair_m<false, 2>(mode, load, st, P);
         else if (NV == 4) launch_pair_m<false, 4>(mode, load, st, P);
+        else if (NV == 10) {   // the library's own shape of the two-phase kernels
+            if (mode == MODE_KLP) launch_pair_a<false, 10, MODE_KLP>(load, st, P);
+            else if (mode == MODE_TV) launch_pair_a<false, 10, MODE_TV>(load, st, P);
+            else launch_pair_a<false, 10, MODE_JS>(load, st, P);
+        }
         else launch_pair_m<false, 8>(mode, load, st, P);
     }
     if (prof) {
@@ -387,7 +392,7 @@ SmallForms small_forms(int kind, int dtype, int div, int B, int rows, long V, bo
     else if (bf16) f.reduction = entries <= (!aligned ? 9 * M / 2 : V > 1L << 17 ? 15 * M / 4 : 2 * M);
     else if (div == FSD_DIV_KL) f.reduction = entries <= 6 * M;
     else {
-        // pairs that the binary32 teams take in a step (8 slots a lane, a wavefront a SIMD)
+        // pairs that the binary32 teams took in a step when these lines were measured (8 slots a lane, a wavefront a SIMD)
         const long step = max_resident_wavefronts() / 8 / team_size((V + 3) / 4, 8), pairs = static_cast<long>(B) * rows;
         if (js) f.reduction = entries <= (long_rows ? 4 * M : 6 * M) && (entries <= M || pairs > step);
         else f.reduction = entries <= (long_rows ? 4 * M : 9 * M / 2) && pairs > (long_rows ? 2 * step : step);
@@ -660,6 +665,18 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
             p.NV = 4;
             p.G = static_cast<int>(G4);
             p.spm = static_cast<int>((p.nslots + G4 - 1) / G4);
+        } else if (k1mode != MODE_LSE) {
+            // The two-phase kernels hold 10 slots a lane, or 8 where the call is of few steps and 8 slots make
+            // less of them (whole calls, us, 8 and 10 slots: 16 sequences of 8, V=64000, 2 and 2 steps 25.9 and 27.6; 8 of 16, V=128256, 4 and 4
+            // steps 37.0 and 38.7; 64 of 16, V=32000, 8 and 7 57.0 and 59.3; but 12 of 6, V=151936, 3 and 3, 75 and 60 wavefronts a team 33.5
+            // and 33.2; 128 of 16, V=128256, 64 and 52 381 and 359; 256 of 16, V=151936, 152 and 121 917 and 831, where one wavefront a SIMD,
+            // with 8 slots and a third set of exponentials, took 936).
+            const long G8 = team_size(p.nslots, 8), G10 = team_size(p.nslots, 10), waves = max_resident_wavefronts() / 4;
+            const auto steps = [&](long G) { const long teams = waves / G > 0 ? waves / G : 1; return (R + teams - 1) / teams; };
+            const bool eight = G8 <= 64 && steps(G8) <= 8 && steps(G8) * 8 < steps(G10) * 10;
+            p.NV = eight ? 8 : 10;
+            p.G = static_cast<int>(eight ? G8 : G10);
+            p.spm = static_cast<int>((p.nslots + p.G - 1) / p.G);
         }
     }
     // exchange words a member posts in this mode: only those are laid out and cleared

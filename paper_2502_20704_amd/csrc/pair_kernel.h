@@ -27,14 +27,13 @@ namespace {
 //             divergence and status.
 //
 // The kernel is persistent and software-pipelined: in a step a wavefront runs phase 1 of pair j
-// and then phase 2 of pair j - LAG from an older set of kept exponentials (LAG = 1, or 2 where
-// the registers allow a third set).  Memory operations return in the order they were issued,
+// and then phase 2 of pair j - 1 from an older set of kept exponentials.  Memory operations return in the order they were issued,
 // which fixes the order of the requests in a step (see `step`): small exchange words first, the
-// next pair's logits as soon as phase 1 has consumed their registers (in the bfloat16 two-phase kernels
-// slot by slot; a whole step ahead where a second set of logit registers fits), and nothing after that
-// waits on memory unless a team member is late.  The bfloat16 two-phase kernels (two wavefronts per SIMD) are bound by
-// vector-ALU issue; the binary32 ones (one wavefront per SIMD) by the exposed latencies, which the
-// longer lag and the earlier prefetch hide.  The single-pass modes (bfloat16 KL, the normalisers
+// next pair's logits as soon as phase 1 has consumed their registers, slot by slot, and nothing after that
+// waits on memory unless a team member is late.  The two-phase kernels run two wavefronts per SIMD: the
+// bfloat16 ones are bound by vector-ALU issue, the binary32 ones of large calls by memory (256 sequences of 16, V=151936: 6.2 TB/s;
+// with one wavefront per SIMD, whose instructions nothing overlaps, a third set of exponentials and 512 registers, a quarter of its
+// instructions moves between the two halves of the register file, 5.5).  The single-pass modes (bfloat16 KL, the normalisers
 // of strict SD) have no phase 2.  Waiting is bounded (spin_limit polls, then FSD_ROW_INTERNAL),
 // so every wavefront reaches the end of the kernel whatever happens; all team members are
 // resident by construction (the grid never exceeds what fits on the device at once).
@@ -384,7 +383,8 @@ template <bool B> struct BoolTag { static constexpr bool value = B; };
 
 // wavefronts per SIMD the register allocation has to leave room for
 constexpr int pair_kernel_waves(bool bf16, int nv, int mode) {
-    return (bf16 && (((nv == 5 || nv == 6) && (mode == MODE_JS || mode == MODE_TV)) || mode == MODE_JSE)) ? 2 : 1;
+    const bool two_phase = mode == MODE_JS || mode == MODE_TV || mode == MODE_KLP || mode == MODE_JSE;
+    return two_phase && (bf16 ? nv == 5 || nv == 6 : nv >= 8) ? 2 : 1;
 }
 
 // TSHARED: target rows are shared between pairs (a tree) and are loaded to stay cached (a template
@@ -472,20 +472,7 @@ void pair_kernel(PairParams P) {
     constexpr int FW = TWO_PHASE ? PW : 4;          // words per member the finisher reads
     constexpr int N1 = TWO_PHASE ? 2 : 4;           // phase-1 words a member posts; both exchange arrays are
                                                     // dense, [pair][member][word]: only what a mode uses is cleared
-    // binary32 logits: the two-phase kernels hold 8 slots of each row per lane and one wavefront per
-    // SIMD anyway, which leaves registers for a second set of logits
-    constexpr bool DEEP = !BF16 && TWO_PHASE && NV == 8;
-    // Phase 2 of a pair runs LAG steps after its phase 1.  With one step, a wavefront's own chain
-    // from one phase 1 to the next still holds the whole latency of the exchange (post, then the
-    // slowest member's words), which only another wavefront on the same SIMD can fill; with two,
-    // every member's words have long been posted when they are looked at.  That takes a third set
-    // of kept exponentials: the binary32 kernels with 8 slots per lane run one wavefront per SIMD
-    // and have the registers.  (The bfloat16 kernels run two per SIMD and are bound by vector-ALU
-    // issue: a third set kept in LDS removed their waits and left their time unchanged, for the
-    // pointwise kernels and again for the entropy-form one at 4 slots per lane, also with the team's
-    // words requested a whole step before they are used.)
-    constexpr int LAG = (TWO_PHASE && !BF16 && NV == 8) ? 2 : 1;
-    constexpr int NB = LAG + 1;                      // sets of kept exponentials
+    constexpr int NB = 2;                            // sets of kept exponentials: phase 2 of a pair runs a step after its phase 1
     // EARLY: the next pair's logits are requested slot by slot, each as soon as the exponentials of this pair's slot have
     // been formed, so that they are on their way for half a phase longer than if all were asked for behind the post (which cost
     // C2's kernel 7 us of 61 in waits for logits, and C4's 20 of 167: both measured with the reads replaced by
@@ -494,7 +481,7 @@ void pair_kernel(PairParams P) {
     // behind the post, slot by slot, and with the words behind the first slot's exponentials: C2 72.9, 70.0, 69.6; C4 186.6, 184.1, 180.3;
     // behind the second or third slot's 69.7 and 181.1, 69.8 and 181.8.  TV: C2 74.3 -> 72.0, C4 201 -> 198.  The
     // single-pass modes do not gain (strict SD at C2 66.5 -> 67.8).
-    constexpr bool EARLY = BF16 && TWO_PHASE;
+    constexpr bool EARLY = TWO_PHASE;
     constexpr int NC = (NE + 3) / 4;                 // chunks of four per row
     constexpr float kTiny = 2e-38f;   // floor of u and v under the logarithm (their weights are then zero or negligible),
                                       // and of p and q where both are normalised (KL)
@@ -511,11 +498,11 @@ void pair_kernel(PairParams P) {
     // does not wait for the prefetch as a spill would).  The bfloat16 two-phase kernels keep 5 of their 12
     // chunks there: that is what lets them hold 6 slots per lane (96 logits a step) in 256 registers,
     // and with two workgroups of 80 KB it takes all of a compute unit's LDS.  (TV at 5 slots per lane,
-    // a shape of the tuning hook, keeps one.)
+    // a shape of the tuning hook, keeps one.)  The binary32 ones keep 5 chunks as well, of 10 or 8.
     // (The least that leaves no register of a step spilled in the entropy form, but for one address of a branch that only a
     // wait that has expired takes.  JS and TV have 30 registers to spare with it; with 3 chunks in LDS JS takes the same time and
     // TV is slower, C2 72.0 -> 73.6 us a call.)
-    constexpr int NL = (JSE || (BF16 && NV == 6 && TWO_PHASE)) ? 5 : (BF16 && NV == 5 && MODE == MODE_TV) ? 1 : 0;
+    constexpr int NL = (JSE || (TWO_PHASE && (BF16 ? NV == 6 : NV >= 8))) ? 5 : (BF16 && NV == 5 && MODE == MODE_TV) ? 1 : 0;
     __shared__ float4 lds_keep[NL ? NB * NL * 2 * kWG : 1];
     auto put4 = [&](auto S, int c, const float (&t4)[4], const float (&d4)[4]) __attribute__((always_inline)) {
         constexpr int s_ = decltype(S)::value;
@@ -675,8 +662,7 @@ void pair_kernel(PairParams P) {
         for (int k = 0; k < NV; ++k) load_one(ra[k], rb[k], k, tptr, dptr, wanted, first);
     };
     // (EARLY, the kernels short of scalar registers: the bounds are hidden from the hoisting of loop invariants, which kept a
-    // mask for every slot across the loop, spilled to lanes of a vector register.  The binary32 kernels, one wavefront a SIMD, are
-    // 1 to 2 % faster with the masks kept.)
+    // mask for every slot across the loop, spilled to lanes of a vector register.)
     auto fill_unowned = [&](uint4 (&ra)[NV], uint4 (&rb)[NV]) __attribute__((always_inline)) {
         int first = sl0, end = sl_end;
         if constexpr (LD == LOAD_WIDE) {
@@ -925,15 +911,13 @@ void pair_kernel(PairParams P) {
     // ---- state of the previous pair, whose phase 2 is still to come (two-phase modes)
     // wsum, dmax: pointwise KL; entropy-form JS: this lane's A_t + S_t and A_d, and sd is this lane's S_d
     struct Pend { int pair; float kt, kd; bool mass_t, mass_d, mask; float wsum, dmax, st, sd; };
-    Pend pend[LAG];   // [0] the last step's pair ... [LAG-1] the one whose phase 2 is due
-#pragma unroll
-    for (int i = 0; i < LAG; ++i) pend[i] = Pend{-1, 0.0f, 0.0f, false, false, false, 0.0f, 0.0f, 0.0f, 0.0f};
+    Pend pend{-1, 0.0f, 0.0f, false, false, false, 0.0f, 0.0f, 0.0f, 0.0f};   // the last step's pair, whose phase 2 is due
     bool js_clamp2 = false;   // entropy-form JS: phase 2 keeps u above the smallest normal number (see phase2)
     // pairs this wavefront has to finish: fin[0] now, fin[i] i steps from now.  A two-phase pair
     // is finished NF steps after its phase 1.  Whoever starts step n has merged the team words of
-    // step n - 1, so every member has ended step n - 2 - LAG and with it phase 2 of the pair of step
-    // n - 2 - 2 LAG: the finisher's words are there when it asks, however far the team has spread.
-    constexpr int NF = TWO_PHASE ? 2 * LAG + 2 : 1;
+    // step n - 1, so every member has ended step n - 3 and with it phase 2 of the pair of step
+    // n - 4: the finisher's words are there when it asks, however far the team has spread.
+    constexpr int NF = TWO_PHASE ? 4 : 1;
     int fin[NF];
 #pragma unroll
     for (int i = 0; i < NF; ++i) fin[i] = -1;
@@ -1128,20 +1112,16 @@ void pair_kernel(PairParams P) {
     // what can overlap: the small exchange words (the previous pair's team words, and the words of a
     // pair this wavefront has to finish) are requested first, at the top of the step, where they sit
     // behind the logits that are about to be used anyway; the logits of the next pair are requested
-    // once phase 1 has consumed the registers (EARLY: slot by slot, with the words before the first of them; in the binary32
-    // two-phase modes after this wavefront's sums are posted: the team's next step waits for every member's post, so nothing
-    // that can wait comes before it); and nothing after that waits on memory unless a team member is late (then the
-    // words are asked for again, behind the prefetch).
-    // (ra, rb) hold the logits of `pair`, the next pair's go to (rna, rnb).  Where registers allow
-    // (DEEP) these are different sets and the next pair is requested at the top of the step, a whole
-    // step ahead; otherwise both names are the same set and the request follows phase 1.
-    // SC names the set that takes this pair's exponentials, SP the one written LAG steps ago.
-    auto step = [&](auto SC, auto SP, uint4 (&ra)[NV], uint4 (&rb)[NV], uint4 (&rna)[NV], uint4 (&rnb)[NV], int pair)
+    // once phase 1 has consumed the registers (EARLY: slot by slot, with the words before the first of them); and nothing after that
+    // waits on memory unless a team member is late (then the words are asked for again, behind the prefetch).
+    // (ra, rb) hold the logits of `pair` and take the next pair's.  SC names the set that takes this pair's
+    // exponentials, SP the one written in the last step.
+    auto step = [&](auto SC, auto SP, uint4 (&ra)[NV], uint4 (&rb)[NV], int pair)
                     __attribute__((always_inline)) {
         unsigned long long w[2] = {1, 1}, w2[2] = {1, 1};
         unsigned long long fw[FW];
         const int fpair = TWO_PHASE ? fin[0] : ((sp_pair >= 0 && iter >= sp_due) ? sp_pair : -1);
-        const Pend due = pend[LAG - 1];
+        const Pend due = pend;
         // Phase 1 and the post of this wavefront's sums are what the whole team waits for: they run at
         // raised priority (and the request for the next pair's logits right behind them); what follows
         // overlaps with the memory latency and does not need it.
@@ -1156,11 +1136,6 @@ void pair_kernel(PairParams P) {
             request_n<FW, EARLY>(finw + words_at(fpair >= 0 ? fpair : pair, FW), GW, 0, fw, fpair >= 0);
         };
         if constexpr (!EARLY) request_words();
-        if constexpr (DEEP) {
-            // this pair's logits arrived in (ra, rb) during the last step; ask for the next pair's now
-            const bool deep_more = pair + pstep < pair_end;
-            load_item(rna, rnb, deep_more ? pair + pstep : pair, deep_more);
-        }
         asm volatile("" ::: "memory");
         fill_unowned(ra, rb);
         // ---- phase 1: maximum, then sums of 2^(z log2e - k) with k = ceil(max log2e)
@@ -1269,7 +1244,7 @@ void pair_kernel(PairParams P) {
                     asm volatile("" ::: "memory");
                     int first = sl0;
                     if constexpr (RECOMPUTE_SLOTS) asm volatile("" : "+v"(first));
-                    load_one(rna[k], rnb[k], k, next_t, next_d, more, first);
+                    load_one(ra[k], rb[k], k, next_t, next_d, more, first);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -1306,12 +1281,10 @@ void pair_kernel(PairParams P) {
         }
         PT(1);   // reductions + exp pass
         asm volatile("" ::: "memory");
-        // ---- the registers that held the logits are free: fetch the next pair (the request is
-        // unconditional: the last step asks for one slot of its own pair, which the caches hold).  In the
-        // binary32 two-phase modes only after the post below: every member's post is what the whole team's next
-        // step waits for.
-        if constexpr (!DEEP && !TWO_PHASE) {
-            load_item(rna, rnb, more ? pair + pstep : pair, more);
+        // ---- the registers that held the logits are free: fetch the next pair, if the slots have not been asked for one by one (the
+        // request is unconditional: the last step asks for one slot of its own pair, which the caches hold)
+        if constexpr (!EARLY) {
+            load_item(ra, rb, more ? pair + pstep : pair, more);
             __builtin_amdgcn_s_setprio(0);
         }
         asm volatile("" ::: "memory");
@@ -1349,12 +1322,7 @@ void pair_kernel(PairParams P) {
         unsigned long long* const post_at = word_at(part1 + words_at(pair, N1), static_cast<unsigned>(member * N1 + (pl & 3)));
         if (pl < N1) post64(post_at, mine);
         asm volatile("" ::: "memory");
-        if constexpr (TWO_PHASE) {
-            if constexpr (!DEEP && !EARLY) {
-                load_item(rna, rnb, more ? pair + pstep : pair, more);
-            }
-            __builtin_amdgcn_s_setprio(0);   // only now does the priority drop
-        }
+        if constexpr (EARLY) __builtin_amdgcn_s_setprio(0);   // only now does the priority drop
         asm volatile("" ::: "memory");
         if constexpr (JSE) wacc += st_lane;   // the lane's A_t + S_t (phase 2 of a later step combines the lanes' sums)
         if constexpr (SHARE) {
@@ -1372,9 +1340,7 @@ void pair_kernel(PairParams P) {
             // the posted value and its address stay in their registers until here: reusing them
             // earlier would make phase 2 wait for the store, and with it for the prefetch
             asm volatile("" ::"v"(mine), "v"(post_at));
-#pragma unroll
-            for (int i = LAG - 1; i > 0; --i) pend[i] = pend[i - 1];
-            pend[0] = Pend{pair, kt, kd, (st > 0.0f) || (st != st), (sd > 0.0f) || (sd != sd), dmax == __builtin_inff(), wacc, dmax, st, JSE ? sd_lane : sd};
+            pend = Pend{pair, kt, kd, (st > 0.0f) || (st != st), (sd > 0.0f) || (sd != sd), dmax == __builtin_inff(), wacc, dmax, st, JSE ? sd_lane : sd};
         }
         // ---- finishing duties: the pair whose turn has come, then note this pair if it is ours
         if (fpair >= 0) finish(fpair, fw);
@@ -1398,11 +1364,7 @@ void pair_kernel(PairParams P) {
         ++iter;
     };
 
-    // DEEP: three sets of logit registers that rotate with the three sets of exponentials (two are in
-    // use at any time; the third saves copying 64 registers a step)
-    static_assert(!DEEP || NB == 3, "the logit sets rotate with the sets of exponentials");
-    constexpr int NR = DEEP ? 3 : 1;
-    uint4 rta[NR][NV], rtb[NR][NV];
+    uint4 rta[NV], rtb[NV];
     int pair = pair0;
     if (P.self_clear) {
         const int n_mine = (pair_end > pair0) ? (pair_end - pair0 + pstep - 1) / pstep : 0;
@@ -1412,7 +1374,7 @@ void pair_kernel(PairParams P) {
     // (a team without pairs, which a tree's last teams can be, posts nothing and nobody waits for it)
     if (pair >= pair_end) return;
     asm volatile("" ::: "memory");
-    load_item(rta[0], rtb[0], pair);
+    load_item(rta, rtb, pair);
     {
         // The first pair's logits are requested before the clearing stores are waited for.  Vector memory
         // operations complete in the order they were issued, so once all but the 2 NV requests above have
@@ -1425,52 +1387,35 @@ void pair_kernel(PairParams P) {
         if (P.self_clear && lane == 0) post64(P.ws.arrive + gwave, P.ws.nonce);
         asm volatile("" ::: "memory");
     }
-    auto one_step = [&](auto SC, auto SP, int pr) __attribute__((always_inline)) {
-        constexpr int c = decltype(SC)::value % NR, n = (decltype(SC)::value + 1) % NR;
-        step(SC, SP, rta[c], rtb[c], rta[n], rtb[n], pr);
-    };
     if constexpr (TWO_PHASE) {
-        // step i keeps its exponentials in set i % NB and reads the set written LAG steps earlier
+        // step i keeps its exponentials in set i % 2 and reads the other
         bool live = pair < pair_end;
         while (live) {
-            one_step(SetId<0>{}, SetId<1 % NB>{}, pair);
+            step(SetId<0>{}, SetId<1>{}, rta, rtb, pair);
             pair += pstep;
             live = pair < pair_end;
             if (live) {
-                one_step(SetId<1>{}, SetId<2 % NB>{}, pair);
+                step(SetId<1>{}, SetId<0>{}, rta, rtb, pair);
                 pair += pstep;
                 live = pair < pair_end;
             }
-            if constexpr (NB == 3) {
-                if (live) {
-                    one_step(SetId<2>{}, SetId<0>{}, pair);
-                    pair += pstep;
-                    live = pair < pair_end;
-                }
-            }
         }
-        // ---- drain: phase 2 of the pairs still pending, oldest first, then the finishes still owed
-#pragma unroll
-        for (int d = LAG; d >= 1; --d) {
-            const Pend pp = pend[d - 1];
-            if (pp.pair >= 0) {
-                unsigned long long w[2], w2[2];
-                float ft, fd;
-                request_n<2>(part1 + words_at(pp.pair, N1), GW, 0, w);
-                request_n<2>(part1 + words_at(pp.pair, N1), GW, 64, w2, GW > 64);
-                const bool ok2 = merge_team(pp, w, w2, ft, fd);
-                const int b = (iter + NB - d) % NB;   // written at step iter - d
-                if (b == 0) phase2(pp, SetId<0>{}, ft, fd, ok2);
-                else if (b == 1) phase2(pp, SetId<1>{}, ft, fd, ok2);
-                else phase2(pp, SetId<NB - 1>{}, ft, fd, ok2);
-            }
+        // ---- drain: phase 2 of the last pair, then the finishes still owed
+        if (pend.pair >= 0) {
+            unsigned long long w[2], w2[2];
+            float ft, fd;
+            request_n<2>(part1 + words_at(pend.pair, N1), GW, 0, w);
+            request_n<2>(part1 + words_at(pend.pair, N1), GW, 64, w2, GW > 64);
+            const bool ok2 = merge_team(pend, w, w2, ft, fd);
+            if (iter & 1) phase2(pend, SetId<0>{}, ft, fd, ok2);   // written at step iter - 1
+            else phase2(pend, SetId<1>{}, ft, fd, ok2);
         }
 #pragma unroll
         for (int i = 0; i < NF; ++i) {
             if (fin[i] >= 0) finish_now(fin[i]);
         }
     } else {
-        for (; pair < pair_end; pair += pstep) one_step(SetId<0>{}, SetId<1>{}, pair);
+        for (; pair < pair_end; pair += pstep) step(SetId<0>{}, SetId<1>{}, rta, rtb, pair);
         if (sp_pair >= 0) finish_now(sp_pair);
     }
     PT(6);   // drain

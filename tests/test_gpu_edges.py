@@ -823,6 +823,30 @@ def test_largest_logit_is_negative(torch_cuda, oracle, V, kind):
         fsd.debug_set_small_calls(prev)
 
 
+# binary32 rows of whole members of 10 slots a lane (20480, 2560), a slot less, an entry more, a few slots in the last member; 8 slots a
+# lane (41000, 41003): two steps of either
+@pytest.mark.parametrize("B,K,V", [(16, 15, 20480), (16, 15, 20476), (16, 15, 20481), (100, 15, 2560), (90, 15, 2572), (8, 16, 41000), (8, 16, 41003)])
+def test_binary32_teams(torch_cuda, oracle, B, K, V):
+    inp = synth.chain_inputs(B, K, V, "f32", "peaked", (0.25, 2.0), seed=V)
+    inp["target"][1, 2] = inp["draft"][1, 2]                              # equal rows
+    inp["draft"][2, 1, : V // 2] = -np.inf                                # half of a draft row masked
+    parent = np.broadcast_to(np.maximum(np.arange(K) // 3 - 1, -1).astype(np.int32), (B, K)).copy()
+    env = pu.Envelope("f32")
+    prev = fsd.debug_set_small_calls(False)
+    try:
+        for div, T in ((fsd.DIV_JS, 0.06), (fsd.DIV_TV, 0.25), (fsd.DIV_KL, 0.25)):
+            what = f"binary32 teams B={B} K={K} V={V} div={div}"
+            print(what, flush=True)
+            g = run_chain(torch_cuda, inp, T, div, seed=5, offset=2)
+            o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], T, div, seed=5, offset=2)
+            pu.check_chain(g, o, T, pu.rel_tol("f32"), what, envelope=env)
+            g = run_tree(torch_cuda, dict(target=inp["target"], draft=inp["draft"], node_tokens=inp["cand"], parent=parent), T, div, 4, seed=5, offset=2)
+            o = oracle.verify_tree(inp["target"], inp["draft"], inp["cand"], parent, 4, T, div, oracle.SAMPLE, seed=5, offset=2)
+            pu.check_tree(g, o, T, pu.rel_tol("f32"), f"tree {what}", envelope=env)
+    finally:
+        fsd.debug_set_small_calls(prev)
+
+
 # 1: one entry; 192, 193: the most that is summed up by rank, one more; 500: more candidates than are counted in registers;
 # 64, 65 rows: the most a lane each, one more (the draw is then a kernel of its own)
 @pytest.mark.parametrize("rows,k", [(13, 1), (13, 2), (13, 192), (13, 193), (13, 500), (64, 40), (65, 40)])
