@@ -200,7 +200,7 @@ struct Residency { int total; unsigned pad_lds; };
 int g_last_grid = 0, g_last_total = 0;
 
 template <typename Kernel>
-Residency residency_of(Kernel kernel, int threads, Residency (&cache)[16]) {
+Residency residency_of(Kernel kernel, int threads, Residency (&cache)[16], int most = 0) {
     int dev = 0;
     (void)hipGetDevice(&dev);
     if (dev < 0 || dev >= 16) dev = 0;
@@ -209,6 +209,7 @@ Residency residency_of(Kernel kernel, int threads, Residency (&cache)[16]) {
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess) per_cu = 1;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 64;
         if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess) lds_cu = 0;
+        if (most > 0 && per_cu > most) per_cu = most;   // (the padding below keeps them apart)
         if (per_cu < 1) per_cu = 1;
         if (cus < 1) cus = 1;
         unsigned pad = 0;
@@ -239,7 +240,7 @@ void launch_pair_k(hipStream_t st, const PairParams& P0) {
     // persistent grid: as many whole teams as fit on the device at once (at least one, whose workgroups
     // fit by the limit on the team size), in whole workgroups; the wavefronts left over leave at once
     static Residency cache[16] = {};
-    const Residency res = residency_of(pair_kernel<BF16, NV, MODE, LD, TSHARED>, kWG, cache);
+    const Residency res = residency_of(pair_kernel<BF16, NV, MODE, LD, TSHARED>, kWG, cache, pair_kernel_most(BF16, NV, MODE));
     const long waves_per_wg = kWG / 64;
     long nteams = res.total * waves_per_wg / P0.G;
     if (nteams > P0.npairs) nteams = P0.npairs;
@@ -285,6 +286,13 @@ void launch_pair_m(int mode, int load, hipStream_t st, const PairParams& P) {
         default: launch_pair_a<BF16, NV, MODE_LSE>(load, st, P); break;
     }
 }
+// the large shape of the bfloat16 single-pass kernels: see where it is chosen
+template <int MODE>
+void launch_pair_single(int load, hipStream_t st, const PairParams& P) {
+    if (load != LOAD_ALIGNED) launch_pair_k<true, 8, MODE, LOAD_WIDE, true>(st, P);
+    else if (P.parent != nullptr) launch_pair_k<true, 8, MODE, LOAD_ALIGNED, true>(st, P);
+    else launch_pair_k<true, 8, MODE, LOAD_ALIGNED>(st, P);
+}
 // rows shorter than a slot: one shape
 template <bool BF16>
 void launch_pair_elem(int mode, hipStream_t st, const PairParams& P) {
@@ -316,6 +324,10 @@ void launch_pair(int dtype, int NV, int mode, int load, hipStream_t st, const Pa
             else launch_pair_a<true, 6, MODE_JS>(load, st, P);
         }
         else if (NV == 5) launch_pair_m<true, 5>(mode, load, st, P);
+        else if (NV == 8) {   // the library's own shape of the single-pass kernels
+            if (mode == MODE_KL) launch_pair_single<MODE_KL>(load, st, P);
+            else launch_pair_single<MODE_LSE>(load, st, P);
+        }
         else launch_pair_m<true, 4>(mode, load, st, P);
     } else {
         if (NV == 2) launch_pair_m<false, 2>(mode, load, st, P);
@@ -652,6 +664,22 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         // entropy form: whole chunks of 64 NV slots per member, so that only the last one with any
         // slots has lanes without one (those lanes cost it selections the others do not pay for)
         if (k1mode == MODE_JSE) p.spm = 64 * p.NV;
+    }
+    if (load != LOAD_ELEM && dtype == FSD_BF16 && !g_shape_nv && (k1mode == MODE_LSE || k1mode == MODE_KL)) {
+        // The bfloat16 single-pass kernels hold 8 slots of each row per lane once the rows are enough for nearly four rounds of their teams
+        // (a step's reductions and exchange, a fifth of its instructions with 4 slots, are then shared by twice the logits); with
+        // fewer the last round is too empty.  A tree's siblings read their target row once.  Whole calls, us, 4 and 8 slots, V=128256: strict SD, 24
+        // sequences of 8 35.7 and 36.3, 40 49.0 and 47.7, 64 66.7 and 64.3, 256 218 and 203; trees of 60, 5 sequences 73.5 and 75.0, 8 87.2 and
+        // 85.9, 32 195.7 and 183.8; KL on trees, 4 32.6 and 33.1, 8 51.1 and 50.4, 32 162 and 155.  KL on chains, whose 4-slot kernel waits for memory
+        // more than it computes, gains from ten rounds on: 48 of 8 51.3 and 51.6, 64 62.3 and 62.0, 200 164 and 161.  Rows that are not 16-byte
+        // aligned, V=128259: strict SD on trees 230 and 220, KL 186 and 186, but on chains 74.9 and 85.8, 72.0 and 83.0.
+        const long G8 = team_size(p.nslots, 8);
+        const long round = max_resident_wavefronts() / 8 * pair_kernel_most(true, 8, k1mode) / G8, rows_read = parent ? R + B : 2L * R;
+        if ((parent || load == LOAD_ALIGNED) && 4 * rows_read >= (k1mode == MODE_KL && !parent ? 40 : 15) * round) {
+            p.NV = 8;
+            p.G = static_cast<int>(G8);
+            p.spm = static_cast<int>((p.nslots + G8 - 1) / G8);
+        }
     }
     if (dtype == FSD_F32 && load != LOAD_ELEM && !g_shape_nv) {
         // (Of what small_call does not take: strict SD above all, and the calls its rule leaves to the teams.)

@@ -387,6 +387,12 @@ constexpr int pair_kernel_waves(bool bf16, int nv, int mode) {
     return two_phase && (bf16 ? nv == 5 || nv == 6 : nv >= 8) ? 2 : 1;
 }
 
+// Workgroups (wavefronts a SIMD) a compute unit takes at most, 0: as many as fit.  The single-pass kernels with 8 slots are faster with three than
+// with the four that fit (strict SD, 64 sequences of 8, V=128256, 64.4 and 65.0 us a call; KL 61.8 and 63.2).
+constexpr int pair_kernel_most(bool bf16, int nv, int mode) {
+    return bf16 && nv == 8 && (mode == MODE_LSE || mode == MODE_KL) ? 3 : 0;
+}
+
 // TSHARED: target rows are shared between pairs (a tree) and are loaded to stay cached (a template
 // parameter, not a run-time decision: see load_item).
 // ---- a call without a clearing kernel ---------------------------------------------------------
@@ -482,6 +488,12 @@ void pair_kernel(PairParams P) {
     // behind the second or third slot's 69.7 and 181.1, 69.8 and 181.8.  TV: C2 74.3 -> 72.0, C4 201 -> 198.  The
     // single-pass modes do not gain (strict SD at C2 66.5 -> 67.8).
     constexpr bool EARLY = TWO_PHASE;
+    // With 8 slots a lane the single-pass kernels sum up the halves of them apart: no longer chains of binary32 additions than
+    // with 4.
+    constexpr bool TWO_SUMS = BF16 && !TWO_PHASE && NV == 8;
+    // The largest bfloat16 logits by 16-bit comparisons, two at once.  (Not KL with 4 slots, which is faster with the four wavefronts a SIMD that
+    // its registers then allow than with five: 64 sequences of 8, V=128256, 61.9 and 64.1 us a call.)
+    constexpr bool PACKED = BF16 && !(MODE == MODE_KL && NV == 4);
     constexpr int NC = (NE + 3) / 4;                 // chunks of four per row
     constexpr float kTiny = 2e-38f;   // floor of u and v under the logarithm (their weights are then zero or negligible),
                                       // and of p and q where both are normalised (KL)
@@ -1148,6 +1160,7 @@ void pair_kernel(PairParams P) {
         tp_cur = tp_next;
         const bool same_target = (SHARE || SHARE_SUM) && iter > 0 && tp_cur == tp_prev;
         float kt, kd, st = 0.0f, sd = 0.0f, wacc = 0.0f, dmax = JSE ? 0.0f : neg_inf();
+        [[maybe_unused]] float st_half = 0.0f, sd_half = 0.0f, wacc_half = 0.0f;   // TWO_SUMS: of the first half of the slots
         const bool more = pair + pstep < pair_end;
         [[maybe_unused]] const char *next_t = nullptr, *next_d = nullptr;
         if constexpr (EARLY) {
@@ -1157,7 +1170,7 @@ void pair_kernel(PairParams P) {
         auto phase1 = [&](auto SAME_T) __attribute__((always_inline)) {
             constexpr bool SAME = decltype(SAME_T)::value;
             float mt = neg_inf(), md = neg_inf();
-            if constexpr (BF16) {
+            if constexpr (PACKED) {
                 if constexpr (!SAME) mt = packed_max<NV>(ra);
                 md = packed_max<NV>(rb);
             } else {
@@ -1175,7 +1188,7 @@ void pair_kernel(PairParams P) {
             }
             PT(0);   // load wait + max pass
             if constexpr (SAME) md = wave_max(md); else wave_max2(mt, md);
-            if constexpr (BF16) {
+            if constexpr (PACKED) {
                 const int sign_t = SAME ? 0 : __float_as_int(mt), sign_d = __float_as_int(md);
                 if ((sign_t | sign_d) < 0) {
                     asm volatile("");   // stays a branch
@@ -1187,6 +1200,12 @@ void pair_kernel(PairParams P) {
             kd = reference_exponent(md);
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
+                if constexpr (TWO_SUMS) {
+                    if (k == NV / 2) {
+                        st_half = st; sd_half = sd; wacc_half = wacc;
+                        st = sd = wacc = 0.0f;
+                    }
+                }
                 float a[VE], c[VE];
                 if constexpr (!SAME) unpack<BF16>(ra[k], a);
                 unpack<BF16>(rb[k], c);
@@ -1302,16 +1321,19 @@ void pair_kernel(PairParams P) {
             mine = (lane == 0) ? w0 : pack2(st, sd);
         } else {
             double pst_;
+            auto lane_sum = [](float half, float rest) __attribute__((always_inline)) {
+                return TWO_SUMS ? static_cast<double>(half) + static_cast<double>(rest) : static_cast<double>(rest);
+            };
             if (SHARE_SUM && same_target) {
                 pst_ = last_sum;
             } else {
-                pst_ = wave_sum(static_cast<double>(st));
+                pst_ = wave_sum(lane_sum(st_half, st));
             }
             if constexpr (SHARE_SUM) { last_kt = kt; last_sum = pst_; }
-            const double psd_ = wave_sum(static_cast<double>(sd));
+            const double psd_ = wave_sum(lane_sum(sd_half, sd));
             double pw_ = 0.0;
             if constexpr (MODE == MODE_KL) {
-                pw_ = wave_sum(static_cast<double>(wacc));
+                pw_ = wave_sum(lane_sum(wacc_half, wacc));
                 if (wave_max(dmax) == __builtin_inff()) pw_ = __builtin_inf();
             }
             mine = (lane == 0) ? w0 : (lane == 1) ? dbits(pst_) : (lane == 2) ? dbits(psd_) : dbits(pw_);

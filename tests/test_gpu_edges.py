@@ -847,6 +847,47 @@ def test_binary32_teams(torch_cuda, oracle, B, K, V):
         fsd.debug_set_small_calls(prev)
 
 
+# bfloat16 rows of whole members of 8 slots a lane (8192), a slot less and more, rows that are not 16-byte aligned, one member with a slot; 4100
+# is below the line in all three calls, so that either side of it is compared
+@pytest.mark.parametrize("V,copies", [(8192, 80), (8184, 80), (8200, 80), (8195, 80), (8, 2000), (4100, 20)])
+def test_bfloat16_single_pass_teams(torch_cuda, oracle, V, copies):
+    """Large calls made of copies of eight sequences: the first copy against the oracle, the others against the first."""
+    torch, B, K = torch_cuda, 8, 12
+    inp = synth.chain_inputs(B, K, V, "bf16", "peaked", (0.25, 2.0), seed=V)
+    inp["target"][1, 2] = inp["draft"][1, 2]                              # equal rows
+    inp["target"][3] = synth.to_bf16_bits(np.full((K + 1, V), -2.0, dtype=np.float32))   # negative throughout, all equal
+    parent = np.broadcast_to(np.maximum(np.arange(K) // 3 - 1, -1).astype(np.int32), (B, K)).copy()
+    dev = pu.to_dev(inp, ("target", "draft", "cand"))
+    many = {k: x.repeat(copies, *(1 for _ in x.shape[1:])) for k, x in dev.items()}
+    parents = torch.from_numpy(parent).cuda().repeat(copies, 1)
+    same = lambda x: x.reshape(copies, B, *x.shape[1:]).view(torch.int32)
+    first = lambda out, keys: {k: v[:B] for k, v in pu.host(out, keys).items()}
+
+    out = fsd.sd_verify_chain(many["target"], many["draft"], many["cand"], seed=5, offset=2)
+    torch.cuda.synchronize()
+    check_sd(first(out, pu.SD_KEYS), oracle.sd_verify_chain(inp["target"], inp["draft"], inp["cand"], seed=5, offset=2), f"SD V={V}")
+    assert (same(out["log_ratio"]) == same(out["log_ratio"])[:1]).all()
+
+    env = pu.Envelope("bf16")
+    out = fsd.fsd_verify_chain(many["target"], many["draft"], many["cand"], 0.25, fsd.DIV_KL, fsd.SAMPLE, 5, 2)
+    torch.cuda.synchronize()
+    o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], 0.25, fsd.DIV_KL, seed=5, offset=2)
+    pu.check_chain(first(out, pu.CHAIN_KEYS), o, 0.25, pu.rel_tol("bf16"), f"KL V={V}", envelope=env)
+    assert (same(out["divergences"]) == same(out["divergences"])[:1]).all()
+
+    out = fsd.fsd_verify_tree(many["target"], many["draft"], many["cand"], parents, 4, 0.25, fsd.DIV_KL, fsd.SAMPLE, 5, 2)
+    torch.cuda.synchronize()
+    o = oracle.verify_tree(inp["target"], inp["draft"], inp["cand"], parent, 4, 0.25, fsd.DIV_KL, oracle.SAMPLE, seed=5, offset=2)
+    pu.check_tree(first(out, pu.TREE_KEYS), o, 0.25, pu.rel_tol("bf16"), f"KL tree V={V}", envelope=env)
+    assert (same(out["divergences"]) == same(out["divergences"])[:1]).all()
+
+    out = fsd.sd_verify_tree(many["target"], many["draft"], many["cand"], parents, 4, seed=5, offset=2)
+    torch.cuda.synchronize()
+    o = oracle.sd_verify_tree(inp["target"], inp["draft"], inp["cand"], parent, 4, seed=5, offset=2)
+    tree = dict(target=inp["target"], draft=inp["draft"], node_tokens=inp["cand"], parent=parent)
+    check_sd_tree(first(out, pu.TREESD_KEYS), o, f"SD tree V={V}", tree)
+
+
 # 1: one entry; 192, 193: the most that is summed up by rank, one more; 500: more candidates than are counted in registers;
 # 64, 65 rows: the most a lane each, one more (the draw is then a kernel of its own)
 @pytest.mark.parametrize("rows,k", [(13, 1), (13, 2), (13, 192), (13, 193), (13, 500), (64, 40), (65, 40)])
