@@ -573,7 +573,7 @@ bool launch_warp_split_k(int B, hipStream_t st, WarpParams& P) {
         }
         if (!P.draw && W >= 2) P.list_keys = static_cast<int>(kSplitKeys / W - 1);
     }
-    if (W < 2 || (P.nslots + W - 1) / W > static_cast<long>(kSplitKeep) * kWarpWG) return false;
+    if (W < 2 || P.nslots > kSplitSlots || (P.nslots + W - 1) / W > static_cast<long>(split_keep(BF16)) * kWarpWG) return false;
     g_last_selection.store(static_cast<int>(W), std::memory_order_relaxed);
     hipLaunchKernelGGL((warp_select<BF16, LD, true, SHARED>), dim3(static_cast<unsigned>(W), static_cast<unsigned>(B)), dim3(kWarpWG), 0, st, P);
     return true;

@@ -85,7 +85,7 @@ __device__ __forceinline__ Interval bin_interval(float top, float scale, int bin
 }
 
 // KEEP: the row fits 16 slots per thread (aligned bfloat16 rows up to 131072 entries), or a share of it
-// kSplitKeep (SPLIT), and is read once into registers; otherwise every pass streams it again, four loads in
+// split_keep (SPLIT), and is read once into registers; otherwise every pass streams it again, four loads in
 // flight per thread.
 constexpr int kWarpKeep = 16;
 constexpr int kWarpList = 8192;   // entries the select can finish from LDS
@@ -93,7 +93,7 @@ constexpr int kWarpFastK = 512;   // largest top-k of the short way
 constexpr int kWarpBins = 2048;   // bins of the value histogram (16 KB of LDS)
 constexpr float kWarpRange = 28.0f;   // what lies further below the maximum weighs less than 2^-40: one bin
 
-// SPLIT: gridDim.x workgroups share a sequence, each with at most kSplitKeep slots of the row per thread, for the
+// SPLIT: gridDim.x workgroups share a sequence, each with at most split_keep slots of the row per thread, for the
 // usual settings (top-k of at most kWarpFastK, or top-p alone).  One workgroup's time is a compute unit
 // reading and passing over a whole row while most of the device is idle, so up to eight share a row and what is left
 // for one of them is the select (rows of 128256 bfloat16 entries: 64 of them under temperature 0.7, top-k 50, top-p 0.9
@@ -114,7 +114,6 @@ constexpr float kWarpRange = 28.0f;   // what lies further below the maximum wei
 // Words and counts lie in the sequence's counter line, which every call clears.  What is left for others is stored
 // with device-scope stores and performed (s_waitcnt) before the count.
 constexpr int kWarpShare = 8;
-constexpr int kSplitKeep = 5;
 constexpr int kSplitBins = kWarpWG;
 constexpr size_t kSplitBytes = 16384;   // a sequence's memory, at least; under top-p 1024 bins and lists of 2048 keys
 constexpr int kSplitKeys = 4096;        // keys and lengths of a sequence's lists under top-k, at most
@@ -124,6 +123,11 @@ constexpr int kRankKeys = 192;          // keys whose weights are summed up by r
 // (two kernels, one under top-k and one under top-p alone: what they have in common is the row and the general selects, and with the
 // one's registers and code in the other the top-p calls took 2 us longer)
 enum { SPLIT_NONE = 0, SPLIT_TOP_K = 1, SPLIT_TOP_P = 2 };
+// Slots of a share a thread keeps: 5, or 8 of binary32 rows, so that four workgroups, which is what 64 sequences have, hold rows of 131072 entries
+// (64 of them, V=128256, top-k 50, top-p 0.9: whole call 135.3 us with 5, where one workgroup a row streams it, 116.0 with 8; bfloat16, whose
+// rows fit either way, 78.8 and 79.2).  Rows of more than kSplitSlots slots are left to one workgroup.
+constexpr int split_keep(bool bf16) { return bf16 ? 5 : 8; }
+constexpr long kSplitSlots = 8L * 5 * kWarpWG;
 template <bool BF16, int LD, bool KEEP, int SHARED = SPLIT_NONE>
 __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     constexpr bool SPLIT = SHARED != SPLIT_NONE, BY_K = SHARED == SPLIT_TOP_K;
@@ -275,7 +279,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
     }
     const char* row = P.target + (static_cast<size_t>(b) * (P.rows + 1) + from) * static_cast<size_t>(P.V) * ES;
 
-    constexpr int NK = SPLIT ? kSplitKeep : kWarpKeep;
+    constexpr int NK = SPLIT ? split_keep(BF16) : kWarpKeep;
     // this workgroup's share of the row
     const long share = SPLIT ? (P.nslots + gridDim.x - 1) / gridDim.x : P.nslots;
     const long sl_lo = SPLIT ? static_cast<long>(blockIdx.x) * share : 0;

@@ -929,6 +929,23 @@ def test_cut_digits_in_several_quarters(torch_cuda, oracle, V, kw):
     check_warped(g, o, 0.01, pu.rel_tol("f32"), f"cuts V={V} {kw}", envelope=pu.Envelope("f32"))
 
 
+# two workgroups a sequence: all slots of their threads in use, rows that are not 16-byte aligned, one slot too many
+@pytest.mark.parametrize("V,workgroups", [(65536, 2), (65533, 2), (65540, 1)])
+@pytest.mark.parametrize("kw", [dict(top_k=40, top_p=0.9, temperature=0.8), dict(top_p=0.8)])
+def test_binary32_shares_of_eight_slots(torch_cuda, oracle, V, workgroups, kw):
+    """25 copies of four sequences: the first copy against the oracle, the cuts of the others against the first's."""
+    inp = synth.chain_inputs(4, 8, V, "f32", "peaked", (0.25, 2.0), seed=V)
+    inp["target"][1, :, V // 3:] = -np.inf
+    inp["target"][2] = np.round(inp["target"][2] * 4) / 4
+    many = {k: np.tile(inp[k], (25,) + (1,) * (inp[k].ndim - 1)) for k in ("target", "draft", "cand")}
+    g = run_warped(torch_cuda, many, 0.05, fsd.DIV_JS, fsd.SAMPLE, 9, 4, **kw)
+    assert fsd.debug_last_selection() == workgroups
+    cuts = g["threshold"].reshape(25, 4)
+    assert (cuts == cuts[:1]).all()
+    o = oracle.verify_chain_warped(inp["target"], inp["draft"], inp["cand"], 0.05, fsd.DIV_JS, fsd.SAMPLE, 9, 4, **kw)
+    check_warped({k: v[:4] for k, v in g.items()}, o, 0.05, pu.rel_tol("f32"), f"shares V={V} {kw}", envelope=pu.Envelope("f32"))
+
+
 def test_draw_with_the_selection_over_malformed_trees(torch_cuda, oracle):
     """A tree with a parent behind its child, one deeper than the call allows and one as it should be: what the draw with the selection
     reports, and that it leaves nothing of the first two."""
