@@ -372,15 +372,18 @@ void launch_sample(int dtype, int load, int kind, dim3 grid, size_t lds, hipStre
 // step with the sampler behind it, and in one launch; (n) is n sequences of 8 unless said otherwise, [n] one tree of n nodes.
 //   reduction  one step of the whole device, until the members' words cost more than the teams' second step.
 //     JS   bfloat16 V=32000 [60] 16.7 14.6, 3 of 60 19.9 19.2; V=64000 (8) 18.6 16.6, (12) 19.6 19.6; V=128256 [30] 18.4 17.1, [36] 19.0 19.5, (4)
-//          18.9 17.3, (5) 19.7 19.1, (6) 20.1 20.9; V=256000, 5 of 4 21.3 20.7; V=210901, 2 of 14 23.6 21.7
-//          binary32 V=32000 [30] 13.8 13.8, [60] 15.1 15.5, 2 of 60 19.2 18.0; V=64000 (4) 15.4 16.1, (6) 18.6 17.8, (12) 23.4 23.0; V=128256 (3) 18.8
-//          18.0, (4) 19.8 19.7, (5) 22.4 23.8.  (From 1 million entries on, where the teams need one step, about 2 million, that is the faster one.)
+//          18.9 17.3, (5) 19.7 19.1, (6) 20.1 20.9, 7 of 5 18.8 18.5, 8 of 5 19.1 19.7; V=256000, 5 of 4 21.3 20.7; V=210901, 2 of 14 23.6 21.7
+//          binary32 V=32000 [30] 13.8 13.8, 22 of 5 17.6 17.6, 28 of 5 19.7 21.1, 7 of 16 nodes 17.8 17.9, 10 of 16 nodes 22.7 21.5; V=50257, 14 of 5 18.1
+//          17.8, 18 of 5 20.2 21.3; V=64000, 11 of 5 18.1 18.0, 16 of 5 20.8 22.6, 6 of 16 nodes 23.0 22.0; V=100000, 7 of 5 17.9 18.7; V=128256, 6 of 5 18.0
+//          19.3.  (From 1 million entries on, where the teams need one step, about 2 million, that is the faster one.  The binary32 lines were
+//          drawn when the teams ran one wavefront a SIMD; chains, by these figures of today, would be with the teams from 3.5 million entries on, 3.25 million of
+//          long rows and under TV.  The routes' tests have the lines where they are.)
 //     TV   bfloat16 V=32000 [60] 15.7 14.9; V=64000 (4) 14.9 14.6, (6) 15.2 16.2; V=128256 (2) 15.1 15.2, (3) 15.6 16.4; V=200000, 4 of 4 18.1 17.6,
 //          6 of 4 19.6 20.1; rows that are not 16-byte aligned V=40265, 21 of 4 19.7 17.6, V=235817, 2 of 9 22.3 19.1
-//          binary32 V=32000 [30] 13.6 14.5, [60] 15.1 16.1, 2 of 60 18.7 18.2; V=64000 (4) 15.2 17.2, (8) 19.4 19.2; V=128256 (3) 18.6 18.6, (4) 19.4 20.5;
-//          V=98752 [41], three steps of the teams, 21.5 20.6
-//     KL   binary32 V=32000 [60] 16.5 15.8; V=64000 (6) 21.0 18.7, (12) 27.1 24.6; V=128256 (4) 22.0 21.7, (6) 26.8 27.2; bfloat16 has a single pass in large
-//          calls: V=32000 [30] 13.3 14.9
+//          binary32 V=32000 [30] 13.6 14.5, [60] 15.1 16.1, 28 of 5 19.5 21.5; V=50257, 14 of 5 18.3 18.4, 18 of 5 19.9 21.4; V=64000 (4) 15.2 17.2, 14 of 5
+//          19.8 21.6; V=98752 [41], three steps of the teams, 21.5 20.6
+//     KL   binary32 V=32000, 22 of 5 19.8 18.8, 37 of 5 25.6 24.7, 10 of 16 nodes 26.3 22.7; V=64000, 11 of 5 20.3 19.3, 19 of 5 25.8 25.2; V=100000, 7 of 5 20.3
+//          20.4, 10 of 5 23.0 25.5; V=128256, 6 of 5 20.1 21.0, 8 of 5 22.6 25.1; bfloat16 has a single pass in large calls: V=32000 [30] 13.3 14.9
 //     Reducible FSD: JS bfloat16 V=64000 (12) 20.5 19.3, V=128256 (4) 19.6 17.1, (6) 20.9 21.0; TV V=64000 (8) 19.5 17.2, V=128256 (5) 20.3 20.9.
 //   one launch draws from all rows, and one workgroup a sequence reads all its words: worth less the more of both there is.
 //     JS   bfloat16 V=128256 (2) 16.4 14.4 11.3, (3) 16.8 15.9 14.8, (4) 18.9 17.3 17.7; [16] 16.7 14.8 12.2, [30] 18.4 17.1 18.6; V=32000 [30] 16.3 14.4
