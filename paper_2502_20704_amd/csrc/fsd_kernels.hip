@@ -235,12 +235,12 @@ Residency residency_of(Kernel kernel, int threads, Residency (&cache)[16], int m
     return cache[dev];
 }
 
-template <bool BF16, int NV, int MODE, int LD, bool TSHARED = false>
+template <bool BF16, int NV, int MODE, int LD, bool TSHARED = false, bool EVEN = false>
 void launch_pair_k(hipStream_t st, const PairParams& P0) {
     // persistent grid: as many whole teams as fit on the device at once (at least one, whose workgroups
     // fit by the limit on the team size), in whole workgroups; the wavefronts left over leave at once
     static Residency cache[16] = {};
-    const Residency res = residency_of(pair_kernel<BF16, NV, MODE, LD, TSHARED>, kWG, cache, pair_kernel_most(BF16, NV, MODE));
+    const Residency res = residency_of(pair_kernel<BF16, NV, MODE, LD, TSHARED, EVEN>, kWG, cache, pair_kernel_most(BF16, NV, MODE));
     const long waves_per_wg = kWG / 64;
     long nteams = res.total * waves_per_wg / P0.G;
     if (nteams > P0.npairs) nteams = P0.npairs;
@@ -252,10 +252,10 @@ void launch_pair_k(hipStream_t st, const PairParams& P0) {
     if (g_prof_pair) {
         // timed launch: the events take the start and the end of this dispatch itself (what a
         // kernel trace shows), not the time between two markers around it in the stream
-        hipExtLaunchKernelGGL((pair_kernel<BF16, NV, MODE, LD, TSHARED>), dim3(static_cast<unsigned>(grid)), dim3(kWG), res.pad_lds, st,
+        hipExtLaunchKernelGGL((pair_kernel<BF16, NV, MODE, LD, TSHARED, EVEN>), dim3(static_cast<unsigned>(grid)), dim3(kWG), res.pad_lds, st,
                               g_prof_pair[0], g_prof_pair[1], 0, P);
     } else {
-        hipLaunchKernelGGL((pair_kernel<BF16, NV, MODE, LD, TSHARED>), dim3(static_cast<unsigned>(grid)), dim3(kWG), res.pad_lds, st, P);
+        hipLaunchKernelGGL((pair_kernel<BF16, NV, MODE, LD, TSHARED, EVEN>), dim3(static_cast<unsigned>(grid)), dim3(kWG), res.pad_lds, st, P);
     }
 }
 template <bool BF16, int NV, int MODE>
@@ -271,6 +271,14 @@ void launch_pair_a(int load, hipStream_t st, const PairParams& P) {
     } else {
         if constexpr (kOwn) {
             if (shared) { launch_pair_k<BF16, NV, MODE, LOAD_WIDE, true>(st, P); return; }
+        }
+        // Chains of bfloat16 rows some of which begin in the middle of a 32-bit word: see pair_kernel's EVEN.  (Other rows would only pay for it, V=128258
+        // 71.7 -> 74.9 us; trees of odd rows 208 -> 211, the entropy form's kernel has no registers left there.)
+        if constexpr (BF16 && (NV == 6 || (NV == 4 && (MODE == MODE_LSE || MODE == MODE_KL)))) {
+            if (P.V % 2 != 0 || ((reinterpret_cast<uintptr_t>(P.target) | reinterpret_cast<uintptr_t>(P.draft)) & 2) != 0) {
+                launch_pair_k<BF16, NV, MODE, LOAD_WIDE, false, true>(st, P);
+                return;
+            }
         }
         launch_pair_k<BF16, NV, MODE, LOAD_WIDE>(st, P);
     }

@@ -470,7 +470,7 @@ __device__ __noinline__ bool team_arrived(const unsigned long long* slots, int G
     return true;
 }
 
-template <bool BF16, int NV, int MODE, int LD, bool TSHARED = false>
+template <bool BF16, int NV, int MODE, int LD, bool TSHARED, bool EVEN = false>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(pair_kernel_waves(BF16, NV, MODE))))
 void pair_kernel(PairParams P) {
     constexpr int VE = Slot<BF16>::VE;
@@ -620,6 +620,15 @@ void pair_kernel(PairParams P) {
     [[maybe_unused]] const unsigned off_last = ((LD == LOAD_WIDE) && s1 > s0 && s1 * VE > P.V) ? static_cast<unsigned>(P.V) * ES - 16u
                                                                             : static_cast<unsigned>(sl_last) * 16u;
     const bool fill_needed = s0 + NV * 64 > s1;   // wavefront-uniform: some lane lacks a slot
+    // EVEN: bfloat16 rows that begin in the middle of a 32-bit word (every second row of an odd vocabulary) are requested two bytes
+    // on, a whole word each, so that a lane holds entries 1 to 8 of its slots; entry 0 comes from the lane before it, and lane 0's is
+    // requested apart (lane k: slot k of the target row, lane 8 + k: of the draft row).  The row's last slot is the 16 bytes that end the row, as
+    // ever.  Requests at odd entries cost more than the moves: 64 sequences of 8, V=128259, 84.4 us a call with them, 78.2 without;
+    // 16 of 5 28.0 and 26.5; strict SD 74.4 and 69.0.
+    [[maybe_unused]] unsigned ahead_t = 0, ahead_d = 0, entry0 = 0;   // bytes, of the rows requested last
+    [[maybe_unused]] auto row_ahead = [&](const char* row) __attribute__((always_inline)) -> unsigned {
+        return P.V > 8 ? static_cast<unsigned>(reinterpret_cast<uintptr_t>(row)) & 2u : 0u;
+    };
     // target rows of the pair in work, of the one before it and of the one requested last (entropy-form JS on
     // a tree: a pair whose target row is its predecessor's takes over that row's exponentials and sums)
     const char *tp_prev = nullptr, *tp_cur = nullptr, *tp_next = nullptr;
@@ -633,14 +642,28 @@ void pair_kernel(PairParams P) {
             if (load_j >= P.rows) { load_j -= P.rows; ++load_b; }
         }
         row_ptrs_bj(pair, load_b, load_j, tptr, dptr);
+        if constexpr (EVEN) { ahead_t = row_ahead(tptr); ahead_d = row_ahead(dptr); }
+    };
+    // EVEN: the entries that no lane before lane 0 has; where a row lies as it should they are not used
+    [[maybe_unused]] auto request_entry0 = [&](const char* tptr, const char* dptr) __attribute__((always_inline)) {
+        const unsigned off = (static_cast<unsigned>(s0) + 64u * (lane & 7)) * 16u, last = static_cast<unsigned>(P.V) * 2u - 2u;
+        const char* const row = (lane & 8) ? dptr : tptr;
+        entry0 = *reinterpret_cast<const unsigned short*>(row + (off < last ? off : last));
+    };
+    // (EVEN: the last 16 bytes of the row, from where it is requested)
+    [[maybe_unused]] auto row_limit = [&](unsigned limit, unsigned ahead) __attribute__((always_inline)) -> unsigned {
+        if constexpr (!EVEN) return limit;
+        const unsigned end = static_cast<unsigned>(P.V) * ES - 16u - ahead;
+        return limit < end ? limit : end;
     };
     // slot k of both rows, for the lane whose first slot is `first` (not wanted: one cached slot for all lanes)
     auto load_one = [&](uint4& a, uint4& b, int k, const char* tptr, const char* dptr, bool wanted, int first) __attribute__((always_inline)) {
         if constexpr (LD == LOAD_WIDE) {
             // (one minimum keeps a lane inside the slice and inside the row)
             const unsigned off = static_cast<unsigned>(first) * 16u + 1024u * k, limit = wanted ? off_last : 0u;
-            a = load_16<LD, !TSHARED>(tptr, off < limit ? off : limit);
-            b = load_16<LD, true>(dptr, off < limit ? off : limit);
+            const unsigned limit_t = row_limit(limit, ahead_t), limit_d = row_limit(limit, ahead_d);
+            a = load_16<LD, !TSHARED>(tptr + ahead_t, off < limit_t ? off : limit_t);
+            b = load_16<LD, true>(dptr + ahead_d, off < limit_d ? off : limit_d);
         } else {
             const int sk = first + 64 * k;
             const long sl = wanted ? (sk < sl_end ? sk : sl_last) : 0;
@@ -662,30 +685,51 @@ void pair_kernel(PairParams P) {
         // being kept: hidden from the hoisting of loop invariants)
         int first = sl0;
         if constexpr (RECOMPUTE_SLOTS) asm volatile("" : "+v"(first));
+        if constexpr (EVEN) request_entry0(tptr, dptr);
         if constexpr (SHARE_SUM) {
             // the target's requests first: with them the draft's are the last in flight whether or not they are
             // made, so the wait for the draft row stays exact
             const unsigned limit = wanted ? off_last : 0u;
-            const auto off_of = [&](int k) __attribute__((always_inline)) {
+            const unsigned limit_t = row_limit(limit, ahead_t), limit_d = row_limit(limit, ahead_d);
+            const auto off_of = [&](int k, unsigned most) __attribute__((always_inline)) {
                 const unsigned off = static_cast<unsigned>(first) * 16u + 1024u * k;
-                return off < limit ? off : limit;
+                return off < most ? off : most;
             };
             if (!again) {
 #pragma unroll
-                for (int k = 0; k < NV; ++k) ra[k] = load_16<LD, false>(tptr, off_of(k));
+                for (int k = 0; k < NV; ++k) ra[k] = load_16<LD, false>(tptr + ahead_t, off_of(k, limit_t));
             }
             asm volatile("" ::: "memory");
 #pragma unroll
-            for (int k = 0; k < NV; ++k) rb[k] = load_16<LD, true>(dptr, off_of(k));
+            for (int k = 0; k < NV; ++k) rb[k] = load_16<LD, true>(dptr + ahead_d, off_of(k, limit_d));
             return;
         }
 #pragma unroll
         for (int k = 0; k < NV; ++k) load_one(ra[k], rb[k], k, tptr, dptr, wanted, first);
     };
+    // EVEN: every lane's entries 0 to 7 from its entries 1 to 8 and the one before them, but for the row's last slot
+    [[maybe_unused]] auto from_ahead = [&](uint4 (&r)[NV], int at) __attribute__((always_inline)) {
+        int first = sl0;
+        if constexpr (EARLY) asm volatile("" : "+v"(first)); else asm volatile("");   // stays a branch
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const int own = static_cast<int>(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(entry0), at + k)) << 16);
+            const unsigned before = static_cast<unsigned>(__builtin_amdgcn_update_dpp(own, static_cast<int>(r[k].w), 0x138, 0xF, 0xF, false));   // wave_shr:1
+            const unsigned pick = (first + 64 * k == P.nslots - 1) ? 0x07060504u : 0x05040302u;
+            r[k].w = __builtin_amdgcn_perm(r[k].w, r[k].z, pick);
+            r[k].z = __builtin_amdgcn_perm(r[k].z, r[k].y, pick);
+            r[k].y = __builtin_amdgcn_perm(r[k].y, r[k].x, pick);
+            r[k].x = __builtin_amdgcn_perm(r[k].x, before, pick);
+        }
+    };
     // (EARLY, the kernels short of scalar registers: the bounds are hidden from the hoisting of loop invariants, which kept a
     // mask for every slot across the loop, spilled to lanes of a vector register.)
     auto fill_unowned = [&](uint4 (&ra)[NV], uint4 (&rb)[NV]) __attribute__((always_inline)) {
         int first = sl0, end = sl_end;
+        if constexpr (EVEN) {
+            if (ahead_t) from_ahead(ra, 0);
+            if (ahead_d) from_ahead(rb, 8);
+        }
         if constexpr (LD == LOAD_WIDE) {
             // the slot that reaches past the end of the row belongs to one lane of the team's last member
             if (s1 > s0 && s1 * VE > P.V) {
@@ -1268,7 +1312,10 @@ void pair_kernel(PairParams P) {
                     // (both arms of the branch on a shared target row make the same requests in the same order, so the
                     // compiler's count of what is in flight stays exact)
                     asm volatile("" ::: "memory");
-                    if (k == 0) request_words();
+                    if (k == 0) {
+                        request_words();
+                        if constexpr (EVEN) request_entry0(next_t, next_d);
+                    }
                     asm volatile("" ::: "memory");
                     int first = sl0;
                     if constexpr (RECOMPUTE_SLOTS) asm volatile("" : "+v"(first));

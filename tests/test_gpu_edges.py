@@ -888,6 +888,45 @@ def test_bfloat16_single_pass_teams(torch_cuda, oracle, V, copies):
     check_sd_tree(first(out, pu.TREESD_KEYS), o, f"SD tree V={V}", tree)
 
 
+# Rows that begin in the middle of a 32-bit word: every second one of an odd vocabulary (9: two slots, the last of one entry; around whole members of 6 and
+# of 4 slots a lane), or all of a tensor that begins there itself (t, d: entries by which the target and the draft are moved); a last slot that is whole
+@pytest.mark.parametrize("V,t,d", [(9, 0, 0), (15, 0, 1), (513, 0, 0), (1535, 1, 0), (2047, 0, 0), (2049, 1, 1), (3071, 0, 0), (3073, 0, 1), (6145, 0, 0),
+                                   (16, 1, 0), (2048, 0, 1), (3072, 1, 1), (3080, 1, 0), (40007, 0, 0)])
+def test_rows_in_the_middle_of_a_word(torch_cuda, oracle, V, t, d):
+    torch, B, K = torch_cuda, 9, 7
+    inp = synth.chain_inputs(B, K, V, "bf16", "peaked", (0.25, 2.0), seed=V)
+    if V > 100:
+        inp["target"][1, 2, V - 3:] = 0xFF80
+        inp["draft"][1, 2, V - 3:] = 0xFF80
+    dev = pu.to_dev(inp, ("target", "draft", "cand"))
+
+    def moved(x, by):
+        flat = torch.zeros(x.numel() + by, dtype=x.dtype, device=x.device)
+        flat[by:] = x.reshape(-1)
+        return flat[by:].view(x.shape)
+
+    target, draft = moved(dev["target"], t), moved(dev["draft"], d)
+    tol, env = pu.rel_tol("bf16"), pu.Envelope("bf16")
+    prev = fsd.debug_set_small_calls(False)
+    try:
+        for div, T in ((fsd.DIV_JS, 0.06), (fsd.DIV_TV, 0.25), (fsd.DIV_KL, 0.2)):
+            what = f"middle of a word V={V} t={t} d={d} div={div}"
+            print(what, flush=True)
+            out = fsd.fsd_verify_chain(target, draft, dev["cand"], T, div, fsd.SAMPLE, 5, 2)
+            torch.cuda.synchronize()
+            o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], T, div, seed=5, offset=2)
+            pu.check_chain(pu.host(out, pu.CHAIN_KEYS), o, T, tol, what, envelope=env)
+            out = fsd.rfsd_verify_chain(target, draft, dev["cand"], T, div, fsd.SAMPLE, 5, 2)
+            torch.cuda.synchronize()
+            o = oracle.rfsd_verify_chain(inp["target"], inp["draft"], inp["cand"], T, div, seed=5, offset=2)
+            check_rfsd(pu.host(out, pu.RFSD_KEYS), o, T, tol, what, envelope=env)
+        out = fsd.sd_verify_chain(target, draft, dev["cand"], seed=5, offset=2)
+        torch.cuda.synchronize()
+        check_sd(pu.host(out, pu.SD_KEYS), oracle.sd_verify_chain(inp["target"], inp["draft"], inp["cand"], seed=5, offset=2), f"SD V={V} t={t} d={d}")
+    finally:
+        fsd.debug_set_small_calls(prev)
+
+
 # 1: one entry; 192, 193: the most that is summed up by rank, one more; 500: more candidates than are counted in registers;
 # 64, 65 rows: the most a lane each, one more (the draw is then a kernel of its own)
 @pytest.mark.parametrize("rows,k", [(13, 1), (13, 2), (13, 192), (13, 193), (13, 500), (64, 40), (65, 40)])
