@@ -30,6 +30,12 @@ __device__ __forceinline__ float key_value(unsigned k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }
 
+// The bound of a list of a row's largest entries, from the upper half of a key that enough of them reach.  A bound of +0 lets
+// -0 in as well, whose key lies right below: the two are one number, and ties at a threshold are kept.
+__device__ __forceinline__ unsigned list_bound(unsigned key) {
+    return key == 0x80000000u ? 0x7FFFFFFFu : key;
+}
+
 // the bitwise or over the wavefront
 __device__ __forceinline__ unsigned wave_or(unsigned v) {
     v |= static_cast<unsigned>(dpp_i<kDppSwap1>(static_cast<int>(v)));
@@ -721,7 +727,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
             s_tmax[tid] = ordered_key(tmax);
             if (tid == 0) s_nlist = 0;
             __syncthreads();
-            const unsigned low = count_select(s_tmax, kWarpWG, k, 16);   // (any bound with k entries at or above it)
+            const unsigned low = list_bound(count_select(s_tmax, kWarpWG, k, 16));   // (any bound with k entries at or above it)
             for_each_at([&](float, unsigned key, int place) {
                 if (key >= low) {
                     const int at = atomicAdd(&s_nlist, 1);
@@ -1000,7 +1006,7 @@ __global__ __launch_bounds__(kWarpWG) void warp_select(WarpParams P) {
         if (tid == 0) { s_need = static_cast<unsigned long long>(P.top_k); s_nlist = 0; }
         __syncthreads();
         lds_select(s_tmax, kWarpWG, one, AsNeeded{}, 16);   // (any bound with k entries at or above it)
-        const unsigned low = s_prefix;   // at most the key of L
+        const unsigned low = list_bound(s_prefix);   // at most the key of L
         for_each([&](float, unsigned key) {
             if (key >= low) {
                 const int at = atomicAdd(&s_nlist, 1);

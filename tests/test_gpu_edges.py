@@ -1005,3 +1005,32 @@ def test_draw_with_the_selection_over_malformed_trees(torch_cuda, oracle):
     for key in ("row_status", "path_len", "path_nodes", "out_tokens"):
         assert (g[key] == o[key]).all(), key
     assert (g["path_len"][:2] == 0).all() and (g["out_tokens"][:2] == -1).all() and (g["path_nodes"][:2] == -1).all()
+
+
+# zeros of either sign: so many that every share has more of them than are kept, or 150 of each behind 100 larger entries, where
+# the nucleus reaches them only if all are counted; several workgroups a row, and one
+@pytest.mark.parametrize("V,dtype,rows,W", [(40000, "bf16", 13, 5), (40003, "f32", 13, 8), (3000, "bf16", 1, 1), (3001, "bf16", 1, 1), (3000, "f32", 1, 1)])
+@pytest.mark.parametrize("ones,zeros,kw", [(20, 1500, dict(top_k=60)), (20, 1500, dict(top_k=60, top_p=0.9)), (100, 150, dict(top_k=120, top_p=0.5))])
+def test_zeros_of_either_sign_tie(torch_cuda, oracle, V, dtype, rows, W, ones, zeros, kw):
+    """A cut at zero keeps +0 and -0 alike, in the draw and in the nucleus' mass."""
+    B = 6
+    rng = np.random.default_rng(V + ones)
+    zeros = min(zeros, V // 3)
+    t = rng.uniform(-9, -1, (B, rows + 1, V)).astype(np.float32)
+    at = rng.permutation(V)
+    t[..., at[:zeros]] = 0.0
+    t[..., at[zeros: 2 * zeros]] = -0.0
+    t[..., at[2 * zeros: 2 * zeros + ones]] = 1.0
+    d = t[:, :rows] + rng.standard_normal((B, rows, V)).astype(np.float32) * np.float32(0.3)
+    inp = dict(target=t, draft=d, cand=rng.integers(0, V, (B, rows)).astype(np.int32))
+    if dtype == "bf16":
+        inp.update(target=synth.to_bf16_bits(t), draft=synth.to_bf16_bits(d))
+    for offset in range(3):
+        what = f"zeros V={V} {dtype} {kw} offset={offset}"
+        print(what, flush=True)
+        g = run_warped(torch_cuda, inp, 0.1, fsd.DIV_TV, fsd.SAMPLE, 9, offset, **kw)
+        assert fsd.debug_last_selection() == W
+        o = oracle.verify_chain_warped(inp["target"], inp["draft"], inp["cand"], 0.1, fsd.DIV_TV, fsd.SAMPLE, 9, offset, **kw)
+        assert (o["threshold"] == 0).all() and (o["slack"] > 1e-5).all()
+        check_warped(g, o, 0.1, pu.rel_tol(dtype), what, envelope=pu.Envelope(dtype))
+        assert (g["out_tokens"] == o["out_tokens"]).all() or (o["gap"] < 1e-6).any(), what
