@@ -370,7 +370,7 @@ int fsd_debug_set_small_calls(int on);
 int fsd_debug_last_route(void);
 
 /* Test hook: workgroups a sequence of the last warped call's selection of kept
- * logits (1: one works alone). */
+ * logits (1: one works alone, or there was nothing to select). */
 int fsd_debug_last_selection(void);
 
 /* Test hook: byte offset, inside a workspace of fsd_workspace_bytes(B,

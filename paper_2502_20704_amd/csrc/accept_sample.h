@@ -667,6 +667,7 @@ __global__ __launch_bounds__(kWG) void accept_sample(SampleParams P) {
         if (lane == 0) {
             P.out_len[b] = n;
             if (P.row_status) P.row_status[b] = final_status;
+            if (P.cut && P.thr == nullptr) P.ws.thr[b] = neg_inf();   // (nothing was selected: nothing is cut)
             if (failed) sequence_of_failed_call_done(P.ws);
         }
     }

@@ -907,8 +907,11 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
                                               : (load == LOAD_ALIGNED ? launch_warp_split<false, LOAD_ALIGNED>(B, st, wp)
                                                                       : launch_warp_split<false, LOAD_WIDE>(B, st, wp)));
         if (split && wp.draw) return (hipGetLastError() == hipSuccess) ? FSD_OK : FSD_ERR_LAUNCH;   // (it has drawn the token as well)
-        if (split || (!want_k && !want_p)) {
-            // launched, or nothing to select: temperature alone keeps everything
+        if (split) {
+            // (launched)
+        } else if (!want_k && !want_p) {
+            // nothing to select: temperature alone keeps everything, and the sampler leaves the cut that says so
+            g_last_selection.store(1, std::memory_order_relaxed);
         } else if (dtype == FSD_BF16) {
             if (keep) warp(warp_select<true, LOAD_ALIGNED, true>);
             else if (load == LOAD_ALIGNED) warp(warp_select<true, LOAD_ALIGNED, false>);

@@ -1034,3 +1034,27 @@ def test_zeros_of_either_sign_tie(torch_cuda, oracle, V, dtype, rows, W, ones, z
         assert (o["threshold"] == 0).all() and (o["slack"] > 1e-5).all()
         check_warped(g, o, 0.1, pu.rel_tol(dtype), what, envelope=pu.Envelope(dtype))
         assert (g["out_tokens"] == o["out_tokens"]).all() or (o["gap"] < 1e-6).any(), what
+
+
+# rows of at most a wavefront's lanes and of more, a tree; one workgroup that draws, and several
+@pytest.mark.parametrize("rows,V,tree", [(4, 33000, False), (70, 2000, False), (13, 40003, True)])
+def test_temperature_alone_cuts_nothing(torch_cuda, oracle, rows, V, tree):
+    """A temperature without top-k and top-p: the cuts left behind are -inf on a workspace that an earlier call has left others on,
+    also where nothing is drawn."""
+    B = 4
+    inp = _random_tree_inputs(np.random.default_rng(V), B, rows, V, "bf16")
+    inp["target"][1, :, V // 2] = 0x7FC0                                  # unusable
+    dev = pu.to_dev(inp, ("target", "draft", "node_tokens", "parent"))
+    ws = torch_cuda.empty(fsd.fsd_workspace_bytes(B, rows, V, fsd.BF16) + 256, dtype=torch_cuda.uint8, device="cuda")
+    ws.fill_(0x3F)
+    for kw in (dict(top_k=30), dict(temperature=0.7)):
+        if tree:
+            out = fsd.fsd_verify_tree_warped(dev["target"], dev["draft"], dev["node_tokens"], dev["parent"], rows, 0.1, fsd.DIV_TV, fsd.SAMPLE, 9, 4,
+                                             workspace=ws, **kw)
+        else:
+            out = fsd.fsd_verify_chain_warped(dev["target"], dev["draft"], dev["node_tokens"], 0.1, fsd.DIV_TV, fsd.SAMPLE, 9, 4, workspace=ws, **kw)
+        torch_cuda.cuda.synchronize()
+        cuts = fsd.debug_warp_thresholds(out, B, rows, V, fsd.BF16).cpu().numpy()
+        assert list(out["row_status"].cpu().numpy()) == [0, fsd.ROW_NONFINITE, 0, 0]
+        assert (cuts[[0, 2, 3]] > -np.inf).all() == ("top_k" in kw), cuts
+    assert (cuts == -np.inf).all() and fsd.debug_last_selection() == 1
