@@ -313,18 +313,11 @@ template <int MODE>   // MODE_JS: twice the divergence in units of ln 2 (MODE_KL
 __device__ __forceinline__ void pointwise_term(float p, float q, float& acc) {
     [[maybe_unused]] constexpr float kTiny = 2e-38f;   // floor of u and v under the logarithm (their weights are then zero or negligible)
     const float d = p - q, sum = p + q;
+    // (JS) p = q = 0: 0 * inf = NaN, which max() drops (u = kTiny, v = 2, both weights zero)
+    // (Both floors in one median instruction, v's at 2^-23, took 0.8 us of 108 off 32 sequences of 10, V=256000, reducible FSD. But u then ends
+    // at 2 - 2^-23, where an entry that only the target has must have 2: 4e-8 of the divergence of disjoint rows, always too little.)
     const float inv = __builtin_amdgcn_rcpf(sum);
-    float u, v;
-    if constexpr (MODE == MODE_JS) {
-        // Both floors in one instruction: u is rounded to multiples of 2^-24 and v to multiples of 2^-23, which are what they are kept
-        // above.  (32 sequences of 10, V=256000, reducible FSD, 108.6 -> 107.7 us a call.)  p = q = 0: 0 * inf = NaN, which the median
-        // drops for the smaller bound (both weights zero).
-        u = __builtin_amdgcn_fmed3f(fmaf(d, inv, 1.0f), 0x1p-24f, 0x1.fffffep0f);
-        v = 2.0f - u;
-    } else {
-        u = fmaxf(fmaf(d, inv, 1.0f), kTiny);
-        v = fmaxf(2.0f - u, kTiny);
-    }
+    float u = fmaxf(fmaf(d, inv, 1.0f), kTiny), v = fmaxf(2.0f - u, kTiny);
     if constexpr (MODE == MODE_KLP) {
         // u = 1 + r and v = 2 - u carry an absolute error of 2^-23: harmless for JS, where a
         // small u or v comes with a small weight, but KL weighs ln(u/v) with the larger of the

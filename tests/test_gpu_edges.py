@@ -1058,3 +1058,29 @@ def test_temperature_alone_cuts_nothing(torch_cuda, oracle, rows, V, tree):
         assert list(out["row_status"].cpu().numpy()) == [0, fsd.ROW_NONFINITE, 0, 0]
         assert (cuts[[0, 2, 3]] > -np.inf).all() == ("top_k" in kw), cuts
     assert (cuts == -np.inf).all() and fsd.debug_last_selection() == 1
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 20000), ("f32", 20000), ("f32", 3001)])
+def test_js_of_disjoint_rows_does_not_lean(torch_cuda, dtype, V):
+    """Rows of disjoint support, whose divergence is ln 2, in the pointwise form: what rounding makes of it lies on either side.  An entry
+    of one row alone weighs its whole probability, whichever row that is; with the next lower number under the logarithm
+    (2 - 2^-23 for 2) a row's half of the divergence would lose 6e-8 to 9e-8 of itself, 3e-8 to 4e-8 of the whole.  The mean of 256
+    roundings to binary32 (6e-8 apart) is 1e-9 off."""
+    B, K = 32, 8
+    inp = synth.chain_inputs(B, K, V, "f32", "gauss2", 1.0, seed=V)
+    first = np.random.default_rng(V).random(V) < 0.5
+    inp["target"][:, :, first] = -np.inf
+    inp["draft"][:, :, ~first] = -np.inf
+    inp["cand"][:] = np.nonzero(first)[0][0]
+    if dtype == "bf16":
+        inp.update(target=synth.to_bf16_bits(inp["target"]), draft=synth.to_bf16_bits(inp["draft"]))
+    swapped = dict(target=np.concatenate([inp["draft"], inp["draft"][:, :1]], 1), draft=inp["target"][:, :K], cand=np.full_like(inp["cand"], np.nonzero(~first)[0][0]))
+    prev = fsd.debug_set_exact_js(True), fsd.debug_set_small_calls(False)
+    try:
+        for run in (run_chain, run_rfsd):
+            err = [(run(torch_cuda, x, 0.1, fsd.DIV_JS, fsd.SAMPLE, 5, 2)["divergences"].astype(np.float64) / np.log(2.0) - 1.0) for x in (inp, swapped)]
+            print(run.__name__, dtype, V, [f"{e.mean():+.2e} rms {np.sqrt((e * e).mean()):.2e}" for e in err], flush=True)
+            assert all(abs(e.mean()) < 2e-8 for e in err)
+    finally:
+        fsd.debug_set_exact_js(prev[0])
+        fsd.debug_set_small_calls(prev[1])
