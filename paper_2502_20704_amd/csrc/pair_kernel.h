@@ -170,6 +170,19 @@ __device__ __noinline__ TeamNorm merge_more_rounds(const unsigned long long* p1,
     }
     return n;
 }
+// the same with sums in binary64
+struct WideNorm { double zt, zd; bool ok; };
+__device__ __noinline__ WideNorm merge_more_rounds_wide(const unsigned long long* p1, int GW, unsigned limit, TeamNorm n, WideNorm z) {
+    for (int base = 128; base < GW; base += 64) {
+        const WordsN<2> r = repoll_n<2>(p1, GW, base, limit);
+        if (!r.ok) z.ok = false;
+        float at, ad;
+        member_terms(r.w, base + static_cast<int>(threadIdx.x & 63) < GW, n, at, ad);
+        z.zt += wave_sum(static_cast<double>(at));
+        z.zd += wave_sum(static_cast<double>(ad));
+    }
+    return z;
+}
 // the divergence words of the members beyond the first round, added in member order (each word
 // holds two binary32 partial sums)
 template <int N> struct Sums { double lo[N], hi[N]; bool ok; };
@@ -490,9 +503,16 @@ void pair_kernel(PairParams P) {
     // behind the second or third slot's 69.7 and 181.1, 69.8 and 181.8.  TV: C2 74.3 -> 72.0, C4 201 -> 198.  The
     // single-pass modes do not gain (strict SD at C2 66.5 -> 67.8).
     constexpr bool EARLY = TWO_PHASE;
-    // With 8 slots a lane the single-pass kernels sum up the halves of them apart: no longer chains of binary32 additions than
-    // with 4.
-    constexpr bool TWO_SUMS = BF16 && !TWO_PHASE && NV == 8;
+    // The larger shapes sum up the halves of a lane's slots apart, so that no chain of binary32 additions is longer than in the smaller ones: the
+    // bfloat16 single-pass kernels with 8 slots (twice 32 entries), the binary32 two-phase ones with 10 (twice 20, phase 2's sums as well).
+    constexpr bool TWO_SUMS = BF16 ? (!TWO_PHASE && NV == 8) : (TWO_PHASE && NV == 10);
+    // With 10 slots a row's normaliser is added up from its members' in binary64.  What rounding makes of it is mostly made there, and less than
+    // a power of two of members, 25 for the 32 of 8 slots, leaves larger partial sums near the end: error of the normaliser in
+    // binary32, V=64000 4.1e-8 and 3.2e-8, of which the lanes' chains are 4e-9 and 3e-9.  Divergences' relative error against 64 bits (1e-8), 8 slots, 10 slots added up in binary32, and as it is: 16
+    // candidates of 64 sequences, V=64000 TV 19.5 20.6 16.6, KL 6.6 7.3 6.2, JS 11.3 11.4 11.2; V=151936 TV 11.7 12.1 9.8, KL 7.8 7.9 6.8, JS 11.8
+    // 12.0 11.7.  Whole calls, us, the last two: 256 sequences of 16, V=151936, JS 831 828, TV 835 831, KL 997 980; 64 of 8, V=128256, 104.9 105.5;
+    // trees of 60 on 32 of them 297 300 (347 with 8 slots).
+    constexpr bool WIDE_MERGE = !BF16 && TWO_PHASE && NV == 10;
     // The largest bfloat16 logits by 16-bit comparisons, two at once.  (Not KL with 4 slots, which is faster with the four wavefronts a SIMD that
     // its registers then allow than with five: 64 sequences of 8, V=128256, 61.9 and 64.1 us a call.)
     constexpr bool PACKED = BF16 && !(MODE == MODE_KL && NV == 4);
@@ -985,10 +1005,22 @@ void pair_kernel(PairParams P) {
     // factors ft, fd with p = e_t ft, q = e_d fd
     auto merge_team = [&](const Pend& pp, unsigned long long (&w)[2], unsigned long long (&w2)[2], float& ft, float& fd) __attribute__((always_inline)) -> bool {
         const unsigned long long* p1 = part1 + words_at(pp.pair, N1);
-        // binary32 is enough: the normalisers enter p and q as common factors
+        // binary32 is enough: the normalisers enter p and q as common factors.  (WIDE_MERGE: see there.)
         TeamNorm n{pp.kt, pp.kd, 0.0f, 0.0f, true};
         n.ok = await_n<2>(p1, GW, 0, P.spin_limit, w);
-        if (GW > 64) {
+        if constexpr (WIDE_MERGE) {
+            float at, ad, at2 = 0.0f, ad2 = 0.0f;
+            member_terms(w, lane < GW, n, at, ad);
+            if (GW > 64) {
+                if (!await_n<2>(p1, GW, 64, P.spin_limit, w2)) n.ok = false;
+                member_terms(w2, 64 + lane < GW, n, at2, ad2);
+            }
+            WideNorm z{wave_sum(static_cast<double>(at) + static_cast<double>(at2)), wave_sum(static_cast<double>(ad) + static_cast<double>(ad2)), n.ok};
+            if (GW > 128) z = merge_more_rounds_wide(p1, GW, P.spin_limit, n, z);
+            n.zt = static_cast<float>(z.zt);
+            n.zd = static_cast<float>(z.zd);
+            n.ok = z.ok;
+        } else if (GW > 64) {
             // members 64..127 were requested with the first 64: a lane adds its two members before the
             // one reduction over the wavefront; larger teams ask for the rest afterwards
             if (!await_n<2>(p1, GW, 64, P.spin_limit, w2)) n.ok = false;
@@ -1080,8 +1112,15 @@ void pair_kernel(PairParams P) {
             word[0] = dbits(share);
         } else if constexpr (MODE == MODE_TV) {
             float A = 0.0f, Bn = 0.0f, MA = 0.0f;
+            [[maybe_unused]] float A_half = 0.0f, Bn_half = 0.0f, MA_half = 0.0f;
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
+                if constexpr (TWO_SUMS) {
+                    if (c == NC / 2) {
+                        A_half = A; Bn_half = Bn; MA_half = MA;
+                        A = Bn = MA = 0.0f;
+                    }
+                }
                 float t4[4], d4[4];
                 get4(S, c, t4, d4);
 #pragma unroll
@@ -1089,6 +1128,7 @@ void pair_kernel(PairParams P) {
                     tv_terms(t4[i], d4[i] * cq, A, Bn, MA);
                 }
             }
+            if constexpr (TWO_SUMS) { A += A_half; Bn += Bn_half; MA += MA_half; }
             // max() drops NaN: an unusable row (NaN factor) is made to reach the side selection
             wave_sumf2(A, Bn);
             MA = wave_sumf(MA);
@@ -1099,8 +1139,12 @@ void pair_kernel(PairParams P) {
             word[1] = pack2(MA, 0.0f);
         } else {
             float acc = 0.0f;
+            [[maybe_unused]] float acc_half = 0.0f;
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
+              if constexpr (TWO_SUMS) {
+                  if (c == NC / 2) { acc_half = acc; acc = 0.0f; }
+              }
               float t4[4], d4[4];
               get4(S, c, t4, d4);
 #pragma unroll
@@ -1113,6 +1157,7 @@ void pair_kernel(PairParams P) {
                 pointwise_term<MODE>(p, q, acc);
               }
             }
+            if constexpr (TWO_SUMS) acc += acc_half;
             acc = wave_sumf(acc);
             if constexpr (MODE != MODE_KLP) acc *= ftc;
             if (ft != ft || fd != fd) acc = ft + fd;   // an unusable row stays NaN
@@ -1360,6 +1405,7 @@ void pair_kernel(PairParams P) {
         // 1e-7 only (common factors of p and q); the single-pass modes take them through a logarithm.
         const unsigned long long w0 = pack2(kt, kd);
         unsigned long long mine;
+        if constexpr (TWO_PHASE && TWO_SUMS) { st += st_half; sd += sd_half; wacc += wacc_half; }
         [[maybe_unused]] const float st_lane = st, sd_lane = sd;
         if constexpr (TWO_PHASE) {
             wave_sumf2(st, sd);

@@ -1084,3 +1084,35 @@ def test_js_of_disjoint_rows_does_not_lean(torch_cuda, dtype, V):
     finally:
         fsd.debug_set_exact_js(prev[0])
         fsd.debug_set_small_calls(prev[1])
+
+
+@pytest.mark.parametrize("V", [64000, 100004])
+def test_binary32_large_calls_are_as_exact_as_with_eight_slots(torch_cuda, V):
+    """The shape that large binary32 calls take, fewer and larger members of a team, against 64 bits: its error (2-norm over 2-norm, 1024 pairs
+    of rows) is no larger than that of the 8-slot shape.  (JS, whose error is mostly the logarithms' own and the same in both, to 1 %.)"""
+    torch, B, K = torch_cuda, 64, 16
+    g = torch.Generator(device="cuda").manual_seed(7)
+    t = torch.randn((B, K + 1, V), generator=g, device="cuda") * 2.0
+    d = t[:, :K] + torch.randn((B, K, V), generator=g, device="cuda") * 0.5
+    cand = torch.zeros((B, K), dtype=torch.int32, device="cuda")
+    exact = {div: [] for div in (fsd.DIV_JS, fsd.DIV_TV, fsd.DIV_KL)}
+    for b in range(B):
+        lp, lq = torch.log_softmax(t[b, :K].double(), -1), torch.log_softmax(d[b].double(), -1)
+        p, q = lp.exp(), lq.exp()
+        lm = (0.5 * (p + q)).log()
+        exact[fsd.DIV_JS].append(0.5 * (p * (lp - lm) + q * (lq - lm)).sum(-1))
+        exact[fsd.DIV_TV].append(0.5 * (p - q).abs().sum(-1))
+        exact[fsd.DIV_KL].append((p * (lp - lq)).sum(-1))
+    for div, most in ((fsd.DIV_JS, 1.01), (fsd.DIV_TV, 1.0), (fsd.DIV_KL, 1.0)):
+        want = torch.stack(exact[div])
+        err = {}
+        for slots in (0, 8):
+            fsd.debug_set_shape(0, slots)
+            try:
+                out = fsd.fsd_verify_chain(t, d, cand, 0.1, div, fsd.SAMPLE, 1, 1)
+                torch.cuda.synchronize()
+            finally:
+                fsd.debug_set_shape(0, 0)
+            err[slots] = float(((out["divergences"].double() - want).norm() / want.norm()).item())
+        print(f"binary32 V={V} div={div}: error", err, flush=True)
+        assert err[0] <= most * err[8], (div, err)
