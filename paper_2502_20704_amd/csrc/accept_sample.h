@@ -341,9 +341,12 @@ __device__ __forceinline__ Best share_best(unsigned long long w) {
     const unsigned at = static_cast<unsigned>(w) & 0x7FFFFFFFu;
     return Best{__uint_as_float(static_cast<unsigned>(w >> 32)), at == 0x7FFFFFFFu ? 0x7FFFFFFF : static_cast<int>(at) - 1};
 }
-// A call that has failed (every workgroup of the last kernel sees that): the last sequence to finish puts the
-// failure word, which nothing looks at after that kernel, back to zero, so that the same call replayed from a captured
-// graph, with the same number, does not find a failure of the last time.  (gridDim.y: the sequences.)
+// A call that has failed, by the one workgroup of a sequence that writes its outputs, once it has: the last sequence to come here puts the
+// failure word, which nothing looks at after this kernel, back to zero, so that the same call replayed from a captured
+// graph, with the same number, does not find a failure of the last time.  Every workgroup that writes outputs has looked at
+// the word by then.  Another one of a sequence may still look, find no failure and work on what the reduction left: it is in bounds whatever
+// that is, and for nothing, since it writes no outputs.  (warp_select: outputs of a call without failure are written by whoever is the last to
+// count itself, and where the writing workgroup has come here it never counts itself, so nobody is the last.)  (gridDim.y: the sequences.)
 __device__ __forceinline__ void sequence_of_failed_call_done(const Ws& w) {
     const unsigned done = atomicAdd(w.counters + 4, 1u);
     if (done == gridDim.y - 1) __hip_atomic_store(reinterpret_cast<unsigned long long*>(w.counters + 2), 0ull, __ATOMIC_RELAXED, AGENT);

@@ -381,6 +381,55 @@ def test_selection_wait_expires_cleanly(torch_cuda, oracle, dtype):
         check_warped(g, o, 0.1, pu.rel_tol(dtype), f"after restoring the poll budget {dtype}", envelope=pu.Envelope(dtype))
 
 
+# (the reduction by teams, and in one step of the device)
+@pytest.mark.parametrize("small", [False, True])
+@pytest.mark.parametrize("tree", [False, True])
+def test_failed_reduction_before_the_draw_with_the_selection(torch_cuda, oracle, tree, small):
+    """A reduction whose waits have a poll budget of zero, in front of the selection that draws the token: all sequences are flagged, with
+    empty outputs, or all are right; the next call on the same workspace is right."""
+    B, N, V = 6, 14, 40000
+    inp = _random_tree_inputs(np.random.default_rng(8), B, N, V, "bf16")
+    dev = pu.to_dev(inp, ("target", "draft", "node_tokens", "parent"))
+    ws = torch_cuda.empty(fsd.fsd_workspace_bytes(B, N, V, fsd.BF16) + 256, dtype=torch_cuda.uint8, device="cuda")
+    length, keys = ("path_len", pu.TREE_KEYS) if tree else ("accept_len", pu.CHAIN_KEYS)
+    args, kw = (0.12, fsd.DIV_JS, fsd.SAMPLE, 5, 2), dict(top_k=50, top_p=0.9, temperature=0.7)
+    if tree:
+        o = oracle.verify_tree_warped(inp["target"], inp["draft"], inp["node_tokens"], inp["parent"], N, *args, **kw)
+    else:
+        o = oracle.verify_chain_warped(inp["target"], inp["draft"], inp["node_tokens"], *args, **kw)
+    assert not pu.near_threshold(o["divs"], 0.12).any() and (o["slack"] >= 1e-5).all() and (o["gap"] >= 1e-6).all()
+
+    def call():
+        if tree:
+            out = fsd.fsd_verify_tree_warped(dev["target"], dev["draft"], dev["node_tokens"], dev["parent"], N, *args, workspace=ws, **kw)
+        else:
+            out = fsd.fsd_verify_chain_warped(dev["target"], dev["draft"], dev["node_tokens"], *args, workspace=ws, **kw)
+        assert fsd.debug_last_selection() > 1 and fsd.debug_last_route() == int(small)
+        torch_cuda.cuda.synchronize()
+        return pu.host(out, keys)
+
+    outputs = [k for k in keys if k in ("accept_len", "path_len", "path_nodes", "out_tokens")]
+    prev_small = fsd.debug_set_small_calls(small)
+    try:
+        for rep in range(3):
+            prev = fsd.debug_set_spin_limit(0)
+            try:
+                g = call()
+            finally:
+                fsd.debug_set_spin_limit(prev)
+            flagged = (g["row_status"] & fsd.ROW_INTERNAL) != 0
+            print("failed reduction", tree, small, "flagged", flagged, flush=True)
+            assert flagged.all() or (g["row_status"] == 0).all()
+            if flagged.all():
+                assert (g[length] == 0).all() and all((g[k] == -1).all() for k in outputs if k != length)
+            else:
+                assert all((g[k] == o[k]).all() for k in outputs)
+            g = call()
+            assert (g["row_status"] == 0).all() and all((g[k] == o[k]).all() for k in outputs)
+    finally:
+        fsd.debug_set_small_calls(prev_small)
+
+
 def _longest_list(row, W, k, inv_temp, VE):
     """The longest list a workgroup of a split top-k leaves: its entries at or above the k-th largest of its 1024
     threads' maxima, of which the upper half of the 32-bit key counts."""
