@@ -677,16 +677,23 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         if (k1mode == MODE_JSE) p.spm = 64 * p.NV;
     }
     if (load != LOAD_ELEM && dtype == FSD_BF16 && !g_shape_nv && (k1mode == MODE_LSE || k1mode == MODE_KL)) {
-        // The bfloat16 single-pass kernels hold 8 slots of each row per lane once the rows are enough for nearly four rounds of their teams
+        // The bfloat16 single-pass kernels hold 8 slots of each row per lane once the rows are enough for several rounds of their teams
         // (a step's reductions and exchange, a fifth of its instructions with 4 slots, are then shared by twice the logits); with
-        // fewer the last round is too empty.  A tree's siblings read their target row once.  Whole calls, us, 4 and 8 slots, V=128256: strict SD, 24
-        // sequences of 8 35.7 and 36.3, 40 49.0 and 47.7, 64 66.7 and 64.3, 256 218 and 203; trees of 60, 5 sequences 73.5 and 75.0, 8 87.2 and
-        // 85.9, 32 195.7 and 183.8; KL on trees, 4 32.6 and 33.1, 8 51.1 and 50.4, 32 162 and 155.  KL on chains, whose 4-slot kernel waits for memory
-        // more than it computes, gains from ten rounds on: 48 of 8 51.3 and 51.6, 64 62.3 and 62.0, 200 164 and 161.  Rows that are not 16-byte
-        // aligned, V=128259: strict SD on trees 230 and 220, KL 186 and 186, but on chains 74.9 and 85.8, 72.0 and 83.0.
+        // fewer the last round is too empty.  A tree's siblings read their target row once.  Whole calls, us, 4 and 8 slots:
+        //   strict SD, from nearly four rounds   V=128256, 24 sequences of 8 35.7 and 36.3, 40 49.0 and 47.7, 64 66.7 and 64.3, 256 218 and 203; trees of 60, 5
+        //     sequences 73.5 and 75.0, 6 79.3 and 76.1, 15 117.3 and 114.4, 32 195.7 and 183.8; V=32000, 24 trees 74.2 and 70.7; V=200000, 4 92.0 and 88.9.  (In
+        //     between a last round that is nearly empty goes either way: V=56128, 20 trees 86.1 and 85.2, 22 84.5 and 86.0.)
+        //   KL, whose 4-slot kernel waits for memory more than it computes   trees of 60, from 24 rounds: V=128256, 8.3 rounds 70.6 and 76.0, 11 93.5 and 96.2, 18
+        //     140.9 and 146.0, 24 184.9 and 180.5, 48 366 and 355; V=32000, 18 143.8 and 142.2, 24 189.4 and 183.3.  Chains, from 32: V=128256, 10 60.8 and
+        //     61.5, 20 107.1 and 107.1, 40 193.3 and 189.2; V=32000, 20 105.2 and 105.7, 28 145.3 and 141.5, 40 195.7 and 188.8; V=200000, 10 60.9 and
+        //     63.2, 28 144.2 and 145.9, 40 192.2 and 192.7.
+        //   rows that are not 16-byte aligned   strict SD on trees, from seven: V=106053, 4.1 rounds 91.7 and 94.8, 6.2 103.2 and 105.4, 7.2 106.7 and 106.5,
+        //     9.3 118.7 and 117.2; V=128259 230 and 220.  KL on trees, 4.1 51.2 and 55.9, 14 133.1 and 134.6, 24 215.3 and 212.1.  But chains, V=128259, strict SD
+        //     74.9 and 85.8, KL 72.0 and 83.0: never.
         const long G8 = team_size(p.nslots, 8);
         const long round = max_resident_wavefronts() / 8 * pair_kernel_most(true, 8, k1mode) / G8, rows_read = parent ? R + B : 2L * R;
-        if ((parent || load == LOAD_ALIGNED) && 4 * rows_read >= (k1mode == MODE_KL && !parent ? 40 : 15) * round) {
+        const long quarters = k1mode == MODE_KL ? (parent ? 4 * 24 : 4 * 32) : load == LOAD_ALIGNED ? 15 : 4 * 7;   // of a round
+        if ((parent || load == LOAD_ALIGNED) && 4 * rows_read >= quarters * round) {
             p.NV = 8;
             p.G = static_cast<int>(G8);
             p.spm = static_cast<int>((p.nslots + G8 - 1) / G8);

@@ -1,5 +1,7 @@
 """GPU parity at the sizes and values where a kernel or a rule of its dispatch can go wrong, against the CPU
 oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -935,6 +937,49 @@ def test_bfloat16_single_pass_teams(torch_cuda, oracle, V, copies):
     o = oracle.sd_verify_tree(inp["target"], inp["draft"], inp["cand"], parent, 4, seed=5, offset=2)
     tree = dict(target=inp["target"], draft=inp["draft"], node_tokens=inp["cand"], parent=parent)
     check_sd_tree(first(out, pu.TREESD_KEYS), o, f"SD tree V={V}", tree)
+
+
+def _last_launch():
+    grid, resident = ctypes.c_int(), ctypes.c_int()
+    fsd.library().fsd_debug_last_launch(ctypes.byref(grid), ctypes.byref(resident))
+    return grid.value, resident.value
+
+
+# (trees of 12, or chains of 12; the rounds of its teams that a call of so many rows is)
+@pytest.mark.parametrize("tree,B,wide", [(True, 640, False), (True, 2000, False), (True, 3000, True), (False, 640, False), (False, 1500, False), (False, 2100, True)])
+def test_bfloat16_kl_takes_the_large_shape_in_large_calls(torch_cuda, oracle, tree, B, wide):
+    """KL over bfloat16 rows: the 8-slot shape from 24 rounds of its teams on over trees and 32 over chains, where it is the faster one, and
+    the 4-slot shape below; copies of eight sequences, the first copy against the oracle and the others against the first."""
+    torch, K, V = torch_cuda, 12, 8192
+    inp = synth.chain_inputs(8, K, V, "bf16", "peaked", (0.25, 2.0), seed=3)
+    parent = np.broadcast_to(np.maximum(np.arange(K) // 3 - 1, -1).astype(np.int32), (8, K)).copy()
+    dev = {k: x.repeat((B + 7) // 8, *(1 for _ in x.shape[1:]))[:B] for k, x in pu.to_dev(inp, ("target", "draft", "cand")).items()}
+    parents = torch.from_numpy(parent).cuda().repeat((B + 7) // 8, 1)[:B]
+    keys = pu.TREE_KEYS if tree else pu.CHAIN_KEYS
+
+    def call(slots):
+        fsd.debug_set_shape(0, slots)
+        try:
+            if tree:
+                out = fsd.fsd_verify_tree(dev["target"], dev["draft"], dev["cand"], parents, 4, 0.25, fsd.DIV_KL, fsd.SAMPLE, 5, 2)
+            else:
+                out = fsd.fsd_verify_chain(dev["target"], dev["draft"], dev["cand"], 0.25, fsd.DIV_KL, fsd.SAMPLE, 5, 2)
+            torch.cuda.synchronize()
+        finally:
+            fsd.debug_set_shape(0, 0)
+        return out, _last_launch()[1]
+
+    out, resident = call(0)
+    assert (resident != call(4)[1]) == wide
+    first = {k: v[:8] for k, v in pu.host(out, keys).items()}
+    if tree:
+        o = oracle.verify_tree(inp["target"], inp["draft"], inp["cand"], parent, 4, 0.25, fsd.DIV_KL, oracle.SAMPLE, seed=5, offset=2)
+        pu.check_tree(first, o, 0.25, pu.rel_tol("bf16"), f"KL tree B={B}", envelope=pu.Envelope("bf16"))
+    else:
+        o = oracle.verify_chain(inp["target"], inp["draft"], inp["cand"], 0.25, fsd.DIV_KL, seed=5, offset=2)
+        pu.check_chain(first, o, 0.25, pu.rel_tol("bf16"), f"KL B={B}", envelope=pu.Envelope("bf16"))
+    got = out["divergences"][: B // 8 * 8].reshape(B // 8, 8, K)
+    assert (got == got[:1]).all()
 
 
 # Rows that begin in the middle of a 32-bit word: every second one of an odd vocabulary (9: two slots, the last of one entry; around whole members of 6 and
