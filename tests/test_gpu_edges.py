@@ -874,6 +874,68 @@ def test_largest_logit_is_negative(torch_cuda, oracle, V, kind):
         fsd.debug_set_small_calls(prev)
 
 
+# one member and three, aligned and not; whole members of the single pass's 8 slots
+@pytest.mark.parametrize("V", [3071, 6145, 8192])
+def test_rows_of_either_sign_one_after_the_other(torch_cuda, oracle, V):
+    """A wavefront looks first for the maximum of the sign that its last pair of rows had.  Calls of several rounds, in which rows of logits, of
+    log-probabilities, of one in either place, of one slice above zero, of signed zeros, masked and unusable ones follow one another in changing
+    order: the first copy against the oracle, the others, which came after other rows, against the first to the bit."""
+    torch, B, K, copies = torch_cuda, 8, 13, 100
+    rng = np.random.default_rng(V)
+    inp = synth.chain_inputs(B, K, V, "f32", "gauss2", 0.7, seed=V)
+    t, d = inp["target"], inp["draft"]
+    for b in range(B):
+        for k in range(K):
+            kind = (3 * b + 5 * k) % 8
+            if kind in (1, 2, 4, 5):
+                t[b, k] -= t[b, k].max() + np.float32(1.0)
+            if kind in (1, 3, 4, 5):
+                d[b, k] -= d[b, k].max() + np.float32(1.0)
+            if kind == 4:
+                t[b, k, -70:] += np.float32(9.0)
+            if kind == 5:
+                t[b, k, rng.permutation(V)[: V // 3]] = 0.0
+                d[b, k, rng.permutation(V)[: V // 3]] = -0.0
+            if kind == 6:
+                masked = rng.permutation(V)[: V // 2]
+                t[b, k, masked] = d[b, k, masked] = -np.inf
+    d[B - 1, 4, V // 2] = np.nan
+    d[B - 1, 9, V // 2] = np.inf
+    t, d = synth.to_bf16_bits(t), synth.to_bf16_bits(d)
+    parent = np.broadcast_to(np.maximum(np.arange(K) // 3 - 1, -1).astype(np.int32), (B, K)).copy()
+    dev = {k: x.repeat(copies, *(1 for _ in x.shape[1:])) for k, x in pu.to_dev(dict(target=t, draft=d, cand=inp["cand"]), ("target", "draft", "cand")).items()}
+    parents = torch.from_numpy(parent).cuda().repeat(copies, 1)
+
+    def first(out, keys, tree):
+        all_ = out["divergences"].reshape(copies, B, K)[:, : B - 1]
+        # (over a tree a row of masked entries may be the first of its siblings or a later one, which takes its sums from the one before: they are
+        # rounded in another order then.  Results of the entropy form are exact to 1e-7.)
+        if tree:
+            assert ((all_ - all_[:1]).abs() <= 1e-6 * (1 + all_.abs())).logical_or(all_ == all_[:1]).all()
+        else:
+            assert (all_.view(torch.int32) == all_[:1].view(torch.int32)).all()
+        assert (out["row_status"].reshape(copies, B) == out["row_status"][:B]).all() and int(out["row_status"][B - 1]) & fsd.ROW_NONFINITE
+        return {k: v[: B - 1] for k, v in pu.host(out, keys).items()}
+
+    env, few = pu.Envelope("bf16"), slice(0, B - 1)
+    for div, T in ((fsd.DIV_JS, 0.06), (fsd.DIV_TV, 0.25), (fsd.DIV_KL, 0.25)):
+        what = f"either sign V={V} div={div}"
+        print(what, flush=True)
+        out = fsd.fsd_verify_chain(dev["target"], dev["draft"], dev["cand"], T, div, fsd.SAMPLE, 5, 2)
+        torch.cuda.synchronize()
+        o = oracle.verify_chain(t[few], d[few], inp["cand"][few], T, div, seed=5, offset=2)
+        pu.check_chain(first(out, pu.CHAIN_KEYS, False), o, T, pu.rel_tol("bf16"), what, envelope=env)
+        out = fsd.fsd_verify_tree(dev["target"], dev["draft"], dev["cand"], parents, 4, T, div, fsd.SAMPLE, 5, 2)
+        torch.cuda.synchronize()
+        o = oracle.verify_tree(t[few], d[few], inp["cand"][few], parent[few], 4, T, div, oracle.SAMPLE, seed=5, offset=2)
+        pu.check_tree(first(out, pu.TREE_KEYS, True), o, T, pu.rel_tol("bf16"), f"tree {what}", envelope=env)
+    out = fsd.sd_verify_chain(dev["target"], dev["draft"], dev["cand"], seed=5, offset=2)
+    torch.cuda.synchronize()
+    got = out["log_ratio"].reshape(copies, B, K)[:, : B - 1].view(torch.int32)
+    assert (got == got[:1]).all()
+    check_sd({k: v[: B - 1] for k, v in pu.host(out, pu.SD_KEYS).items()}, oracle.sd_verify_chain(t[few], d[few], inp["cand"][few], seed=5, offset=2), f"SD either sign V={V}")
+
+
 # binary32 rows of whole members of 10 slots a lane (20480, 2560), a slot less, an entry more, a few slots in the last member; 8 slots a
 # lane (41000, 41003): two steps of either
 @pytest.mark.parametrize("B,K,V", [(16, 15, 20480), (16, 15, 20476), (16, 15, 20481), (100, 15, 2560), (90, 15, 2572), (8, 16, 41000), (8, 16, 41003)])
