@@ -714,12 +714,14 @@ int run(int kind, const void* target, const void* draft, const int32_t* tokens, 
         } else if (k1mode != MODE_LSE) {
             // The two-phase kernels hold 10 slots a lane, or 8 where the call is of few steps and 8 slots make
             // less of them (whole calls, us, 8 and 10 slots: 16 sequences of 8, V=64000, 2 and 2 steps 25.9 and 27.6; 8 of 16, V=128256, 4 and 4
-            // steps 37.0 and 38.7; 64 of 16, V=32000, 8 and 7 57.0 and 59.3; but 12 of 6, V=151936, 3 and 3, 75 and 60 wavefronts a team 33.5
-            // and 33.2; 128 of 16, V=128256, 64 and 52 381 and 359; 256 of 16, V=151936, 152 and 121 917 and 831, where one wavefront a SIMD,
-            // with 8 slots and a third set of exponentials, took 936).
+            // steps 37.0 and 38.7; 64 of 16, V=32000, 8 and 7 57.0 and 59.3; 128 of 16, V=128256, 64 and 52 381 and 359; 256 of 16, V=151936, 152 and
+            // 121 917 and 831, where one wavefront a SIMD, with 8 slots and a third set of exponentials, took 936).  Not where 8 slots make a team
+            // one of more rounds of 64 members, whose words every merge then reads in more rounds: 12 of 6, V=151936, 3 and 3 steps, 75 and 60 members 33.5
+            // and 33.2; 5 of 8, V=400000, 4 and 4, 196 and 157 48.5 and 46.5; but 5 of 8, V=200000, 2 and 2, 98 and 79 JS 29.2 and 30.7, KL 32.6 and
+            // 35.2; 8 of 8, V=256000, 4 and 4, 125 and 100 40.0 and 41.3, KL 45.3 and 47.6.  Such teams up to four steps: 14 of 8, V=200000, 6 and 5 52.5 and 51.5.
             const long G8 = team_size(p.nslots, 8), G10 = team_size(p.nslots, 10), waves = max_resident_wavefronts() / 4;
             const auto steps = [&](long G) { const long teams = waves / G > 0 ? waves / G : 1; return (R + teams - 1) / teams; };
-            const bool eight = G8 <= 64 && steps(G8) <= 8 && steps(G8) * 8 < steps(G10) * 10;
+            const bool eight = (G8 + 63) / 64 == (G10 + 63) / 64 && steps(G8) <= (G8 <= 64 ? 8 : 4) && steps(G8) * 8 < steps(G10) * 10;
             p.NV = eight ? 8 : 10;
             p.G = static_cast<int>(eight ? G8 : G10);
             p.spm = static_cast<int>((p.nslots + p.G - 1) / p.G);

@@ -874,6 +874,29 @@ def test_largest_logit_is_negative(torch_cuda, oracle, V, kind):
         fsd.debug_set_small_calls(prev)
 
 
+# two and two steps of teams of 98 and 79 (of 8 slots a lane and of 10), five and four; teams of 75 and 60, of 196 and 157
+@pytest.mark.parametrize("B,K,V,eight", [(5, 8, 200000, True), (12, 8, 200000, False), (12, 6, 151936, False), (4, 8, 400004, False)])
+def test_binary32_shapes_of_wide_rows(torch_cuda, B, K, V, eight):
+    """Which shape a binary32 call of few steps and wide rows takes, and that its results are those of the other one to rounding."""
+    torch = torch_cuda
+    g = torch.Generator(device="cuda").manual_seed(B)
+    t = torch.randn((B, K + 1, V), generator=g, device="cuda") * 2.0
+    d = t[:, :K] + torch.randn((B, K, V), generator=g, device="cuda") * 0.5
+    cand = torch.zeros((B, K), dtype=torch.int32, device="cuda")
+    for div in (fsd.DIV_JS, fsd.DIV_TV, fsd.DIV_KL):
+        got, grid = {}, {}
+        for slots in (0, 8):
+            fsd.debug_set_shape(0, slots)
+            try:
+                out = fsd.fsd_verify_chain(t, d, cand, 0.1, div, fsd.SAMPLE, 1, 1)
+                torch.cuda.synchronize()
+            finally:
+                fsd.debug_set_shape(0, 0)
+            got[slots], grid[slots] = out["divergences"].double(), _last_launch()[0]
+        assert (grid[0] == grid[8]) == eight, grid
+        assert ((got[0] - got[8]).abs() <= 4e-6 * got[8]).all()
+
+
 # one member and three, aligned and not; whole members of the single pass's 8 slots
 @pytest.mark.parametrize("V", [3071, 6145, 8192])
 def test_rows_of_either_sign_one_after_the_other(torch_cuda, oracle, V):
