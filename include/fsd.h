@@ -348,8 +348,9 @@ int fsd_debug_set_self_clear(int on);
 /* Tuning hook: shape of the vocabulary-reduction kernel.  `wavefronts` per
  * workgroup must be 4 (or 0 = default); `slots_per_thread` is the number of
  * 16-byte slots of each row a lane holds: 2, 4 or 8 (bfloat16: 2, 4 or 5), 0 =
- * the library's own choice (32 vocabulary entries per lane and row; 48 for the
- * bfloat16 JS and TV kernels, 16 for small binary32 calls).  A shape
+ * the library's own choice (bfloat16: 48 vocabulary entries per lane for JS and
+ * TV, 32 for KL and strict SD or 64 in large calls; binary32: 40, or 32 in calls of few
+ * steps and for strict SD, or 16 in small calls).  A shape
  * that would need more than 256 wavefronts per row pair is ignored.  Results
  * do not depend on the shape beyond the rounding order of the partial sums. */
 int fsd_debug_set_shape(int wavefronts, int slots_per_thread);

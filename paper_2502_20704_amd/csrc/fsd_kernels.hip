@@ -383,9 +383,9 @@ void launch_sample(int dtype, int load, int kind, dim3 grid, size_t lds, hipStre
 //          18.9 17.3, (5) 19.7 19.1, (6) 20.1 20.9, 7 of 5 18.8 18.5, 8 of 5 19.1 19.7; V=256000, 5 of 4 21.3 20.7; V=210901, 2 of 14 23.6 21.7
 //          binary32 V=32000 [30] 13.8 13.8, 22 of 5 17.6 17.6, 28 of 5 19.7 21.1, 7 of 16 nodes 17.8 17.9, 10 of 16 nodes 22.7 21.5; V=50257, 14 of 5 18.1
 //          17.8, 18 of 5 20.2 21.3; V=64000, 11 of 5 18.1 18.0, 16 of 5 20.8 22.6, 6 of 16 nodes 23.0 22.0; V=100000, 7 of 5 17.9 18.7; V=128256, 6 of 5 18.0
-//          19.3.  (From 1 million entries on, where the teams need one step, about 2 million, that is the faster one.  The binary32 lines were
-//          drawn when the teams ran one wavefront a SIMD; chains, by these figures of today, would be with the teams from 3.5 million entries on, 3.25 million of
-//          long rows and under TV.  The routes' tests have the lines where they are.)
+//          19.3.  (From 1 million entries on, where the teams need one step, about 2 million, that is the faster one.  The binary32 lines
+//          come from teams of one wavefront a SIMD, as `step` below does; with today's the break-even of chains lies at 3.5 million entries, of long rows and
+//          under TV at 3.25, and what lies between the two is up to 11 % slower in one step of the device than it would be with the teams.)
 //     TV   bfloat16 V=32000 [60] 15.7 14.9; V=64000 (4) 14.9 14.6, (6) 15.2 16.2; V=128256 (2) 15.1 15.2, (3) 15.6 16.4; V=200000, 4 of 4 18.1 17.6,
 //          6 of 4 19.6 20.1; rows that are not 16-byte aligned V=40265, 21 of 4 19.7 17.6, V=235817, 2 of 9 22.3 19.1
 //          binary32 V=32000 [30] 13.6 14.5, [60] 15.1 16.1, 28 of 5 19.5 21.5; V=50257, 14 of 5 18.3 18.4, 18 of 5 19.9 21.4; V=64000 (4) 15.2 17.2, 14 of 5
@@ -415,7 +415,7 @@ SmallForms small_forms(int kind, int dtype, int div, int B, int rows, long V, bo
     else if (bf16) f.reduction = entries <= (!aligned ? 9 * M / 2 : V > 1L << 17 ? 15 * M / 4 : 2 * M);
     else if (div == FSD_DIV_KL) f.reduction = entries <= 6 * M;
     else {
-        // pairs that the binary32 teams took in a step when these lines were measured (8 slots a lane, a wavefront a SIMD)
+        // pairs that teams of 8 slots a lane and a wavefront a SIMD take in a step (see the table above)
         const long step = max_resident_wavefronts() / 8 / team_size((V + 3) / 4, 8), pairs = static_cast<long>(B) * rows;
         if (js) f.reduction = entries <= (long_rows ? 4 * M : 6 * M) && (entries <= M || pairs > step);
         else f.reduction = entries <= (long_rows ? 4 * M : 9 * M / 2) && pairs > (long_rows ? 2 * step : step);
@@ -531,12 +531,14 @@ long list_keys(long k, long T) {
     return static_cast<long>(n * 1.0625 + 4.0 * sqrt(static_cast<double>(T) * (expm1(x) - x))) + 1;
 }
 
-// Rows of fewer entries are left to one workgroup, whose selection the extra stores, the count and the second reading
-// then outweigh.  Whole calls on 8 sequences, one workgroup a row and several (us):
-//   top-k 50, top-p 0.9   bfloat16   V=16000 44.5 and 45.2, 24000 39.5 and 39.3; V=20001 42.5 and 43.5, 24001 43.4 and 42.8
-//                         binary32   V=32000 43.6 and 43.8, 40000 48.3 and 47.5; V=16001 48.4 and 49.8, 20001 43.5 and 43.3
-//   top-p 0.95            bfloat16   V=8200 40.3 and 39.7;                       V=12001 42.8 and 43.4, 16001 47.8 and 47.4
-//                         binary32   V=16000 44.4 and 44.9, 20000 51.7 and 50.9; V=12001 44.6 and 44.6, 16001 (1 sequence) 33.4 and 32.4
+// Rows of fewer entries are left to one workgroup.  Whole calls, one workgroup a row and several (us):
+//   top-p 0.95, 8 sequences   bfloat16   V=8200 40.3 and 39.7;              V=12001 42.8 and 43.4, 16001 47.8 and 47.4
+//                             binary32   V=16000 44.4 and 44.9, 20000 51.7 and 50.9; V=12001 44.6 and 44.6, 16001 (1 sequence) 33.4 and 32.4
+//   top-k 50, top-p 0.9, 8 sequences of 32   bfloat16   V=16000 32.0 and 28.8, 24000 34.9 and 31.4; V=16001 34.2 and 32.2, 24001 38.6 and 35.3
+//                             binary32   V=16000 35.1 and 30.9, 32000 43.9 and 39.1, 40000 49.2 and 42.9; V=16001 36.8 and 32.5, 20001 41.3 and 35.8
+// Under top-k the lines are those of a selection with a draw kernel behind it on either side, where both took the same time (of 8 sequences,
+// bfloat16 V=24000 39.5 and 39.3, binary32 40000 48.3 and 47.5, 20001 43.5 and 43.3).  That is what a recorded call, a long chain or a large top-k still has;
+// where several workgroups draw the token as well they are the faster ones below the lines too, by the second row's 2 to 7 us.
 // (Binary32 rows are streamed by the one workgroup, unaligned ones of either type with moves for their last slot.)
 constexpr long split_least(bool bf16, bool aligned, bool top_k) {
     return top_k ? (bf16 ? 24000 : aligned ? 40000 : 20000) : (!aligned ? 16000 : bf16 ? 0 : 20000);

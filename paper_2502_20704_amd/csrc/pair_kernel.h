@@ -327,7 +327,7 @@ __device__ __forceinline__ void pointwise_term(float p, float q, float& acc) {
     [[maybe_unused]] constexpr float kTiny = 2e-38f;   // floor of u and v under the logarithm (their weights are then zero or negligible)
     const float d = p - q, sum = p + q;
     // (JS) p = q = 0: 0 * inf = NaN, which max() drops (u = kTiny, v = 2, both weights zero)
-    // (Both floors in one median instruction, v's at 2^-23, took 0.8 us of 108 off 32 sequences of 10, V=256000, reducible FSD. But u then ends
+    // (Both floors in one median instruction, v's at 2^-23, took 0.4 us of 109 off 32 sequences of 10, V=256000, reducible FSD. But u then ends
     // at 2 - 2^-23, where an entry that only the target has must have 2: 4e-8 of the divergence of disjoint rows, always too little.)
     const float inv = __builtin_amdgcn_rcpf(sum);
     float u = fmaxf(fmaf(d, inv, 1.0f), kTiny), v = fmaxf(2.0f - u, kTiny);
@@ -706,19 +706,19 @@ void pair_kernel(PairParams P) {
         if constexpr (SHARE_SUM) {
             // the target's requests first: with them the draft's are the last in flight whether or not they are
             // made, so the wait for the draft row stays exact
+            static_assert(!EVEN, "a tree's rows are requested where they begin");
             const unsigned limit = wanted ? off_last : 0u;
-            const unsigned limit_t = row_limit(limit, ahead_t), limit_d = row_limit(limit, ahead_d);
-            const auto off_of = [&](int k, unsigned most) __attribute__((always_inline)) {
+            const auto off_of = [&](int k) __attribute__((always_inline)) {
                 const unsigned off = static_cast<unsigned>(first) * 16u + 1024u * k;
-                return off < most ? off : most;
+                return off < limit ? off : limit;
             };
             if (!again) {
 #pragma unroll
-                for (int k = 0; k < NV; ++k) ra[k] = load_16<LD, false>(tptr + ahead_t, off_of(k, limit_t));
+                for (int k = 0; k < NV; ++k) ra[k] = load_16<LD, false>(tptr, off_of(k));
             }
             asm volatile("" ::: "memory");
 #pragma unroll
-            for (int k = 0; k < NV; ++k) rb[k] = load_16<LD, true>(dptr + ahead_d, off_of(k, limit_d));
+            for (int k = 0; k < NV; ++k) rb[k] = load_16<LD, true>(dptr, off_of(k));
             return;
         }
 #pragma unroll
